@@ -90,7 +90,7 @@ struct pv_ctx {
   uint32_t *d_block_cnt = nullptr, *d_offsets = nullptr, *d_queue = nullptr, *d_qcount = nullptr,
            *d_pcounts = nullptr, *d_poffsets = nullptr, *d_gbase = nullptr,
            *d_scan_tmp = nullptr;
-  float* d_partial = nullptr;
+  double* d_partial = nullptr;  // per-workgroup sums of the energy gradients
   uint32_t* d_scan_tmp_c = nullptr;  // scan scratch of the overlapped photon compaction
   // overlapped compaction (pv_compact_photons_async): the event its stream
   // records when done, waited for by the next work that conflicts with it
@@ -1233,7 +1233,7 @@ pv_status pv_reserve(pv_ctx* ctx, uint32_t max_paths, uint32_t max_bounces) {
     CK(dalloc(A, &ctx->d_pcounts, (size_t)nb * max_bounces));
     CK(dalloc(A, &ctx->d_poffsets, (size_t)nb * max_bounces));
     CK(dalloc(A, &ctx->d_gbase, 2));
-    CK(dalloc(A, &ctx->d_partial, (size_t)nb * 3 * (256 + PV_MAX_LIGHTS)));
+    CK(dalloc(A, &ctx->d_partial, pv::grad_part_words((uint32_t)ctx->n_cu)));
     CK(dalloc(A, &ctx->d_scan_tmp, pv::scan_tmp_words(nb * max_bounces)));
     CK(dalloc(A, &ctx->d_scan_tmp_c, pv::scan_tmp_words(nb * max_bounces)));
     const size_t task_cap = (size_t)nb * pv::kBlock * max_bounces;  // a region of kBlock * B per tile
@@ -1880,8 +1880,8 @@ pv_status pv_energy_forward(pv_ctx* ctx, const pv_path_store* store, const float
   pv_status st = bind_store(ctx, store);
   if (st) return st;
   if (!d_albedo || !d_power || !d_E) return fail(ctx, PV_ERR_ARG, "NULL argument");
-  CK(pv::launch_energy_fwd(ctx->d_scene, ctx->d_path_tiles, path_blocks(store->n_paths), d_albedo, d_power, d_E,
-                           ctx->stream));
+  CK(pv::launch_energy_fwd(ctx->d_scene, ctx->d_path_tiles, path_blocks(store->n_paths), store->max_bounces, d_albedo,
+                           d_power, d_E, ctx->stream));
   return PV_OK;
 }
 
@@ -1891,9 +1891,9 @@ pv_status pv_energy_backward(pv_ctx* ctx, const pv_path_store* store, const floa
   pv_status st = bind_store(ctx, store);
   if (st) return st;
   if (!d_albedo || !d_power || !d_gE || !d_g_albedo || !d_g_power) return fail(ctx, PV_ERR_ARG, "NULL argument");
-  if (ctx->n_materials > 256) return fail(ctx, PV_ERR_CAPACITY, "backward supports at most 256 materials");
-  CK(pv::launch_energy_bwd(ctx->d_scene, ctx->d_path_tiles, path_blocks(store->n_paths), d_albedo, d_power, d_gE,
-                           ctx->n_materials, ctx->n_lights, ctx->d_partial, d_g_albedo, d_g_power, ctx->stream));
+  if (ctx->n_materials > pv::kMaxGradMaterials) return fail(ctx, PV_ERR_CAPACITY, "backward supports at most 256 materials");
+  CK(pv::launch_energy_bwd(ctx->d_scene, store->n_paths, store->max_bounces, d_albedo, d_power, d_gE, ctx->n_materials,
+                           ctx->n_lights, (uint32_t)ctx->n_cu, ctx->d_partial, d_g_albedo, d_g_power, ctx->stream));
   return PV_OK;
 }
 

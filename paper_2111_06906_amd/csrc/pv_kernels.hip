@@ -10,7 +10,7 @@
 //   k_mark_all      full invalidation (baseline / frame 0)
 //   k_retrace       persistent re-trace over the device work queue
 //   k_photon_count / k_photon_scatter   compaction of existing photons
-//   k_energy_fwd / k_energy_bwd / k_reduce_partials   differentiation form
+//   k_energy_fwd / k_energy_bwd / k_energy_sum   differentiation form
 #include "pv_device.h"
 #include "pv_launch.h"
 
@@ -1666,6 +1666,28 @@ __global__ __launch_bounds__(kBlock) void k_photon_scatter(const SceneDev* __res
 // ---------------------------------------------------------------------------
 // differentiation form
 
+// Three floats of a [..][3] array as one 12-byte access.
+struct F3 {
+  float x, y, z;
+};
+
+// hit ids of a path's rows but the last, all requested before the first is
+// used and without waiting for the path's length: rows past its end are in
+// bounds (row min(r, B - 1)) and their values unused
+template <int kRows>
+__device__ inline void load_hits(const SceneDev& S, uint32_t p, uint32_t* hit) {
+  const PV_GLOBAL float4* pos = G(S.pos);
+#pragma unroll
+  for (int r = 0; r + 1 < kRows; ++r)
+    hit[r] = __float_as_uint(pos[(size_t)min((uint32_t)r, S.B - 1) * S.stride + p].w);
+}
+
+// Deposited energies, one thread per path.  Bound by memory: 16 B of every
+// photon row but the last (a hit id takes its row's whole line) and 12 B
+// written per slot.  Measured at 1M paths x 7 rows of a 50k-triangle scene,
+// one MI355X: 43 us, 4.2 TB/s of row lines and output
+// (45 us with the rows read one after another).
+template <int kRows>
 __global__ __launch_bounds__(kBlock) void k_energy_fwd(const SceneDev* __restrict__ scenes, const uint2* __restrict__ tiles,
                                                        const float* __restrict__ albedo, const float* __restrict__ power,
                                                        float* __restrict__ E) {
@@ -1673,89 +1695,205 @@ __global__ __launch_bounds__(kBlock) void k_energy_fwd(const SceneDev* __restric
   const SceneDev& S = scenes[tile.x];
   uint32_t p = tile.y + threadIdx.x;
   if (p >= S.n_paths) return;
-  uint32_t n = min(info_nseg(S.info[p]), S.B);
+  uint32_t hit[kRows];
+  load_hits<kRows>(S, p, hit);
+  uint32_t n = min(info_nseg(G(S.info)[p]), S.B);
   int l = light_of(S, p);
   if (l < 0) return;
   float N = (float)S.lights[l].path_count;
   float3 e = f3(__fdiv_rn(power[3 * l], N), __fdiv_rn(power[3 * l + 1], N), __fdiv_rn(power[3 * l + 2], N));
   const size_t np = S.n_paths;
-  for (uint32_t r = 0; r < S.B; ++r) {
-    float* o = E + 3 * ((size_t)r * np + p);
-    if (r < n) {
+#pragma unroll
+  for (int r = 0; r < kRows; ++r) {
+    if ((uint32_t)r >= S.B) break;
+    F3 o{0.0f, 0.0f, 0.0f};
+    if ((uint32_t)r < n) {
       if (r > 0) {
-        uint32_t m = mat_of(S, __float_as_uint(S.pos[(size_t)(r - 1) * S.stride + p].w));
+        const uint32_t m = mat_of(S, hit[r - 1]);
         e = f3(__fmul_rn(e.x, albedo[3 * m]), __fmul_rn(e.y, albedo[3 * m + 1]), __fmul_rn(e.z, albedo[3 * m + 2]));
       }
-      o[0] = e.x;
-      o[1] = e.y;
-      o[2] = e.z;
-    } else {
-      o[0] = o[1] = o[2] = 0.0f;
+      o = F3{e.x, e.y, e.z};
     }
+    *reinterpret_cast<F3*>(E + 3 * ((size_t)r * np + p)) = o;
   }
 }
 
-// One thread per path.  With P_j = prod_{i<j} rho_i (photon j has energy
-// Phi/N * P_j) and R_i = g_{i+1} + rho_{i+1} R_{i+1} (R_{n-1} = 0, photon
-// rows 0..n-1, vertex i = row i), the contribution of vertex i to the
+// Gradients, one thread per path.  With P_j = prod_{i<j} rho_i (photon j has
+// energy Phi/N * P_j) and R_i = g_{i+1} + rho_{i+1} R_{i+1} (R_{n-1} = 0,
+// photon rows 0..n-1, vertex i = row i), the contribution of vertex i to the
 // albedo gradient is Phi/N * P_i * R_i (division free), and the power
-// gradient is sum_j g_j P_j / N.  Block partials go to
-// partial[block][M*3 + L*3], which a fixed-order FP64 reduction sums across
-// blocks; inside a block the contributions meet in FP32 LDS atomics, whose
-// order follows the scheduling, so the gradients agree from run to run only
-// to FP32 rounding of those sums, not bit for bit.
-__global__ __launch_bounds__(kBlock) void k_energy_bwd(const SceneDev* __restrict__ scenes, const uint2* __restrict__ tiles,
-                                                       const float* __restrict__ albedo, const float* __restrict__ power,
-                                                       const float* __restrict__ gE, uint32_t n_mat,
-                                                       float* __restrict__ partial) {
-  extern __shared__ float acc[];  // n_mat*3 + n_lights*3
-  uint2 tile = tiles[blockIdx.x];
-  const SceneDev& S = scenes[tile.x];
-  const uint32_t width = 3 * (n_mat + S.n_lights);
-  for (uint32_t i = threadIdx.x; i < width; i += blockDim.x) acc[i] = 0.0f;
-  __syncthreads();
-  uint32_t p = tile.y + threadIdx.x;
-  if (p < S.n_paths) {
-    uint32_t n = min(info_nseg(S.info[p]), S.B);
-    int l = light_of(S, p);
-    if (l < 0) n = 0;
-    float N = l >= 0 ? (float)S.lights[l].path_count : 1.0f;
-    const size_t np = S.n_paths;
-    uint32_t mats[PV_MAX_BOUNCES];
-    for (uint32_t r = 0; r + 1 < n; ++r) mats[r] = mat_of(S, __float_as_uint(S.pos[(size_t)r * S.stride + p].w));
-    for (int c = 0; c < 3; ++c) {
-      // prefix products P_r for r = 0..n-1
-      float P[PV_MAX_BOUNCES];
-      float pr = 1.0f;
-      float gp = 0.0f;
-      for (uint32_t r = 0; r < n; ++r) {
-        if (r > 0) pr *= albedo[3 * mats[r - 1] + c];
-        P[r] = pr;
-        gp += gE[3 * ((size_t)r * np + p) + c] * pr;
-      }
-      if (n == 0) break;
-      atomicAdd(&acc[3 * n_mat + 3 * l + c], gp / N);
-      float scale = power[3 * l + c] / N;
-      float R = 0.0f;
-      for (int i = (int)n - 2; i >= 0; --i) {
-        // R_i = g_{i+1} + rho_{i+1} R_{i+1}
-        float g1 = gE[3 * ((size_t)(i + 1) * np + p) + c];
-        float rho1 = (i + 1 <= (int)n - 2) ? albedo[3 * mats[i + 1] + c] : 0.0f;
-        R = g1 + rho1 * R;
-        atomicAdd(&acc[3 * mats[i] + c], scale * P[i] * R);
+// gradient is sum_j g_j P_j / N.
+//
+// A resident grid of single-wave workgroups walks the paths 64 at a time.
+// Every path's rows and upstream gradients are read once into registers; the
+// sums are kept in LDS as 'cols' columns of FP32 accumulators per material
+// and light, [row][column][channel], a lane adding to the column lane mod
+// cols by a plain read, add and write: with 64 columns no two lanes meet,
+// with fewer the lanes that share a column take turns.  LDS float atomics on
+// one shared set cost about 120 cycles a wave instruction whatever the
+// conflicts (one or 64 copies timed the same) and were more than half of the
+// kernel.  Every kGradFold rounds the columns are folded into FP64 registers,
+// so an FP32 accumulator takes fewer additions than the 256 paths of a tile
+// would give it; each workgroup's FP64 sums go to their own slots, which
+// k_energy_sum adds in a fixed order (FP64 atomics of every workgroup on one
+// set took about 100 us).  Bound by memory: 16 B of every photon row but the
+// last and 12 B of upstream gradient per photon.  Measured at 1M paths x 7
+// rows, 32 materials, one MI355X: 68 us and 7 us for
+// the sum, 2.6 TB/s of row lines and gradients (143 us and 901 us with LDS
+// atomics, three reads of the gradients and one thread per accumulator
+// summing 3907 parts).
+template <int kRows>
+__global__ __launch_bounds__(64) void k_energy_bwd(const SceneDev* __restrict__ scenes, const float* __restrict__ albedo,
+                                                   const float* __restrict__ power, const float* __restrict__ gE,
+                                                   uint32_t n_mat, uint32_t cols, double* __restrict__ part) {
+  extern __shared__ float sh[];
+  const SceneDev& S = scenes[0];
+  const uint32_t rows = n_mat + S.n_lights, width = 3 * rows, lane = threadIdx.x;
+  float* rho_s = sh;             // [n_mat][3]
+  float* acc = sh + 3 * n_mat;  // [n_mat + n_lights][cols][3]
+  // the lights' path ranges and Phi / N, read here once: a global read inside
+  // the loop would make it wait for the loads in flight
+  __shared__ uint32_t lbase[PV_MAX_LIGHTS], lcount[PV_MAX_LIGHTS];
+  __shared__ float lscale[PV_MAX_LIGHTS][3];
+  if (lane < S.n_lights) {
+    const LightDev lt = G(S.lights)[lane];
+    lbase[lane] = lt.path_base;
+    lcount[lane] = lt.path_count;
+    for (int c = 0; c < 3; ++c) lscale[lane][c] = power[3 * lane + c] / (float)lt.path_count;
+  }
+  for (uint32_t i = lane; i < 3 * n_mat; i += 64) rho_s[i] = albedo[i];
+  const uint32_t turn = lane / cols, col = 3 * (lane & (cols - 1));
+  for (uint32_t i = lane; i < width * cols; i += 64) acc[i] = 0.0f;
+  constexpr int kOwn = (3 * (kMaxGradMaterials + PV_MAX_LIGHTS) + 63) / 64;
+  double own[kOwn];  // accumulators lane, lane + 64, ... of the width
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) own[k] = 0.0;
+  // lanes of one wave: LDS operations take effect in program order; the
+  // fence keeps the compiler from moving one lane's access across another's
+  auto sync_wave = [] {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  };
+  auto fold = [&] {
+    sync_wave();
+#pragma unroll
+    for (int k = 0; k < kOwn; ++k) {
+      const uint32_t i = lane + (uint32_t)k * 64;
+      if (i >= width) break;
+      float* a = acc + (size_t)(i / 3) * cols * 3 + i % 3;
+      for (uint32_t q = 0; q < cols; ++q) {
+        own[k] += (double)a[3 * q];
+        a[3 * q] = 0.0f;
       }
     }
+    sync_wave();
+  };
+  auto add = [&](bool on, uint32_t row, float x, float y, float z) {
+    for (uint32_t s = 0; s < 64 / cols; ++s) {
+      if (on && turn == s) {
+        float* a = acc + (size_t)row * cols * 3 + col;
+        a[0] += x;
+        a[1] += y;
+        a[2] += z;
+      }
+      sync_wave();
+    }
+  };
+  sync_wave();
+  const size_t np = S.n_paths;
+  // the next round's loads are issued before this round's sums, so that they
+  // are in flight during them
+  uint32_t info, mat[kRows], ninfo, nhit[kRows];
+  F3 g[kRows], ng[kRows];
+  auto load = [&](uint32_t base) {
+    const uint32_t p = min(base + lane, S.n_paths - 1);
+    ninfo = G(S.info)[p];
+    load_hits<kRows>(S, p, nhit);
+#pragma unroll
+    for (int r = 0; r < kRows; ++r)
+      ng[r] = *(const PV_GLOBAL F3*)(G(gE) + 3 * ((size_t)min((uint32_t)r, S.B - 1) * np + p));
+  };
+  uint32_t held = 0;  // rounds since the last fold
+  if (blockIdx.x * 64 < S.n_paths) load(blockIdx.x * 64);
+  for (uint32_t base = blockIdx.x * 64; base < S.n_paths; base += gridDim.x * 64) {
+    if (held == kGradFold) {
+      fold();
+      held = 0;
+    }
+    ++held;
+    const uint32_t p = min(base + lane, S.n_paths - 1);
+    info = ninfo;
+#pragma unroll
+    for (int r = 0; r < kRows; ++r) {
+      g[r] = ng[r];
+      if (r + 1 < kRows) mat[r] = mat_of(S, nhit[r]);
+    }
+    if (base + gridDim.x * 64 < S.n_paths) load(base + gridDim.x * 64);  // uniform
+    int l = -1;
+    for (uint32_t i = 0; i < S.n_lights; ++i) l = p - lbase[i] < lcount[i] ? (int)i : l;
+    // lanes past the last path, paths without a photon or a light add nothing
+    const uint32_t n = base + lane < S.n_paths && l >= 0 ? min(info_nseg(info), S.B) : 0u;
+    float rho[kRows][3];
+#pragma unroll
+    for (int r = 0; r + 1 < kRows; ++r) {
+      for (int c = 0; c < 3; ++c) rho[r][c] = rho_s[3 * mat[r] + c];
+    }
+    const int lc = max(l, 0);
+    const float N = (float)max(lcount[lc], 1u);
+    float P[kRows][3], gp[3], R[3], scale[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      float pr = 1.0f;
+      gp[c] = 0.0f;
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        if ((uint32_t)r < n) {
+          if (r > 0) pr *= rho[r - 1][c];
+          gp[c] += (c == 0 ? g[r].x : (c == 1 ? g[r].y : g[r].z)) * pr;
+        }
+        P[r][c] = pr;
+      }
+      scale[c] = lscale[lc][c];
+      R[c] = 0.0f;
+    }
+    add(n > 0, n_mat + (uint32_t)lc, gp[0] / N, gp[1] / N, gp[2] / N);
+#pragma unroll
+    for (int i = kRows - 2; i >= 0; --i) {
+      const bool on = (uint32_t)(i + 1) < n;
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        // R_i = g_{i+1} + rho_{i+1} R_{i+1}
+        const float g1 = c == 0 ? g[i + 1].x : (c == 1 ? g[i + 1].y : g[i + 1].z);
+        const float rho1 = (uint32_t)(i + 2) < n ? rho[i + 1 < kRows - 1 ? i + 1 : 0][c] : 0.0f;
+        R[c] = on ? g1 + rho1 * R[c] : 0.0f;
+      }
+      add(on, mat[i], scale[0] * P[i][0] * R[0], scale[1] * P[i][1] * R[1], scale[2] * P[i][2] * R[2]);
+    }
   }
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < width; i += blockDim.x) partial[(size_t)blockIdx.x * width + i] = acc[i];
+  fold();
+#pragma unroll
+  for (int k = 0; k < kOwn; ++k) {
+    const uint32_t i = lane + (uint32_t)k * 64;
+    if (i < width) part[(size_t)blockIdx.x * width + i] = own[k];
+  }
 }
 
-__global__ void k_reduce_partials(const float* __restrict__ partial, uint32_t n_blocks, uint32_t width,
-                                  float* __restrict__ g_albedo, uint32_t n_mat3, float* __restrict__ g_power) {
-  uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= width) return;
+// sums of the workgroups' parts: 16 accumulators per workgroup, 16 threads
+// each (every 16th part, then a fixed-order tree)
+__global__ __launch_bounds__(kBlock) void k_energy_sum(const double* __restrict__ part, uint32_t n_parts, uint32_t width,
+                                                       float* __restrict__ g_albedo, uint32_t n_mat3,
+                                                       float* __restrict__ g_power) {
+  __shared__ double sh[16][17];
+  const uint32_t e = threadIdx.x & 15u, q = threadIdx.x >> 4, i = blockIdx.x * 16 + e;
   double s = 0.0;
-  for (uint32_t b = 0; b < n_blocks; ++b) s += (double)partial[(size_t)b * width + i];
+  if (i < width) {
+#pragma unroll 8
+    for (uint32_t b = q; b < n_parts; b += 16) s += part[(size_t)b * width + i];
+  }
+  sh[e][q] = s;
+  __syncthreads();
+  if (q != 0 || i >= width) return;
+  for (uint32_t k = 1; k < 16; ++k) s += sh[e][k];
   if (i < n_mat3)
     g_albedo[i] = (float)s;
   else
@@ -2035,25 +2173,55 @@ hipError_t launch_scene_photon_base(const SceneDev* scenes, int n_scenes, const 
   return hipGetLastError();
 }
 
-hipError_t launch_energy_fwd(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const float* albedo,
-                             const float* power, float* E, hipStream_t s) {
+// rows of the per-path register arrays: 8 for the usual bounce limits, else
+// all PV_MAX_BOUNCES
+constexpr int kFewRows = 8;
+
+hipError_t launch_energy_fwd(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t B,
+                             const float* albedo, const float* power, float* E, hipStream_t s) {
   if (!n_tiles) return hipSuccess;
-  hipLaunchKernelGGL(k_energy_fwd, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, albedo, power, E);
+  if (B <= (uint32_t)kFewRows)
+    hipLaunchKernelGGL(k_energy_fwd<kFewRows>, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, albedo, power, E);
+  else
+    hipLaunchKernelGGL(k_energy_fwd<PV_MAX_BOUNCES>, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, albedo, power,
+                       E);
   return hipGetLastError();
 }
 
-hipError_t launch_energy_bwd(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const float* albedo,
-                             const float* power, const float* gE, uint32_t n_mat, uint32_t n_lights, float* partial,
-                             float* g_albedo, float* g_power, hipStream_t s) {
-  uint32_t width = 3 * (n_mat + n_lights);
-  if (n_tiles) {
-    hipLaunchKernelGGL(k_energy_bwd, dim3(n_tiles), dim3(kBlock), width * sizeof(float), s, scenes, tiles, albedo,
-                       power, gE, n_mat, partial);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(k_reduce_partials, dim3((width + 255) / 256), dim3(256), 0, s, partial, n_tiles, width, g_albedo,
-                     3 * n_mat, g_power);
+// Columns of the gradient accumulators: as many (a power of two, at most one
+// per lane) as keep a wave's accumulators near 26 KB, six waves per compute
+// unit at 32 materials; at 256 materials eight lanes take turns on a column.
+static uint32_t grad_cols(uint32_t rows) {
+  uint32_t cols = 64;
+  while (cols > 8 && rows * cols * 12 > 27 * 1024) cols >>= 1;
+  return cols;
+}
+// LDS bytes of a workgroup: the accumulators and the albedos (rows: materials and lights)
+static uint32_t grad_lds(uint32_t rows) { return rows * (grad_cols(rows) + 1) * 12; }
+// single-wave workgroups per compute unit: what the LDS holds, at most 16
+static uint32_t grad_waves_per_cu(uint32_t rows) { return std::min(16u, 160u * 1024 / grad_lds(rows)); }
+
+uint32_t grad_part_words(uint32_t n_cu) {
+  uint32_t most = 0;
+  for (uint32_t rows = 2; rows <= kMaxGradMaterials + PV_MAX_LIGHTS; ++rows)
+    most = std::max(most, grad_waves_per_cu(rows) * 3 * rows);
+  return most * n_cu;
+}
+
+hipError_t launch_energy_bwd(const SceneDev* scene, uint32_t n_paths, uint32_t B, const float* albedo,
+                             const float* power, const float* gE, uint32_t n_mat, uint32_t n_lights, uint32_t n_cu,
+                             double* part, float* g_albedo, float* g_power, hipStream_t s) {
+  if (n_mat < 1 || n_mat > kMaxGradMaterials || n_lights < 1 || n_lights > PV_MAX_LIGHTS) return hipErrorInvalidValue;
+  const uint32_t rows = n_mat + n_lights, width = 3 * rows, cols = grad_cols(rows);
+  // an empty store: one workgroup writes zero sums
+  const dim3 g(std::max(1u, std::min((n_paths + 63) / 64, n_cu * grad_waves_per_cu(rows))));
+  const size_t lds = grad_lds(rows);
+  if (B <= (uint32_t)kFewRows)
+    hipLaunchKernelGGL(k_energy_bwd<kFewRows>, g, dim3(64), lds, s, scene, albedo, power, gE, n_mat, cols, part);
+  else
+    hipLaunchKernelGGL(k_energy_bwd<PV_MAX_BOUNCES>, g, dim3(64), lds, s, scene, albedo, power, gE, n_mat, cols, part);
+  hipLaunchKernelGGL(k_energy_sum, dim3((width + 15) / 16), dim3(kBlock), 0, s, part, g.x, width, g_albedo, 3 * n_mat,
+                     g_power);
   return hipGetLastError();
 }
 

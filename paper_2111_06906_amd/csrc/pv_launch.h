@@ -97,10 +97,15 @@ struct DmWork {
 hipError_t launch_dm_update(const SceneDev* table, const SceneDev* scene, const uint2* tiles, uint32_t n_tiles,
                             uint32_t cells, uint32_t n_lights, const DmWork& D, uint32_t* block_cnt, uint64_t seed,
                             uint32_t frame, const uint32_t* frame_ptr, hipStream_t s);
-hipError_t launch_energy_fwd(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const float* albedo,
-                             const float* power, float* E, hipStream_t s);
-hipError_t launch_energy_bwd(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const float* albedo,
-                             const float* power, const float* gE, uint32_t n_mat, uint32_t n_lights, float* partial,
-                             float* g_albedo, float* g_power, hipStream_t s);
+hipError_t launch_energy_fwd(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t B,
+                             const float* albedo, const float* power, float* E, hipStream_t s);
+// Gradients over one scene's store.  part: grad_part_words(n_cu) doubles, the
+// sums of each workgroup
+constexpr uint32_t kMaxGradMaterials = 256;
+constexpr uint32_t kGradFold = 32;  // rounds of 64 paths between two folds into FP64
+uint32_t grad_part_words(uint32_t n_cu);
+hipError_t launch_energy_bwd(const SceneDev* scene, uint32_t n_paths, uint32_t B, const float* albedo,
+                             const float* power, const float* gE, uint32_t n_mat, uint32_t n_lights, uint32_t n_cu,
+                             double* part, float* g_albedo, float* g_power, hipStream_t s);
 
 }  // namespace pv
