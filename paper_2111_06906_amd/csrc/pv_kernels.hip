@@ -1603,11 +1603,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
     unsigned long long b = block_sum_u64(n_photons, sred);
     unsigned long long c = block_sum_u64(n_acc, sred);
     unsigned long long d = block_sum_u64(n_trunc, sred);
+    // most workgroups of a short queue have nothing to add, and additions to
+    // one line serialise: 2048 workgroups' four cost 90 us of a 123 us launch
+    // over 2000 paths, and about 50 us of every frame
     if (threadIdx.x == 0) {
-      atomicAdd(&stats->rays_traced, a);
-      atomicAdd(&stats->photons_written, b);
-      atomicAdd(&stats->reuse_accepted, c);
-      atomicAdd(&stats->paths_truncated, d);
+      if (a) atomicAdd(&stats->rays_traced, a);
+      if (b) atomicAdd(&stats->photons_written, b);
+      if (c) atomicAdd(&stats->reuse_accepted, c);
+      if (d) atomicAdd(&stats->paths_truncated, d);
     }
   }
 }
