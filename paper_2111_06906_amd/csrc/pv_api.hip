@@ -29,6 +29,7 @@ using pv::Node;
 using pv::ObjDev;
 using pv::SceneDev;
 using pv::Tri;
+using pv::Wide;
 
 namespace {
 
@@ -558,6 +559,66 @@ void host_boxes(HostBvh& h, const float* v9_leaf_order, float extra = 0.0f) {
   }
 }
 
+// The four-wide form of a binary hierarchy: from a node's two children, the
+// internal one of largest surface area is replaced by its own two until there
+// are four; empty slots are never entered.  The boxes are taken
+// from 'h' (host_boxes), quantised into the grid (qc, qs).  Appends to 'out',
+// whose indices and the leaves' codes are absolute ('leaf' maps a leaf code
+// of h); slot[2 i + side] names the slot that took child 'side' of node i.
+// Returns the root code.
+template <typename LeafMap>
+int32_t build_wide(const HostBvh& h, const float qc[3], float qs, LeafMap leaf, std::vector<Wide>& out,
+                   std::vector<uint32_t>* slot) {
+  if (h.root < 0) return leaf(h.root);
+  if (slot) slot->assign(2 * h.nodes.size(), pv::kSlotNone);
+  struct Ref {
+    int32_t node;   // binary node holding the child's box
+    uint32_t side;
+  };
+  auto box = [&](Ref r) { return reinterpret_cast<const float*>(&h.nodes[r.node]) + 6 * r.side; };
+  auto code = [&](Ref r) { return r.side ? h.nodes[r.node].d.y : h.nodes[r.node].d.x; };
+  auto area = [&](Ref r) {
+    const float* b = box(r);
+    const float x = b[3] - b[0], y = b[4] - b[1], z = b[5] - b[2];
+    return x * y + y * z + z * x;
+  };
+  struct Item {
+    int32_t node;     // binary node to collapse
+    uint32_t parent;  // four-wide node and slot that name it (kSlotNone: the root)
+  };
+  const uint32_t base = (uint32_t)out.size();
+  std::vector<Item> stack{{h.root, pv::kSlotNone}};
+  while (!stack.empty()) {
+    const Item it = stack.back();
+    stack.pop_back();
+    Ref c[4] = {{it.node, 0}, {it.node, 1}, {-1, 0}, {-1, 0}};
+    uint32_t n = 2;
+    while (n < 4) {
+      int best = -1;
+      for (uint32_t k = 0; k < n; ++k)
+        if (code(c[k]) >= 0 && (best < 0 || area(c[k]) > area(c[best]))) best = (int)k;
+      if (best < 0) break;
+      const int32_t open = code(c[best]);
+      c[best] = {open, 0};
+      c[n++] = {open, 1};
+    }
+    const uint32_t id = (uint32_t)out.size();
+    if (it.parent != pv::kSlotNone) out[it.parent >> 2].child[it.parent & 3u] = (int32_t)id;
+    Wide w{};
+    for (uint32_t k = 0; k < 4; ++k) {
+      for (int ax = 0; ax < 3; ++ax)
+        w.plane[3 * k + ax] =
+            k < n ? pv::wide_planes(box(c[k])[ax], box(c[k])[3 + ax], qc[ax], qs) : pv::kPlanesNone;
+      if (k < n && code(c[k]) < 0) w.child[k] = leaf(code(c[k]));
+      if (k < n && slot) (*slot)[2 * (size_t)c[k].node + c[k].side] = 4 * id + k;
+    }
+    out.push_back(w);
+    for (uint32_t k = n; k-- > 0;)
+      if (code(c[k]) >= 0) stack.push_back({code(c[k]), 4 * id + k});
+  }
+  return (int32_t)base;
+}
+
 bool finite_all(const float* p, size_t n) {
   for (size_t i = 0; i < n; ++i)
     if (!std::isfinite(p[i])) return false;
@@ -876,9 +937,12 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
 
     // static world: topology + boxes on the host
     std::vector<Node> nodes;  // static, then objects, then the top-level trees
+    std::vector<Wide> wide;   // their four-wide forms
     std::vector<Tri> stris;
     hs.n_static = S;
-    hs.sroot = pv::kRootNone;
+    hs.sroot = hs.swroot = pv::kRootNone;
+    hs.qs = 64.0f;  // without static triangles: coordinates of about 1 mid-range
+    hs.qinv = 1.0f / 64.0f;
     uint32_t depth = 0, obj_depth = 0;  // deepest leaf: all hierarchies, object hierarchies
     for (int k = 0; k < 3; ++k) {
       hs.sbox[k] = INFINITY;
@@ -901,8 +965,6 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       if (hb.max_depth > kMaxDepth) return fail(ctx, PV_ERR_CAPACITY, "static hierarchy too deep");
       depth = std::max(depth, hb.max_depth);
       host_boxes(hb, v9.data());
-      nodes = std::move(hb.nodes);
-      hs.sroot = hb.root;
       for (size_t i = 0; i < v9.size(); ++i) {
         const int k = (int)(i % 3);
         hs.sbox[k] = std::min(hs.sbox[k], v9[i]);
@@ -912,6 +974,22 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         hs.sbox[k] = pad_lo(hs.sbox[k]);
         hs.sbox[3 + k] = pad_hi(hs.sbox[3 + k]);
       }
+      // the planes' grid: centred on the static world, the largest half
+      // extent scaled to (128, 256] by a power of two: objects up to 255
+      // times as far out keep finite planes, planes under 2^-22 of the half
+      // extent from the centre lose digits
+      float half = 0.0f;
+      for (int k = 0; k < 3; ++k) {
+        hs.qc[k] = 0.5f * (hs.sbox[k] + hs.sbox[3 + k]);
+        half = std::max(half, 0.5f * (hs.sbox[3 + k] - hs.sbox[k]));
+      }
+      int ex = 0;
+      if (half > 0.0f && std::isfinite(half)) (void)std::frexp(half, &ex);
+      hs.qs = std::ldexp(1.0f, std::min(100, std::max(-100, 8 - ex)));
+      hs.qinv = 1.0f / hs.qs;
+      hs.swroot = build_wide(hb, hs.qc, hs.qs, [](int32_t c) { return c; }, wide, nullptr);
+      nodes = std::move(hb.nodes);
+      hs.sroot = hb.root;
     }
 
     const uint32_t static_depth = depth;
@@ -922,7 +1000,8 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     std::vector<uint32_t> level_nodes, level_off;
     std::vector<uint4> dspan;          // per object node: its children's record ranges
     std::vector<uint32_t> dspan_obj;   // and its object
-    std::vector<Node> onodes;          // the objects' topologies with object-space boxes
+    std::vector<Wide> owide;           // the objects' four-wide topologies with object-space boxes
+    std::vector<uint2> wslot;          // per object node: the four-wide slots of its children
     const uint32_t obj_node_first = (uint32_t)nodes.size();
     uint32_t tri_base = 0, gbase = S;
     for (uint32_t o = 0; o < d->n_objects; ++o) {
@@ -989,22 +1068,19 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       ob.n_nodes = (uint32_t)hb.nodes.size();
       ob.root = rebase(hb.root);
       {
-        // the same topology with fixed object-space boxes; internal child
-        // codes count from the region's start until it is placed below
+        // the four-wide forms: with world boxes written each frame, and with
+        // fixed object-space boxes (node codes counted from the region's
+        // start until it is placed below)
         std::vector<float> lv9(9 * (size_t)n);
         for (uint32_t i = 0; i < n; ++i)
           std::memcpy(&lv9[9 * (size_t)i], v + 9 * (size_t)hb.order[i], 9 * sizeof(float));
-        HostBvh os = hb;
-        host_boxes(os, lv9.data(), kObjSpacePad);
-        const int32_t obase = (int32_t)onodes.size();
-        auto orebase = [&](int32_t c) { return c >= 0 ? c + obase : rebase(c); };
-        for (Node nd : os.nodes) {
-          nd.d.x = orebase(nd.d.x);
-          nd.d.y = orebase(nd.d.y);
-          nd.d.z = -1;
-          onodes.push_back(nd);
-        }
-        ob.oroot = orebase(hb.root);
+        host_boxes(hb, lv9.data(), kObjSpacePad);
+        auto leaf = [&](int32_t c) { return rebase(c); };
+        std::vector<uint32_t> slot;
+        ob.wroot = ob.sah_wroot = build_wide(hb, hs.qc, hs.qs, leaf, wide, &slot);
+        for (size_t i = 0; i < slot.size(); i += 2) wslot.push_back(make_uint2(slot[i], slot[i + 1]));
+        const float zero[3] = {0.0f, 0.0f, 0.0f};
+        ob.oroot = build_wide(hb, zero, hs.qs, leaf, owide, nullptr);
       }
       tri_base += n;
       gbase += n;
@@ -1016,6 +1092,8 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       objs[o].sah_root = objs[o].root;
       objs[o].lbvh_base = (uint32_t)nodes.size();
       nodes.resize(nodes.size() + (objs[o].n_tris - 1), Node{});
+      objs[o].lbvh_wbase = (uint32_t)wide.size();
+      wide.resize(wide.size() + (objs[o].n_tris - 1), Wide{});
     }
     const uint32_t lbvh_nodes = (uint32_t)nodes.size() - lbvh_first;
     // traversal addresses node records by a 32-bit byte offset
@@ -1023,26 +1101,31 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       return fail(ctx, PV_ERR_CAPACITY, "too many hierarchy nodes");
     hs.top_base = (uint32_t)nodes.size();
     nodes.resize(nodes.size() + 2 * (size_t)pv::kTopNodes, Node{});
-    // the object-space copies after the top-level trees
-    hs.onode_first = (uint32_t)nodes.size();
-    for (Node nd : onodes) {
-      if (nd.d.x >= 0) nd.d.x += (int32_t)hs.onode_first;
-      if (nd.d.y >= 0) nd.d.y += (int32_t)hs.onode_first;
-      nodes.push_back(nd);
+    hs.wtop_base = (uint32_t)wide.size();
+    wide.resize(wide.size() + 2 * (size_t)pv::kTopNodes, Wide{});
+    // the object-space forms after the top-level trees
+    const int32_t ofirst = (int32_t)wide.size();
+    for (Wide w : owide) {
+      for (int32_t& c : w.child)
+        if (c > 0) c += ofirst;  // 0: an unused slot, or a tree's own root, which no node names
+      wide.push_back(w);
     }
     for (ObjDev& ob : objs)
-      if (ob.oroot >= 0) ob.oroot += (int32_t)hs.onode_first;
-    if (nodes.size() * sizeof(Node) > (size_t)UINT32_MAX) return fail(ctx, PV_ERR_CAPACITY, "too many hierarchy nodes");
+      if (ob.oroot >= 0) ob.oroot += ofirst;
+    if (wide.size() * sizeof(Wide) > (size_t)UINT32_MAX) return fail(ctx, PV_ERR_CAPACITY, "too many hierarchy nodes");
     Node* d_nodes;
+    Wide* d_wide;
     Tri* d_tris;
     float* d_dlocal;
     uint32_t *d_dgid, *d_lnodes, *d_loff;
     ObjDev* d_objs;
     CK(upload(A, &d_nodes, nodes.data(), nodes.size(), s));
+    CK(upload(A, &d_wide, wide.data(), wide.size(), s));
     CK(dalloc(A, &d_tris, (size_t)S + n_dyn));
     if (S) CK(hipMemcpyAsync(d_tris, stris.data(), sizeof(Tri) * S, hipMemcpyHostToDevice, s));
     const int32_t no_roots[2] = {pv::kRootNone, pv::kRootNone};  // set per frame by the top-level build
     CK(upload(A, &hs.top, no_roots, 2, s));
+    CK(upload(A, &hs.wtop, no_roots, 2, s));
     CK(upload(A, &d_dlocal, dlocal.data(), dlocal.size(), s));
     CK(upload(A, &d_dgid, dgid.data(), dgid.size(), s));
     {
@@ -1069,6 +1152,9 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       uint32_t* d_span_obj;
       CK(upload(A, &d_span, dspan.data(), dspan.size(), s));
       CK(upload(A, &d_span_obj, dspan_obj.data(), dspan_obj.size(), s));
+      uint2* d_wslot;
+      CK(upload(A, &d_wslot, wslot.data(), wslot.size(), s));
+      hs.wslot = d_wslot;
       hs.dspan = d_span;
       hs.dspan_obj = d_span_obj;
     }
@@ -1093,6 +1179,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       lw.n_nodes = lbvh_nodes;
     }
     hs.nodes = d_nodes;
+    hs.wide = d_wide;
     hs.tris = d_tris;
     hs.dlocal = d_dlocal;
     hs.dtri_gid = d_dgid;

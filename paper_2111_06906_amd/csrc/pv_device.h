@@ -31,17 +31,23 @@ __device__ __forceinline__ const PV_GLOBAL T* G(const T* p) {
 
 constexpr int kBlock = 256;        // threads per block of the streaming kernels
 // Traversal stack: entries per lane, all in LDS (dynamic shared memory sized
-// per launch from the scene's hierarchy depths).  A depth-first walk holds at
-// most one entry per internal ancestor of the node it visits, plus the
-// sentinel at the bottom, and writes the far child one slot above the top:
-// a walk through a top-level tree of depth t into a hierarchy of depth d needs
-// t + d + 2 entries.
+// per launch from the scene's hierarchy depths).  A depth-first walk of a
+// binary hierarchy holds at most one entry per internal ancestor of the node
+// it visits, plus the sentinel at the bottom, and writes the far child one
+// slot above the top: a walk through a top-level tree of depth t into a
+// hierarchy of depth d needs t + d + 2 entries.  A four-wide walk leaves up to
+// three entries per node; it gives up before it would pass the same number
+// (walk_run) and the binary walk answers the query.
 constexpr int kMaxStack = 40;
 constexpr int kTopDepth = 7;  // top-level tree depth bound (the static root beside a median split of <= 64 objects)
 constexpr int kMaxDepth = kMaxStack - kTopDepth - 2;
+// the walk_run of a shallow scene: the sentinel, the entries of one full node
+// and one slot above them
+constexpr uint32_t kMinStack = 12;
 static_assert((1 << (kTopDepth - 1)) >= PV_MAX_OBJECTS, "top-level depth bound");
 __host__ __device__ inline uint32_t stack_entries(uint32_t top_depth, uint32_t depth) {
-  return top_depth + depth + 2;
+  const uint32_t n = top_depth + depth + 2;
+  return n > kMinStack ? n : kMinStack;
 }
 constexpr uint32_t kHitNone = 0xFFFFFFFFu;
 
@@ -74,6 +80,49 @@ __host__ __device__ inline int leaf_code(uint32_t first, uint32_t count) {
 __host__ __device__ inline uint32_t leaf_first(int code) { return ((uint32_t)~code) >> 3; }
 __host__ __device__ inline uint32_t leaf_count(int code) { return (((uint32_t)~code) & 7u) + 1u; }
 
+// Four-wide node of one 64-byte line: the walks' own form of the hierarchies.
+// Planes are FP16 in the scene's grid, (coordinate - qc) * qs with qs a power
+// of two, rounded outwards, so a quantised box contains its FP32 box; child
+// k's planes are words 3 k .. 3 k + 2, (lower plane | upper plane << 16) per
+// axis; codes as in Node.  An unused slot holds +inf in every plane, which no
+// query's interval reaches.
+struct alignas(64) Wide {
+  uint32_t plane[12];
+  int32_t child[4];
+};
+constexpr uint32_t kPlanesNone = 0x7C007C00u;  // +inf, +inf
+constexpr uint32_t kSlotNone = 0xFFFFFFFFu;
+
+__host__ __device__ inline uint32_t float_bits(float x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __float_as_uint(x);
+#else
+  uint32_t u;
+  __builtin_memcpy(&u, &x, 4);
+  return u;
+#endif
+}
+
+// the largest FP16 value not above x, never a subnormal (a plane between 0
+// and the smallest normal value goes outwards to one of the two)
+__host__ __device__ inline uint32_t half_down(float x) {
+  if (!(x < 65504.0f)) return 0x7BFFu;
+  if (x < -65504.0f) return 0xFC00u;
+  const uint32_t u = float_bits(x), m = u & 0x7FFFFFFFu;
+  if (m < 0x38800000u) return (u >> 31) && m ? 0x8400u : 0u;
+  const uint32_t h = (m - 0x38000000u) >> 13;
+  return (u >> 31) ? 0x8000u | (h + ((m & 0x1FFFu) ? 1u : 0u)) : h;
+}
+__host__ __device__ inline uint32_t half_up(float x) { return half_down(-x) ^ 0x8000u; }
+
+// planes of one axis of a box [lo, hi] in the grid (c, s); the subtraction's
+// rounding (2^-24 of its result) goes outwards by twice as much
+__host__ __device__ inline uint32_t wide_planes(float lo, float hi, float c, float s) {
+  const float a = (lo - c) * s, b = (hi - c) * s;
+  const float ra = a < 0.0f ? -a : a, rb = b < 0.0f ? -b : b;
+  return half_down(a - ra * 1.1920929e-7f) | (half_up(b + rb * 1.1920929e-7f) << 16);
+}
+
 // Triangle record in BVH leaf order: t0 = (v0, id), t1 = (v1, material), t2 = (v2, 0).
 struct alignas(16) Tri {
   float4 t0, t1, t2;
@@ -92,7 +141,10 @@ struct ObjDev {
   uint32_t n_levels;   // depth levels holding internal nodes
   int32_t sah_root;    // root of the upload-time topology (refit each frame)
   uint32_t lbvh_base;  // first node of its region for the per-frame rebuilt radix tree
-  int32_t oroot;       // root of the upload-time topology with object-space boxes
+  int32_t oroot;       // root of the four-wide upload-time topology with object-space boxes
+  int32_t wroot;       // root of the current hierarchy's four-wide form
+  int32_t sah_wroot;   // the same of the upload-time topology
+  uint32_t lbvh_wbase; // first four-wide node of its region for the rebuilt radix tree
   uint32_t pad_;
 };
 
@@ -126,6 +178,12 @@ struct SceneDev {
   uint32_t top_base;      // first top-level node
   uint32_t n_static;
   int32_t sroot;          // static root code (kRootNone without static triangles)
+  // the four-wide form: [static][objects][rebuilt objects][2 x kTopNodes][objects in object space]
+  Wide* wide;
+  int32_t* wtop;          // [2] per frame: four-wide roots of the whole scene and of the moved objects
+  uint32_t wtop_base;     // first four-wide top-level node
+  int32_t swroot;         // static root code in 'wide'
+  float qc[3], qs, qinv;  // grid of the planes: centre, scale (a power of two), 1 / scale
   float sbox[6];          // static world box (lo, hi)
   // dynamic objects
   const float* dlocal;    // [n][9] object-space vertices in leaf order
@@ -146,10 +204,10 @@ struct SceneDev {
   const uint4* dspan;
   const uint32_t* dspan_obj;
   uint32_t obj_node_first, n_obj_nodes;
-  // the same topologies with fixed object-space boxes (padded for the error
-  // of mapping a world segment into object space), nodes [onode_first,
-  // onode_first + n_obj_nodes); ObjDev::oroot is an object's root among them
-  uint32_t onode_first;
+  // where the box of each child of those nodes goes in the four-wide form:
+  // four-wide node * 4 + slot, kSlotNone for a child whose own children took
+  // its place
+  const uint2* wslot;
   // lights
   const LightDev* lights;
   float* light_xf_cur;    // [L][12]
@@ -180,6 +238,28 @@ struct SceneDev {
   // when none; first cell of each light in the maps of all lights
   int32_t dm[4];
   uint32_t dm_off[PV_MAX_LIGHTS + 1];
+};
+
+// Writer of child boxes into four-wide slots.  Holds the grid and the array in
+// registers: read from the descriptor at every write they would be loaded
+// again after each store.
+struct PlaneWriter {
+  PV_GLOBAL Wide* wide;
+  float cx, cy, cz, s;
+  __device__ explicit PlaneWriter(const SceneDev& S)
+      : wide(G(S.wide)), cx(S.qc[0]), cy(S.qc[1]), cz(S.qc[2]), s(S.qs) {}
+  __device__ void put(uint32_t slot, float lx, float ly, float lz, float hx, float hy, float hz) const {
+    PV_GLOBAL uint32_t* w = wide[slot >> 2].plane + 3 * (slot & 3u);
+    w[0] = wide_planes(lx, hx, cx, s);
+    w[1] = wide_planes(ly, hy, cy, s);
+    w[2] = wide_planes(lz, hz, cz, s);
+  }
+  __device__ void none(uint32_t slot) const {
+    PV_GLOBAL uint32_t* w = wide[slot >> 2].plane + 3 * (slot & 3u);
+    w[0] = w[1] = w[2] = kPlanesNone;
+    wide[slot >> 2].child[slot & 3u] = 0;
+  }
+  __device__ void child(uint32_t slot, int32_t code) const { wide[slot >> 2].child[slot & 3u] = code; }
 };
 
 // Device scratch of the per-frame object hierarchy rebuild (linear BVH over
@@ -319,13 +399,24 @@ __device__ inline float box_entry(float lx, float ly, float lz, float hx, float 
   return t0 <= t1 ? t0 : __builtin_inff();
 }
 
+// entry parameter of a box regardless of the query's interval
+__device__ inline float slab_entry(float lx, float ly, float lz, float hx, float hy, float hz, const Ray& r) {
+  const float tx0 = fmaf(lx, r.inv.x, r.oi.x), tx1 = fmaf(hx, r.inv.x, r.oi.x);
+  const float ty0 = fmaf(ly, r.inv.y, r.oi.y), ty1 = fmaf(hy, r.inv.y, r.oi.y);
+  const float tz0 = fmaf(lz, r.inv.z, r.oi.z), tz1 = fmaf(hz, r.inv.z, r.oi.z);
+  return fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), fminf(tz0, tz1));
+}
+
 // Watertight ray/triangle test (Woop, Benthin, Wald, JCGT 2013), two-sided.
 // Returns true with *t when the triangle is crossed at a parameter strictly
 // inside (tmin, tmax).  The edge functions are evaluated without contraction
 // so that triangles sharing an edge see the same value with opposite sign.
 // Written without early exits (the caller's loop stays one predicated block);
 // only an exactly zero edge function takes the double-precision branch.
-__device__ inline bool tri_hit(const Ray& r, float3 v0, float3 v1, float3 v2, float tmax, float* t_out) {
+// near_tb (may be null): set when the triangle is crossed past tmin within
+// 2.5e-7 (relative) of tmax.
+__device__ inline bool tri_hit(const Ray& r, float3 v0, float3 v1, float3 v2, float tmax, float* t_out,
+                               bool* near_tb) {
   float3 A = sub(v0, r.o), B = sub(v1, r.o), C = sub(v2, r.o);
   float Akz = comp(A, r.kz), Bkz = comp(B, r.kz), Ckz = comp(C, r.kz);
   float Ax = comp(A, r.kx) - r.sx * Akz, Ay = comp(A, r.ky) - r.sy * Akz;
@@ -349,6 +440,8 @@ __device__ inline bool tri_hit(const Ray& r, float3 v0, float3 v1, float3 v2, fl
   det = neg ? -det : det;
   const bool ok = !mixed && det != 0.0f && T > r.tmin * det && T < tmax * det;
   *t_out = T / det;
+  if (near_tb)
+    *near_tb = !mixed && det != 0.0f && T > r.tmin * det && fabsf(fmaf(-tmax, det, T)) <= 2.5e-7f * T;
   return ok;
 }
 
@@ -372,10 +465,10 @@ struct Hit {
 // idling until the longest walk of the wave ends (Aila and Laine 2009,
 // dynamic ray fetch).
 //
-// The inner loop over internal nodes has no branch besides its exit: the far
-// child is always written one slot above the top of the stack and the stack
-// pointer moves by +1 (both children entered), 0 (one) or -1 (none: the top
-// entry, read ahead, becomes the next node).  A sentinel at the bottom ends
+// The inner loop over internal nodes has no branch besides its exit: each
+// further child is always written one slot above the top of the stack and the
+// stack pointer moves past it when that child is entered; when none is, the
+// top entry, read ahead, becomes the next node.  A sentinel at the bottom ends
 // the walk.
 struct Walk {
   int32_t cur;    // next node or leaf; kRootNone once the stack is exhausted
@@ -384,6 +477,7 @@ struct Walk {
   float tb;       // closest crossing so far (the ray's tmax initially)
   uint32_t gid;   // its global triangle id, kHitNone when none
   uint32_t rec;   // its record in the scene's triangle array
+  bool redo;      // the binary walk must answer: near tie, or out of stack
 };
 
 __device__ inline bool is_leaf(int32_t c) { return (uint32_t)c > 0x80000000u; }  // c < 0, c != kRootNone
@@ -398,62 +492,146 @@ __device__ inline void walk_start(Walk& w, int32_t root, float tmax, StackCol co
   w.tb = tmax;
   w.gid = kHitNone;
   w.rec = 0;
+  w.redo = false;
+}
+
+// Parameters of a query's box tests: 1 / direction and (centre - origin) /
+// direction in the planes' grid, and per axis 16 where the direction is
+// negative (the upper plane is then the nearer one).
+struct Slab {
+  float3 inv, oi;
+  uint32_t rx, ry, rz;
+};
+
+__device__ inline Slab make_slab(float3 inv, float3 oi, float scale) {
+  Slab q;
+  q.inv = mul(inv, scale);
+  q.oi = oi;
+  q.rx = inv.x < 0.0f ? 16u : 0u;
+  q.ry = inv.y < 0.0f ? 16u : 0u;
+  q.rz = inv.z < 0.0f ? 16u : 0u;
+  return q;
+}
+
+// a world-space query against the scene's four-wide nodes
+__device__ inline Slab world_slab(const SceneDev& S, const Ray& r) {
+  const float3 c = f3(S.qc[0] - r.o.x, S.qc[1] - r.o.y, S.qc[2] - r.o.z);
+  return make_slab(r.inv, f3(c.x * r.inv.x, c.y * r.inv.y, c.z * r.inv.z), S.qinv);
+}
+
+// a condition as the wave's mask, and a mask's bit of this lane: conditions
+// combined as masks are scalar work beside the vector pipeline
+__device__ __forceinline__ uint64_t wave_mask(bool c) { return __builtin_amdgcn_ballot_w64(c); }
+__device__ __forceinline__ bool lane_bit(uint64_t m) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_inverse_ballot_w64(m);
+#else
+  return m != 0;
+#endif
+}
+
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+
+// both parameters of an axis' planes, nearer one first: a rotation by the
+// axis' sign instead of a minimum and a maximum, and mixed-precision fused
+// multiply-adds that read the FP16 planes in place
+__device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, float oi, float* n, float* f) {
+  const half2v h = __builtin_bit_cast(half2v, __builtin_amdgcn_alignbit(w, w, rot));
+  *n = __builtin_fmaf((float)h.x, inv, oi);
+  *f = __builtin_fmaf((float)h.y, inv, oi);
 }
 
 // Speculative traversal (Aila and Laine 2009): a lane that reaches a leaf
 // while holding none keeps it pending and continues with the next stack
 // entry, until every lane still walking holds a leaf; then the wave tests
-// leaves together.  Leaves are tested in the same depth-first order as
-// without postponement and culling only uses an older (larger) closest
-// distance, so the result is the same.
+// leaves together.
 //
-// Boxes are tested with the slab parameters (binv, boi) and triangles with
-// the ray r itself: a walk through a rigid object's hierarchy in its own
-// object space passes the object-space ray's parameters for the boxes, with
-// the same parameter interval, while triangles stay in world space.
-__device__ inline void walk_run(const PV_GLOBAL Node* __restrict__ nodes, const PV_GLOBAL Tri* __restrict__ tris,
-                                const Ray& r, float3 binv, float3 boi, bool any, StackCol col, Walk& w,
+// Nodes are four wide with FP16 planes: one 64-byte line, four 16-byte loads,
+// per visit, as the binary FP32 node took, and about a fifth of the visits (22
+// against 109 for a ray of the 3M-path, 380k-triangle interior), so a shorter
+// chain of dependent loads and fewer of them.  Bound by vector issue: about
+// 90 instructions a visit.  Measured there, one MI355X: full trace 5.66 to
+// 4.85 ms, partial re-trace 2.30 to 1.98 ms, verification traversal 224 to
+// 178 us.
+//
+// Boxes are tested with the slab parameters q and triangles with the ray r
+// itself: a walk through a rigid object's hierarchy in its own object space
+// passes the object-space parameters for the boxes, with the same parameter
+// interval, while triangles stay in world space.
+//
+// w.redo asks the caller to take walk_exact's answer instead: set when a walk
+// would leave more entries than 'limit' (the top's address there) allows, and,
+// with kTies, when two crossings lie within 2.5e-7 of each other, twice the
+// rounding that lets the order of their tests decide.
+template <bool kTies>
+__device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const PV_GLOBAL Tri* __restrict__ tris,
+                                const Ray& r, const Slab& q, bool any, StackCol col, StackCol limit, Walk& w,
                                 int min_active) {
   int32_t cur = w.cur, leaf = w.leaf;
-  // top: the stack's top entry (entry sp - 1); the far child goes one entry
-  // above it.  Once the sentinel itself is taken top points one entry below
-  // the column's first, which every launch allocates and nothing uses.
+  // top: the stack's top entry (entry sp - 1).  Once the sentinel itself is
+  // taken top points one entry below the column's first, which every launch
+  // allocates and nothing uses.
   StackCol top = col + (w.sp - 1) * kBlock;
   float tb = w.tb;
   uint32_t gid = w.gid, rec = w.rec;
-  const float tmin = r.tmin;
+  bool redo = w.redo;
+  const float tmin = __builtin_canonicalizef(r.tmin);
   while (true) {
     while (cur >= 0) {
-      const int32_t below = top[0];
+      const int32_t below = top[0], below2 = top[-kBlock];
       // node records are addressed by a 32-bit byte offset (arrays < 4 GiB)
-      const Node nd = *(const PV_GLOBAL Node*)((const PV_GLOBAL char*)nodes + ((uint32_t)cur << 6));
-      // slab entry and exit of both children; the query interval enters by
-      // comparisons only (min/max with it would need canonical operands)
-      float tx0 = fmaf(nd.a.x, binv.x, boi.x), tx1 = fmaf(nd.a.w, binv.x, boi.x);
-      float ty0 = fmaf(nd.a.y, binv.y, boi.y), ty1 = fmaf(nd.b.x, binv.y, boi.y);
-      float tz0 = fmaf(nd.a.z, binv.z, boi.z), tz1 = fmaf(nd.b.y, binv.z, boi.z);
-      const float e0 = fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), fminf(tz0, tz1));
-      const float x0 = fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), fmaxf(tz0, tz1));
-      tx0 = fmaf(nd.b.z, binv.x, boi.x), tx1 = fmaf(nd.c.y, binv.x, boi.x);
-      ty0 = fmaf(nd.b.w, binv.y, boi.y), ty1 = fmaf(nd.c.z, binv.y, boi.y);
-      tz0 = fmaf(nd.c.x, binv.z, boi.z), tz1 = fmaf(nd.c.w, binv.z, boi.z);
-      const float e1 = fmaxf(fmaxf(fminf(tx0, tx1), fminf(ty0, ty1)), fminf(tz0, tz1));
-      const float x1 = fminf(fminf(fmaxf(tx0, tx1), fmaxf(ty0, ty1)), fmaxf(tz0, tz1));
-      // the slab interval meets [tmin, tb]
-      const bool a0 = e0 <= x0, b0 = e0 <= tb, c0 = x0 >= tmin;
-      const bool a1 = e1 <= x1, b1 = e1 <= tb, c1 = x1 >= tmin;
-      const bool le = e0 <= e1;
-      const bool h0 = a0 && b0 && c0, h1 = a1 && b1 && c1;
-      const bool near0 = h0 && (!h1 || le);  // a missed child comes last
-      top[kBlock] = near0 ? nd.d.y : nd.d.x;
-      const StackCol up = top + kBlock, down = top - kBlock;
-      top = (h0 && h1) ? up : ((h0 || h1) ? top : down);
-      cur = (h0 || h1) ? (near0 ? nd.d.x : nd.d.y) : below;
+      const PV_GLOBAL uint4* np = (const PV_GLOBAL uint4*)((const PV_GLOBAL char*)nodes + ((uint32_t)cur << 6));
+      const uint4 na = np[0], nb = np[1], nc = np[2], nd = np[3];
+      const uint32_t pl[12] = {na.x, na.y, na.z, na.w, nb.x, nb.y, nb.z, nb.w, nc.x, nc.y, nc.z, nc.w};
+      int32_t c[4] = {(int32_t)nd.x, (int32_t)nd.y, (int32_t)nd.z, (int32_t)nd.w};
+      float e[4];
+      uint64_t h[4];  // entered children, as wave masks
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        float nx, ny, nz, fx, fy, fz;
+        plane_pair(pl[3 * k], q.rx, q.inv.x, q.oi.x, &nx, &fx);
+        plane_pair(pl[3 * k + 1], q.ry, q.inv.y, q.oi.y, &ny, &fy);
+        plane_pair(pl[3 * k + 2], q.rz, q.inv.z, q.oi.z, &nz, &fz);
+        e[k] = fmaxf(fmaxf(nx, ny), nz);
+        const float ex = fminf(fminf(fx, fy), fz);
+        // the slab interval meets [tmin, tb]
+        h[k] = wave_mask(fmaxf(e[k], tmin) <= fminf(ex, tb));
+      }
+      // nearest entered child first, the others nearly in order (a child not
+      // entered comes last of its pair); exchanges of the masks are scalar work
+      auto order = [&](int i, int j) {
+        const uint64_t sw = h[j] & (~h[i] | wave_mask(e[j] < e[i]));
+        const bool x = lane_bit(sw);
+        const int32_t u = x ? c[j] : c[i], v = x ? c[i] : c[j];
+        const uint64_t hu = h[i] | h[j], hv = h[i] & h[j];
+        e[i] = x ? e[j] : e[i];
+        c[i] = u, c[j] = v, h[i] = hu, h[j] = hv;
+      };
+      order(0, 1);
+      order(2, 3);
+      order(0, 2);
+      top[kBlock] = c[3];
+      const StackCol t0 = top - kBlock;
+      top = lane_bit(h[3]) ? top + kBlock : top;
+      top[kBlock] = c[2];
+      top = lane_bit(h[2]) ? top + kBlock : top;
+      top[kBlock] = c[1];
+      top = lane_bit(h[1]) ? top + kBlock : top;
+      top = lane_bit(h[0]) ? top : t0;
+      // the entry that the next pop takes, from registers
+      const int32_t pushed = lane_bit(h[1]) ? c[1] : (lane_bit(h[2]) ? c[2] : c[3]);
+      int32_t next = lane_bit(h[0]) ? below : below2;
+      next = lane_bit(h[1] | h[2] | h[3]) ? pushed : next;
+      cur = lane_bit(h[0]) ? c[0] : below;
+      if (top > limit) {  // rare: no room for another full node
+        redo = true;
+        cur = kRootNone;
+        leaf = 0;
+        break;
+      }
       // postpone a reached leaf and go on with the next stack entry (once the
       // sentinel itself was taken, cur is kRootNone and nothing is postponed)
-      const int32_t next = top[0];
-      const bool lf = is_leaf(cur), em = leaf == 0;
-      const bool post = em && lf;
+      const bool post = leaf == 0 && is_leaf(cur);
       leaf = post ? cur : leaf;
       cur = post ? next : cur;
       top = post ? top - kBlock : top;
@@ -470,7 +648,9 @@ __device__ inline void walk_run(const PV_GLOBAL Node* __restrict__ nodes, const 
       for (uint32_t i = f; i < f + n; ++i) {
         const Tri tr = tris[i];
         float t;
-        const bool hit = tri_hit(r, xyz(tr.t0), xyz(tr.t1), xyz(tr.t2), tb, &t);
+        bool near_tb = false;
+        const bool hit = tri_hit(r, xyz(tr.t0), xyz(tr.t1), xyz(tr.t2), tb, &t, kTies ? &near_tb : nullptr);
+        if (kTies) redo = near_tb || (redo && !hit);  // a clearly closer crossing ends a tie
         tb = hit ? t : tb;
         gid = hit ? __float_as_uint(tr.t0.w) : gid;
         rec = hit ? i : rec;
@@ -494,12 +674,57 @@ __device__ inline void walk_run(const PV_GLOBAL Node* __restrict__ nodes, const 
   w.tb = tb;
   w.gid = gid;
   w.rec = rec;
+  w.redo = redo;
 }
 
-// the same walk with world-space boxes
-__device__ inline void walk_run(const PV_GLOBAL Node* __restrict__ nodes, const PV_GLOBAL Tri* __restrict__ tris,
-                                const Ray& r, bool any, StackCol col, Walk& w, int min_active) {
-  walk_run(nodes, tris, r, r.inv, r.oi, any, col, w, min_active);
+// The answer to a world-space query by the order that settles near ties: the
+// binary FP32 hierarchy depth first, the child entered first (the first child
+// when both at once) before the other, a later crossing taken only when
+// strictly closer.  Two crossings within rounding of each other (an edge of a
+// wall on a floor) are otherwise decided by the order of their tests, which
+// the four-wide walk's looser boxes change.  Rare (one ray in 10^4), so
+// nothing here is tuned.  any: stop at the first crossing.
+__device__ inline void walk_exact(const PV_GLOBAL Node* __restrict__ nodes, const PV_GLOBAL Tri* __restrict__ tris,
+                                  const Ray& r0, int32_t root, bool any, StackCol col, Walk& w) {
+  const Ray r = make_ray(r0.o, r0.d, r0.tmin, r0.tmax);
+  StackCol top = col;
+  top[0] = kRootNone;
+  int32_t cur = root;
+  float tb = r.tmax;
+  uint32_t gid = kHitNone, rec = 0;
+  while (cur != kRootNone) {
+    if (cur >= 0) {
+      const Node nd = *(const PV_GLOBAL Node*)((const PV_GLOBAL char*)nodes + ((uint32_t)cur << 6));
+      const float e0 = box_entry(nd.a.x, nd.a.y, nd.a.z, nd.a.w, nd.b.x, nd.b.y, r, tb);
+      const float e1 = box_entry(nd.b.z, nd.b.w, nd.c.x, nd.c.y, nd.c.z, nd.c.w, r, tb);
+      const bool h0 = e0 != __builtin_inff(), h1 = e1 != __builtin_inff();
+      const bool near0 = h0 && (!h1 || slab_entry(nd.a.x, nd.a.y, nd.a.z, nd.a.w, nd.b.x, nd.b.y, r) <=
+                                           slab_entry(nd.b.z, nd.b.w, nd.c.x, nd.c.y, nd.c.z, nd.c.w, r));
+      if (h0 && h1) {
+        top += kBlock;
+        top[0] = near0 ? nd.d.y : nd.d.x;
+      }
+      cur = near0 ? nd.d.x : nd.d.y;
+      if (h0 || h1) continue;
+    } else {
+      const uint32_t f = leaf_first(cur), n = leaf_count(cur);
+      for (uint32_t i = f; i < f + n; ++i) {
+        const Tri tr = tris[i];
+        float t;
+        if (tri_hit(r, xyz(tr.t0), xyz(tr.t1), xyz(tr.t2), tb, &t, nullptr)) {
+          tb = t;
+          gid = __float_as_uint(tr.t0.w);
+          rec = i;
+        }
+      }
+      if (any && gid != kHitNone) break;
+    }
+    cur = top[0];
+    top -= kBlock;
+  }
+  w.tb = tb;
+  w.gid = gid;
+  w.rec = rec;
 }
 
 // ---------------------------------------------------------------------------

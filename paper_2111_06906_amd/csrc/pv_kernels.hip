@@ -181,6 +181,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_update_objects(SceneDev* scenes
   if (!S.obj_moved[o]) return;
   const ObjDev ob = S.objs[o];
   const uint32_t* off = S.dlevel_off + ob.lvl_base;
+  const PlaneWriter wide(S);
   for (uint32_t lv = 0; lv < ob.n_levels; ++lv) {
     const uint32_t e = off[lv + 1];
     for (uint32_t i = off[lv] + threadIdx.x; i < e; i += blockDim.x) {
@@ -192,6 +193,9 @@ __global__ __launch_bounds__(kRefitBlock) void k_update_objects(SceneDev* scenes
       nd->a = make_float4(b[0], b[1], b[2], b[3]);
       nd->b = make_float4(b[4], b[5], b[6], b[7]);
       nd->c = make_float4(b[8], b[9], b[10], b[11]);
+      const uint2 ws = S.wslot[S.dlevel_nodes[i] - S.obj_node_first];
+      if (ws.x != kSlotNone) wide.put(ws.x, b[0], b[1], b[2], b[3], b[4], b[5]);
+      if (ws.y != kSlotNone) wide.put(ws.y, b[6], b[7], b[8], b[9], b[10], b[11]);
     }
     __syncthreads();
   }
@@ -200,6 +204,7 @@ __global__ __launch_bounds__(kRefitBlock) void k_update_objects(SceneDev* scenes
     child_box(S, ob.sah_root, b);
     for (int k = 0; k < 6; ++k) S.obj_aabb[6 * o + k] = b[k];
     const_cast<ObjDev*>(S.objs)[o].root = ob.sah_root;  // the refit topology is the current one
+    const_cast<ObjDev*>(S.objs)[o].wroot = ob.sah_wroot;
   }
 }
 
@@ -209,14 +214,18 @@ __global__ __launch_bounds__(kRefitBlock) void k_update_objects(SceneDev* scenes
 // only (the set that verification and the walk's clearance tests query).
 // The objects of a tree are split at their median along the widest axis of
 // their box centres, recursively; the static hierarchy, whose box spans the
-// scene and would widen every node above it, is the root's first child and
-// the objects' tree the second (nearly every query enters the static side
-// first).  One wave per tree, one lane per position of the item order, one
-// level of the recursion per step: every range of the level is stably sorted
-// by rank along its own axis, at once.  A range [lo, hi) splits at
-// mid = (lo + hi) / 2, and each split position belongs to exactly one
-// internal node, so node mid - 1 of the tree's block holds that range (node
-// n - 1 the root above the static hierarchy).
+// scene and would widen every node above it, is the root's first child
+// (nearly every query enters the static side first).  One wave per tree, one
+// lane per position of the item order, one level of the recursion per step:
+// every range of the level is stably sorted by rank along its own axis, at
+// once.  A range [lo, hi) splits at mid = (lo + hi) / 2, and each split
+// position belongs to exactly one range, so node mid - 1 of the tree's block
+// holds that range (node n - 1 the root above the static hierarchy).  Sorting
+// only permutes a range's own items, so all nodes are written once the order
+// is final, lane mid - 1 writing its range's from the range's four quarters:
+// the binary node from the halves, and, for the ranges of every second level,
+// the four-wide node from the quarters (of the scene's root from the static
+// hierarchy and the halves).
 
 constexpr int kTopLevels = kTopDepth - 1;  // median levels over <= PV_MAX_OBJECTS objects
 
@@ -224,10 +233,14 @@ __global__ __launch_bounds__(128) void k_build_top(SceneDev* scenes) {
   static_assert(PV_MAX_OBJECTS <= 64, "one lane per object");
   static_assert((1 << kTopLevels) >= PV_MAX_OBJECTS, "median levels");
   __shared__ float sbx[2][2][6][64];  // [tree][buffer][box component][position]
-  __shared__ int32_t scode[2][2][64];
+  __shared__ int2 scode[2][2][64];    // (binary, four-wide) root codes
   SceneDev& S = scenes[blockIdx.x];
   const int which = threadIdx.x >> 6;  // tree of this wave
   const uint32_t lane = threadIdx.x & 63u;
+  const PlaneWriter wide(S);
+  PV_GLOBAL Node* nodes = G(S.nodes);
+  float sbox[6];
+  for (int k = 0; k < 6; ++k) sbox[k] = S.sbox[k];
   // items of the tree in object order (moved objects compacted by ballot)
   const bool have = lane < S.n_obj;
   const bool take = have && (which == 0 || S.obj_moved[lane] != 0);
@@ -236,10 +249,9 @@ __global__ __launch_bounds__(128) void k_build_top(SceneDev* scenes) {
   if (take) {
     const uint32_t i = (uint32_t)__popcll(mm & lanemask_lt());
     for (int k = 0; k < 6; ++k) sbx[which][0][k][i] = S.obj_aabb[6 * lane + k];
-    scode[which][0][i] = S.objs[lane].root;
+    scode[which][0][i] = make_int2(S.objs[lane].root, S.objs[lane].wroot);
   }
   __syncthreads();
-  const uint32_t first = S.top_base + (uint32_t)which * kTopNodes;
   uint32_t lo = 0, hi = n;  // range of this lane's position
   int buf = 0;
   for (int level = 0; level < kTopLevels; ++level) {
@@ -270,7 +282,7 @@ __global__ __launch_bounds__(128) void k_build_top(SceneDev* scenes) {
     }
     float mb[6];
     for (int k = 0; k < 6; ++k) mb[k] = bx[k][lane];
-    const int32_t mc = scode[which][buf][lane];
+    const int2 mc = scode[which][buf][lane];
     if (lane < n) {
       for (int k = 0; k < 6; ++k) sbx[which][buf ^ 1][k][dst] = mb[k];
       scode[which][buf ^ 1][dst] = mc;
@@ -279,54 +291,110 @@ __global__ __launch_bounds__(128) void k_build_top(SceneDev* scenes) {
     buf ^= 1;
     if (live) {
       const uint32_t mid = (lo + hi) / 2;
-      if (lane == lo) {  // one lane per range writes its node
-        const float(*nb)[64] = sbx[which][buf];
-        float cb[2][6];
-        int32_t ch[2];
-        for (int side = 0; side < 2; ++side) {
-          const uint32_t a = side ? mid : lo, b = side ? hi : mid;
-          for (int k = 0; k < 3; ++k) {
-            cb[side][k] = __builtin_inff();
-            cb[side][3 + k] = -__builtin_inff();
-          }
-          for (uint32_t q = a; q < b; ++q)
-            for (int k = 0; k < 3; ++k) {
-              cb[side][k] = fminf(cb[side][k], nb[k][q]);
-              cb[side][3 + k] = fmaxf(cb[side][3 + k], nb[3 + k][q]);
-            }
-          ch[side] = b - a == 1 ? scode[which][buf][a] : (int32_t)(first + (a + b) / 2 - 1);
-        }
-        Node& nd = S.nodes[first + mid - 1];
-        nd.a = make_float4(cb[0][0], cb[0][1], cb[0][2], cb[0][3]);
-        nd.b = make_float4(cb[0][4], cb[0][5], cb[1][0], cb[1][1]);
-        nd.c = make_float4(cb[1][2], cb[1][3], cb[1][4], cb[1][5]);
-        nd.d = make_int4(ch[0], ch[1], -1, 0);
-      }
       if (lane < mid) hi = mid;
       else lo = mid;
     }
   }
+  const float(*bx)[64] = sbx[which][buf];
+  const int2* code = scode[which][buf];
+  const int32_t sroot = S.sroot, swroot = S.swroot;
+  const bool above = which == 0 && sroot != kRootNone;  // the static hierarchy beside the objects
+  const uint32_t first = S.top_base + (uint32_t)which * kTopNodes;
+  const uint32_t wfirst = S.wtop_base + (uint32_t)which * kTopNodes;
+  // root codes of a range of one or more items (its node's index is its split position - 1)
+  auto bin = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].x : (int32_t)(first + (a + b) / 2 - 1); };
+  auto wid = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].y : (int32_t)(wfirst + (a + b) / 2 - 1); };
+  if (lane + 1 < n) {
+    // the range that splits at lane + 1
+    uint32_t a = 0, b = n, depth = 0;
+    while ((a + b) / 2 != lane + 1) {
+      const uint32_t m = (a + b) / 2;
+      if (lane + 1 < m) b = m;
+      else a = m;
+      ++depth;
+    }
+    const uint32_t mid = lane + 1;
+    // quarters (a half of one item is its own first quarter)
+    const uint32_t q[5] = {a, mid - a == 1 ? mid : (a + mid) / 2, mid, b - mid == 1 ? b : (mid + b) / 2, b};
+    float bb[4][6];
+    for (int j = 0; j < 4; ++j) {
+      for (int k = 0; k < 3; ++k) {
+        bb[j][k] = __builtin_inff();
+        bb[j][3 + k] = -__builtin_inff();
+      }
+      for (uint32_t i = q[j]; i < q[j + 1]; ++i)
+        for (int k = 0; k < 3; ++k) {
+          bb[j][k] = fminf(bb[j][k], bx[k][i]);
+          bb[j][3 + k] = fmaxf(bb[j][3 + k], bx[3 + k][i]);
+        }
+    }
+    float cb[2][6];
+    for (int k = 0; k < 3; ++k)
+      for (int h = 0; h < 2; ++h) {
+        cb[h][k] = fminf(bb[2 * h][k], bb[2 * h + 1][k]);
+        cb[h][3 + k] = fmaxf(bb[2 * h][3 + k], bb[2 * h + 1][3 + k]);
+      }
+    PV_GLOBAL Node& nd = nodes[first + lane];
+    nd.a = make_float4(cb[0][0], cb[0][1], cb[0][2], cb[0][3]);
+    nd.b = make_float4(cb[0][4], cb[0][5], cb[1][0], cb[1][1]);
+    nd.c = make_float4(cb[1][2], cb[1][3], cb[1][4], cb[1][5]);
+    nd.d = make_int4(bin(a, mid), bin(mid, b), -1, 0);
+    if (((depth + (above ? 1u : 0u)) & 1u) == 0) {
+      const uint32_t w = 4 * (wfirst + lane);
+      for (int j = 0; j < 4; ++j) {
+        if (q[j] < q[j + 1]) {
+          wide.put(w + j, bb[j][0], bb[j][1], bb[j][2], bb[j][3], bb[j][4], bb[j][5]);
+          wide.child(w + j, wid(q[j], q[j + 1]));
+        } else {
+          wide.none(w + j);
+        }
+      }
+    }
+    if (above && depth == 0) {
+      // the scene's root: the static hierarchy and the halves of the objects
+      const uint32_t w = 4 * (wfirst + n - 1);
+      wide.put(w, sbox[0], sbox[1], sbox[2], sbox[3], sbox[4], sbox[5]);
+      wide.child(w, swroot);
+      for (int h = 0; h < 2; ++h) wide.put(w + 1 + h, cb[h][0], cb[h][1], cb[h][2], cb[h][3], cb[h][4], cb[h][5]);
+      wide.child(w + 1, wid(a, mid));
+      wide.child(w + 2, wid(mid, b));
+      wide.none(w + 3);
+    }
+  }
   if (lane != 0) return;
-  // root of the objects' tree: its node, the single object, or none
-  int32_t root = n == 0 ? kRootNone : (n == 1 ? scode[which][buf][0] : (int32_t)(first + n / 2 - 1));
-  if (which == 0 && S.sroot != kRootNone && n > 0) {
+  // roots: the objects' tree, the single object, or none; the static
+  // hierarchy alone or above them
+  int32_t root = n == 0 ? kRootNone : bin(0, n), wroot = n == 0 ? kRootNone : wid(0, n);
+  if (above && n > 0) {
     float ob[6] = {__builtin_inff(), __builtin_inff(), __builtin_inff(),
                    -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-    for (uint32_t q = 0; q < n; ++q)
+    for (uint32_t i = 0; i < n; ++i)
       for (int k = 0; k < 3; ++k) {
-        ob[k] = fminf(ob[k], sbx[0][buf][k][q]);
-        ob[3 + k] = fmaxf(ob[3 + k], sbx[0][buf][3 + k][q]);
+        ob[k] = fminf(ob[k], bx[k][i]);
+        ob[3 + k] = fmaxf(ob[3 + k], bx[3 + k][i]);
       }
-    Node& nd = S.nodes[first + n - 1];
-    nd.a = make_float4(S.sbox[0], S.sbox[1], S.sbox[2], S.sbox[3]);
-    nd.b = make_float4(S.sbox[4], S.sbox[5], ob[0], ob[1]);
+    PV_GLOBAL Node& nd = nodes[first + n - 1];
+    nd.a = make_float4(sbox[0], sbox[1], sbox[2], sbox[3]);
+    nd.b = make_float4(sbox[4], sbox[5], ob[0], ob[1]);
     nd.c = make_float4(ob[2], ob[3], ob[4], ob[5]);
-    nd.d = make_int4(S.sroot, root, -1, 0);
+    nd.d = make_int4(sroot, root, -1, 0);
     root = (int32_t)(first + n - 1);
-  } else if (which == 0 && S.sroot != kRootNone) {
-    root = S.sroot;
+    if (n == 1) {
+      const uint32_t w = 4 * wfirst;
+      wide.put(w, sbox[0], sbox[1], sbox[2], sbox[3], sbox[4], sbox[5]);
+      wide.child(w, swroot);
+      wide.put(w + 1, ob[0], ob[1], ob[2], ob[3], ob[4], ob[5]);
+      wide.child(w + 1, wroot);
+      wide.none(w + 2);
+      wide.none(w + 3);
+    }
+    wroot = (int32_t)(wfirst + n - 1);
+  } else if (above) {
+    root = sroot;
+    wroot = swroot;
   }
   S.top[which] = root;
+  S.wtop[which] = wroot;
 }
 
 // ---------------------------------------------------------------------------
@@ -757,7 +825,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_gather(const SceneDev* __rest
 template <bool kSingle>
 __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restrict__ scenes,
                                                          const uint32_t* __restrict__ gbase, int n_scenes,
-                                                         VerifyWork W, int min_active) {
+                                                         VerifyWork W, int min_active, uint32_t entries) {
   extern __shared__ int32_t sstack[];  // traversal stacks, launch-time size
   __shared__ MovedSet M;                // single scene: the moved objects' boxes
   __shared__ int32_t mroot[PV_MAX_OBJECTS];  // and their hierarchies' roots
@@ -767,6 +835,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
   __shared__ int32_t moroot[PV_MAX_OBJECTS];
   __shared__ float minv[PV_MAX_OBJECTS][12];
   const StackCol col = (StackCol)(sstack + kBlock + threadIdx.x);  // entry 0 of the column; entry -1 spare
+  const StackCol limit = col + (int)(entries - 5) * kBlock;  // top from which a full node would pass the last entry
   if (kSingle) {
     if (threadIdx.x < 64) {
       const SceneDev& S0 = scenes[0];
@@ -776,7 +845,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
       if (mv) {
         const uint32_t i = (uint32_t)__popcll(mm & lanemask_lt());
         const ObjDev ob = G(S0.objs)[o];
-        mroot[i] = ob.root;
+        mroot[i] = ob.wroot;
         // inverse of the 3x3 part by cofactors in FP64
         const PV_GLOBAL float* x = G(S0.obj_xf_cur) + 12 * o;
         const double m0 = x[0], m1 = x[1], m2 = x[2], m4 = x[4], m5 = x[5], m6 = x[6];
@@ -810,9 +879,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
   w.cur = kRootNone;
   w.leaf = 0;
   Ray r;
-  float3 binv = f3(0.0f, 0.0f, 0.0f), boi = binv;  // slab parameters of the walk's boxes
+  Slab qb{};  // slab parameters of the walk's boxes
   uint32_t gp = 0, j = 0;
-  bool busy = false, drained = false;
+  bool busy = false, drained = false, vis_task = false;
   const SceneDev* S = scenes;
   while (true) {
     // lanes without a task take the next ones; a task whose path already
@@ -838,9 +907,8 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
                                     : xyz(G(S->pos)[(size_t)(j - 1) * stride + q]);
             const float3 b = xyz(G(S->pos)[(size_t)j * stride + q]);
             r = segment_ray(a, b, S->eps_end);
-            binv = r.inv;
-            boi = r.oi;
-            int32_t root = G(S->top)[1];
+            qb = world_slab(*S, r);
+            int32_t root = G(S->wtop)[1];
             if (kSingle && !vis) {
               // the objects whose boxes the segment reaches, from LDS: one
               // object is walked from its own root (its box is the only one
@@ -874,12 +942,13 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
                 const float dx = copysignf(fmaxf(fabsf(od.x), tiny), od.x);
                 const float dy = copysignf(fmaxf(fabsf(od.y), tiny), od.y);
                 const float dz = copysignf(fmaxf(fabsf(od.z), tiny), od.z);
-                binv = f3(__builtin_amdgcn_rcpf(dx), __builtin_amdgcn_rcpf(dy), __builtin_amdgcn_rcpf(dz));
-                boi = f3(-(oa.x * binv.x), -(oa.y * binv.y), -(oa.z * binv.z));
+                const float3 binv = f3(__builtin_amdgcn_rcpf(dx), __builtin_amdgcn_rcpf(dy), __builtin_amdgcn_rcpf(dz));
+                qb = make_slab(binv, f3(-(oa.x * binv.x), -(oa.y * binv.y), -(oa.z * binv.z)), S->qinv);
                 root = moroot[only];
               }
             }
-            if (vis) root = G(S->top)[0];
+            if (vis) root = G(S->wtop)[0];
+            vis_task = vis;
             walk_start(w, root, r.tmax, col);
             busy = root != kRootNone;
           }
@@ -891,8 +960,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
       continue;
     }
     if (busy) {
-      walk_run(G(S->nodes), G(S->tris), r, binv, boi, true, col, w, min_active);
+      walk_run<false>(G(S->wide), G(S->tris), r, qb, true, col, limit, w, min_active);
       if (walk_done(w)) {
+        if (w.redo) walk_exact(G(S->nodes), G(S->tris), r, G(S->top)[vis_task ? 0 : 1], true, col, w);
         if (w.gid != kHitNone) atomicMin(&W.first[gp], j);
         busy = false;
       }
@@ -1360,11 +1430,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
                                                     int n_scenes, const uint32_t* __restrict__ queue,
                                                     const uint32_t* __restrict__ qcount, float T,
                                                     uint64_t seed, uint32_t frame_arg, const uint32_t* frame_ptr,
-                                                    pv_stats* stats, int min_active, uint32_t* __restrict__ deal_ctr) {
+                                                    pv_stats* stats, int min_active, uint32_t entries,
+                                                    uint32_t* __restrict__ deal_ctr) {
   extern __shared__ int32_t sstack[];  // traversal stacks, launch-time size
   __shared__ unsigned long long sred[kBlock / 64];
   __shared__ SceneTab stab;
   const StackCol col = (StackCol)(sstack + kBlock + threadIdx.x);  // entry 0 of the column; entry -1 spare
+  const StackCol limit = col + (int)(entries - 5) * kBlock;  // top from which a full node would pass the last entry
   const uint32_t frame = frame_ptr ? *frame_ptr : frame_arg;
   uint32_t n_rays = 0, n_photons = 0, n_acc = 0, n_trunc = 0;
   const PV_LDS SceneTab* tab = nullptr;
@@ -1382,6 +1454,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
   L.mode = ST_IDLE;
   L.p = 0;
   Ray r;             // the lane's current query
+  Slab qb{};         // its box-test parameters
   Walk wk;           // its walk through the hierarchy
   wk.cur = kRootNone;
   wk.leaf = 0;
@@ -1446,12 +1519,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
         }
       }
       r = make_ray(qo, qd, tmin, tmax);
-      walk_start(wk, G(S.top)[any ? 1 : 0], tmax, col);
+      qb = world_slab(S, r);
+      walk_start(wk, G(S.wtop)[any ? 1 : 0], tmax, col);
       tracing = true;
       if (!any) ++n_rays;
     }
-    if (tracing) walk_run(G(S.nodes), G(S.tris), r, any, col, wk, min_active);
+    if (tracing) walk_run<true>(G(S.wide), G(S.tris), r, qb, any, col, limit, wk, min_active);
     if (!tracing || !walk_done(wk)) continue;
+    if (wk.redo && !(any && wk.gid != kHitNone)) walk_exact(G(S.nodes), G(S.tris), r, G(S.top)[any ? 1 : 0], any, col, wk);
     // ---- the walk is finished: its query's ray is r (origin xa of a walk
     // segment, direction of a sampled bounce)
     tracing = false;
@@ -2036,7 +2111,7 @@ hipError_t launch_verify(const SceneDev* scenes, const uint2* tiles, uint32_t n_
                          int n_scenes, VerifyWork W, uint32_t* block_cnt, pv_stats* stats, uint32_t stack,
                          uint32_t trace_blocks, int min_active, uint32_t* scan_tmp, hipStream_t s) {
   if (!n_tiles) return hipSuccess;
-  if (stack < 2 || stack > (uint32_t)kMaxStack || trace_blocks == 0 || min_active < 1 || min_active > 64)
+  if (stack < kMinStack || stack > (uint32_t)kMaxStack || trace_blocks == 0 || min_active < 1 || min_active > 64)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_verify_scan, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, W, block_cnt, stats);
   hipError_t e = launch_scan(W.tcount, W.toff, n_tiles, W.total, scan_tmp, s);
@@ -2045,12 +2120,12 @@ hipError_t launch_verify(const SceneDev* scenes, const uint2* tiles, uint32_t n_
   const dim3 gt(trace_blocks), gf(verify_finish_blocks(trace_blocks));
   if (n_scenes == 1) {
     hipLaunchKernelGGL(k_verify_trace<true>, gt, dim3(kBlock), stack_bytes(stack), s, scenes, gbase, n_scenes, W,
-                       min_active);
+                       min_active, stack);
     hipLaunchKernelGGL(k_verify_finish<true>, gf, dim3(kBlock), 0, s, scenes, gbase, n_scenes, W, block_cnt, n_tiles,
                        stats);
   } else {
     hipLaunchKernelGGL(k_verify_trace<false>, gt, dim3(kBlock), stack_bytes(stack), s, scenes, gbase, n_scenes, W,
-                       min_active);
+                       min_active, stack);
     hipLaunchKernelGGL(k_verify_finish<false>, gf, dim3(kBlock), 0, s, scenes, gbase, n_scenes, W, block_cnt, n_tiles,
                        stats);
   }
@@ -2101,23 +2176,23 @@ template <bool kSingle>
 static void retrace_variant(int v, dim3 g, size_t lds, hipStream_t s, const SceneDev* scenes, const uint32_t* gbase, int n_scenes,
                             const uint32_t* queue, const uint32_t* qcount, float T, uint64_t seed,
                             uint32_t frame, const uint32_t* frame_ptr, pv_stats* stats, int min_active,
-                            uint32_t* deal_ctr) {
+                            uint32_t entries, uint32_t* deal_ctr) {
   switch (v) {
     case 1:
       hipLaunchKernelGGL((k_retrace<kSingle, 5>), g, dim3(kBlock), lds, s, scenes, gbase, n_scenes, queue, qcount,
-                         T, seed, frame, frame_ptr, stats, min_active, deal_ctr);
+                         T, seed, frame, frame_ptr, stats, min_active, entries, deal_ctr);
       break;
     case 2:
       hipLaunchKernelGGL((k_retrace<kSingle, 6>), g, dim3(kBlock), lds, s, scenes, gbase, n_scenes, queue, qcount,
-                         T, seed, frame, frame_ptr, stats, min_active, deal_ctr);
+                         T, seed, frame, frame_ptr, stats, min_active, entries, deal_ctr);
       break;
     case 3:
       hipLaunchKernelGGL((k_retrace<kSingle, 8>), g, dim3(kBlock), lds, s, scenes, gbase, n_scenes, queue, qcount,
-                         T, seed, frame, frame_ptr, stats, min_active, deal_ctr);
+                         T, seed, frame, frame_ptr, stats, min_active, entries, deal_ctr);
       break;
     default:
       hipLaunchKernelGGL((k_retrace<kSingle, 4>), g, dim3(kBlock), lds, s, scenes, gbase, n_scenes, queue, qcount,
-                         T, seed, frame, frame_ptr, stats, min_active, deal_ctr);
+                         T, seed, frame, frame_ptr, stats, min_active, entries, deal_ctr);
       break;
   }
 }
@@ -2126,7 +2201,7 @@ hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_s
                           const uint32_t* qcount, float T, uint64_t seed, uint32_t frame,
                           const uint32_t* frame_ptr, pv_stats* stats, uint32_t n_blocks, int variant, uint32_t stack,
                           int min_active, const OrderWork& O, hipStream_t s) {
-  if (stack < 2 || stack > (uint32_t)kMaxStack || min_active < 1 || min_active > 64) return hipErrorInvalidValue;
+  if (stack < kMinStack || stack > (uint32_t)kMaxStack || min_active < 1 || min_active > 64) return hipErrorInvalidValue;
   // the queue reordered by first invalid segment (see k_order_hist)
   hipLaunchKernelGGL(k_order_hist, dim3(O.tiles), dim3(kBlock), 0, s, scenes, gbase, n_scenes, queue_in, qcount, O.hist,
                      O.tiles);
@@ -2137,10 +2212,10 @@ hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_s
   const uint32_t* queue = O.queue;
   if (n_scenes == 1)
     retrace_variant<true>(variant, dim3(n_blocks), stack_bytes(stack), s, scenes, gbase, n_scenes, queue, qcount, T, seed, frame,
-                          frame_ptr, stats, min_active, O.deal);
+                          frame_ptr, stats, min_active, stack, O.deal);
   else
     retrace_variant<false>(variant, dim3(n_blocks), stack_bytes(stack), s, scenes, gbase, n_scenes, queue, qcount, T, seed, frame,
-                           frame_ptr, stats, min_active, O.deal);
+                           frame_ptr, stats, min_active, stack, O.deal);
   return hipGetLastError();
 }
 

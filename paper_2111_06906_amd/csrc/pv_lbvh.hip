@@ -397,7 +397,35 @@ __global__ __launch_bounds__(kBlock) void k_lbvh_nodes(SceneDev* __restrict__ sc
   if (i == 0) W.parent_node[node - W.first_node] = -1;
 }
 
-// depth of every leaf (its internal ancestors), maximum per object
+// four-wide form of binary node i of a rebuilt tree: an internal child gives
+// way to its own two (every node gets one; a walk meets those of every second
+// level)
+__device__ inline void collapse_rebuilt(const SceneDev& S, const ObjDev& ob, uint32_t i) {
+  const PlaneWriter wide(S);
+  const PV_GLOBAL Node* nodes = G(S.nodes);
+  const Node nd = nodes[ob.lbvh_base + i];
+  const uint32_t w = 4 * (ob.lbvh_wbase + i);
+  const int32_t ch[2] = {nd.d.x, nd.d.y};
+  const float* f = reinterpret_cast<const float*>(&nd);
+  auto put = [&](uint32_t slot, const float* b, int32_t code) {
+    wide.put(slot, b[0], b[1], b[2], b[3], b[4], b[5]);
+    wide.child(slot, code < 0 ? code : code - (int32_t)ob.lbvh_base + (int32_t)ob.lbvh_wbase);
+  };
+  for (uint32_t side = 0; side < 2; ++side) {
+    if (ch[side] < 0) {
+      put(w + 2 * side, f + 6 * side, ch[side]);
+      wide.none(w + 2 * side + 1);
+    } else {
+      const Node cn = nodes[ch[side]];
+      const float* g = reinterpret_cast<const float*>(&cn);
+      put(w + 2 * side, g, cn.d.x);
+      put(w + 2 * side + 1, g + 6, cn.d.y);
+    }
+  }
+}
+
+// depth of every leaf (its internal ancestors), maximum per object, and the
+// rebuilt nodes' four-wide forms
 __global__ __launch_bounds__(kBlock) void k_lbvh_depth(const SceneDev* __restrict__ scenes, LbvhWork W,
                                                        const uint64_t* __restrict__ key) {
   const SceneDev& S = scenes[0];
@@ -412,6 +440,9 @@ __global__ __launch_bounds__(kBlock) void k_lbvh_depth(const SceneDev* __restric
     if (S.objs[o].n_tris > 1)
       for (int32_t p = W.parent_leaf[g]; p >= 0 && depth < kDepthGuard; p = W.parent_node[(uint32_t)p - W.first_node])
         ++depth;
+    const ObjDev ob = S.objs[o];
+    const uint32_t i = g - ob.tri_base;
+    if (i + 1 < ob.n_tris) collapse_rebuilt(S, ob, i);
   }
   // one atomic per wave when the wave's leaves share an object
   const uint64_t act = __ballot(valid);
@@ -435,15 +466,16 @@ __global__ void k_lbvh_finish(SceneDev* __restrict__ scenes, LbvhWork W, const u
   if (o >= S.n_obj) return;
   const ObjDev ob = S.objs[o];
   Box b;
-  int32_t root;
+  int32_t root, wroot;
   if (ob.n_tris == 1) {
-    root = leaf_code(S.n_static + val[ob.tri_base], 1);
+    root = wroot = leaf_code(S.n_static + val[ob.tri_base], 1);
     b = tri_box(S.tris[leaf_first(root)]);
   } else {
     // the rebuilt tree replaces the refit topology only within the depth the
     // traversal stacks were sized for
     if (W.odepth[o] > max_depth) return;
     root = (int32_t)ob.lbvh_base;
+    wroot = (int32_t)ob.lbvh_wbase;
     b = range_box(W.pyr, W.n_dyn, ob.tri_base, ob.tri_base + ob.n_tris);
   }
   S.obj_aabb[6 * o + 0] = b.lo.x;
@@ -453,6 +485,7 @@ __global__ void k_lbvh_finish(SceneDev* __restrict__ scenes, LbvhWork W, const u
   S.obj_aabb[6 * o + 4] = b.hi.y;
   S.obj_aabb[6 * o + 5] = b.hi.z;
   objs[o].root = root;
+  objs[o].wroot = wroot;
 }
 
 // Per-frame refit of the upload-time topologies of the moved objects: every
@@ -471,6 +504,10 @@ __global__ __launch_bounds__(kBlock) void k_refit_nodes(SceneDev* __restrict__ s
   nd.a = make_float4(b0.lo.x, b0.lo.y, b0.lo.z, b0.hi.x);
   nd.b = make_float4(b0.hi.y, b0.hi.z, b1.lo.x, b1.lo.y);
   nd.c = make_float4(b1.lo.z, b1.hi.x, b1.hi.y, b1.hi.z);
+  const uint2 ws = S.wslot[i];
+  const PlaneWriter wide(S);
+  if (ws.x != kSlotNone) wide.put(ws.x, b0.lo.x, b0.lo.y, b0.lo.z, b0.hi.x, b0.hi.y, b0.hi.z);
+  if (ws.y != kSlotNone) wide.put(ws.y, b1.lo.x, b1.lo.y, b1.lo.z, b1.hi.x, b1.hi.y, b1.hi.z);
 }
 
 // each moved object's box (the union of its records) and its refit topology
@@ -489,6 +526,7 @@ __global__ void k_refit_objects(SceneDev* __restrict__ scenes, LbvhWork W) {
   S.obj_aabb[6 * o + 4] = b.hi.y;
   S.obj_aabb[6 * o + 5] = b.hi.z;
   objs[o].root = ob.sah_root;
+  objs[o].wroot = ob.sah_wroot;
 }
 
 hipError_t launch_refit_objects(SceneDev* scenes, LbvhWork W, uint32_t n_obj, uint32_t n_obj_nodes, hipStream_t s) {

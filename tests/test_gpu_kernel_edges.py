@@ -77,3 +77,68 @@ def test_energy_and_gradients_at_edges(E, counts, B, n_mat):
         np.testing.assert_allclose(ga.cpu().numpy(), rho.grad.numpy(), rtol=50 * 2.0 ** -24, atol=0)
         np.testing.assert_allclose(gp.cpu().numpy(), phi.grad.numpy(), rtol=50 * 2.0 ** -24, atol=0)
     ctx.close()
+
+
+# The four-wide walk gives up where it would leave more entries than the stack
+# holds and where two crossings lie within rounding of each other; the binary
+# walk then answers.
+
+
+def _crowded(n_static, n_obj, frames=3):
+    """The tiny box filled with large overlapping triangles, static ones and
+    an object's: a ray enters nearly every box of both hierarchies, so walks
+    leave as many entries as their trees allow."""
+    sc = scenes.make_tiny(n_paths=2048 + 3, max_bounces=3, frames=frames, seed=21)
+    rng = np.random.default_rng(21)
+    st = rng.uniform(0.05, 0.95, (n_static, 3, 3)).astype(np.float32)
+    ob = rng.uniform(-0.25, 0.25, (n_obj, 3, 3)).astype(np.float32)
+    sc.static_verts = np.concatenate([sc.static_verts, st])
+    sc.static_mat = np.concatenate([sc.static_mat, np.zeros(n_static, np.uint32)])
+    sc.obj_local = [np.concatenate([sc.obj_local[0], ob])]
+    sc.obj_mat = [np.concatenate([sc.obj_mat[0], np.ones(n_obj, np.uint32)])]
+    return sc
+
+
+@pytest.mark.parametrize("T", [-1.0, 0.01])
+def test_walk_out_of_stack_lockstep(E, T):
+    from tests.test_gpu_parity import _lockstep
+    _lockstep(E, _crowded(120, 60), 3, T, "crowded box T=%g" % T)
+
+
+def test_walk_out_of_stack_visibility(E):
+    # a point light's visibility tasks walk the whole scene during verification
+    from tests.test_gpu_parity import _lockstep
+    sc = _crowded(120, 60)
+    sc.light_half = np.zeros((1, 2), np.float32)
+    sc.light_xforms = sc.light_xforms.copy()
+    sc.light_xforms[:, 0, 3] += 0.01 * np.arange(sc.light_xforms.shape[0], dtype=np.float32)
+    _lockstep(E, sc, 3, 0.01, "crowded box, moving point light")
+
+
+def test_ties_between_coincident_triangles(E):
+    # every static triangle twice: each closest crossing is a tie, and the
+    # paths are those of the scene without the copies, bit for bit
+    one = scenes.make_rooms("ties", 2, 2, 3000, 2, (16, 8), 4000 + 5, 5, 3, 0.01, 31, n_lights=2, lights_move=True)
+    two = scenes.make_rooms("ties", 2, 2, 3000, 2, (16, 8), 4000 + 5, 5, 3, 0.01, 31, n_lights=2, lights_move=True)
+    S = one.n_static
+    two.static_verts = np.concatenate([one.static_verts, one.static_verts])
+    two.static_mat = np.concatenate([one.static_mat, one.static_mat])
+    got = []
+    for sc in (one, two):
+        ctx = E.Context(sc)
+        st = ctx.new_store()
+        ctx.frame_begin(0)
+        ctx.initial_trace(st, sc.seed, 0)
+        for f in (1, 2):
+            ctx.frame_begin(f)
+            ctx.verify(st)
+            ctx.retrace(st, 0.01, sc.seed, f)
+        got.append(st.to_numpy())
+        ctx.close()
+    a, b = got
+    for k in ("pos", "energy", "origin"):
+        assert np.array_equal(a[k].view(np.uint32), b[k].view(np.uint32)), k
+    assert np.array_equal(a["info"], b["info"])
+    none = b["hit"] == 0xFFFFFFFF
+    hit = np.where(none, b["hit"], np.where(b["hit"] < 2 * S, b["hit"] % S, b["hit"] - S))
+    assert np.array_equal(a["hit"], hit)
