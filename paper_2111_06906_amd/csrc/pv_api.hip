@@ -105,12 +105,12 @@ struct pv_ctx {
   Alloc dm_mem;
   pv::DmWork dw{};
   // tuning (pv_set_tuning / pv_autotune)
-  int retrace_variant = 0;
+  int retrace_variant = 1;  // five waves per SIMD: 96 registers, no spills
   // defaults: the settings the autotuner picks on the 3M-path, 380k-triangle
   // interior (twice the workgroups that fit at once: the later ones take
   // what is left of the dealt work lists)
   int retrace_blocks_per_cu = 8;
-  int walk_min_active = 40;  // a wave's re-trace walk yields once fewer lanes are still walking
+  int walk_min_active = 28;  // a wave's re-trace walk yields once fewer lanes are still walking
   int verify_blocks_per_cu = 8;  // persistent verification traversal workgroups per compute unit
   int verify_min_active = 16;    // yield threshold of the verification walks
   float tune_report[7] = {0, 0, 0, 0, 0, 0, 0};  // pv_autotune_report
@@ -955,12 +955,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       for (uint32_t i = 0; i < S; ++i) {
         const float* v = d->h_static_verts + 9 * (size_t)hb.order[i];
         std::memcpy(&v9[9 * (size_t)i], v, 9 * sizeof(float));
-        uint32_t gid = hb.order[i];
-        stris[i].t0 = make_float4(v[0], v[1], v[2], 0.0f);
-        stris[i].t1 = make_float4(v[3], v[4], v[5], 0.0f);
-        stris[i].t2 = make_float4(v[6], v[7], v[8], 0.0f);
-        std::memcpy(&stris[i].t0.w, &gid, 4);
-        std::memcpy(&stris[i].t1.w, &tri_mat[gid], 4);
+        stris[i] = pv::make_tri(v, hb.order[i]);
       }
       if (hb.max_depth > kMaxDepth) return fail(ctx, PV_ERR_CAPACITY, "static hierarchy too deep");
       depth = std::max(depth, hb.max_depth);
@@ -1133,14 +1128,17 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       // refit topology's order, which k_transform keeps current)
       std::vector<uint32_t> grec((size_t)S + n_dyn, 0u);
       for (uint32_t i = 0; i < S; ++i) {
-        uint32_t g;
-        std::memcpy(&g, &stris[i].t0.w, 4);
-        grec[g] = i;
+        grec[stris[i].gid] = i;
       }
       for (size_t k = 0; k < dgid.size(); ++k) grec[dgid[k]] = S + (uint32_t)k;
       uint32_t* d_grec;
       CK(upload(A, &d_grec, grec.data(), grec.size(), s));
       hs.gid_rec = d_grec;
+      std::vector<uint32_t> rmat((size_t)S + n_dyn);
+      for (size_t g = 0; g < rmat.size(); ++g) rmat[grec[g]] = tri_mat[g];
+      uint32_t* d_rmat;
+      CK(upload(A, &d_rmat, rmat.data(), rmat.size(), s));
+      hs.rec_mat = d_rmat;
     }
     CK(upload(A, &d_lnodes, level_nodes.data(), level_nodes.size(), s));
     CK(upload(A, &d_loff, level_off.data(), level_off.size(), s));
@@ -1203,7 +1201,8 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       lights[l].kind = d->h_light_kind ? d->h_light_kind[l] : PV_LIGHT_AREA;
       lights[l].param[0] = lights[l].kind != PV_LIGHT_AREA ? d->h_light_param[2 * l] : 0.0f;
       lights[l].param[1] = lights[l].kind != PV_LIGHT_AREA ? d->h_light_param[2 * l + 1] : 0.0f;
-      lights[l].pad[0] = lights[l].pad[1] = 0;
+      for (int c = 0; c < 3; ++c) lights[l].e1[c] = 0.0f;
+      lights[l].pad[0] = lights[l].pad[1] = lights[l].pad[2] = 0;
     }
     LightDev* d_lights;
     CK(upload(A, &d_lights, lights.data(), lights.size(), s));
@@ -1278,6 +1277,7 @@ pv_status pv_set_light_paths(pv_ctx* ctx, const uint32_t* h_counts) {
   for (uint32_t l = 0; l < ctx->n_lights; ++l) {
     lights[l].path_base = base;
     lights[l].path_count = h_counts[l];
+    for (int c = 0; c < 3; ++c) lights[l].e1[c] = lights[l].power[c] / (float)h_counts[l];
     ctx->h_light_paths[l] = h_counts[l];
     base += h_counts[l];
   }
@@ -1666,9 +1666,9 @@ pv_status pv_object_hierarchy_info(pv_ctx* ctx, uint32_t obj, uint32_t* out) {
           }
           seen[i - first] = 1;
           const Tri& t = tris[i - first];
-          const float4 v[3] = {t.t0, t.t1, t.t2};
           for (int q = 0; q < 3; ++q) {
-            const float b[6] = {v[q].x, v[q].y, v[q].z, v[q].x, v[q].y, v[q].z};
+            const float* v = t.v[q];
+            const float b[6] = {v[0], v[1], v[2], v[0], v[1], v[2]};
             if (!inside(b, it.box)) ok = false;
           }
         }

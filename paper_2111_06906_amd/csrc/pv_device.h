@@ -123,10 +123,22 @@ __host__ __device__ inline uint32_t wide_planes(float lo, float hi, float c, flo
   return half_down(a - ra * 1.1920929e-7f) | (half_up(b + rb * 1.1920929e-7f) << 16);
 }
 
-// Triangle record in BVH leaf order: t0 = (v0, id), t1 = (v1, material), t2 = (v2, 0).
-struct alignas(16) Tri {
-  float4 t0, t1, t2;
+// Triangle record in BVH leaf order, one 64-byte line: each vertex as x, y, z,
+// x, y, so that a query reads its three coordinates in any cyclic order (its
+// own axis order of the watertight test) with one 12-byte load and no
+// selection but that of the sign, and the global triangle id.
+struct alignas(64) Tri {
+  float v[3][5];
+  uint32_t gid;
 };
+
+__host__ __device__ inline Tri make_tri(const float* w9, uint32_t gid) {
+  Tri t;
+  for (int i = 0; i < 3; ++i)
+    for (int k = 0; k < 5; ++k) t.v[i][k] = w9[3 * i + k % 3];
+  t.gid = gid;
+  return t;
+}
 
 // ---------------------------------------------------------------------------
 // scene as seen by kernels (one entry per scene of a batch; plain calls use one)
@@ -151,10 +163,11 @@ struct ObjDev {
 struct LightDev {
   float half[2];
   float power[3];
+  float e1[3];      // photon power of Section 3, power / path_count
   uint32_t path_base, path_count;
   int32_t kind;     // PV_LIGHT_AREA / PV_LIGHT_SPOT / PV_LIGHT_CAMERA
   float param[2];   // spot: cos of the cone half-angle; camera: tan of the half field of view along u, v
-  uint32_t pad[2];
+  uint32_t pad[3];
 };
 
 struct LeafRec {          // a leaf of a hierarchy built on the host
@@ -226,6 +239,7 @@ struct SceneDev {
   uint32_t stride, n_paths, B;
   uint32_t verify_boxes;  // 1: a segment that reaches a moved object's box is invalid (no triangle test)
   uint32_t energy_test;   // Equation 2's E_N: PV_ENERGY_ALBEDO or PV_ENERGY_COSINE_RATIO
+  const uint32_t* rec_mat;  // [T] material of each record of the leaf-order triangle array
   const uint32_t* gid_rec;  // [T] record of each global triangle id in the leaf-order triangle array
   float eps_end, eps_close, radius;
   uint32_t gpath_base;    // offset of this scene's paths in the work-queue id space
@@ -343,45 +357,65 @@ __device__ inline float3 xyz(float4 v) { return f3(v.x, v.y, v.z); }
 __device__ inline float comp(float3 v, int k) { return k == 0 ? v.x : (k == 1 ? v.y : v.z); }
 
 // ---------------------------------------------------------------------------
-// ray / segment query state
+// ray / segment query state of the triangle tests (Woop, Benthin, Wald 2013):
+// the direction's largest component is the test's third axis, the other two
+// follow in cyclic order, exchanged when that component is negative
 struct Ray {
-  float3 o, d, inv;   // origin, direction (not necessarily unit), 1/direction
-  float3 oi;          // -o / d per axis: slab parameters are fma(bound, inv, oi)
-  float tmin, tmax;   // open interval of the parameter
-  int kx, ky, kz;     // watertight-test axis permutation
+  float3 ro;          // origin, components in the test's axis order
+  float3 d;           // direction (not necessarily unit)
+  float tmin;         // lower end of the open interval of the parameter
+  uint32_t axes;      // first axis of the cyclic order, + 4 when exchanged
   float sx, sy, sz;   // shear constants
 };
 
-__device__ inline Ray make_ray(float3 o, float3 d, float tmin, float tmax) {
+__device__ inline Ray make_ray(float3 o, float3 d, float tmin) {
   Ray r;
-  r.o = o;
   r.d = d;
-  const float tiny = 1e-30f;
-  float dx = fabsf(d.x) > tiny ? d.x : copysignf(tiny, d.x);
-  float dy = fabsf(d.y) > tiny ? d.y : copysignf(tiny, d.y);
-  float dz = fabsf(d.z) > tiny ? d.z : copysignf(tiny, d.z);
-  r.inv = f3(1.0f / dx, 1.0f / dy, 1.0f / dz);
-  r.oi = f3(-(o.x * r.inv.x), -(o.y * r.inv.y), -(o.z * r.inv.z));
   r.tmin = tmin;
-  r.tmax = tmax;
-  // Woop, Benthin, Wald 2013: largest |d| component becomes z
-  float ax = fabsf(d.x), ay = fabsf(d.y), az = fabsf(d.z);
-  int kz = (ax > ay) ? (ax > az ? 0 : 2) : (ay > az ? 1 : 2);
-  int kx = kz == 2 ? 0 : kz + 1;
-  int ky = kx == 2 ? 0 : kx + 1;
-  if (comp(d, kz) < 0.0f) {
-    int t = kx;
-    kx = ky;
-    ky = t;
-  }
-  r.kx = kx;
-  r.ky = ky;
-  r.kz = kz;
-  float dkz = comp(d, kz);
-  r.sx = comp(d, kx) / dkz;
-  r.sy = comp(d, ky) / dkz;
-  r.sz = 1.0f / dkz;
+  const float ax = fabsf(d.x), ay = fabsf(d.y), az = fabsf(d.z);
+  const int kz = (ax > ay) ? (ax > az ? 0 : 2) : (ay > az ? 1 : 2);
+  const float dz = kz == 0 ? d.x : (kz == 1 ? d.y : d.z);
+  const bool sw = dz < 0.0f;
+  r.axes = (kz == 2 ? 0u : (uint32_t)kz + 1u) + (sw ? 4u : 0u);
+  auto order = [&](float3 v) {
+    const float3 c = kz == 2 ? v : (kz == 0 ? f3(v.y, v.z, v.x) : f3(v.z, v.x, v.y));
+    return f3(sw ? c.y : c.x, sw ? c.x : c.y, c.z);
+  };
+  r.ro = order(o);
+  const float3 e = order(d);
+  r.sx = e.x / e.z;
+  r.sy = e.y / e.z;
+  r.sz = 1.0f / e.z;
   return r;
+}
+
+// the origin in world axis order
+__device__ inline float3 ray_origin(const Ray& r) {
+  const bool sw = (r.axes & 4u) != 0;
+  const float x = sw ? r.ro.y : r.ro.x, y = sw ? r.ro.x : r.ro.y, z = r.ro.z;
+  const uint32_t k = r.axes & 3u;
+  return k == 0u ? f3(x, y, z) : (k == 1u ? f3(z, x, y) : f3(y, z, x));
+}
+
+// what box tests read of a query: slab parameters are fma(bound, inv, oi)
+struct BoxRay {
+  float3 inv;         // 1 / direction
+  float3 oi;          // -origin / direction
+  float tmin, tmax;
+};
+
+// components kept at least 'tiny' from zero, sign kept
+__device__ inline float3 off_zero(float3 d) {
+  const float tiny = 1e-30f;
+  return f3(copysignf(fmaxf(fabsf(d.x), tiny), d.x), copysignf(fmaxf(fabsf(d.y), tiny), d.y),
+            copysignf(fmaxf(fabsf(d.z), tiny), d.z));
+}
+
+// 1 / d from the hardware reciprocal (1 ulp): moves a slab parameter by about
+// 1e-7 of itself, far inside the 1e-6 padding of every stored box
+__device__ inline float3 rcp3(float3 d) {
+  d = off_zero(d);
+  return f3(__builtin_amdgcn_rcpf(d.x), __builtin_amdgcn_rcpf(d.y), __builtin_amdgcn_rcpf(d.z));
 }
 
 // Slab test of one box against the ray's current [tmin, tmax]; returns the
@@ -389,7 +423,7 @@ __device__ inline Ray make_ray(float3 o, float3 d, float tmin, float tmax) {
 // bound * (1/d) - o/d; its error (relative 2^-24 of o/d, i.e. about 6e-8 of
 // the origin's coordinates in distance) stays far inside the 1e-6 padding of
 // every stored box, so the test remains conservative.
-__device__ inline float box_entry(float lx, float ly, float lz, float hx, float hy, float hz, const Ray& r,
+__device__ inline float box_entry(float lx, float ly, float lz, float hx, float hy, float hz, const BoxRay& r,
                                   float tmax) {
   float tx0 = fmaf(lx, r.inv.x, r.oi.x), tx1 = fmaf(hx, r.inv.x, r.oi.x);
   float ty0 = fmaf(ly, r.inv.y, r.oi.y), ty1 = fmaf(hy, r.inv.y, r.oi.y);
@@ -400,7 +434,7 @@ __device__ inline float box_entry(float lx, float ly, float lz, float hx, float 
 }
 
 // entry parameter of a box regardless of the query's interval
-__device__ inline float slab_entry(float lx, float ly, float lz, float hx, float hy, float hz, const Ray& r) {
+__device__ inline float slab_entry(float lx, float ly, float lz, float hx, float hy, float hz, const BoxRay& r) {
   const float tx0 = fmaf(lx, r.inv.x, r.oi.x), tx1 = fmaf(hx, r.inv.x, r.oi.x);
   const float ty0 = fmaf(ly, r.inv.y, r.oi.y), ty1 = fmaf(hy, r.inv.y, r.oi.y);
   const float tz0 = fmaf(lz, r.inv.z, r.oi.z), tz1 = fmaf(hz, r.inv.z, r.oi.z);
@@ -415,13 +449,18 @@ __device__ inline float slab_entry(float lx, float ly, float lz, float hx, float
 // only an exactly zero edge function takes the double-precision branch.
 // near_tb (may be null): set when the triangle is crossed past tmin within
 // 2.5e-7 (relative) of tmax.
-__device__ inline bool tri_hit(const Ray& r, float3 v0, float3 v1, float3 v2, float tmax, float* t_out,
+__device__ inline bool tri_hit(const Ray& r, const PV_GLOBAL Tri* __restrict__ tri, float tmax, float* t_out,
                                bool* near_tb) {
-  float3 A = sub(v0, r.o), B = sub(v1, r.o), C = sub(v2, r.o);
-  float Akz = comp(A, r.kz), Bkz = comp(B, r.kz), Ckz = comp(C, r.kz);
-  float Ax = comp(A, r.kx) - r.sx * Akz, Ay = comp(A, r.ky) - r.sy * Akz;
-  float Bx = comp(B, r.kx) - r.sx * Bkz, By = comp(B, r.ky) - r.sy * Bkz;
-  float Cx = comp(C, r.kx) - r.sx * Ckz, Cy = comp(C, r.ky) - r.sy * Ckz;
+  struct V {
+    float x, y, z;
+  };
+  const PV_GLOBAL float* base = &tri->v[0][0] + (r.axes & 3u);
+  const V a = *(const PV_GLOBAL V*)base, b = *(const PV_GLOBAL V*)(base + 5), c = *(const PV_GLOBAL V*)(base + 10);
+  const bool sw = (r.axes & 4u) != 0;
+  const float Akz = a.z - r.ro.z, Bkz = b.z - r.ro.z, Ckz = c.z - r.ro.z;
+  const float Ax = ((sw ? a.y : a.x) - r.ro.x) - r.sx * Akz, Ay = ((sw ? a.x : a.y) - r.ro.y) - r.sy * Akz;
+  const float Bx = ((sw ? b.y : b.x) - r.ro.x) - r.sx * Bkz, By = ((sw ? b.x : b.y) - r.ro.y) - r.sy * Bkz;
+  const float Cx = ((sw ? c.y : c.x) - r.ro.x) - r.sx * Ckz, Cy = ((sw ? c.x : c.y) - r.ro.y) - r.sy * Ckz;
   float U = __fsub_rn(__fmul_rn(Cx, By), __fmul_rn(Cy, Bx));
   float V = __fsub_rn(__fmul_rn(Ax, Cy), __fmul_rn(Ay, Cx));
   float W = __fsub_rn(__fmul_rn(Bx, Ay), __fmul_rn(By, Ax));
@@ -455,6 +494,7 @@ struct Hit {
   uint32_t gid;  // its global triangle id, kHitNone when none
   uint32_t rec;  // its record in the scene's triangle array
 };
+constexpr uint32_t kRecNone = 0xFFFFFFFFu;
 
 // Depth-first walk of the scene hierarchy from a root (near child first), in
 // resumable form for persistent kernels.  any = stop at the first crossing
@@ -475,8 +515,7 @@ struct Walk {
   int32_t leaf;   // a reached leaf whose test is postponed, 0 when none
   int sp;         // stack entries in use
   float tb;       // closest crossing so far (the ray's tmax initially)
-  uint32_t gid;   // its global triangle id, kHitNone when none
-  uint32_t rec;   // its record in the scene's triangle array
+  uint32_t rec;   // its record in the scene's triangle array, kRecNone when none
   bool redo;      // the binary walk must answer: near tie, or out of stack
 };
 
@@ -490,8 +529,7 @@ __device__ inline void walk_start(Walk& w, int32_t root, float tmax, StackCol co
   w.cur = root;
   w.leaf = 0;
   w.tb = tmax;
-  w.gid = kHitNone;
-  w.rec = 0;
+  w.rec = kRecNone;
   w.redo = false;
 }
 
@@ -514,9 +552,9 @@ __device__ inline Slab make_slab(float3 inv, float3 oi, float scale) {
 }
 
 // a world-space query against the scene's four-wide nodes
-__device__ inline Slab world_slab(const SceneDev& S, const Ray& r) {
-  const float3 c = f3(S.qc[0] - r.o.x, S.qc[1] - r.o.y, S.qc[2] - r.o.z);
-  return make_slab(r.inv, f3(c.x * r.inv.x, c.y * r.inv.y, c.z * r.inv.z), S.qinv);
+__device__ inline Slab world_slab(const SceneDev& S, float3 o, float3 inv) {
+  const float3 c = f3(S.qc[0] - o.x, S.qc[1] - o.y, S.qc[2] - o.z);
+  return make_slab(inv, f3(c.x * inv.x, c.y * inv.y, c.z * inv.z), S.qinv);
 }
 
 // a condition as the wave's mask, and a mask's bit of this lane: conditions
@@ -543,16 +581,16 @@ __device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, 
 
 // Speculative traversal (Aila and Laine 2009): a lane that reaches a leaf
 // while holding none keeps it pending and continues with the next stack
-// entry, until every lane still walking holds a leaf; then the wave tests
+// entry, until most lanes still walking hold a leaf; then the wave tests
 // leaves together.
 //
 // Nodes are four wide with FP16 planes: one 64-byte line, four 16-byte loads,
 // per visit, as the binary FP32 node took, and about a fifth of the visits (22
 // against 109 for a ray of the 3M-path, 380k-triangle interior), so a shorter
 // chain of dependent loads and fewer of them.  Bound by vector issue: about
-// 90 instructions a visit.  Measured there, one MI355X: full trace 5.66 to
-// 4.85 ms, partial re-trace 2.30 to 1.98 ms, verification traversal 224 to
-// 178 us.
+// 85 instructions a visit.  Measured there, one MI355X, four-wide against
+// binary: full trace 4.85 against 5.66 ms, partial re-trace 1.98 against 2.30
+// ms, verification traversal 178 against 224 us.
 //
 // Boxes are tested with the slab parameters q and triangles with the ray r
 // itself: a walk through a rigid object's hierarchy in its own object space
@@ -573,7 +611,7 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
   // allocates and nothing uses.
   StackCol top = col + (w.sp - 1) * kBlock;
   float tb = w.tb;
-  uint32_t gid = w.gid, rec = w.rec;
+  uint32_t rec = w.rec;
   bool redo = w.redo;
   const float tmin = __builtin_canonicalizef(r.tmin);
   while (true) {
@@ -635,7 +673,11 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
       leaf = post ? cur : leaf;
       cur = post ? next : cur;
       top = post ? top - kBlock : top;
-      if (__ballot(leaf == 0) == 0) break;  // every lane still here holds a leaf
+      // once at most a third of the lanes still here hold no leaf, the wave
+      // tests leaves: waiting for the last lane left 33 of 64 lanes active on
+      // average and took 5% longer on partial re-traces, waiting for half of
+      // them 1% longer on full traces
+      if (3 * __popcll(__ballot(leaf == 0)) <= __popcll(__ballot(1))) break;
     }
     if (leaf == 0 && is_leaf(cur)) {
       leaf = cur;
@@ -646,13 +688,11 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
     while (leaf != 0) {
       const uint32_t f = leaf_first(leaf), n = leaf_count(leaf);
       for (uint32_t i = f; i < f + n; ++i) {
-        const Tri tr = tris[i];
         float t;
         bool near_tb = false;
-        const bool hit = tri_hit(r, xyz(tr.t0), xyz(tr.t1), xyz(tr.t2), tb, &t, kTies ? &near_tb : nullptr);
+        const bool hit = tri_hit(r, tris + i, tb, &t, kTies ? &near_tb : nullptr);
         if (kTies) redo = near_tb || (redo && !hit);  // a clearly closer crossing ends a tie
         tb = hit ? t : tb;
-        gid = hit ? __float_as_uint(tr.t0.w) : gid;
         rec = hit ? i : rec;
         found |= hit;
       }
@@ -672,7 +712,6 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
   w.leaf = leaf;
   w.sp = (int)(top - col) / kBlock + 1;
   w.tb = tb;
-  w.gid = gid;
   w.rec = rec;
   w.redo = redo;
 }
@@ -685,21 +724,29 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
 // the four-wide walk's looser boxes change.  Rare (one ray in 10^4), so
 // nothing here is tuned.  any: stop at the first crossing.
 __device__ inline void walk_exact(const PV_GLOBAL Node* __restrict__ nodes, const PV_GLOBAL Tri* __restrict__ tris,
-                                  const Ray& r0, int32_t root, bool any, StackCol col, Walk& w) {
-  const Ray r = make_ray(r0.o, r0.d, r0.tmin, r0.tmax);
+                                  const Ray& r, float tmax, int32_t root, bool any, StackCol col, Walk& w) {
+  const float3 o = ray_origin(r), d = r.d;
+  BoxRay q;
+  const float tiny = 1e-30f;
+  q.inv = f3(1.0f / (fabsf(d.x) > tiny ? d.x : copysignf(tiny, d.x)),
+             1.0f / (fabsf(d.y) > tiny ? d.y : copysignf(tiny, d.y)),
+             1.0f / (fabsf(d.z) > tiny ? d.z : copysignf(tiny, d.z)));
+  q.oi = f3(-(o.x * q.inv.x), -(o.y * q.inv.y), -(o.z * q.inv.z));
+  q.tmin = r.tmin;
+  q.tmax = tmax;
   StackCol top = col;
   top[0] = kRootNone;
   int32_t cur = root;
-  float tb = r.tmax;
-  uint32_t gid = kHitNone, rec = 0;
+  float tb = tmax;
+  uint32_t rec = kRecNone;
   while (cur != kRootNone) {
     if (cur >= 0) {
       const Node nd = *(const PV_GLOBAL Node*)((const PV_GLOBAL char*)nodes + ((uint32_t)cur << 6));
-      const float e0 = box_entry(nd.a.x, nd.a.y, nd.a.z, nd.a.w, nd.b.x, nd.b.y, r, tb);
-      const float e1 = box_entry(nd.b.z, nd.b.w, nd.c.x, nd.c.y, nd.c.z, nd.c.w, r, tb);
+      const float e0 = box_entry(nd.a.x, nd.a.y, nd.a.z, nd.a.w, nd.b.x, nd.b.y, q, tb);
+      const float e1 = box_entry(nd.b.z, nd.b.w, nd.c.x, nd.c.y, nd.c.z, nd.c.w, q, tb);
       const bool h0 = e0 != __builtin_inff(), h1 = e1 != __builtin_inff();
-      const bool near0 = h0 && (!h1 || slab_entry(nd.a.x, nd.a.y, nd.a.z, nd.a.w, nd.b.x, nd.b.y, r) <=
-                                           slab_entry(nd.b.z, nd.b.w, nd.c.x, nd.c.y, nd.c.z, nd.c.w, r));
+      const bool near0 = h0 && (!h1 || slab_entry(nd.a.x, nd.a.y, nd.a.z, nd.a.w, nd.b.x, nd.b.y, q) <=
+                                           slab_entry(nd.b.z, nd.b.w, nd.c.x, nd.c.y, nd.c.z, nd.c.w, q));
       if (h0 && h1) {
         top += kBlock;
         top[0] = near0 ? nd.d.y : nd.d.x;
@@ -709,35 +756,43 @@ __device__ inline void walk_exact(const PV_GLOBAL Node* __restrict__ nodes, cons
     } else {
       const uint32_t f = leaf_first(cur), n = leaf_count(cur);
       for (uint32_t i = f; i < f + n; ++i) {
-        const Tri tr = tris[i];
         float t;
-        if (tri_hit(r, xyz(tr.t0), xyz(tr.t1), xyz(tr.t2), tb, &t, nullptr)) {
+        if (tri_hit(r, tris + i, tb, &t, nullptr)) {
           tb = t;
-          gid = __float_as_uint(tr.t0.w);
           rec = i;
         }
       }
-      if (any && gid != kHitNone) break;
+      if (any && rec != kRecNone) break;
     }
     cur = top[0];
     top -= kBlock;
   }
   w.tb = tb;
-  w.gid = gid;
   w.rec = rec;
 }
 
 // ---------------------------------------------------------------------------
 // Philox4x64-10 (Salmon, Moraes, Dror, Shaw, SC'11) from its published
 // definition; uniforms are the top 24 bits of each word times 2^-24.
+// The 128-bit products are formed from four 32 x 32 + 64 bit multiply-adds.
+__device__ inline void mul64(uint64_t m, uint64_t c, uint64_t* lo, uint64_t* hi) {
+  const uint32_t ml = (uint32_t)m, mh = (uint32_t)(m >> 32), cl = (uint32_t)c, ch = (uint32_t)(c >> 32);
+  const uint64_t p0 = (uint64_t)ml * cl;
+  const uint64_t p1 = (uint64_t)mh * cl + (p0 >> 32);
+  const uint64_t p2 = (uint64_t)ml * ch + (uint32_t)p1;
+  *hi = ((uint64_t)mh * ch + (p1 >> 32)) + (p2 >> 32);
+  *lo = (p2 << 32) | (uint32_t)p0;
+}
+
 __device__ inline void philox4x64(uint64_t c[4], uint64_t k0, uint64_t k1) {
   const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
   const uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    uint64_t lo0 = M0 * c[0], hi0 = __umul64hi(M0, c[0]);
-    uint64_t lo1 = M1 * c[2], hi1 = __umul64hi(M1, c[2]);
-    uint64_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
+    uint64_t lo0, hi0, lo1, hi1;
+    mul64(M0, c[0], &lo0, &hi0);
+    mul64(M1, c[2], &lo1, &hi1);
+    const uint64_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
     c[0] = n0;
     c[1] = lo1;
     c[2] = n2;
@@ -758,19 +813,15 @@ __device__ inline void draw4(uint64_t seed, uint64_t path, uint64_t frame, uint6
 // Shirley-Chiu concentric map to the unit disk, lifted to the cosine-weighted
 // hemisphere (Malley): local (x, y, z).
 __device__ inline float3 cosine_local(float u1, float u2) {
-  float a = 2.0f * u1 - 1.0f, b = 2.0f * u2 - 1.0f, r, phi;
+  const float a = 2.0f * u1 - 1.0f, b = 2.0f * u2 - 1.0f;
   const float PI4 = 0.78539816339744830962f;
-  if (a == 0.0f && b == 0.0f) {
-    r = 0.0f;
-    phi = 0.0f;
-  } else if (fabsf(a) > fabsf(b)) {
-    r = a;
-    phi = PI4 * (b / a);
-  } else {
-    r = b;
-    phi = 2.0f * PI4 - PI4 * (a / b);
-  }
-  float x = r * cosf(phi), y = r * sinf(phi);
+  const bool zero = a == 0.0f && b == 0.0f, wide = fabsf(a) > fabsf(b);
+  const float q = (wide ? b : a) / (wide ? a : b);  // one division for both wedges
+  const float r = zero ? 0.0f : (wide ? a : b);
+  const float phi = zero ? 0.0f : (wide ? PI4 * q : 2.0f * PI4 - PI4 * q);
+  float sn, cs;
+  sincosf(phi, &sn, &cs);
+  const float x = r * cs, y = r * sn;
   // height above the disk point at radius |r|; (1-|r|) is exact for |r| >= 1/2
   float ar = fabsf(r);
   float z2 = (1.0f - ar) * (1.0f + ar);

@@ -117,17 +117,16 @@ __device__ inline float pad_hi(float x) { return x + (1e-6f + fabsf(x) * 1e-6f);
 // of an internal node's two child boxes
 __device__ inline void child_box(const SceneDev& S, int32_t code, float* b) {
   if (code < 0) {
-    uint32_t f = leaf_first(code), c = leaf_count(code);
+    uint32_t f = leaf_first(code), n = leaf_count(code);
     float lo[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
     float hi[3] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-    for (uint32_t i = f; i < f + c; ++i) {
-      Tri t = S.tris[i];
-      float4 vs[3] = {t.t0, t.t1, t.t2};
-      for (int k = 0; k < 3; ++k) {
-        lo[0] = fminf(lo[0], vs[k].x); hi[0] = fmaxf(hi[0], vs[k].x);
-        lo[1] = fminf(lo[1], vs[k].y); hi[1] = fmaxf(hi[1], vs[k].y);
-        lo[2] = fminf(lo[2], vs[k].z); hi[2] = fmaxf(hi[2], vs[k].z);
-      }
+    for (uint32_t i = f; i < f + n; ++i) {
+      const Tri t = S.tris[i];
+      for (int k = 0; k < 3; ++k)
+        for (int c = 0; c < 3; ++c) {
+          lo[c] = fminf(lo[c], t.v[k][c]);
+          hi[c] = fmaxf(hi[c], t.v[k][c]);
+        }
     }
     for (int k = 0; k < 3; ++k) {
       b[k] = pad_lo(lo[k]);
@@ -161,12 +160,7 @@ __global__ __launch_bounds__(kBlock) void k_transform(SceneDev* scenes, const ui
     for (int k = 0; k < 3; ++k)
 #pragma unroll
       for (int r = 0; r < 3; ++r) w[3 * k + r] = xform_coord(m, r, v[3 * k], v[3 * k + 1], v[3 * k + 2]);
-    uint32_t gid = S.dtri_gid[rec];
-    Tri t;
-    t.t0 = make_float4(w[0], w[1], w[2], __uint_as_float(gid));
-    t.t1 = make_float4(w[3], w[4], w[5], __uint_as_float(S.tri_mat[gid]));
-    t.t2 = make_float4(w[6], w[7], w[8], 0.0f);
-    S.tris[S.n_static + rec] = t;
+    S.tris[S.n_static + rec] = make_tri(w, S.dtri_gid[rec]);
   }
 }
 
@@ -458,7 +452,7 @@ __device__ inline bool on_moved(const MovedSet& M, uint32_t hit) {
 // same decision as box_entry(...) != inf when tmin <= tmax, with the interval
 // entering by comparisons (the slab parameters are fma results, so the
 // min/max need no operand canonicalisation)
-__device__ inline bool slab_hit(float4 lo, float4 hi, const Ray& r) {
+__device__ inline bool slab_hit(float4 lo, float4 hi, const BoxRay& r) {
   const float x0 = fmaf(lo.x, r.inv.x, r.oi.x), x1 = fmaf(hi.x, r.inv.x, r.oi.x);
   const float y0 = fmaf(lo.y, r.inv.y, r.oi.y), y1 = fmaf(hi.y, r.inv.y, r.oi.y);
   const float z0 = fmaf(lo.z, r.inv.z, r.oi.z), z1 = fmaf(hi.z, r.inv.z, r.oi.z);
@@ -468,7 +462,7 @@ __device__ inline bool slab_hit(float4 lo, float4 hi, const Ray& r) {
 }
 
 // whether a ray reaches any moved object's box within its interval
-__device__ inline bool reaches_moved_box(const MovedSet& M, const Ray& r) {
+__device__ inline bool reaches_moved_box(const MovedSet& M, const BoxRay& r) {
   bool h = false;
   for (int i = 0; i < M.n; ++i) {
     const float4 lo = M.lo[i], hi = M.hi[i];
@@ -477,11 +471,12 @@ __device__ inline bool reaches_moved_box(const MovedSet& M, const Ray& r) {
   return h;
 }
 
-__device__ inline Ray segment_ray(float3 a, float3 b, float eps) {
+__device__ inline Ray segment_ray(float3 a, float3 b, float eps, float* tmax) {
   float3 d = sub(b, a);
   float L = length(d);
   float tmin = L > 0.0f ? eps / L : 1.0f;
-  return make_ray(a, d, tmin, 1.0f - tmin);
+  *tmax = 1.0f - tmin;
+  return make_ray(a, d, tmin);
 }
 
 // The box-test part of segment_ray, for filters only: 1/d from the hardware
@@ -489,15 +484,10 @@ __device__ inline Ray segment_ray(float3 a, float3 b, float eps) {
 // move slab parameters by about 1e-7 of the segment or widen the tested
 // interval, far inside the 1e-6 padding of every stored box, so a segment that
 // crosses a triangle inside a box always reaches that box.
-__device__ inline Ray segment_box_ray(float3 a, float3 b, float eps) {
-  Ray r;
+__device__ inline BoxRay segment_box_ray(float3 a, float3 b, float eps) {
+  BoxRay r;
   const float3 d = sub(b, a);
-  const float tiny = 1e-30f;
-  // |d| raised to at least tiny, sign kept (the same values as a select)
-  const float dx = copysignf(fmaxf(fabsf(d.x), tiny), d.x);
-  const float dy = copysignf(fmaxf(fabsf(d.y), tiny), d.y);
-  const float dz = copysignf(fmaxf(fabsf(d.z), tiny), d.z);
-  r.inv = f3(__builtin_amdgcn_rcpf(dx), __builtin_amdgcn_rcpf(dy), __builtin_amdgcn_rcpf(dz));
+  r.inv = rcp3(d);
   r.oi = f3(-(a.x * r.inv.x), -(a.y * r.inv.y), -(a.z * r.inv.z));
   const float L2 = dot(d, d);
   r.tmin = L2 > 0.0f ? eps * __builtin_amdgcn_rsqf(L2) * (1.0f - 1e-5f) : 1.0f;
@@ -699,7 +689,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_scan(const SceneDev* __restri
       // Rows are tested up to the scene's bounce limit (uniform), not the
       // path's own count, so that no lane-dependent branch splits the loop.
       // Box hits are collected as wave masks (one per row, scalar registers).
-      Ray rs[kPreRows];
+      BoxRay rs[kPreRows];
       uint64_t hit[kPreRows];
       uint32_t mv = 0;
 #pragma unroll
@@ -906,8 +896,10 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
             const float3 a = j == 0 ? f3(org[q], org[stride + q], org[2 * stride + q])
                                     : xyz(G(S->pos)[(size_t)(j - 1) * stride + q]);
             const float3 b = xyz(G(S->pos)[(size_t)j * stride + q]);
-            r = segment_ray(a, b, S->eps_end);
-            qb = world_slab(*S, r);
+            float tmax;
+            r = segment_ray(a, b, S->eps_end, &tmax);
+            const BoxRay br = segment_box_ray(a, b, S->eps_end);
+            qb = world_slab(*S, a, br.inv);
             int32_t root = G(S->wtop)[1];
             if (kSingle && !vis) {
               // the objects whose boxes the segment reaches, from LDS: one
@@ -918,7 +910,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
               int only = 0;
               for (int i = 0; i < M.n; ++i) {
                 const float4 lo = M.lo[i], hi = M.hi[i];
-                const bool h = box_entry(lo.x, lo.y, lo.z, hi.x, hi.y, hi.z, r, r.tmax) != __builtin_inff();
+                const bool h = box_entry(lo.x, lo.y, lo.z, hi.x, hi.y, hi.z, br, br.tmax) != __builtin_inff();
                 nh += h ? 1u : 0u;
                 only = h ? i : only;
               }
@@ -938,18 +930,14 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
                                      mi[3] * tb.x + mi[4] * tb.y + mi[5] * tb.z,
                                      mi[6] * tb.x + mi[7] * tb.y + mi[8] * tb.z);
                 const float3 od = sub(ob, oa);
-                const float tiny = 1e-30f;
-                const float dx = copysignf(fmaxf(fabsf(od.x), tiny), od.x);
-                const float dy = copysignf(fmaxf(fabsf(od.y), tiny), od.y);
-                const float dz = copysignf(fmaxf(fabsf(od.z), tiny), od.z);
-                const float3 binv = f3(__builtin_amdgcn_rcpf(dx), __builtin_amdgcn_rcpf(dy), __builtin_amdgcn_rcpf(dz));
+                const float3 binv = rcp3(od);
                 qb = make_slab(binv, f3(-(oa.x * binv.x), -(oa.y * binv.y), -(oa.z * binv.z)), S->qinv);
                 root = moroot[only];
               }
             }
             if (vis) root = G(S->wtop)[0];
             vis_task = vis;
-            walk_start(w, root, r.tmax, col);
+            walk_start(w, root, tmax, col);
             busy = root != kRootNone;
           }
         }
@@ -962,8 +950,8 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
     if (busy) {
       walk_run<false>(G(S->wide), G(S->tris), r, qb, true, col, limit, w, min_active);
       if (walk_done(w)) {
-        if (w.redo) walk_exact(G(S->nodes), G(S->tris), r, G(S->top)[vis_task ? 0 : 1], true, col, w);
-        if (w.gid != kHitNone) atomicMin(&W.first[gp], j);
+        if (w.redo) walk_exact(G(S->nodes), G(S->tris), r, 1.0f - r.tmin, G(S->top)[vis_task ? 0 : 1], true, col, w);
+        if (w.rec != kRecNone) atomicMin(&W.first[gp], j);
         busy = false;
       }
     }
@@ -1205,15 +1193,13 @@ __global__ __launch_bounds__(kBlock) void k_mark_all(const SceneDev* __restrict_
 
 constexpr float kTFar = 16.0f;
 
+__device__ inline float3 tri_vertex(const PV_GLOBAL Tri* t, int i) { return f3(t->v[i][0], t->v[i][1], t->v[i][2]); }
+
 __device__ inline float3 hit_normal(const SceneDev& S, const Hit& h) {
-  Tri t = G(S.tris)[h.rec];
-  float3 v0 = xyz(t.t0), v1 = xyz(t.t1), v2 = xyz(t.t2);
+  const PV_GLOBAL Tri* t = G(S.tris) + h.rec;
+  const float3 v0 = tri_vertex(t, 0), v1 = tri_vertex(t, 1), v2 = tri_vertex(t, 2);
   float3 n = cross(sub(v1, v0), sub(v2, v0));
   return mul(n, 1.0f / length(n));
-}
-
-__device__ inline uint32_t hit_material(const SceneDev& S, const Hit& h) {
-  return __float_as_uint(G(S.tris)[h.rec].t1.w);
 }
 
 __device__ inline float3 vertex(const SceneDev& S, uint32_t p, uint32_t j) {
@@ -1313,83 +1299,132 @@ __device__ inline void clear_rows(const SceneDev& S, uint32_t p, uint32_t from) 
 __device__ inline float3 normalize3(float3 v) { return mul(v, 1.0f / length(v)); }
 
 
+// Bound by vector issue (91% of a full trace's cycles at five waves per SIMD).
+// 96 registers hold five waves without spills because little outlives a walk
+// (struct Lane); sampling, hit normals, photon writes and path ends are shared
+// by the modes that need them, since a wave holds lanes of several modes at
+// once and would run each mode's copy in turn.  Measured over the 3M-path,
+// 380k-triangle interior, one MI355X: full trace 4.08 ms (4.85 with a copy
+// per mode, all of a path's state kept and four waves), partial re-trace
+// 1.63 ms (1.98).
+//
 // Re-trace state machine: every iteration each busy lane issues exactly one
 // query (closest hit over the scene, or any hit against the moved objects),
 // then advances its path; lanes whose path is finished take the next path of
 // the work queue (persistent while-while scheme, Aila & Laine 2009).
 enum : uint32_t {
   ST_IDLE = 0,   // needs a path
-  ST_FIRST,      // trace segment k from x (direction w), naive continuation
-  ST_TAIL,       // sample a bounce from photon 'row' and trace it
+  ST_LIGHT,      // draw a new light sample and trace its ray
+  ST_DIR,        // trace from x along w, naive continuation
+  ST_TAIL,       // sample a bounce at x and trace it
   ST_WCHECK,     // walk: is segment j (origin unchanged) still valid?
   ST_WTRACE,     // walk: trace segment j
   ST_WSKIP,      // walk: accepted close re-hit; is segment j+1 clear?
   ST_END         // queue exhausted
 };
 
+// What a lane keeps while its query is walked: its path, the packed state, and
+// four words whose meaning follows from the mode.  Everything else (the
+// vertex, its normal, the material) is used up when the next query is set up,
+// in the same round of the loop, so that it takes no registers during walks.
 struct Lane {
-  const SceneDev* S;
-  uint32_t p, mode, n, k, cell, j, newn, row, mat, hgid;
-  int l;
-  float3 x, w, ntri, e, hp;
+  uint32_t s;  // scene of a batch
+  uint32_t p;
+  // mode, j (walk: segment), newn (photons the path will have), row1 (photon
+  // that the ray of ST_LIGHT, ST_DIR or ST_TAIL writes): 4 bits each
+  uint32_t st;
+  // ST_DIR and ST_TAIL: energy arriving at x and its material (ST_LIGHT, and
+  // ST_DIR from the light: the energy of the first photon); ST_WSKIP: the
+  // accepted re-hit and its triangle
+  float3 e;
+  uint32_t mat;
 };
 
-__device__ inline void finish(Lane& L) {
-  clear_rows(*L.S, L.p, L.newn);
-  G(L.S->info)[L.p] = info_pack(L.cell, L.newn, 0, 0, 0);
-  L.mode = ST_IDLE;
+__device__ inline uint32_t lane_mode(uint32_t st) { return st & 15u; }
+__device__ inline uint32_t lane_j(uint32_t st) { return (st >> 4) & 15u; }
+__device__ inline uint32_t lane_newn(uint32_t st) { return (st >> 8) & 15u; }
+__device__ inline uint32_t lane_row1(uint32_t st) { return st >> 12; }
+__device__ inline uint32_t lane_state(uint32_t mode, uint32_t j, uint32_t newn, uint32_t row1) {
+  return mode | (j << 4) | (newn << 8) | (row1 << 12);
 }
 
-// after writing photon 'row' (position x, triangle normal, material, energy):
-// continue sampling or finish
-__device__ inline void to_tail(Lane& L) {
-  if (L.row + 1 < L.S->B) {
-    L.mode = ST_TAIL;
-  } else {
-    L.newn = L.row + 1;
-    finish(L);
-  }
-}
-
-__device__ inline void start_path(Lane& L, float T, uint64_t seed, uint32_t frame, const PV_LDS SceneTab* tab) {
-  const SceneDev& S = *L.S;
-  uint32_t w = G(S.info)[L.p];
-  L.n = min(info_nseg(w), S.B);
-  L.k = info_start(w);
-  L.cell = info_cell(w);
-  L.l = tab ? light_of(*tab, L.p) : light_of(S, L.p);
+// A queued path's first query: its mode, and for ST_DIR the vertex x and the
+// direction w.  A path without the replace bit stays idle.
+__device__ inline void start_path(const SceneDev& S, Lane& L, float T, const PV_LDS SceneTab* tab, float3* x,
+                                  float3* wd) {
+  const uint32_t w = G(S.info)[L.p];
+  const uint32_t n = min(info_nseg(w), S.B);
+  uint32_t k = info_start(w);
+  const int l = tab ? light_of(*tab, L.p) : light_of(S, L.p);
   bool reuse = info_reuse(w) != 0;
-  if (!info_replace(w) || L.l < 0) {
-    L.mode = ST_IDLE;
+  if (!info_replace(w) || l < 0) {
+    L.st = ST_IDLE;
     return;
   }
-  if (L.k >= L.n) {
-    L.k = 0;
+  if (k >= n) {
+    k = 0;
     reuse = false;
   }
-  if (L.k == 0 && !reuse) {
-    // new light sample: position uniform on the rectangle, direction
-    // cosine-weighted about the light normal (one Philox draw, tag 0)
-    const PV_GLOBAL float* xf = G(S.light_xf_cur) + 12 * L.l;
-    const PV_GLOBAL LightDev* lt = G(S.lights) + L.l;
-    float3 eu = f3(xf[0], xf[4], xf[8]), ev = f3(xf[1], xf[5], xf[9]);
-    float3 nl = normalize3(f3(xf[2], xf[6], xf[10])), c = f3(xf[3], xf[7], xf[11]);
-    float u[4];
-    draw4(seed, L.p, frame, 0, 0, u);
+  if (k == 0) {
+    const PV_GLOBAL LightDev* lt = G(S.lights) + l;
+    L.e = f3(lt->e1[0], lt->e1[1], lt->e1[2]);
+  }
+  if (k == 0 && !reuse) {
+    L.st = lane_state(ST_LIGHT, 0, 0, 0);
+  } else if (T < 0.0f) {
+    *x = vertex(S, L.p, k);
+    *wd = normalize3(sub(vertex(S, L.p, k + 1), *x));
+    if (k > 0) {
+      L.e = energy_row(S, L.p, k - 1);
+      L.mat = mat_of(S, vertex_hit(S, L.p, k));
+    }
+    L.st = lane_state(ST_DIR, 0, 0, k);
+  } else {
+    // After the triangle test segment k is known to be blocked.  After the
+    // box test it only reached a moved object's box, and Section 3.3 casts no
+    // ray for a segment that the box crosses but no triangle: with its origin
+    // unchanged the walk first checks it against the moved triangles.
+    const bool origin_moved = k == 0 && G(S.light_moved)[l] != 0;
+    L.st = lane_state((S.verify_boxes && !origin_moved) ? ST_WCHECK : ST_WTRACE, k, n, 0);
+  }
+}
+
+// The ray of a sampled vertex: a new light sample (position uniform on the
+// rectangle, direction cosine-weighted about the light normal, Philox tag 0)
+// or a diffuse bounce about n at x (tag 1).  Both draw here, so that lanes
+// starting a path share the draw and the disk map with the lanes that bounce.
+// Sets x and the stored origin for a light sample; returns the direction.
+__device__ inline float3 sample_ray(const SceneDev& S, const Lane& L, uint64_t seed, uint32_t frame,
+                                    const PV_LDS SceneTab* tab, float3* x, float3 n) {
+  const bool light = lane_mode(L.st) == ST_LIGHT;
+  float u[4];
+  draw4(seed, L.p, frame, light ? 0u : lane_row1(L.st), light ? 0u : 1u, u);
+  float3 lc = cosine_local(light ? u[2] : u[0], light ? u[3] : u[1]);
+  float3 tt, bb, nn = n;
+  float3 w = f3(0.0f, 0.0f, 0.0f);
+  bool done = false;
+  if (light) {
+    const int l = tab ? light_of(*tab, L.p) : light_of(S, L.p);
+    const PV_GLOBAL float* xf = G(S.light_xf_cur) + 12 * l;
+    tt = f3(xf[0], xf[4], xf[8]);
+    bb = f3(xf[1], xf[5], xf[9]);
+    nn = normalize3(f3(xf[2], xf[6], xf[10]));
+    const float3 c = f3(xf[3], xf[7], xf[11]);
+    const LightDev ld = G(S.lights)[l];
     float3 x0;
-    const LightDev ld = *lt;
     if (S.dm[0] > 0) {
       // distribution maps: the sample is drawn inside the path's cell
-      dm_sample((const float*)xf, ld, S.dm, L.cell, u, &x0, &L.w);
+      dm_sample((const float*)xf, ld, S.dm, info_cell(G(S.info)[L.p]), u, &x0, &w);
+      done = true;
     } else if (ld.kind == PV_LIGHT_CAMERA) {
       // uniform over the near plane at unit distance
-      const float x = (2.0f * u[0] - 1.0f) * ld.param[0], y = (2.0f * u[1] - 1.0f) * ld.param[1];
+      const float px = (2.0f * u[0] - 1.0f) * ld.param[0], py = (2.0f * u[1] - 1.0f) * ld.param[1];
       x0 = c;
-      L.w = mul(add(add(mul(eu, x), mul(ev, y)), nl), 1.0f / sqrtf(x * x + y * y + 1.0f));
+      w = mul(add(add(mul(tt, px), mul(bb, py)), nn), 1.0f / sqrtf(px * px + py * py + 1.0f));
+      done = true;
     } else {
-      float a = (2.0f * u[0] - 1.0f) * ld.half[0], b = (2.0f * u[1] - 1.0f) * ld.half[1];
-      x0 = add(c, add(mul(eu, a), mul(ev, b)));
-      float3 lc = cosine_local(u[2], u[3]);
+      const float a = (2.0f * u[0] - 1.0f) * ld.half[0], b = (2.0f * u[1] - 1.0f) * ld.half[1];
+      x0 = add(c, add(mul(tt, a), mul(bb, b)));
       if (ld.kind == PV_LIGHT_SPOT) {
         // the disk point scaled to the cone's radius, then lifted: with the
         // unit disk's height z0, 1 - sr^2 r^2 = cos^2 + sr^2 z0^2 (no
@@ -1400,29 +1435,18 @@ __device__ inline void start_path(Lane& L, float T, uint64_t seed, uint32_t fram
         lc.y *= sr;
         lc.z = sqrtf(ld.param[0] * ld.param[0] + (sr * sr) * (z0 * z0));
       }
-      L.w = add(add(mul(eu, lc.x), mul(ev, lc.y)), mul(nl, lc.z));
     }
     const size_t stride = S.stride;
     PV_GLOBAL float* org = G(S.origin);
     org[L.p] = x0.x;
     org[stride + L.p] = x0.y;
     org[2 * stride + L.p] = x0.z;
-    L.x = x0;
-    L.mode = ST_FIRST;
-  } else if (T < 0.0f) {
-    L.x = vertex(S, L.p, L.k);
-    L.w = normalize3(sub(vertex(S, L.p, L.k + 1), L.x));
-    L.mode = ST_FIRST;
+    *x = x0;
   } else {
-    L.j = L.k;
-    L.newn = L.n;
-    // After the triangle test segment k is known to be blocked.  After the
-    // box test it only reached a moved object's box, and Section 3.3 casts no
-    // ray for a segment that the box crosses but no triangle: with its origin
-    // unchanged the walk first checks it against the moved triangles.
-    const bool origin_moved = L.k == 0 && G(S.light_moved)[L.l] != 0;
-    L.mode = (S.verify_boxes && !origin_moved) ? ST_WCHECK : ST_WTRACE;
+    onb(nn, &tt, &bb);
   }
+  const float3 q = add(add(mul(tt, lc.x), mul(bb, lc.y)), mul(nn, lc.z));
+  return done ? w : q;
 }
 
 template <bool kSingle, int kWaves>
@@ -1433,35 +1457,183 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
                                                     pv_stats* stats, int min_active, uint32_t entries,
                                                     uint32_t* __restrict__ deal_ctr) {
   extern __shared__ int32_t sstack[];  // traversal stacks, launch-time size
-  __shared__ unsigned long long sred[kBlock / 64];
+  __shared__ uint32_t scount[4];
   __shared__ SceneTab stab;
   const StackCol col = (StackCol)(sstack + kBlock + threadIdx.x);  // entry 0 of the column; entry -1 spare
   const StackCol limit = col + (int)(entries - 5) * kBlock;  // top from which a full node would pass the last entry
   const uint32_t frame = frame_ptr ? *frame_ptr : frame_arg;
-  uint32_t n_rays = 0, n_photons = 0, n_acc = 0, n_trunc = 0;
+  uint32_t n_rays = 0, n_photons = 0, n_acc = 0, n_trunc = 0;  // of the wave
   const PV_LDS SceneTab* tab = nullptr;
+  if (threadIdx.x < 4) scount[threadIdx.x] = 0;
   if (kSingle) {
     load_tab(scenes[0], stab);
     tab = (const PV_LDS SceneTab*)&stab;
   }
   __shared__ uint32_t sgb[kSingle ? 1 : kLdsScenes + 1];
   if (!kSingle) gbase = stage_gbase(gbase, n_scenes, sgb);
+  __syncthreads();
   // the work queue, dealt by deal() from the counters 'deal_ctr'
   const uint32_t count = *qcount;
   const uint32_t wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   Lane L;
-  L.S = scenes;
-  L.mode = ST_IDLE;
+  L.s = 0;
+  L.st = ST_IDLE;
   L.p = 0;
+  L.e = f3(0.0f, 0.0f, 0.0f);
+  L.mat = 0;
   Ray r;             // the lane's current query
-  Slab qb{};         // its box-test parameters
   Walk wk;           // its walk through the hierarchy
   wk.cur = kRootNone;
   wk.leaf = 0;
   bool tracing = false, any = false;
   while (true) {
-    // refill idle lanes from the queue
-    const bool want = L.mode == ST_IDLE;
+    const SceneDev& S = scenes[kSingle ? 0u : L.s];
+    // ---- walk; the box-test parameters follow from the ray, a few
+    // instructions beside the walk's thousands, and hold no registers outside
+    if (tracing) {
+      const Slab q = world_slab(S, ray_origin(r), rcp3(r.d));
+      walk_run<true>(G(S.wide), G(S.tris), r, q, any, col, limit, wk, min_active);
+    }
+    // ---- lanes whose walk is finished advance their path.  What several
+    // modes share is done once for all of them: the new vertex with its
+    // normal and material before the switch, the photon written, the start
+    // of a tail and the end of a path after it
+    float3 x = f3(0.0f, 0.0f, 0.0f), nw = x;  // ST_DIR: vertex, direction; ST_TAIL: vertex, normal
+    bool write = false, accepted = false, cut = false;
+    if (tracing && walk_done(wk)) {
+      tracing = false;
+      if (wk.redo && !(any && wk.rec != kRecNone))
+        walk_exact(G(S.nodes), G(S.tris), r, any ? 1.0f - r.tmin : kTFar, G(S.top)[any ? 1 : 0], any, col, wk);
+      Hit h;
+      h.t = wk.tb;
+      h.rec = wk.rec;
+      const bool hit = h.rec != kRecNone;
+      h.gid = kHitNone;
+      const float3 qd = r.d, xa = ray_origin(r);
+      float3 nh = x, en = x;
+      uint32_t mat = 0, row = 0;
+      if (hit && !any) {
+        x = add(xa, mul(qd, h.t));
+        nh = hit_normal(S, h);
+        h.gid = G(S.tris)[h.rec].gid;
+        mat = G(S.rec_mat)[h.rec];
+      }
+      uint32_t mode = lane_mode(L.st), j = lane_j(L.st), newn = lane_newn(L.st);
+      bool tail = false;  // the photon written is followed by sampled bounces
+      bool end = false;   // the path ends with newn photons
+      uint32_t hgid = h.gid;
+      switch (mode) {
+        case ST_LIGHT:
+        case ST_DIR:
+        case ST_TAIL: {
+          row = lane_row1(L.st);
+          if (!hit) {
+            cut = end = true;
+            newn = row;
+            break;
+          }
+          en = row == 0 ? L.e : reflect_energy(S, L.e, L.mat);
+          write = tail = true;
+          break;
+        }
+        case ST_WCHECK: {
+          if (hit)
+            mode = ST_WTRACE;
+          else
+            end = ++j >= newn;
+          break;
+        }
+        case ST_WTRACE: {
+          if (!hit) {
+            cut = end = true;
+            newn = j;
+            break;
+          }
+          en = energy_row(S, L.p, j);
+          row = j;
+          write = true;
+          if (j == newn - 1) {
+            end = true;
+            break;
+          }
+          float3 xc = vertex(S, L.p, j + 2);
+          float3 d2 = sub(xc, x);
+          float c1 = dot(qd, nh), l2 = length(d2);
+          float c2 = l2 > 0.0f ? dot(d2, nh) / l2 : 0.0f;
+          float3 eN = (c1 * c2 < 0.0f) ? reflect_energy(S, en, mat) : f3(0.0f, 0.0f, 0.0f);
+          if (S.energy_test == PV_ENERGY_COSINE_RATIO && c1 * c2 < 0.0f) {
+            // the kept direction's cosine at the new vertex over the one at the
+            // old vertex (its stored triangle, from x_{j+1} to x_{j+2})
+            const PV_GLOBAL Tri* to = G(S.tris) + G(S.gid_rec)[vertex_hit(S, L.p, j + 1)];
+            const float3 o0 = tri_vertex(to, 0);
+            const float3 no = cross(sub(tri_vertex(to, 1), o0), sub(tri_vertex(to, 2), o0));
+            const float3 d3 = sub(xc, vertex(S, L.p, j + 1));
+            const float den = fabsf(dot(d3, no)), num = fabsf(c2) * length(d3) * length(no);
+            const float ratio = den > 0.0f ? num / den : 0.0f;
+            eN = mul(eN, ratio);
+          }
+          float3 eo = energy_row(S, L.p, j + 1);
+          if (!eq2(eN, eo, T)) {
+            // energies differ: keep the new hit and re-sample the rest
+            tail = true;
+            break;
+          }
+          accepted = true;
+          float dist = length(sub(x, vertex(S, L.p, j + 1)));
+          auto moved = [&](uint32_t id) { return tab ? on_moved_obj(*tab, id) : on_moved_obj(S, id); };
+          if (dist <= S.eps_close && !moved(h.gid) && !moved(vertex_hit(S, L.p, j + 1)) &&
+              !moved(vertex_hit(S, L.p, j + 2))) {
+            L.e = x;
+            L.mat = h.gid;
+            mode = ST_WSKIP;  // the next segment must also be clear
+            write = false;
+            break;
+          }
+          ++j;
+          break;
+        }
+        case ST_WSKIP: {
+          if (!hit) {
+            j += 2;
+            end = j >= newn;
+            mode = ST_WCHECK;
+          } else {
+            en = energy_row(S, L.p, j);
+            row = j;
+            x = L.e;
+            hgid = L.mat;
+            write = true;
+            ++j;
+            mode = ST_WTRACE;
+          }
+          break;
+        }
+        default:
+          break;
+      }
+      if (write) put_photon(S, L.p, row, x, hgid, en);
+      if (tail) {
+        // continue sampling from photon 'row' on the side the ray came from,
+        // or finish
+        nw = dot(nh, qd) > 0.0f ? mul(nh, -1.0f) : nh;
+        L.mat = mat;
+        L.e = en;
+        mode = ST_TAIL;
+        newn = row + 1;
+        end = row + 1 >= S.B;
+      }
+      L.st = lane_state(mode, j, newn, row + 1);
+      if (end) {
+        clear_rows(S, L.p, newn);
+        G(S.info)[L.p] = info_pack(info_cell(G(S.info)[L.p]), newn, 0, 0, 0);
+        L.st = ST_IDLE;
+      }
+    }
+    n_photons += (uint32_t)__popcll(__ballot(write));
+    n_acc += (uint32_t)__popcll(__ballot(accepted));
+    n_trunc += (uint32_t)__popcll(__ballot(cut));
+    // ---- idle lanes take the next paths of the queue
+    const bool want = lane_mode(L.st) == ST_IDLE;
     if (__ballot(want)) {
       const uint32_t qi = deal(deal_ctr, wave, count, want);
       if (want) {
@@ -1470,222 +1642,72 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
           if (kSingle) {
             L.p = gp;
           } else {
-            uint32_t s = scene_of(gbase, n_scenes, gp);
-            L.S = scenes + s;
-            L.p = gp - gbase[s];
+            L.s = scene_of(gbase, n_scenes, gp);
+            L.p = gp - gbase[L.s];
           }
-          start_path(L, T, seed, frame, tab);
           // a path without the replace bit is skipped (stays idle this round)
+          start_path(scenes[kSingle ? 0u : L.s], L, T, tab, &x, &nw);
         } else {
-          L.mode = ST_END;
+          L.st = ST_END;
         }
       }
     }
-    if (__ballot(L.mode != ST_END && L.mode != ST_IDLE) == 0) {
-      if (__ballot(L.mode == ST_IDLE) == 0) break;
+    const uint32_t mode = lane_mode(L.st);
+    if (__ballot(mode != ST_END && mode != ST_IDLE) == 0) {
+      if (__ballot(mode == ST_IDLE) == 0) break;
       continue;
     }
-    const SceneDev& S = kSingle ? scenes[0] : *L.S;
-    const bool busy = L.mode != ST_IDLE && L.mode != ST_END;
-    // ---- a lane with a path and no walk in progress starts its next query
-    if (busy && !tracing) {
+    // ---- lanes with a path and no walk in progress start their next query
+    const bool start = !tracing && mode != ST_IDLE && mode != ST_END;
+    if (start) {
+      const SceneDev& Q = scenes[kSingle ? 0u : L.s];
       any = false;
-      float3 qo = L.x, qd = L.w;
-      float tmin = S.eps_end, tmax = kTFar;
-      if (L.mode == ST_TAIL) {
-        float3 nrm = dot(L.ntri, L.w) > 0.0f ? mul(L.ntri, -1.0f) : L.ntri;
-        float u[4];
-        draw4(seed, L.p, frame, L.row + 1, 1, u);
-        float3 lc = cosine_local(u[0], u[1]);
-        float3 tt, bb;
-        onb(nrm, &tt, &bb);
-        qd = add(add(mul(tt, lc.x), mul(bb, lc.y)), mul(nrm, lc.z));
-      } else if (L.mode == ST_WCHECK || L.mode == ST_WTRACE || L.mode == ST_WSKIP) {
-        uint32_t sj = L.mode == ST_WSKIP ? L.j + 1 : L.j;
-        const float3 xa = vertex(S, L.p, sj), xb = vertex(S, L.p, sj + 1);
-        if (L.mode == ST_WCHECK && (tab ? on_moved_obj(*tab, vertex_hit(S, L.p, sj + 1))
-                                        : on_moved_obj(S, vertex_hit(S, L.p, sj + 1))))
-          L.mode = ST_WTRACE;
-        qo = xa;
-        if (L.mode == ST_WTRACE) {
-          qd = normalize3(sub(xb, xa));
+      float3 qd = nw;  // ST_DIR
+      float tmin = Q.eps_end, tmax = kTFar;
+      if (mode == ST_LIGHT || mode == ST_TAIL) {
+        qd = sample_ray(Q, L, seed, frame, tab, &x, nw);
+      } else if (mode != ST_DIR) {
+        const uint32_t j = lane_j(L.st), sj = mode == ST_WSKIP ? j + 1 : j;
+        x = vertex(Q, L.p, sj);
+        const float3 xb = vertex(Q, L.p, sj + 1);
+        bool trace = mode == ST_WTRACE;
+        if (mode == ST_WCHECK && (tab ? on_moved_obj(*tab, vertex_hit(Q, L.p, sj + 1))
+                                      : on_moved_obj(Q, vertex_hit(Q, L.p, sj + 1)))) {
+          trace = true;
+          L.st = lane_state(ST_WTRACE, j, lane_newn(L.st), 0);
+        }
+        if (trace) {
+          qd = normalize3(sub(xb, x));
         } else {
-          // any hit of the segment xa -> xb against the moved objects
+          // any hit of the segment x -> xb against the moved objects
           any = true;
-          qd = sub(xb, xa);
+          qd = sub(xb, x);
           float len = length(qd);
-          tmin = len > 0.0f ? S.eps_end / len : 1.0f;
+          tmin = len > 0.0f ? Q.eps_end / len : 1.0f;
           tmax = 1.0f - tmin;
         }
       }
-      r = make_ray(qo, qd, tmin, tmax);
-      qb = world_slab(S, r);
-      walk_start(wk, G(S.wtop)[any ? 1 : 0], tmax, col);
+      r = make_ray(x, qd, tmin);
+      walk_start(wk, G(Q.wtop)[any ? 1 : 0], tmax, col);
       tracing = true;
-      if (!any) ++n_rays;
     }
-    if (tracing) walk_run<true>(G(S.wide), G(S.tris), r, qb, any, col, limit, wk, min_active);
-    if (!tracing || !walk_done(wk)) continue;
-    if (wk.redo && !(any && wk.gid != kHitNone)) walk_exact(G(S.nodes), G(S.tris), r, G(S.top)[any ? 1 : 0], any, col, wk);
-    // ---- the walk is finished: its query's ray is r (origin xa of a walk
-    // segment, direction of a sampled bounce)
-    tracing = false;
-    Hit h;
-    h.t = wk.tb;
-    h.gid = wk.gid;
-    h.rec = wk.rec;
-    const float3 wn = r.d, qd = r.d, xa = r.o;
-    // ---- advance the state machine with the result
-    const bool hit = h.gid != kHitNone;
-    switch (L.mode) {
-      case ST_FIRST: {
-        if (!hit) {
-          ++n_trunc;
-          L.newn = L.k;
-          finish(L);
-          break;
-        }
-        float3 xn = add(L.x, mul(L.w, h.t));
-        float3 en;
-        if (L.k == 0) {
-          const PV_GLOBAL LightDev* lt = G(S.lights) + L.l;
-          float N = (float)lt->path_count;
-          en = f3(__fdiv_rn(lt->power[0], N), __fdiv_rn(lt->power[1], N), __fdiv_rn(lt->power[2], N));
-        } else {
-          en = reflect_energy(S, energy_row(S, L.p, L.k - 1), mat_of(S, vertex_hit(S, L.p, L.k)));
-        }
-        put_photon(S, L.p, L.k, xn, h.gid, en);
-        ++n_photons;
-        L.x = xn;
-        L.ntri = hit_normal(S, h);
-        L.mat = hit_material(S, h);
-        L.e = en;
-        L.row = L.k;
-        to_tail(L);
-        break;
-      }
-      case ST_TAIL: {
-        if (!hit) {
-          ++n_trunc;
-          L.newn = L.row + 1;
-          finish(L);
-          break;
-        }
-        float3 xn = add(L.x, mul(wn, h.t));
-        float3 en = reflect_energy(S, L.e, L.mat);
-        L.row += 1;
-        put_photon(S, L.p, L.row, xn, h.gid, en);
-        ++n_photons;
-        L.x = xn;
-        L.w = wn;
-        L.ntri = hit_normal(S, h);
-        L.mat = hit_material(S, h);
-        L.e = en;
-        to_tail(L);
-        break;
-      }
-      case ST_WCHECK: {
-        if (hit) {
-          L.mode = ST_WTRACE;
-        } else if (++L.j >= L.newn) {
-          finish(L);
-        }
-        break;
-      }
-      case ST_WTRACE: {
-        if (!hit) {
-          ++n_trunc;
-          L.newn = L.j;
-          finish(L);
-          break;
-        }
-        float3 hp = add(xa, mul(qd, h.t));
-        float3 ej = energy_row(S, L.p, L.j);
-        if (L.j == L.newn - 1) {
-          put_photon(S, L.p, L.j, hp, h.gid, ej);
-          ++n_photons;
-          finish(L);
-          break;
-        }
-        float3 xc = vertex(S, L.p, L.j + 2);
-        float3 d2 = sub(xc, hp);
-        float3 nh = hit_normal(S, h);
-        float c1 = dot(qd, nh), l2 = length(d2);
-        float c2 = l2 > 0.0f ? dot(d2, nh) / l2 : 0.0f;
-        uint32_t mat = hit_material(S, h);
-        float3 en = (c1 * c2 < 0.0f) ? reflect_energy(S, ej, mat) : f3(0.0f, 0.0f, 0.0f);
-        if (S.energy_test == PV_ENERGY_COSINE_RATIO && c1 * c2 < 0.0f) {
-          // the kept direction's cosine at the new vertex over the one at the
-          // old vertex (its stored triangle, from x_{j+1} to x_{j+2})
-          const Tri to = G(S.tris)[G(S.gid_rec)[vertex_hit(S, L.p, L.j + 1)]];
-          const float3 no = cross(sub(xyz(to.t1), xyz(to.t0)), sub(xyz(to.t2), xyz(to.t0)));
-          const float3 d3 = sub(xc, vertex(S, L.p, L.j + 1));
-          const float den = fabsf(dot(d3, no)), num = fabsf(c2) * length(d3) * length(no);
-          const float ratio = den > 0.0f ? num / den : 0.0f;
-          en = mul(en, ratio);
-        }
-        float3 eo = energy_row(S, L.p, L.j + 1);
-        if (!eq2(en, eo, T)) {
-          // energies differ: keep the new hit and re-sample the rest
-          put_photon(S, L.p, L.j, hp, h.gid, ej);
-          ++n_photons;
-          L.x = hp;
-          L.w = qd;
-          L.ntri = nh;
-          L.mat = mat;
-          L.e = ej;
-          L.row = L.j;
-          to_tail(L);
-          break;
-        }
-        ++n_acc;
-        float dist = length(sub(hp, vertex(S, L.p, L.j + 1)));
-        auto moved = [&](uint32_t hit) { return tab ? on_moved_obj(*tab, hit) : on_moved_obj(S, hit); };
-        if (dist <= S.eps_close && !moved(h.gid) && !moved(vertex_hit(S, L.p, L.j + 1)) &&
-            !moved(vertex_hit(S, L.p, L.j + 2))) {
-          L.hp = hp;
-          L.hgid = h.gid;
-          L.mode = ST_WSKIP;  // the next segment must also be clear
-          break;
-        }
-        put_photon(S, L.p, L.j, hp, h.gid, ej);
-        ++n_photons;
-        ++L.j;
-        L.mode = ST_WTRACE;
-        break;
-      }
-      case ST_WSKIP: {
-        if (!hit) {
-          L.j += 2;
-          if (L.j >= L.newn)
-            finish(L);
-          else
-            L.mode = ST_WCHECK;
-        } else {
-          put_photon(S, L.p, L.j, L.hp, L.hgid, energy_row(S, L.p, L.j));
-          ++n_photons;
-          ++L.j;
-          L.mode = ST_WTRACE;
-        }
-        break;
-      }
-      default:
-        break;
-    }
+    n_rays += (uint32_t)__popcll(__ballot(start && !any));
   }
   if (stats) {
-    unsigned long long a = block_sum_u64(n_rays, sred);
-    unsigned long long b = block_sum_u64(n_photons, sred);
-    unsigned long long c = block_sum_u64(n_acc, sred);
-    unsigned long long d = block_sum_u64(n_trunc, sred);
+    if (lane_id() == 0) {
+      if (n_rays) atomicAdd(&scount[0], n_rays);
+      if (n_photons) atomicAdd(&scount[1], n_photons);
+      if (n_acc) atomicAdd(&scount[2], n_acc);
+      if (n_trunc) atomicAdd(&scount[3], n_trunc);
+    }
+    __syncthreads();
     // most workgroups of a short queue have nothing to add, and additions to
     // one line serialise: 2048 workgroups' four cost 90 us of a 123 us launch
     // over 2000 paths, and about 50 us of every frame
-    if (threadIdx.x == 0) {
-      if (a) atomicAdd(&stats->rays_traced, a);
-      if (b) atomicAdd(&stats->photons_written, b);
-      if (c) atomicAdd(&stats->reuse_accepted, c);
-      if (d) atomicAdd(&stats->paths_truncated, d);
+    if (threadIdx.x < 4 && scount[threadIdx.x]) {
+      unsigned long long* to[4] = {&stats->rays_traced, &stats->photons_written, &stats->reuse_accepted,
+                                   &stats->paths_truncated};
+      atomicAdd(to[threadIdx.x], (unsigned long long)scount[threadIdx.x]);
     }
   }
 }

@@ -67,9 +67,12 @@ __device__ inline uint32_t object_of_record(const SceneDev& S, uint32_t r) {
   return lo;
 }
 
+__device__ inline float3 vertex_of(const Tri& t, int i) { return make_float3(t.v[i][0], t.v[i][1], t.v[i][2]); }
+
 __device__ inline float3 centroid(const Tri& t) {
   const float s = 1.0f / 3.0f;
-  return make_float3((t.t0.x + t.t1.x + t.t2.x) * s, (t.t0.y + t.t1.y + t.t2.y) * s, (t.t0.z + t.t1.z + t.t2.z) * s);
+  const float3 a = vertex_of(t, 0), b = vertex_of(t, 1), c = vertex_of(t, 2);
+  return make_float3((a.x + b.x + c.x) * s, (a.y + b.y + c.y) * s, (a.z + b.z + c.z) * s);
 }
 
 // 10 bits spread to every third bit
@@ -104,10 +107,11 @@ __device__ inline Box join(const Box& a, const Box& b) {
 
 // a leaf's box: the padded box of its triangle (as the refit computes it)
 __device__ inline Box tri_box(const Tri& t) {
-  return {make_float3(pad_lo(fminf(fminf(t.t0.x, t.t1.x), t.t2.x)), pad_lo(fminf(fminf(t.t0.y, t.t1.y), t.t2.y)),
-                      pad_lo(fminf(fminf(t.t0.z, t.t1.z), t.t2.z))),
-          make_float3(pad_hi(fmaxf(fmaxf(t.t0.x, t.t1.x), t.t2.x)), pad_hi(fmaxf(fmaxf(t.t0.y, t.t1.y), t.t2.y)),
-                      pad_hi(fmaxf(fmaxf(t.t0.z, t.t1.z), t.t2.z)))};
+  const float3 a = vertex_of(t, 0), b = vertex_of(t, 1), c = vertex_of(t, 2);
+  return {make_float3(pad_lo(fminf(fminf(a.x, b.x), c.x)), pad_lo(fminf(fminf(a.y, b.y), c.y)),
+                      pad_lo(fminf(fminf(a.z, b.z), c.z))),
+          make_float3(pad_hi(fmaxf(fmaxf(a.x, b.x), c.x)), pad_hi(fmaxf(fmaxf(a.y, b.y), c.y)),
+                      pad_hi(fmaxf(fmaxf(a.z, b.z), c.z)))};
 }
 
 __device__ inline Box pyr_get(const float4* pyr, uint32_t i) {
