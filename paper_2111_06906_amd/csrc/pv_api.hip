@@ -1425,7 +1425,7 @@ pv_status pv_verify_paths(pv_ctx* ctx, const pv_path_store* store, pv_stats* d_s
   if (!ctx->frame_started) return fail(ctx, PV_ERR_STATE, "no transforms given (pv_frame_begin or pv_update_*)");
   uint32_t nb = path_blocks(store->n_paths);
   CK(pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw, ctx->d_block_cnt, d_stats,
-                       ctx->stack_moved, verify_blocks(ctx), ctx->verify_min_active, ctx->d_scan_tmp, ctx->stream));
+                       ctx->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active, ctx->d_scan_tmp, ctx->stream));
   ctx->counts_ready = true;
   ctx->queue_stale = true;
   return PV_OK;
@@ -1479,7 +1479,7 @@ pv_status pv_retrace_paths(pv_ctx* ctx, const pv_path_store* store, float thresh
   if ((st = wait_compaction(ctx))) return st;
   uint32_t blocks = (uint32_t)(ctx->n_cu * ctx->retrace_blocks_per_cu);
   CK(pv::launch_retrace(ctx->d_scene, ctx->d_gbase, 1, ctx->d_queue, ctx->d_qcount, threshold, seed,
-                        frame, nullptr, d_stats, blocks, ctx->retrace_variant, ctx->stack_entries,
+                        frame, nullptr, d_stats, blocks, (uint32_t)ctx->n_cu, ctx->retrace_variant, ctx->stack_entries,
                         ctx->walk_min_active, ctx->ow, ctx->stream));
   return PV_OK;
 }
@@ -1776,7 +1776,7 @@ pv_status pv_autotune(pv_ctx* ctx, const pv_path_store* store, float threshold, 
       e = copy_store(false);
       if (e == hipSuccess)
         e = pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw, ctx->d_block_cnt,
-                              nullptr, ctx->stack_moved, verify_blocks(ctx), ctx->verify_min_active, ctx->d_scan_tmp, s);
+                              nullptr, ctx->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active, ctx->d_scan_tmp, s);
       if (e == hipSuccess)
         e = pv::launch_scan(ctx->d_block_cnt, ctx->d_offsets, nb, ctx->d_qcount, ctx->d_scan_tmp, s);
       if (e == hipSuccess)
@@ -1784,7 +1784,7 @@ pv_status pv_autotune(pv_ctx* ctx, const pv_path_store* store, float threshold, 
       if (e == hipSuccess) e = hipEventRecord(e0, s);
       if (e == hipSuccess)
         e = pv::launch_retrace(ctx->d_scene, ctx->d_gbase, 1, ctx->d_queue, ctx->d_qcount, threshold,
-                               seed, frame, nullptr, nullptr, (uint32_t)(ctx->n_cu * bpc), v, ctx->stack_entries,
+                               seed, frame, nullptr, nullptr, (uint32_t)(ctx->n_cu * bpc), (uint32_t)ctx->n_cu, v, ctx->stack_entries,
                                min_active, ctx->ow, s);
       if (e == hipSuccess) e = hipEventRecord(e1, s);
       if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -1817,7 +1817,7 @@ pv_status pv_autotune(pv_ctx* ctx, const pv_path_store* store, float threshold, 
           if (err == hipSuccess) err = hipEventRecord(e0, s);
           if (err == hipSuccess)
             err = pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw, ctx->d_block_cnt,
-                                    nullptr, ctx->stack_moved, verify_blocks(ctx), ctx->verify_min_active,
+                                    nullptr, ctx->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active,
                                     ctx->d_scan_tmp, s);
           if (err == hipSuccess) err = hipEventRecord(e1, s);
           if (err == hipSuccess) err = hipEventSynchronize(e1);
@@ -2005,7 +2005,7 @@ static pv_status batch_enqueue(pv_batch* b, pv_stats* d_stats, const float* cons
   }
   CK(pv::launch_build_top(b->d_scenes, (int)b->n, st));
   CK(pv::launch_verify(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->d_gbase, (int)b->n, b->vw, b->d_block_cnt,
-                       d_stats, b->stack_moved, verify_blocks(ctx), ctx->verify_min_active, b->d_scan_tmp, st));
+                       d_stats, b->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active, b->d_scan_tmp, st));
   // distribution maps: compute DM_C, prune, fill, scene by scene (each
   // rewrites its own tiles' replace counts before the queue is built)
   for (const pv_batch::Dm& d : b->dms)
@@ -2014,7 +2014,7 @@ static pv_status batch_enqueue(pv_batch* b, pv_stats* d_stats, const float* cons
   CK(pv::launch_scan(b->d_block_cnt, b->d_offsets, b->n_path_tiles, b->d_qcount, b->d_scan_tmp, st));
   CK(pv::launch_scatter_queue(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->d_offsets, b->d_queue, st));
   CK(pv::launch_retrace(b->d_scenes, b->d_gbase, (int)b->n, b->d_queue, b->d_qcount, b->T, b->seed, 0,
-                        frame_ptr, d_stats, (uint32_t)(ctx->n_cu * ctx->retrace_blocks_per_cu), ctx->retrace_variant,
+                        frame_ptr, d_stats, (uint32_t)(ctx->n_cu * ctx->retrace_blocks_per_cu), (uint32_t)ctx->n_cu, ctx->retrace_variant,
                         b->stack_entries, ctx->walk_min_active, b->ow, st));
   CK(pv::launch_photon_count(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->d_pcounts, st));
   CK(pv::launch_scan(b->d_pcounts, b->d_poffsets, b->n_counts, b->d_ptotal, b->d_scan_tmp, st));

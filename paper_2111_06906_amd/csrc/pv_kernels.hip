@@ -607,6 +607,21 @@ __device__ inline uint32_t deal(uint32_t* __restrict__ ctrs, uint32_t wave, uint
   return idx < count ? idx : kNoEntry;
 }
 
+// A list shorter than the lanes of 'waves' waves is spread over that many
+// waves instead: wave w takes entries [w q, (w + 1) q) with its first q lanes,
+// q = ceil(count / waves), and nothing is dealt.  (64: the list is dealt.)
+// A wave's time is the sum over its rounds of the longest walk among its
+// lanes, so that few lanes per wave finish sooner as long as waves share no
+// SIMD with many others: 45k paths of a 60k-path frame, 24 objects, re-traced
+// in 340 us over three workgroups per compute unit (all of which fit beside
+// each other at the largest stack), 360 over two, 382 over one and 445 dealt;
+// their verification tasks in 69 us over two, 77 over one, 84 over four and
+// 81 dealt.
+constexpr uint32_t kSpreadRetrace = 3, kSpreadVerify = 2;  // workgroups per compute unit
+__device__ inline uint32_t wave_quota(uint32_t count, uint32_t waves) {
+  return min(64u, max(1u, (count + waves - 1) / waves));
+}
+
 // the counters start at zero for a launch (cleared by a kernel that precedes
 // it in the stream, so that the sequence can be captured in a graph)
 __device__ inline void deal_reset(uint32_t* ctrs) {
@@ -815,7 +830,8 @@ __global__ __launch_bounds__(kBlock) void k_verify_gather(const SceneDev* __rest
 template <bool kSingle>
 __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restrict__ scenes,
                                                          const uint32_t* __restrict__ gbase, int n_scenes,
-                                                         VerifyWork W, int min_active, uint32_t entries) {
+                                                         VerifyWork W, int min_active, uint32_t entries,
+                                                         uint32_t spread_waves) {
   extern __shared__ int32_t sstack[];  // traversal stacks, launch-time size
   __shared__ MovedSet M;                // single scene: the moved objects' boxes
   __shared__ int32_t mroot[PV_MAX_OBJECTS];  // and their hierarchies' roots
@@ -865,6 +881,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
   if (!kSingle) gbase = stage_gbase(gbase, n_scenes, sgb);
   const uint32_t total = *W.total;
   const uint32_t wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  const uint32_t quota = wave_quota(total, spread_waves);
+  if (quota < 64) min_active = max(1, (int)(quota * (uint32_t)min_active / 64u));
+  bool fresh = true;  // this wave has not taken its share of a spread list
   Walk w;
   w.cur = kRootNone;
   w.leaf = 0;
@@ -878,7 +897,14 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
     // failed at an earlier segment is dropped (the minimum only decreases)
     const bool want = !busy && !drained;
     if (__ballot(want)) {
-      const uint32_t t = deal(W.deal, wave, total, want);
+      uint32_t t;
+      if (quota < 64) {
+        const uint32_t e = wave * quota + lane_id();
+        t = fresh && lane_id() < quota && e < total ? e : kNoEntry;
+        fresh = false;
+      } else {
+        t = deal(W.deal, wave, total, want);
+      }
       if (want) {
         if (t == kNoEntry) {
           drained = true;
@@ -1455,7 +1481,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
                                                     const uint32_t* __restrict__ qcount, float T,
                                                     uint64_t seed, uint32_t frame_arg, const uint32_t* frame_ptr,
                                                     pv_stats* stats, int min_active, uint32_t entries,
-                                                    uint32_t* __restrict__ deal_ctr) {
+                                                    uint32_t spread_waves, uint32_t* __restrict__ deal_ctr) {
   extern __shared__ int32_t sstack[];  // traversal stacks, launch-time size
   __shared__ uint32_t scount[4];
   __shared__ SceneTab stab;
@@ -1475,6 +1501,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
   // the work queue, dealt by deal() from the counters 'deal_ctr'
   const uint32_t count = *qcount;
   const uint32_t wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  const uint32_t quota = wave_quota(count, spread_waves);
+  if (quota < 64) min_active = max(1, (int)(quota * (uint32_t)min_active / 64u));
+  bool fresh = true;  // this wave has not taken its share of a spread queue
   Lane L;
   L.s = 0;
   L.st = ST_IDLE;
@@ -1635,7 +1664,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
     // ---- idle lanes take the next paths of the queue
     const bool want = lane_mode(L.st) == ST_IDLE;
     if (__ballot(want)) {
-      const uint32_t qi = deal(deal_ctr, wave, count, want);
+      uint32_t qi;
+      if (quota < 64) {
+        const uint32_t e = wave * quota + lane_id();
+        qi = fresh && lane_id() < quota && e < count ? e : kNoEntry;
+        fresh = false;
+      } else {
+        qi = deal(deal_ctr, wave, count, want);
+      }
       if (want) {
         if (qi != kNoEntry) {
           uint32_t gp = G(queue)[qi];
@@ -2131,7 +2167,7 @@ uint32_t verify_finish_blocks(uint32_t trace_blocks) { return std::max(1u, trace
 
 hipError_t launch_verify(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint32_t* gbase,
                          int n_scenes, VerifyWork W, uint32_t* block_cnt, pv_stats* stats, uint32_t stack,
-                         uint32_t trace_blocks, int min_active, uint32_t* scan_tmp, hipStream_t s) {
+                         uint32_t trace_blocks, uint32_t n_cu, int min_active, uint32_t* scan_tmp, hipStream_t s) {
   if (!n_tiles) return hipSuccess;
   if (stack < kMinStack || stack > (uint32_t)kMaxStack || trace_blocks == 0 || min_active < 1 || min_active > 64)
     return hipErrorInvalidValue;
@@ -2140,14 +2176,15 @@ hipError_t launch_verify(const SceneDev* scenes, const uint2* tiles, uint32_t n_
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_verify_gather, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, W);
   const dim3 gt(trace_blocks), gf(verify_finish_blocks(trace_blocks));
+  const uint32_t spread = std::min(4 * trace_blocks, 4 * kSpreadVerify * n_cu);
   if (n_scenes == 1) {
     hipLaunchKernelGGL(k_verify_trace<true>, gt, dim3(kBlock), stack_bytes(stack), s, scenes, gbase, n_scenes, W,
-                       min_active, stack);
+                       min_active, stack, spread);
     hipLaunchKernelGGL(k_verify_finish<true>, gf, dim3(kBlock), 0, s, scenes, gbase, n_scenes, W, block_cnt, n_tiles,
                        stats);
   } else {
     hipLaunchKernelGGL(k_verify_trace<false>, gt, dim3(kBlock), stack_bytes(stack), s, scenes, gbase, n_scenes, W,
-                       min_active, stack);
+                       min_active, stack, spread);
     hipLaunchKernelGGL(k_verify_finish<false>, gf, dim3(kBlock), 0, s, scenes, gbase, n_scenes, W, block_cnt, n_tiles,
                        stats);
   }
@@ -2198,31 +2235,31 @@ template <bool kSingle>
 static void retrace_variant(int v, dim3 g, size_t lds, hipStream_t s, const SceneDev* scenes, const uint32_t* gbase, int n_scenes,
                             const uint32_t* queue, const uint32_t* qcount, float T, uint64_t seed,
                             uint32_t frame, const uint32_t* frame_ptr, pv_stats* stats, int min_active,
-                            uint32_t entries, uint32_t* deal_ctr) {
+                            uint32_t entries, uint32_t spread_waves, uint32_t* deal_ctr) {
   switch (v) {
     case 1:
       hipLaunchKernelGGL((k_retrace<kSingle, 5>), g, dim3(kBlock), lds, s, scenes, gbase, n_scenes, queue, qcount,
-                         T, seed, frame, frame_ptr, stats, min_active, entries, deal_ctr);
+                         T, seed, frame, frame_ptr, stats, min_active, entries, spread_waves, deal_ctr);
       break;
     case 2:
       hipLaunchKernelGGL((k_retrace<kSingle, 6>), g, dim3(kBlock), lds, s, scenes, gbase, n_scenes, queue, qcount,
-                         T, seed, frame, frame_ptr, stats, min_active, entries, deal_ctr);
+                         T, seed, frame, frame_ptr, stats, min_active, entries, spread_waves, deal_ctr);
       break;
     case 3:
       hipLaunchKernelGGL((k_retrace<kSingle, 8>), g, dim3(kBlock), lds, s, scenes, gbase, n_scenes, queue, qcount,
-                         T, seed, frame, frame_ptr, stats, min_active, entries, deal_ctr);
+                         T, seed, frame, frame_ptr, stats, min_active, entries, spread_waves, deal_ctr);
       break;
     default:
       hipLaunchKernelGGL((k_retrace<kSingle, 4>), g, dim3(kBlock), lds, s, scenes, gbase, n_scenes, queue, qcount,
-                         T, seed, frame, frame_ptr, stats, min_active, entries, deal_ctr);
+                         T, seed, frame, frame_ptr, stats, min_active, entries, spread_waves, deal_ctr);
       break;
   }
 }
 
 hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_scenes, const uint32_t* queue_in,
                           const uint32_t* qcount, float T, uint64_t seed, uint32_t frame,
-                          const uint32_t* frame_ptr, pv_stats* stats, uint32_t n_blocks, int variant, uint32_t stack,
-                          int min_active, const OrderWork& O, hipStream_t s) {
+                          const uint32_t* frame_ptr, pv_stats* stats, uint32_t n_blocks, uint32_t n_cu, int variant,
+                          uint32_t stack, int min_active, const OrderWork& O, hipStream_t s) {
   if (stack < kMinStack || stack > (uint32_t)kMaxStack || min_active < 1 || min_active > 64) return hipErrorInvalidValue;
   // the queue reordered by first invalid segment (see k_order_hist)
   hipLaunchKernelGGL(k_order_hist, dim3(O.tiles), dim3(kBlock), 0, s, scenes, gbase, n_scenes, queue_in, qcount, O.hist,
@@ -2234,10 +2271,10 @@ hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_s
   const uint32_t* queue = O.queue;
   if (n_scenes == 1)
     retrace_variant<true>(variant, dim3(n_blocks), stack_bytes(stack), s, scenes, gbase, n_scenes, queue, qcount, T, seed, frame,
-                          frame_ptr, stats, min_active, stack, O.deal);
+                          frame_ptr, stats, min_active, stack, std::min(4 * n_blocks, 4 * kSpreadRetrace * n_cu), O.deal);
   else
     retrace_variant<false>(variant, dim3(n_blocks), stack_bytes(stack), s, scenes, gbase, n_scenes, queue, qcount, T, seed, frame,
-                           frame_ptr, stats, min_active, stack, O.deal);
+                           frame_ptr, stats, min_active, stack, std::min(4 * n_blocks, 4 * kSpreadRetrace * n_cu), O.deal);
   return hipGetLastError();
 }
 

@@ -40,7 +40,7 @@ hipError_t launch_build_top(SceneDev* scenes, int n_scenes, hipStream_t s);
 // 'scan_tmp': scan_tmp_words(n_tiles) words.
 hipError_t launch_verify(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint32_t* gbase,
                          int n_scenes, VerifyWork W, uint32_t* block_cnt, pv_stats* stats, uint32_t stack,
-                         uint32_t trace_blocks, int min_active, uint32_t* scan_tmp, hipStream_t s);
+                         uint32_t trace_blocks, uint32_t n_cu, int min_active, uint32_t* scan_tmp, hipStream_t s);
 // blocks of the finishing kernel for a traversal grid (sizes W.part: 4 words
 // per path tile plus 2 per finishing block)
 uint32_t verify_finish_blocks(uint32_t trace_blocks);
@@ -67,8 +67,8 @@ uint32_t order_tiles(uint32_t max_entries);
 // paths are re-traced in the order of their first invalid segment
 hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_scenes, const uint32_t* queue_in,
                           const uint32_t* qcount, float T, uint64_t seed, uint32_t frame,
-                          const uint32_t* frame_ptr, pv_stats* stats, uint32_t n_blocks, int variant, uint32_t stack,
-                          int min_active, const OrderWork& O, hipStream_t s);
+                          const uint32_t* frame_ptr, pv_stats* stats, uint32_t n_blocks, uint32_t n_cu, int variant,
+                          uint32_t stack, int min_active, const OrderWork& O, hipStream_t s);
 hipError_t launch_photon_count(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t* counts,
                                hipStream_t s);
 hipError_t launch_photon_scatter(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t B,
