@@ -88,7 +88,7 @@ struct pv_ctx {
   Alloc res_mem;
   uint32_t max_paths = 0, max_bounces = 0, max_blocks = 0;
   uint2* d_path_tiles = nullptr;
-  uint32_t *d_block_cnt = nullptr, *d_offsets = nullptr, *d_queue = nullptr, *d_qcount = nullptr,
+  uint32_t *d_queue = nullptr, *d_qcount = nullptr,
            *d_pcounts = nullptr, *d_poffsets = nullptr, *d_gbase = nullptr,
            *d_scan_tmp = nullptr;
   double* d_partial = nullptr;  // per-workgroup sums of the energy gradients
@@ -118,6 +118,7 @@ struct pv_ctx {
   bool bound = false;
   bool counts_ready = false;   // per-block replace counts written by verify
   bool queue_stale = false;    // verify ran after the last queue build
+  bool queue_ordered = false;  // ow.queue holds the queue in the re-trace's order
   pv_path_store bstore{};
 };
 
@@ -131,7 +132,7 @@ struct pv_batch {
   SceneDev* d_scenes = nullptr;
   uint2 *d_path_tiles = nullptr, *d_obj_tiles = nullptr, *d_xf_tiles = nullptr;
   uint32_t n_path_tiles = 0, n_obj_tiles = 0, n_xf_tiles = 0;
-  uint32_t *d_block_cnt = nullptr, *d_offsets = nullptr, *d_queue = nullptr, *d_qcount = nullptr,
+  uint32_t *d_queue = nullptr, *d_qcount = nullptr,
            *d_gbase = nullptr, *d_pcounts = nullptr, *d_poffsets = nullptr, *d_ptotal = nullptr, *d_pbase = nullptr,
            *d_frame = nullptr, *d_scan_tmp = nullptr;
   uint32_t n_counts = 0;
@@ -644,8 +645,6 @@ std::vector<uint2> xf_tiles(uint32_t scene, const uint32_t* obj_tris, uint32_t n
 // grid of the verification traversal kernel (persistent, grid-stride)
 constexpr int kMaxVerifyBlocksPerCu = 32;
 uint32_t verify_blocks(const pv_ctx* ctx) { return (uint32_t)(ctx->n_cu * ctx->verify_blocks_per_cu); }
-// the largest traversal grid any tuning can pick (sizes the statistics slots)
-uint32_t verify_blocks_max(const pv_ctx* ctx) { return (uint32_t)(ctx->n_cu * kMaxVerifyBlocksPerCu); }
 
 // Work that writes what an overlapped compaction reads (the photon rows and
 // segment counts, the scene descriptor) or reuses its scratch is ordered
@@ -1306,16 +1305,14 @@ pv_status pv_reserve(pv_ctx* ctx, uint32_t max_paths, uint32_t max_bounces) {
     uint32_t nb = path_blocks(max_paths);
     std::vector<uint2> tiles = make_tiles(0, max_paths);
     CK(upload(A, &ctx->d_path_tiles, tiles.data(), tiles.size(), ctx->stream));
-    CK(dalloc(A, &ctx->d_block_cnt, nb));
-    CK(dalloc(A, &ctx->d_offsets, nb));
     CK(dalloc(A, &ctx->d_queue, max_paths));
-    ctx->ow.tiles = pv::order_tiles(max_paths);
+    const uint32_t chunks = pv::queue_chunks(nb);
     CK(dalloc(A, &ctx->ow.queue, max_paths));
-    CK(dalloc(A, &ctx->ow.hist, 8 * (size_t)ctx->ow.tiles));
-    CK(dalloc(A, &ctx->ow.hoff, 8 * (size_t)ctx->ow.tiles));
-    CK(dalloc(A, &ctx->ow.htotal, 1));
-    CK(dalloc(A, &ctx->ow.scan_tmp, pv::scan_tmp_words(8 * ctx->ow.tiles)));
-    CK(dalloc(A, &ctx->ow.deal, (size_t)pv::kDealGroups * pv::kDealStride));
+    CK(dalloc(A, &ctx->ow.hist, 8 * (size_t)chunks));
+    CK(dalloc(A, &ctx->ow.hoff, 8 * (size_t)chunks));
+    CK(dalloc(A, &ctx->ow.scan_tmp, pv::scan_tmp_words(8 * chunks)));
+    CK(dalloc(A, &ctx->ow.deal, pv::kDealWords));
+    CK(hipMemsetAsync(ctx->ow.deal, 0, 4 * (size_t)pv::kDealWords, ctx->stream));
     CK(dalloc(A, &ctx->d_qcount, 1));
     CK(dalloc(A, &ctx->d_pcounts, (size_t)nb * max_bounces));
     CK(dalloc(A, &ctx->d_poffsets, (size_t)nb * max_bounces));
@@ -1329,9 +1326,10 @@ pv_status pv_reserve(pv_ctx* ctx, uint32_t max_paths, uint32_t max_bounces) {
     CK(dalloc(A, &ctx->vw.tcount, nb));
     CK(dalloc(A, &ctx->vw.toff, nb));
     CK(dalloc(A, &ctx->vw.total, 1));
-    CK(dalloc(A, &ctx->vw.deal, (size_t)pv::kDealGroups * pv::kDealStride));
+    CK(dalloc(A, &ctx->vw.deal, pv::kDealWords));
+    CK(hipMemsetAsync(ctx->vw.deal, 0, 4 * (size_t)pv::kDealWords, ctx->stream));
     CK(dalloc(A, &ctx->vw.first, max_paths));
-    CK(dalloc(A, &ctx->vw.part, 4 * (size_t)nb + 2 * (size_t)pv::verify_finish_blocks(verify_blocks_max(ctx))));
+    CK(dalloc(A, &ctx->vw.part, 4 * (size_t)nb));
     CK(hipMemsetAsync(ctx->d_qcount, 0, 4, ctx->stream));
     CK(hipStreamSynchronize(ctx->stream));
     ctx->max_paths = max_paths;
@@ -1424,7 +1422,7 @@ pv_status pv_verify_paths(pv_ctx* ctx, const pv_path_store* store, pv_stats* d_s
   if ((st = commit_pending(ctx))) return st;
   if (!ctx->frame_started) return fail(ctx, PV_ERR_STATE, "no transforms given (pv_frame_begin or pv_update_*)");
   uint32_t nb = path_blocks(store->n_paths);
-  CK(pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw, ctx->d_block_cnt, d_stats,
+  CK(pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw, d_stats,
                        ctx->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active, ctx->d_scan_tmp, ctx->stream));
   ctx->counts_ready = true;
   ctx->queue_stale = true;
@@ -1437,9 +1435,9 @@ pv_status pv_build_queue(pv_ctx* ctx, const pv_path_store* store) {
   if (st) return st;
   if (!ctx->counts_ready) return fail(ctx, PV_ERR_STATE, "pv_verify_paths has not been called");
   uint32_t nb = path_blocks(store->n_paths);
-  CK(pv::launch_scan(ctx->d_block_cnt, ctx->d_offsets, nb, ctx->d_qcount, ctx->d_scan_tmp, ctx->stream));
-  CK(pv::launch_scatter_queue(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_offsets, ctx->d_queue, ctx->stream));
+  CK(pv::launch_build_queue(ctx->d_scene, ctx->d_path_tiles, nb, ctx->ow, ctx->d_queue, ctx->d_qcount, ctx->stream));
   ctx->queue_stale = false;
+  ctx->queue_ordered = true;
   return PV_OK;
 }
 
@@ -1449,10 +1447,9 @@ pv_status pv_queue_all(pv_ctx* ctx, const pv_path_store* store) {
   if (st) return st;
   if ((st = wait_compaction(ctx))) return st;
   uint32_t nb = path_blocks(store->n_paths);
-  CK(pv::launch_mark_all(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_block_cnt, ctx->stream));
-  CK(pv::launch_scan(ctx->d_block_cnt, ctx->d_offsets, nb, ctx->d_qcount, ctx->d_scan_tmp, ctx->stream));
-  CK(pv::launch_scatter_queue(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_offsets, ctx->d_queue, ctx->stream));
+  CK(pv::launch_mark_all(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_queue, ctx->d_qcount, ctx->stream));
   ctx->queue_stale = false;
+  ctx->queue_ordered = false;  // full paths all: already in the re-trace's order
   return PV_OK;
 }
 
@@ -1478,9 +1475,10 @@ pv_status pv_retrace_paths(pv_ctx* ctx, const pv_path_store* store, float thresh
   if (ctx->queue_stale && (st = pv_build_queue(ctx, store))) return st;
   if ((st = wait_compaction(ctx))) return st;
   uint32_t blocks = (uint32_t)(ctx->n_cu * ctx->retrace_blocks_per_cu);
-  CK(pv::launch_retrace(ctx->d_scene, ctx->d_gbase, 1, ctx->d_queue, ctx->d_qcount, threshold, seed,
+  CK(pv::launch_retrace(ctx->d_scene, ctx->d_gbase, 1, ctx->queue_ordered ? ctx->ow.queue : ctx->d_queue,
+                        ctx->d_qcount, threshold, seed,
                         frame, nullptr, d_stats, blocks, (uint32_t)ctx->n_cu, ctx->retrace_variant, ctx->stack_entries,
-                        ctx->walk_min_active, ctx->ow, ctx->stream));
+                        ctx->walk_min_active, ctx->ow.deal, ctx->stream));
   return PV_OK;
 }
 
@@ -1602,7 +1600,7 @@ pv_status pv_update_distribution(pv_ctx* ctx, const pv_path_store* store, uint64
   if ((st = wait_compaction(ctx))) return st;
   const uint32_t nb = path_blocks(store->n_paths);
   CK(pv::launch_dm_update(ctx->d_scene, ctx->d_scene, ctx->d_path_tiles, nb, ctx->dm_cells, ctx->n_lights, ctx->dw,
-                          ctx->d_block_cnt, seed, frame, nullptr, ctx->stream));
+                          seed, frame, nullptr, ctx->stream));
   if (d_dm_c)
     CK(hipMemcpyAsync(d_dm_c, ctx->dw.dm_c, 4 * (size_t)ctx->dm_cells, hipMemcpyDeviceToDevice, ctx->stream));
   if (d_pruned)
@@ -1775,17 +1773,15 @@ pv_status pv_autotune(pv_ctx* ctx, const pv_path_store* store, float threshold, 
     for (int rep = 0; rep < kTuneReps && e == hipSuccess; ++rep) {
       e = copy_store(false);
       if (e == hipSuccess)
-        e = pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw, ctx->d_block_cnt,
+        e = pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw,
                               nullptr, ctx->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active, ctx->d_scan_tmp, s);
       if (e == hipSuccess)
-        e = pv::launch_scan(ctx->d_block_cnt, ctx->d_offsets, nb, ctx->d_qcount, ctx->d_scan_tmp, s);
-      if (e == hipSuccess)
-        e = pv::launch_scatter_queue(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_offsets, ctx->d_queue, s);
+        e = pv::launch_build_queue(ctx->d_scene, ctx->d_path_tiles, nb, ctx->ow, ctx->d_queue, ctx->d_qcount, s);
       if (e == hipSuccess) e = hipEventRecord(e0, s);
       if (e == hipSuccess)
-        e = pv::launch_retrace(ctx->d_scene, ctx->d_gbase, 1, ctx->d_queue, ctx->d_qcount, threshold,
+        e = pv::launch_retrace(ctx->d_scene, ctx->d_gbase, 1, ctx->ow.queue, ctx->d_qcount, threshold,
                                seed, frame, nullptr, nullptr, (uint32_t)(ctx->n_cu * bpc), (uint32_t)ctx->n_cu, v, ctx->stack_entries,
-                               min_active, ctx->ow, s);
+                               min_active, ctx->ow.deal, s);
       if (e == hipSuccess) e = hipEventRecord(e1, s);
       if (e == hipSuccess) e = hipEventSynchronize(e1);
       float ms = 0;
@@ -1816,7 +1812,7 @@ pv_status pv_autotune(pv_ctx* ctx, const pv_path_store* store, float threshold, 
           err = copy_store(false);
           if (err == hipSuccess) err = hipEventRecord(e0, s);
           if (err == hipSuccess)
-            err = pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw, ctx->d_block_cnt,
+            err = pv::launch_verify(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_gbase, 1, ctx->vw,
                                     nullptr, ctx->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active,
                                     ctx->d_scan_tmp, s);
           if (err == hipSuccess) err = hipEventRecord(e1, s);
@@ -1877,6 +1873,7 @@ pv_status pv_autotune(pv_ctx* ctx, const pv_path_store* store, float threshold, 
   ctx->retrace_blocks_per_cu = best_b;
   ctx->walk_min_active = best_m;
   ctx->counts_ready = false;
+  ctx->queue_ordered = true;
   ctx->tune_report[0] = best_verify;
   ctx->tune_report[3] = best;
   if (out_ms) *out_ms = best;
@@ -1897,11 +1894,9 @@ pv_status pv_compact_photons(pv_ctx* ctx, const pv_path_store* store, float* d_o
   if (!d_count || (capacity && (!d_out_pos || !d_out_energy))) return fail(ctx, PV_ERR_ARG, "output is NULL");
   if ((st = wait_compaction(ctx))) return st;
   uint32_t nb = path_blocks(store->n_paths);
-  CK(pv::launch_photon_count(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_pcounts, ctx->stream));
-  CK(pv::launch_scan(ctx->d_pcounts, ctx->d_poffsets, nb * store->max_bounces, d_count, ctx->d_scan_tmp,
-                     ctx->stream));
-  CK(pv::launch_photon_scatter(ctx->d_scene, ctx->d_path_tiles, nb, store->max_bounces, ctx->d_poffsets, d_out_pos,
-                               d_out_energy, capacity, ctx->stream));
+  CK(pv::launch_compact(ctx->d_scene, 1, ctx->d_path_tiles, nb, store->max_bounces, nb * store->max_bounces,
+                        ctx->d_pcounts, ctx->d_poffsets, ctx->d_scan_tmp, d_out_pos, d_out_energy, capacity, d_count,
+                        nullptr, ctx->stream));
   return PV_OK;
 }
 
@@ -1931,10 +1926,8 @@ pv_status pv_compact_photons_noalloc(pv_ctx* ctx, const pv_path_store* store, fl
   uint32_t* offsets = counts + a;
   uint32_t* tmp = offsets + a;
   const uint32_t nb = path_blocks(store->n_paths);
-  CK(pv::launch_photon_count(ctx->d_scene, ctx->d_path_tiles, nb, counts, ctx->stream));
-  CK(pv::launch_scan(counts, offsets, (uint32_t)n, d_count, tmp, ctx->stream));
-  CK(pv::launch_photon_scatter(ctx->d_scene, ctx->d_path_tiles, nb, store->max_bounces, offsets, d_out_pos,
-                               d_out_energy, capacity, ctx->stream));
+  CK(pv::launch_compact(ctx->d_scene, 1, ctx->d_path_tiles, nb, store->max_bounces, (uint32_t)n, counts, offsets, tmp,
+                        d_out_pos, d_out_energy, capacity, d_count, nullptr, ctx->stream));
   return PV_OK;
 }
 
@@ -1952,10 +1945,9 @@ pv_status pv_compact_photons_async(pv_ctx* ctx, const pv_path_store* store, floa
   CK(hipEventRecord(ctx->ev_store, ctx->stream));
   CK(hipStreamWaitEvent(s, ctx->ev_store, 0));
   uint32_t nb = path_blocks(store->n_paths);
-  CK(pv::launch_photon_count(ctx->d_scene, ctx->d_path_tiles, nb, ctx->d_pcounts, s));
-  CK(pv::launch_scan(ctx->d_pcounts, ctx->d_poffsets, nb * store->max_bounces, d_count, ctx->d_scan_tmp_c, s));
-  CK(pv::launch_photon_scatter(ctx->d_scene, ctx->d_path_tiles, nb, store->max_bounces, ctx->d_poffsets, d_out_pos,
-                               d_out_energy, capacity, s));
+  CK(pv::launch_compact(ctx->d_scene, 1, ctx->d_path_tiles, nb, store->max_bounces, nb * store->max_bounces,
+                        ctx->d_pcounts, ctx->d_poffsets, ctx->d_scan_tmp_c, d_out_pos, d_out_energy, capacity, d_count,
+                        nullptr, s));
   CK(hipEventRecord(ctx->ev_compact, s));
   ctx->compact_pending = true;
   return PV_OK;
@@ -2004,23 +1996,19 @@ static pv_status batch_enqueue(pv_batch* b, pv_stats* d_stats, const float* cons
     CK(pv::launch_update_objects(b->d_scenes, b->d_obj_tiles, b->n_obj_tiles, b->d_xf_tiles, b->n_xf_tiles, st));
   }
   CK(pv::launch_build_top(b->d_scenes, (int)b->n, st));
-  CK(pv::launch_verify(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->d_gbase, (int)b->n, b->vw, b->d_block_cnt,
+  CK(pv::launch_verify(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->d_gbase, (int)b->n, b->vw,
                        d_stats, b->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active, b->d_scan_tmp, st));
-  // distribution maps: compute DM_C, prune, fill, scene by scene (each
-  // rewrites its own tiles' replace counts before the queue is built)
+  // distribution maps: compute DM_C, prune, fill, scene by scene
   for (const pv_batch::Dm& d : b->dms)
     CK(pv::launch_dm_update(b->d_scenes, b->d_scenes + d.scene, b->d_path_tiles + d.tile_base, d.n_tiles, d.cells,
-                            d.n_lights, d.D, b->d_block_cnt + d.tile_base, b->seed, 0, frame_ptr, st));
-  CK(pv::launch_scan(b->d_block_cnt, b->d_offsets, b->n_path_tiles, b->d_qcount, b->d_scan_tmp, st));
-  CK(pv::launch_scatter_queue(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->d_offsets, b->d_queue, st));
-  CK(pv::launch_retrace(b->d_scenes, b->d_gbase, (int)b->n, b->d_queue, b->d_qcount, b->T, b->seed, 0,
+                            d.n_lights, d.D, b->seed, 0, frame_ptr, st));
+  CK(pv::launch_build_queue(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->ow, b->d_queue, b->d_qcount, st));
+  CK(pv::launch_retrace(b->d_scenes, b->d_gbase, (int)b->n, b->ow.queue, b->d_qcount, b->T, b->seed, 0,
                         frame_ptr, d_stats, (uint32_t)(ctx->n_cu * ctx->retrace_blocks_per_cu), (uint32_t)ctx->n_cu, ctx->retrace_variant,
-                        b->stack_entries, ctx->walk_min_active, b->ow, st));
-  CK(pv::launch_photon_count(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->d_pcounts, st));
-  CK(pv::launch_scan(b->d_pcounts, b->d_poffsets, b->n_counts, b->d_ptotal, b->d_scan_tmp, st));
-  CK(pv::launch_photon_scatter(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->max_bounces, b->d_poffsets,
-                               b->d_out_pos, b->d_out_en, b->capacity, st));
-  CK(pv::launch_scene_photon_base(b->d_scenes, (int)b->n, b->d_poffsets, b->d_ptotal, b->d_pbase, st));
+                        b->stack_entries, ctx->walk_min_active, b->ow.deal, st));
+  CK(pv::launch_compact(b->d_scenes, (int)b->n, b->d_path_tiles, b->n_path_tiles, b->max_bounces, b->n_counts,
+                        b->d_pcounts, b->d_poffsets, b->d_scan_tmp, b->d_out_pos, b->d_out_en, b->capacity,
+                        b->d_ptotal, b->d_pbase, st));
   return PV_OK;
 }
 
@@ -2100,11 +2088,11 @@ pv_status pv_batch_create(pv_batch** out, pv_ctx* const* contexts, const pv_path
     Alloc& A = b->mem;
     hipStream_t s = b->stream;
     auto chk = [&](hipError_t e) { return e == hipSuccess; };
+    const uint32_t chunks = pv::queue_chunks((uint32_t)ptiles.size());
     bool ok = chk(upload(A, &b->d_scenes, table.data(), n, s)) && chk(upload(A, &b->d_path_tiles, ptiles.data(), ptiles.size(), s)) &&
               chk(upload(A, &b->d_obj_tiles, otiles.data(), otiles.size(), s)) &&
               chk(upload(A, &b->d_xf_tiles, xtiles.data(), xtiles.size(), s)) &&
               chk(upload(A, &b->d_gbase, gbase.data(), gbase.size(), s)) &&
-              chk(dalloc(A, &b->d_block_cnt, ptiles.size())) && chk(dalloc(A, &b->d_offsets, ptiles.size())) &&
               chk(dalloc(A, &b->d_queue, total_paths)) && chk(dalloc(A, &b->d_qcount, 1)) &&
               chk(dalloc(A, &b->d_pcounts, counts)) &&
               chk(dalloc(A, &b->d_poffsets, counts)) && chk(dalloc(A, &b->d_ptotal, 1)) &&
@@ -2114,13 +2102,13 @@ pv_status pv_batch_create(pv_batch** out, pv_ctx* const* contexts, const pv_path
               chk(dalloc(A, &b->vw.tmp, task_cap)) && chk(dalloc(A, &b->vw.tasks, task_cap)) &&
               chk(dalloc(A, &b->vw.tcount, ptiles.size())) && chk(dalloc(A, &b->vw.toff, ptiles.size())) &&
               chk(dalloc(A, &b->vw.total, 1)) && chk(dalloc(A, &b->vw.first, total_paths)) &&
-              (b->ow.tiles = pv::order_tiles((uint32_t)total_paths), true) &&
-              chk(dalloc(A, &b->ow.queue, total_paths)) && chk(dalloc(A, &b->ow.hist, 8 * (size_t)b->ow.tiles)) &&
-              chk(dalloc(A, &b->ow.hoff, 8 * (size_t)b->ow.tiles)) && chk(dalloc(A, &b->ow.htotal, 1)) &&
-              chk(dalloc(A, &b->ow.scan_tmp, pv::scan_tmp_words(8 * b->ow.tiles))) &&
-              chk(dalloc(A, &b->ow.deal, (size_t)pv::kDealGroups * pv::kDealStride)) &&
-              chk(dalloc(A, &b->vw.deal, (size_t)pv::kDealGroups * pv::kDealStride)) &&
-              chk(dalloc(A, &b->vw.part, 4 * ptiles.size() + 2 * (size_t)pv::verify_finish_blocks(verify_blocks_max(ctx)))) &&
+              chk(dalloc(A, &b->ow.queue, total_paths)) && chk(dalloc(A, &b->ow.hist, 8 * (size_t)chunks)) &&
+              chk(dalloc(A, &b->ow.hoff, 8 * (size_t)chunks)) &&
+              chk(dalloc(A, &b->ow.scan_tmp, pv::scan_tmp_words(8 * chunks))) &&
+              chk(dalloc(A, &b->ow.deal, pv::kDealWords)) && chk(dalloc(A, &b->vw.deal, pv::kDealWords)) &&
+              chk(hipMemsetAsync(b->ow.deal, 0, 4 * (size_t)pv::kDealWords, s)) &&
+              chk(hipMemsetAsync(b->vw.deal, 0, 4 * (size_t)pv::kDealWords, s)) &&
+              chk(dalloc(A, &b->vw.part, 4 * ptiles.size())) &&
               chk(upload(A, &b->d_obj_in, const_cast<const float**>(d_obj_xf), n, s)) &&
               chk(upload(A, &b->d_light_in, const_cast<const float**>(d_light_xf), n, s));
     for (pv_batch::Dm& d : b->dms) {

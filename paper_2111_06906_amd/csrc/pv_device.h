@@ -321,8 +321,8 @@ __host__ __device__ inline uint32_t pyr_entries(uint32_t n) {
 
 // Verification work lists (device scratch).  A task is one segment whose ray
 // reaches a moved object's box: (global path id << 4) | segment.  Each path
-// tile first writes its tasks into a region of its own; a scan of the
-// per-tile counts and a gather make them one list.  No atomics are needed:
+// tile first writes its tasks into a region of its own; a gather makes them
+// one list.  No atomics are needed:
 // device-wide atomics on one word from thousands of blocks serialise.
 struct VerifyWork {
   uint32_t* tmp;     // tasks by tile: region of a tile = kBlock * B entries
@@ -331,8 +331,8 @@ struct VerifyWork {
   uint32_t* toff;    // [tiles] their offsets in the compacted list
   uint32_t* total;   // [1] tasks in all
   uint32_t* first;   // [paths] first invalid segment found so far (global path id)
-  uint32_t* part;    // per-block statistics: [scan blocks][4], then [finish blocks][2]
-  uint32_t* deal;    // [kDealGroups * kDealStride] refill counters of the traversal
+  uint32_t* part;    // statistics of each tile: [tiles][4]
+  uint32_t* deal;    // [kDealWords] refill counters of the traversal, zero between launches
 };
 
 // Persistent kernels take their work lists a refill at a time from one of
@@ -341,6 +341,7 @@ struct VerifyWork {
 // g, g + kDealGroups, ... in order.
 constexpr uint32_t kDealGroups = 64;
 constexpr uint32_t kDealStride = 32;
+constexpr uint32_t kDealWords = (kDealGroups + 1) * kDealStride;  // and a line for the groups that are done
 
 // ---------------------------------------------------------------------------
 // small vector helpers (FP32)

@@ -197,14 +197,12 @@ __global__ __launch_bounds__(64) void k_dm_rank0(const SceneDev* __restrict__ sc
 
 // Fill DM_C: the i-th re-sampled path of a light (path order) takes the cell
 // where the running sum of the deficits passes i ('dex': exclusive scan of
-// the deficits of all cells, dex[cells] their total); also the tile's
-// replace count for the work queue.
+// the deficits of all cells, dex[cells] their total).
 __global__ __launch_bounds__(kBlock) void k_dm_fill(const SceneDev* __restrict__ scenes,
                                                     const uint2* __restrict__ tiles, const uint32_t* __restrict__ dex,
                                                     const uint32_t* __restrict__ toff,
-                                                    const uint32_t* __restrict__ rank0,
-                                                    uint32_t* __restrict__ block_cnt) {
-  __shared__ uint32_t ws[kBlock / 64], wr[kBlock / 64];
+                                                    const uint32_t* __restrict__ rank0) {
+  __shared__ uint32_t ws[kBlock / 64];
   const uint2 tile = tiles[blockIdx.x];
   const SceneDev& S = scenes[tile.x];
   const uint32_t p = tile.y + threadIdx.x;
@@ -213,19 +211,10 @@ __global__ __launch_bounds__(kBlock) void k_dm_fill(const SceneDev* __restrict__
   uint32_t w = have ? G(S.info)[p] : 0u;
   const bool f = l >= 0 && resampled(w);
   const uint64_t b = __ballot(f);
-  const uint64_t rb = __ballot(have && info_replace(w));
-  if (lane() == 0) {
-    ws[threadIdx.x >> 6] = (uint32_t)__popcll(b);
-    wr[threadIdx.x >> 6] = (uint32_t)__popcll(rb);
-  }
+  if (lane() == 0) ws[threadIdx.x >> 6] = (uint32_t)__popcll(b);
   __syncthreads();
   uint32_t before = 0;
   for (uint32_t i = 0; i < (threadIdx.x >> 6); ++i) before += ws[i];
-  if (threadIdx.x == 0) {
-    uint32_t t = 0;
-    for (int i = 0; i < kBlock / 64; ++i) t += wr[i];
-    block_cnt[blockIdx.x] = t;  // resampled paths already carry the replace bit
-  }
   if (!f) return;
   const uint32_t i = toff[blockIdx.x] + before + (uint32_t)__popcll(b & lanes_below()) - rank0[l];
   const uint32_t lo = S.dm_off[l], cells = S.dm_off[l + 1] - lo, base = dex[lo];
@@ -243,7 +232,7 @@ __global__ __launch_bounds__(kBlock) void k_dm_fill(const SceneDev* __restrict__
 }
 
 hipError_t launch_dm_update(const SceneDev* table, const SceneDev* scene, const uint2* tiles, uint32_t n_tiles,
-                            uint32_t cells, uint32_t n_lights, const DmWork& D, uint32_t* block_cnt, uint64_t seed,
+                            uint32_t cells, uint32_t n_lights, const DmWork& D, uint64_t seed,
                             uint32_t frame, const uint32_t* frame_ptr, hipStream_t s) {
   if (!n_tiles || !cells) return hipSuccess;
   if (n_lights < 1 || n_lights > PV_MAX_LIGHTS) return hipErrorInvalidValue;
@@ -259,8 +248,7 @@ hipError_t launch_dm_update(const SceneDev* table, const SceneDev* scene, const 
   e = launch_scan(D.tcnt, D.toff, n_tiles, D.ttotal, D.scan_tmp2, s);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_dm_rank0, dim3(n_lights), dim3(64), 0, s, scene, D.toff, D.rank0);
-  hipLaunchKernelGGL(k_dm_fill, dim3(n_tiles), dim3(kBlock), 0, s, table, tiles, D.dex, D.toff, D.rank0,
-                     block_cnt);
+  hipLaunchKernelGGL(k_dm_fill, dim3(n_tiles), dim3(kBlock), 0, s, table, tiles, D.dex, D.toff, D.rank0);
   return hipGetLastError();
 }
 

@@ -6,7 +6,7 @@
 //   k_verify        Section 3.1 origin update + Section 3.2 dynamic occlusions,
 //                   first invalid segment, per-block replace counts
 //   k_scan          exclusive scan of per-block counts (single block)
-//   k_scatter_queue stable re-trace work queue (wave ballot + prefix)
+//   k_queue_hist / k_queue_scatter   stable re-trace work queue and its order
 //   k_mark_all      full invalidation (baseline / frame 0)
 //   k_retrace       persistent re-trace over the device work queue
 //   k_photon_count / k_photon_scatter   compaction of existing photons
@@ -622,10 +622,49 @@ __device__ inline uint32_t wave_quota(uint32_t count, uint32_t waves) {
   return min(64u, max(1u, (count + waves - 1) / waves));
 }
 
-// the counters start at zero for a launch (cleared by a kernel that precedes
-// it in the stream, so that the sequence can be captured in a graph)
-__device__ inline void deal_reset(uint32_t* ctrs) {
-  if (blockIdx.x == 0 && threadIdx.x < kDealGroups) ctrs[threadIdx.x * kDealStride] = 0;
+// The counters are zero between launches: the last workgroup to end a launch
+// that dealt from them clears them again (arrivals are counted per group, then
+// over the groups, so that no word takes more than a few dozen additions).
+// Called by every thread of the workgroup, after its last deal().
+__device__ inline void deal_done(uint32_t* __restrict__ ctrs) {
+  __shared__ uint32_t last;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const uint32_t groups = min(kDealGroups, gridDim.x), g = blockIdx.x % groups;
+    const uint32_t members = (gridDim.x - g + groups - 1) / groups;
+    last = 0;
+    if (atomicAdd(ctrs + g * kDealStride + 1, 1u) + 1 == members)
+      last = atomicAdd(ctrs + kDealGroups * kDealStride, 1u) + 1 == groups ? 1u : 0u;
+  }
+  __syncthreads();
+  if (!last) return;
+  if (threadIdx.x < kDealGroups) {
+    uint32_t* c = ctrs + threadIdx.x * kDealStride;
+    __hip_atomic_store(c, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(c + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (threadIdx.x == 0)
+    __hip_atomic_store(ctrs + kDealGroups * kDealStride, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// sum of in[0 .. n) by the whole workgroup, result to all (n up to a few
+// thousand: read with 16-byte loads, in is 16-byte aligned)
+__device__ inline uint32_t block_prefix(const uint32_t* __restrict__ in, uint32_t n, uint32_t* sh) {
+  uint32_t v = 0;
+  const uint4* in4 = reinterpret_cast<const uint4*>(in);
+#pragma unroll 4
+  for (uint32_t i = threadIdx.x; i < n / 4; i += kBlock) {
+    const uint4 q = in4[i];
+    v += q.x + q.y + q.z + q.w;
+  }
+  if (threadIdx.x < n % 4) v += in[n / 4 * 4 + threadIdx.x];
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+  __syncthreads();
+  if (lane_id() == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  uint32_t t = 0;
+  for (int w = 0; w < kBlock / 64; ++w) t += sh[w];
+  return t;
 }
 
 // Verification runs as a short chain of kernels without atomics.
@@ -635,13 +674,12 @@ __device__ inline void deal_reset(uint32_t* ctrs) {
 //    tile's own region; scanning stops at the first segment whose end photon
 //    is on a moved object (that segment is invalid whatever lies before it).
 //    Writes the information word as if no task were blocked (final for paths
-//    without tasks) and the tile's replace count over those paths.
-//  scan of the per-tile task counts, k_verify_gather: one compact task list.
+//    without tasks).
+//  k_verify_gather: one compact task list.
 //  k_verify_trace: the tasks as independent any-hit queries against the
 //    moved objects, every lane busy; a blocked segment lowers its path's
 //    first invalid segment (atomic minimum on that path's own word).
-//  k_verify_finish: information words of the paths with tasks, whose replace
-//    bits it adds to their tiles' counts (the work queue's block counts).
+//  k_verify_finish: information words of the paths with tasks, statistics.
 // The result equals the in-order test of Section 3.2: the first invalid
 // segment is the minimum over blocked segments and the first moved endpoint.
 
@@ -653,7 +691,7 @@ static_assert(PV_MAX_BOUNCES <= 15, "segment indices below kVisTask");
 
 __global__ __launch_bounds__(kBlock) void k_verify_scan(const SceneDev* __restrict__ scenes,
                                                         const uint2* __restrict__ tiles, VerifyWork W,
-                                                        uint32_t* __restrict__ block_cnt, pv_stats* stats) {
+                                                        pv_stats* stats) {
   __shared__ MovedSet M;
   __shared__ unsigned long long sred[kBlock / 64];
   __shared__ uint32_t swt[kBlock / 64];
@@ -792,18 +830,16 @@ __global__ __launch_bounds__(kBlock) void k_verify_scan(const SceneDev* __restri
     inv = info_replace(out);
     if (nt > 0) ex = inv = 0;  // counted by k_verify_finish
   }
-  {
+  if (stats) {
     // per-block counts go to their own slots and are summed by
-    // k_verify_stats: one counter word shared by every block would serialise
+    // k_verify_finish: one counter word shared by every block would serialise
     // thousands of atomics.  Each count is at most kBlock * 15 < 2^16 per
-    // block, so the four travel as 16-bit fields of one sum.  The replace
-    // count of the tile is one of them.
+    // block, so the four travel as 16-bit fields of one sum.
     static_assert(kBlock * 15 < (1 << 16), "16-bit fields");
     const unsigned long long packed = (unsigned long long)ex | ((unsigned long long)inv << 16) |
                                       ((unsigned long long)lost << 32) | ((unsigned long long)nt << 48);
     const unsigned long long sum = block_sum_u64(packed, sred);
-    if (tid == 0) block_cnt[blockIdx.x] = (uint32_t)((sum >> 16) & 0xffffu);
-    if (stats && tid == 0) {
+    if (tid == 0) {
       uint32_t* o = W.part + 4 * (size_t)blockIdx.x;
       o[0] = (uint32_t)(sum & 0xffffu);
       o[1] = (uint32_t)((sum >> 16) & 0xffffu);
@@ -813,15 +849,43 @@ __global__ __launch_bounds__(kBlock) void k_verify_scan(const SceneDev* __restri
   }
 }
 
-// one block per path tile: its tasks to their place in the compacted list
+// A workgroup moves the tasks of kGatherTiles path tiles, a wave a tile at a
+// time, to their place in the compacted list.  The tiles' offsets come from
+// 'toff', or, for a few thousand tiles, from the counts themselves: every
+// workgroup sums the counts before its own (at most 64 KB from L2, 8 KB on
+// average for 3M paths), which takes less than the launch of a scan (8 us).
+constexpr uint32_t kGatherTiles = 8;
+constexpr uint32_t kInlineTiles = 16384;
+
 __global__ __launch_bounds__(kBlock) void k_verify_gather(const SceneDev* __restrict__ scenes,
-                                                          const uint2* __restrict__ tiles, VerifyWork W) {
-  const SceneDev& S = scenes[tiles[blockIdx.x].x];
-  const uint32_t n = W.tcount[blockIdx.x];
-  const PV_GLOBAL uint32_t* src = G(W.tmp) + S.task_base + (size_t)(blockIdx.x - S.tile_base) * kBlock * S.B;
-  PV_GLOBAL uint32_t* dst = G(W.tasks) + W.toff[blockIdx.x];
-  for (uint32_t i = threadIdx.x; i < n; i += kBlock) dst[i] = src[i];
-  deal_reset(W.deal);
+                                                          const uint2* __restrict__ tiles, uint32_t n_tiles,
+                                                          VerifyWork W, const uint32_t* __restrict__ toff) {
+  __shared__ uint32_t sh[kBlock / 64];
+  __shared__ uint32_t cnt[kGatherTiles], off[kGatherTiles];
+  const uint32_t t0 = blockIdx.x * kGatherTiles, m = min(kGatherTiles, n_tiles - t0);
+  const uint32_t before = toff ? 0u : block_prefix(W.tcount, t0, sh);
+  if (threadIdx.x < 64) {
+    const uint32_t i = threadIdx.x;
+    const uint32_t c = i < m ? W.tcount[t0 + i] : 0u;
+    uint32_t x = c;
+    for (int o = 1; o < 64; o <<= 1) {
+      const uint32_t y = __shfl_up(x, o, 64);
+      if ((int)i >= o) x += y;
+    }
+    if (i < m) {
+      cnt[i] = c;
+      off[i] = toff ? toff[t0 + i] : before + x - c;
+    }
+    if (!toff && t0 + m == n_tiles && i == 63) *W.total = before + x;
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x >> 6; i < m; i += kBlock / 64) {
+    const uint2 tile = tiles[t0 + i];
+    const SceneDev& S = scenes[tile.x];
+    const PV_GLOBAL uint32_t* src = G(W.tmp) + S.task_base + (size_t)(t0 + i - S.tile_base) * kBlock * S.B;
+    PV_GLOBAL uint32_t* dst = G(W.tasks) + off[i];
+    for (uint32_t k = lane_id(); k < cnt[i]; k += 64) dst[k] = src[k];
+  }
 }
 
 // Persistent: a lane whose walk has finished takes the wave's next task
@@ -982,94 +1046,91 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
       }
     }
   }
+  if (quota >= 64) deal_done(W.deal);  // uniform over the grid
 }
 
 // The tasks of a path are adjacent in the list: the thread holding a path's
-// first task writes its information word.
-// The replace bits are added to the tiles' counts with one atomic per tile a
-// wave's lanes reach (a wave's tasks belong to one or two tiles of paths).
+// first task writes its information word.  The statistics are the scan's
+// per-tile counts, summed by the first kStatBlocks workgroups, and this
+// kernel's own, added with one atomic per counter and workgroup (few and large
+// workgroups for that reason: an addition to one line takes about 11 ns).
+constexpr uint32_t kFinishBlocks = 256, kStatBlocks = 16;
+constexpr int kFinishThreads = 1024;
+
 template <bool kSingle>
-__global__ __launch_bounds__(kBlock) void k_verify_finish(const SceneDev* __restrict__ scenes,
+__global__ __launch_bounds__(kFinishThreads) void k_verify_finish(const SceneDev* __restrict__ scenes,
                                                           const uint32_t* __restrict__ gbase, int n_scenes,
-                                                          VerifyWork W, uint32_t* __restrict__ block_cnt,
-                                                          uint32_t n_scan_blocks, pv_stats* stats) {
-  __shared__ unsigned long long sred[kBlock / 64];
+                                                          VerifyWork W, uint32_t n_tiles, pv_stats* stats) {
+  __shared__ uint32_t sred[4][kFinishThreads / 64];
   __shared__ uint32_t sgb[kSingle ? 1 : kLdsScenes + 1];
   if (!kSingle) gbase = stage_gbase(gbase, n_scenes, sgb);
   const uint32_t total = *W.total;
   uint32_t ex = 0, inv = 0;
-  // the lanes of a wave hold consecutive tasks: they stay in step and leave
-  // the loop together except in its last round
-  for (uint32_t t = blockIdx.x * kBlock + threadIdx.x; t < total; t += gridDim.x * kBlock) {
-    const uint32_t gp = G(W.tasks)[t] >> 4;
-    uint32_t tile = kNoEntry;  // the tile whose count this lane raises
-    if (!(t > 0 && (G(W.tasks)[t - 1] >> 4) == gp)) {
-      uint32_t s = 0;
-      if (!kSingle) s = scene_of(gbase, n_scenes, gp);
-      const SceneDev& S = scenes[s];
-      const uint32_t q = gp - S.gpath_base;
-      const uint32_t w = G(S.info)[q];  // as written by the scan
-      const uint32_t n = info_nseg(w), k = G(W.first)[gp];
-      if (k < n) {
-        G(S.info)[q] = info_pack(info_cell(w), n, k, 1, 1);
-        ex += k + 1;
+  // kIlp tasks at a time: their loads (task, then word and first) overlap
+  constexpr uint32_t kIlp = 4;
+  const uint32_t step = gridDim.x * kFinishThreads;
+  for (uint32_t t0 = blockIdx.x * kFinishThreads + threadIdx.x; t0 < total; t0 += kIlp * step) {
+    uint32_t gp[kIlp], w[kIlp], k[kIlp];
+    PV_GLOBAL uint32_t* word[kIlp];
+    bool use[kIlp];
+#pragma unroll
+    for (uint32_t i = 0; i < kIlp; ++i) {
+      const uint32_t t = t0 + i * step;
+      use[i] = t < total;
+      gp[i] = use[i] ? G(W.tasks)[t] >> 4 : 0u;
+      if (use[i] && t > 0) use[i] = (G(W.tasks)[t - 1] >> 4) != gp[i];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kIlp; ++i) {
+      w[i] = 0;
+      k[i] = 0;
+      if (!use[i]) continue;
+      const SceneDev& S = scenes[kSingle ? 0u : scene_of(gbase, n_scenes, gp[i])];
+      word[i] = G(S.info) + (gp[i] - S.gpath_base);
+      w[i] = *word[i];  // as written by the scan
+      k[i] = G(W.first)[gp[i]];
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kIlp; ++i) {
+      if (!use[i]) continue;
+      const uint32_t n = info_nseg(w[i]);
+      if (k[i] < n) {
+        *word[i] = info_pack(info_cell(w[i]), n, k[i], 1, 1);
+        ex += k[i] + 1;
         inv += 1;
-        tile = S.tile_base + q / kBlock;
       } else {
         ex += n;
       }
     }
-    while (true) {
-      const uint64_t m = __ballot(tile != kNoEntry);
-      if (!m) break;
-      const int leader = __ffsll((long long)m) - 1;
-      const uint32_t lt = __shfl(tile, leader, 64);
-      const uint64_t same = __ballot(tile == lt);
-      if ((int)lane_id() == leader) atomicAdd(block_cnt + lt, (uint32_t)__popcll(same));
-      if (tile == lt) tile = kNoEntry;
+  }
+  if (!stats) return;
+  // counts of one launch fit 32 bits each (at most 15 per path of 2^28)
+  uint32_t lost = 0, tasks = 0;
+  if (blockIdx.x < kStatBlocks) {
+    const uint4* __restrict__ p4 = reinterpret_cast<const uint4*>(W.part);  // one record per tile
+#pragma unroll 4
+    for (uint32_t b = blockIdx.x * kFinishThreads + threadIdx.x; b < n_tiles; b += min(gridDim.x, kStatBlocks) * kFinishThreads) {
+      const uint4 r = p4[b];
+      ex += r.x;
+      inv += r.y;
+      lost += r.z;
+      tasks += r.w;
     }
   }
-  if (stats) {
-    // both counts of a block fit 32 bits (at most 15 and 1 per path): one sum
-    const unsigned long long sum = block_sum_u64((unsigned long long)ex | ((unsigned long long)inv << 32), sred);
-    if (threadIdx.x == 0) {
-      uint32_t* o = W.part + 4 * (size_t)n_scan_blocks + 2 * (size_t)blockIdx.x;
-      o[0] = (uint32_t)(sum & 0xffffffffull);
-      o[1] = (uint32_t)(sum >> 32);
-    }
-  }
-}
-
-// sum of the per-block statistics of one verification call into pv_stats
-// (a few blocks, each adding its part with one atomic per counter)
-__global__ __launch_bounds__(1024) void k_verify_stats(const uint32_t* __restrict__ part, uint32_t n_scan,
-                                                       uint32_t n_fin, pv_stats* stats) {
-  __shared__ unsigned long long sh[4][1024 / 64];
-  unsigned long long a[4] = {0, 0, 0, 0};
-  const uint4* __restrict__ p4 = reinterpret_cast<const uint4*>(part);  // one record per scan block
-  const uint32_t step = gridDim.x * blockDim.x;
-  for (uint32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < n_scan; b += step) {
-    const uint4 r = p4[b];
-    a[0] += r.x;
-    a[1] += r.y;
-    a[2] += r.z;
-    a[3] += r.w;
-  }
-  for (uint32_t b = blockIdx.x * blockDim.x + threadIdx.x; b < n_fin; b += step)
-    for (int k = 0; k < 2; ++k) a[k] += part[4 * (size_t)n_scan + 2 * (size_t)b + k];
-  for (int k = 0; k < 4; ++k) {
-    for (int o = 32; o > 0; o >>= 1) a[k] += __shfl_down(a[k], o, 64);
-    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = a[k];
-  }
+  uint32_t v[4] = {ex, inv, lost, tasks};
+  for (int c = 0; c < 4; ++c)
+    for (int o = 32; o > 0; o >>= 1) v[c] += __shfl_down(v[c], o, 64);
+  if (lane_id() == 0)
+    for (int c = 0; c < 4; ++c) sred[c][threadIdx.x >> 6] = v[c];
   __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long t[4] = {0, 0, 0, 0};
-    for (int k = 0; k < 4; ++k)
-      for (uint32_t w = 0; w < blockDim.x / 64; ++w) t[k] += sh[k][w];
-    atomicAdd(&stats->segments_examined, t[0]);
-    atomicAdd(&stats->paths_invalid, t[1]);
-    atomicAdd(&stats->paths_light_lost, t[2]);
-    atomicAdd(&stats->verify_box_hits, t[3]);
+  if (threadIdx.x < 4) {
+    unsigned long long t = 0;
+    for (int w = 0; w < kFinishThreads / 64; ++w) t += sred[threadIdx.x][w];
+    unsigned long long* to[4] = {&stats->segments_examined, &stats->paths_invalid, &stats->paths_light_lost,
+                                 &stats->verify_box_hits};
+    unsigned long long* at = to[0];
+    for (uint32_t c = 1; c < 4; ++c) at = threadIdx.x == c ? to[c] : at;
+    if (t) atomicAdd(at, t);
   }
 }
 
@@ -1123,6 +1184,14 @@ __global__ __launch_bounds__(1024) void k_scan(const uint32_t* __restrict__ in, 
 // and k_scan_add.
 constexpr uint32_t kScanPer = 16;
 constexpr uint32_t kScanTile = 1024 * kScanPer;
+
+// total of the scan tiles before tile 'tiles' (called by whole waves)
+__device__ inline uint32_t scan_tile_offset(const uint32_t* __restrict__ sums, uint32_t tiles) {
+  uint32_t v = 0;
+  for (uint32_t t = lane_id(); t < tiles; t += 64) v += sums[t];
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
+}
 
 __global__ __launch_bounds__(1024) void k_scan_tiles(const uint32_t* __restrict__ in, uint32_t* __restrict__ out,
                                                      uint32_t n, uint32_t* __restrict__ tile_sums) {
@@ -1181,37 +1250,183 @@ __global__ __launch_bounds__(256) void k_scan_add(uint32_t* __restrict__ out, ui
   if (i < n) out[i] += tile_off[i / kScanTile];
 }
 
-// stable queue: ascending global path ids with the replace bit
-__global__ __launch_bounds__(kBlock) void k_scatter_queue(const SceneDev* __restrict__ scenes, const uint2* __restrict__ tiles,
-                                                          const uint32_t* __restrict__ offsets, uint32_t* __restrict__ queue) {
-  __shared__ uint32_t wcnt[kBlock / 64];
-  uint2 tile = tiles[blockIdx.x];
-  const SceneDev& S = scenes[tile.x];
-  uint32_t p = tile.y + threadIdx.x;
-  bool flag = p < S.n_paths && info_replace(S.info[p]);
-  uint64_t bal = __ballot(flag);
-  if (lane_id() == 0) wcnt[threadIdx.x >> 6] = (uint32_t)__popcll(bal);
-  __syncthreads();
-  uint32_t pre = 0;
-  for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) pre += wcnt[w];
-  if (flag) queue[offsets[blockIdx.x] + pre + (uint32_t)__popcll(bal & lanemask_lt())] = S.gpath_base + p;
-}
-
 // full invalidation: every path replace=1, start=0, reuse_light=0; queue = all
 __global__ __launch_bounds__(kBlock) void k_mark_all(const SceneDev* __restrict__ scenes, const uint2* __restrict__ tiles,
-                                                     uint32_t* __restrict__ block_cnt) {
-  __shared__ unsigned long long sred[kBlock / 64];
-  uint2 tile = tiles[blockIdx.x];
+                                                     uint32_t* __restrict__ queue, uint32_t* __restrict__ qcount) {
+  const uint2 tile = tiles[blockIdx.x];
   const SceneDev& S = scenes[tile.x];
-  uint32_t p = tile.y + threadIdx.x;
-  uint32_t f = 0;
-  if (p < S.n_paths) {
-    uint32_t w = S.info[p];
-    S.info[p] = info_pack(info_cell(w), info_nseg(w), 0, 1, 0);
-    f = 1;
+  const uint32_t p = tile.y + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x == 0) *qcount = S.n_paths;
+  if (p >= S.n_paths) return;
+  const uint32_t w = S.info[p];
+  S.info[p] = info_pack(info_cell(w), info_nseg(w), 0, 1, 0);
+  queue[p] = p;
+}
+
+// The work queue: ascending global path ids with the replace bit, and the same
+// ids in the order in which the re-trace takes them.  A path's re-trace costs
+// up to one ray per segment from its first invalid one on, so the persistent
+// re-trace kernel is given the paths by that segment, smallest first (a stable
+// counting sort over kOrderBuckets buckets): the refills deal the long paths
+// first and the last refills of a launch are short paths, so the waves finish
+// closer together.  Two launches over chunks of kChunkTiles path tiles: counts
+// per bucket and chunk, then the scatter of both lists.  For up to
+// kInlineChunks chunks every workgroup of the scatter sums the counts itself
+// (at most 32 KB from L2, less than the 5 us of another launch; twice as many
+// chunks made the scatter 5 us longer); else it adds the tiles' totals to the
+// offsets of a scan in tiles ('hoff', 'sums').
+constexpr int kOrderBuckets = 8;
+constexpr uint32_t kChunkTiles = 4;
+constexpr uint32_t kInlineChunks = 1024;
+
+__device__ inline uint32_t order_bucket(uint32_t w, uint32_t B) {
+  const uint32_t n = min(info_nseg(w), B), k = info_start(w);
+  return min(k < n ? k : 0u, (uint32_t)kOrderBuckets - 1u);  // k >= n: a new light sample, a full path
+}
+
+// lanes of the wave with the same bucket as this one
+__device__ inline uint64_t bucket_peers(bool valid, uint32_t b) {
+  static_assert(kOrderBuckets == 8, "three bucket bits");
+  uint64_t peers = __ballot(valid);
+  for (int bit = 0; bit < 3; ++bit) {
+    const bool set = ((b >> bit) & 1u) != 0;
+    const uint64_t m = __ballot(valid && set);
+    peers &= set ? m : ~m;
   }
-  unsigned long long c = block_sum_u64(f, sred);
-  if (threadIdx.x == 0) block_cnt[blockIdx.x] = (uint32_t)c;
+  return peers;
+}
+
+// counts of one chunk, bucket-major (hist[bucket * stride + chunk])
+__global__ __launch_bounds__(kBlock) void k_queue_hist(const SceneDev* __restrict__ scenes,
+                                                       const uint2* __restrict__ tiles, uint32_t n_tiles,
+                                                       uint32_t* __restrict__ hist, uint32_t stride) {
+  __shared__ uint32_t h[kOrderBuckets];
+  if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0;
+  uint32_t w[kChunkTiles], B[kChunkTiles];
+#pragma unroll
+  for (uint32_t i = 0; i < kChunkTiles; ++i) {
+    const uint32_t t = blockIdx.x * kChunkTiles + i;
+    w[i] = 0;
+    B[i] = 0;
+    if (t < n_tiles) {
+      const uint2 tile = tiles[t];
+      const SceneDev& S = scenes[tile.x];
+      const uint32_t p = tile.y + threadIdx.x;
+      B[i] = S.B;
+      if (p < S.n_paths) w[i] = G(S.info)[p];
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kChunkTiles; ++i) {
+    const bool f = info_replace(w[i]) != 0;
+    const uint32_t b = order_bucket(w[i], B[i]);
+    const uint64_t peers = bucket_peers(f, b);
+    if (f && (peers & lanemask_lt()) == 0) atomicAdd(&h[b], (uint32_t)__popcll(peers));
+  }
+  __syncthreads();
+  if (threadIdx.x < kOrderBuckets) hist[threadIdx.x * stride + blockIdx.x] = h[threadIdx.x];
+}
+
+__global__ __launch_bounds__(kBlock) void k_queue_scatter(const SceneDev* __restrict__ scenes,
+                                                          const uint2* __restrict__ tiles, uint32_t n_tiles,
+                                                          const uint32_t* __restrict__ hist,
+                                                          const uint32_t* __restrict__ hoff,
+                                                          const uint32_t* __restrict__ sums, uint32_t stride,
+                                                          uint32_t* __restrict__ queue, uint32_t* __restrict__ ordered,
+                                                          uint32_t* __restrict__ qcount) {
+  constexpr uint32_t kWaves = kBlock / 64, kCells = kChunkTiles * kWaves;
+  __shared__ uint32_t tot[kOrderBuckets], bef[kOrderBuckets];  // entries of a bucket: all, in earlier chunks
+  __shared__ uint32_t cell[kCells][kOrderBuckets + 1];         // counts per (tile, wave): buckets, all; then offsets
+  const uint32_t tid = threadIdx.x, wv = tid >> 6, chunk = blockIdx.x;
+  uint32_t w[kChunkTiles], gp[kChunkTiles], bk[kChunkTiles];
+#pragma unroll
+  for (uint32_t i = 0; i < kChunkTiles; ++i) {
+    const uint32_t t = chunk * kChunkTiles + i;
+    w[i] = 0;
+    gp[i] = 0;
+    bk[i] = 0;
+    if (t < n_tiles) {
+      const uint2 tile = tiles[t];
+      const SceneDev& S = scenes[tile.x];
+      const uint32_t p = tile.y + tid;
+      gp[i] = S.gpath_base + p;
+      bk[i] = S.B;
+      if (p < S.n_paths) w[i] = G(S.info)[p];
+    }
+  }
+  // totals and earlier chunks of two buckets per wave
+  for (uint32_t b = 2 * wv; b < 2 * wv + 2; ++b) {
+    uint32_t all = 0, before = 0;
+    if (hoff) {
+      // exclusive scan over all buckets: a bucket's entries start at its first
+      all = hoff[b * stride] + scan_tile_offset(sums, b * stride / kScanTile);
+      before = hoff[b * stride + chunk] + scan_tile_offset(sums, (b * stride + chunk) / kScanTile) - all;
+    } else {
+      const uint4* h4 = reinterpret_cast<const uint4*>(hist + (size_t)b * stride);
+#pragma unroll 4
+      for (uint32_t q = lane_id(); q < stride / 4; q += 64) {
+        const uint4 v = h4[q];
+        all += v.x + v.y + v.z + v.w;
+        const uint32_t c = 4 * q;
+        before += (c < chunk ? v.x : 0u) + (c + 1 < chunk ? v.y : 0u) + (c + 2 < chunk ? v.z : 0u) +
+                  (c + 3 < chunk ? v.w : 0u);
+      }
+      for (int o = 32; o > 0; o >>= 1) {
+        all += __shfl_xor(all, o, 64);
+        before += __shfl_xor(before, o, 64);
+      }
+    }
+    if (lane_id() == 0) {
+      tot[b] = all;
+      bef[b] = before;
+    }
+  }
+  uint32_t rank[kChunkTiles], qrank[kChunkTiles];
+  for (uint32_t i = tid; i < kCells * (kOrderBuckets + 1); i += kBlock) (&cell[0][0])[i] = 0;
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kChunkTiles; ++i) {
+    const bool f = info_replace(w[i]) != 0;
+    bk[i] = order_bucket(w[i], bk[i]);
+    const uint64_t peers = bucket_peers(f, bk[i]), all = __ballot(f);
+    rank[i] = (uint32_t)__popcll(peers & lanemask_lt());
+    qrank[i] = (uint32_t)__popcll(all & lanemask_lt());
+    if (f && rank[i] == 0) cell[i * kWaves + wv][bk[i]] = (uint32_t)__popcll(peers);
+    if (lane_id() == 0) cell[i * kWaves + wv][kOrderBuckets] = (uint32_t)__popcll(all);
+  }
+  __syncthreads();
+  // offsets of the cells: a thread per bucket, and one for the whole queue
+  if (tid <= (uint32_t)kOrderBuckets) {
+    uint32_t at = 0;
+    if (tid < (uint32_t)kOrderBuckets) {
+      at = bef[tid];
+      if (hoff)
+        at += tot[tid];
+      else
+        for (uint32_t b = 0; b < tid; ++b) at += tot[b];
+    } else {
+      for (uint32_t b = 0; b < (uint32_t)kOrderBuckets; ++b) at += bef[b];
+    }
+    uint32_t v[kCells];
+#pragma unroll
+    for (uint32_t c = 0; c < kCells; ++c) v[c] = cell[c][tid];
+#pragma unroll
+    for (uint32_t c = 0; c < kCells; ++c) {
+      cell[c][tid] = at;
+      at += v[c];
+    }
+    // the last chunk's end is the length of the queue
+    if (tid == (uint32_t)kOrderBuckets && chunk == gridDim.x - 1) *qcount = at;
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kChunkTiles; ++i) {
+    if (!info_replace(w[i])) continue;
+    const uint32_t c = i * kWaves + wv;
+    queue[cell[c][kOrderBuckets] + qrank[i]] = gp[i];
+    ordered[cell[c][bk[i]] + rank[i]] = gp[i];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1729,6 +1944,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
     }
     n_rays += (uint32_t)__popcll(__ballot(start && !any));
   }
+  if (quota >= 64) deal_done(deal_ctr);  // uniform over the grid
   if (stats) {
     if (lane_id() == 0) {
       if (n_rays) atomicAdd(&scount[0], n_rays);
@@ -1770,27 +1986,58 @@ __global__ __launch_bounds__(kBlock) void k_photon_count(const SceneDev* __restr
   }
 }
 
+// The photons of one (row, path tile) to their place.  Offsets: up to
+// kInlineCounts counts, every workgroup sums the counts before its own (at
+// most 24 KB from L2, less than a scan launch takes); else the scan's offset
+// within its scan tile and the totals of the scan tiles before it.  The
+// workgroup of the last count also writes the number of photons, and the
+// first one, for a batch, every scene's first photon.
+constexpr uint32_t kInlineCounts = 6144;
+
+struct PhotonOffsets {
+  const uint32_t* counts;
+  const uint32_t* off;   // null: sum the counts
+  const uint32_t* sums;  // totals of the scan tiles
+  uint32_t n_counts;
+  uint32_t* total;
+  uint32_t* base;        // null, or [n_scenes + 1]
+  int n_scenes;
+};
+
 __global__ __launch_bounds__(kBlock) void k_photon_scatter(const SceneDev* __restrict__ scenes, const uint2* __restrict__ tiles,
-                                                           const uint32_t* __restrict__ offsets,
-                                                           float* __restrict__ out_pos, float* __restrict__ out_e,
-                                                           uint32_t capacity) {
+                                                           PhotonOffsets O, float* __restrict__ out_pos,
+                                                           float* __restrict__ out_e, uint32_t capacity) {
   __shared__ uint32_t wcnt[kBlock / 64];
+  __shared__ uint32_t sh[kBlock / 64];
   uint32_t r = blockIdx.y;
   uint2 tile = tiles[blockIdx.x];
   const SceneDev& S = scenes[tile.x];
+  if (O.base && blockIdx.x == 0 && r == 0) {
+    for (int i = threadIdx.x; i <= O.n_scenes; i += kBlock) {
+      // a scene's first count; behind the last scene with paths, all photons
+      const uint32_t c = i < O.n_scenes ? scenes[i].count_base : O.n_counts;
+      const uint32_t k = min(c, O.n_counts - 1);
+      uint32_t v = O.off[k] + (c > k ? O.counts[k] : 0u);
+      for (uint32_t t = 0; t < k / kScanTile; ++t) v += O.sums[t];
+      O.base[i] = v;
+    }
+  }
   if (r >= S.B) return;
   uint32_t p = tile.y + threadIdx.x;
   bool flag = p < S.n_paths && min(info_nseg(S.info[p]), S.B) > r;
+  const uint32_t c = S.count_base + r * S.n_blocks + tile.y / kBlock;
+  const uint32_t first = O.off ? O.off[c] + scan_tile_offset(O.sums, c / kScanTile) : block_prefix(O.counts, c, sh);
   uint64_t bal = __ballot(flag);
   if (lane_id() == 0) wcnt[threadIdx.x >> 6] = (uint32_t)__popcll(bal);
   __syncthreads();
+  if (c == O.n_counts - 1 && threadIdx.x == 0) *O.total = first + O.counts[c];
   uint32_t pre = 0;
   for (uint32_t w = 0; w < (threadIdx.x >> 6); ++w) pre += wcnt[w];
   if (!flag) return;
-  uint32_t idx = offsets[S.count_base + r * S.n_blocks + tile.y / kBlock] + pre + (uint32_t)__popcll(bal & lanemask_lt());
+  uint32_t idx = first + pre + (uint32_t)__popcll(bal & lanemask_lt());
   if (idx >= capacity) return;
   size_t i = (size_t)r * S.stride + p;
-  float4 x = S.pos[i], e = S.energy[i];
+  float4 x = G(S.pos)[i], e = G(S.energy)[i];
   out_pos[3 * (size_t)idx + 0] = x.x;
   out_pos[3 * (size_t)idx + 1] = x.y;
   out_pos[3 * (size_t)idx + 2] = x.z;
@@ -2037,100 +2284,6 @@ __global__ __launch_bounds__(kBlock) void k_energy_sum(const double* __restrict_
 }
 
 // ---------------------------------------------------------------------------
-// Re-trace work order.  A path's re-trace costs up to one ray per segment from
-// its first invalid one on, so the queue (ascending path ids, as the caller
-// sees it) is handed to the persistent re-trace kernel reordered by that
-// segment, smallest first (a stable counting sort over kOrderBuckets
-// buckets): the refills deal the long paths first and the last refills of a
-// launch are short paths, so the waves finish closer together.
-
-constexpr uint32_t kOrderTile = 2048;  // queue entries per tile of the reorder
-constexpr int kOrderBuckets = 8;
-
-__device__ inline uint32_t order_bucket(const SceneDev* scenes, const uint32_t* gbase, int n_scenes, uint32_t gp) {
-  const uint32_t s = scene_of(gbase, n_scenes, gp);
-  const SceneDev& S = scenes[s];
-  const uint32_t w = G(S.info)[gp - gbase[s]];
-  const uint32_t n = min(info_nseg(w), S.B), k = info_start(w);
-  return min(k < n ? k : 0u, (uint32_t)kOrderBuckets - 1u);  // k >= n: a new light sample, a full path
-}
-
-__global__ __launch_bounds__(kBlock) void k_order_hist(const SceneDev* __restrict__ scenes,
-                                                       const uint32_t* __restrict__ gbase, int n_scenes,
-                                                       const uint32_t* __restrict__ queue,
-                                                       const uint32_t* __restrict__ qcount, uint32_t* __restrict__ hist,
-                                                       uint32_t tiles) {
-  __shared__ uint32_t h[kOrderBuckets];
-  __shared__ uint32_t sgb[kLdsScenes + 1];
-  if (n_scenes > 1) gbase = stage_gbase(gbase, n_scenes, sgb);  // uniform
-  if (threadIdx.x < kOrderBuckets) h[threadIdx.x] = 0;
-  __syncthreads();
-  const uint32_t count = *qcount, base = blockIdx.x * kOrderTile;
-  const uint32_t end = min(base + kOrderTile, count);
-  for (uint32_t e = base + threadIdx.x; e < end; e += kBlock)
-    atomicAdd(&h[order_bucket(scenes, gbase, n_scenes, queue[e])], 1u);
-  __syncthreads();
-  if (threadIdx.x < kOrderBuckets) hist[threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
-}
-
-// stable scatter of one tile: entries in index order, kBlock at a time; an
-// entry's slot is its (bucket, tile) start plus the entries of its bucket
-// placed by earlier rounds, lower waves and lower lanes (ballots over the
-// bucket's bits)
-__global__ __launch_bounds__(kBlock) void k_order_scatter(const SceneDev* __restrict__ scenes,
-                                                          const uint32_t* __restrict__ gbase, int n_scenes,
-                                                          const uint32_t* __restrict__ queue,
-                                                          const uint32_t* __restrict__ qcount,
-                                                          const uint32_t* __restrict__ hoff, uint32_t tiles,
-                                                          uint32_t* __restrict__ out, uint32_t* __restrict__ deal_ctr) {
-  constexpr int kWaves = kBlock / 64;
-  static_assert(kOrderBuckets == 8, "three bucket bits");
-  __shared__ uint32_t run[kOrderBuckets];
-  __shared__ uint32_t wc[kWaves][kOrderBuckets];
-  __shared__ uint32_t sgb[kLdsScenes + 1];
-  deal_reset(deal_ctr);  // the re-trace that follows deals from these
-  if (n_scenes > 1) gbase = stage_gbase(gbase, n_scenes, sgb);  // uniform
-  const uint32_t count = *qcount, base = blockIdx.x * kOrderTile;
-  if (base >= count) return;  // uniform over the block
-  const uint32_t tid = threadIdx.x, w = tid >> 6;
-  if (tid < kOrderBuckets) run[tid] = hoff[tid * tiles + blockIdx.x];
-  for (uint32_t r = 0; r < kOrderTile / kBlock; ++r) {
-    __syncthreads();
-    if (tid < kWaves * kOrderBuckets) wc[tid / kOrderBuckets][tid % kOrderBuckets] = 0;
-    __syncthreads();
-    const uint32_t e = base + r * kBlock + tid;
-    const bool valid = e < count;
-    uint32_t gp = 0, b = 0;
-    if (valid) {
-      gp = queue[e];
-      b = order_bucket(scenes, gbase, n_scenes, gp);
-    }
-    uint64_t peers = __ballot(valid);
-    for (int bit = 0; bit < 3; ++bit) {
-      const bool set = ((b >> bit) & 1u) != 0;
-      const uint64_t m = __ballot(valid && set);
-      peers &= set ? m : ~m;
-    }
-    const uint32_t rank = (uint32_t)__popcll(peers & lanemask_lt());
-    if (valid && rank == 0) wc[w][b] = (uint32_t)__popcll(peers);
-    __syncthreads();
-    if (valid) {
-      uint32_t before = 0;
-      for (uint32_t q = 0; q < w; ++q) before += wc[q][b];
-      out[run[b] + before + rank] = gp;
-    }
-    __syncthreads();
-    if (tid < kOrderBuckets) {
-      uint32_t add = 0;
-      for (int q = 0; q < kWaves; ++q) add += wc[q][tid];
-      run[tid] += add;
-    }
-  }
-}
-
-uint32_t order_tiles(uint32_t max_entries) { return (max_entries + kOrderTile - 1) / kOrderTile; }
-
-// ---------------------------------------------------------------------------
 // launch wrappers (host side)
 
 hipError_t launch_frame_begin(SceneDev* scenes, int n_scenes, const float* const* obj_in,
@@ -2163,34 +2316,31 @@ hipError_t launch_build_top(SceneDev* scenes, int n_scenes, hipStream_t s) {
 // whose sentinel was taken points there)
 static size_t stack_bytes(uint32_t entries) { return (size_t)(entries + 1) * kBlock * sizeof(int32_t); }
 
-uint32_t verify_finish_blocks(uint32_t trace_blocks) { return std::max(1u, trace_blocks / 2); }
-
 hipError_t launch_verify(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint32_t* gbase,
-                         int n_scenes, VerifyWork W, uint32_t* block_cnt, pv_stats* stats, uint32_t stack,
-                         uint32_t trace_blocks, uint32_t n_cu, int min_active, uint32_t* scan_tmp, hipStream_t s) {
+                         int n_scenes, VerifyWork W, pv_stats* stats, uint32_t stack, uint32_t trace_blocks,
+                         uint32_t n_cu, int min_active, uint32_t* scan_tmp, hipStream_t s) {
   if (!n_tiles) return hipSuccess;
   if (stack < kMinStack || stack > (uint32_t)kMaxStack || trace_blocks == 0 || min_active < 1 || min_active > 64)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_verify_scan, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, W, block_cnt, stats);
-  hipError_t e = launch_scan(W.tcount, W.toff, n_tiles, W.total, scan_tmp, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_verify_gather, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, W);
-  const dim3 gt(trace_blocks), gf(verify_finish_blocks(trace_blocks));
+  hipLaunchKernelGGL(k_verify_scan, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, W, stats);
+  const uint32_t* toff = nullptr;
+  if (n_tiles > kInlineTiles) {
+    hipError_t e = launch_scan(W.tcount, W.toff, n_tiles, W.total, scan_tmp, s);
+    if (e != hipSuccess) return e;
+    toff = W.toff;
+  }
+  hipLaunchKernelGGL(k_verify_gather, dim3((n_tiles + kGatherTiles - 1) / kGatherTiles), dim3(kBlock), 0, s, scenes,
+                     tiles, n_tiles, W, toff);
+  const dim3 gt(trace_blocks), gf(std::min(kFinishBlocks, (n_tiles + 3) / 4));
   const uint32_t spread = std::min(4 * trace_blocks, 4 * kSpreadVerify * n_cu);
   if (n_scenes == 1) {
     hipLaunchKernelGGL(k_verify_trace<true>, gt, dim3(kBlock), stack_bytes(stack), s, scenes, gbase, n_scenes, W,
                        min_active, stack, spread);
-    hipLaunchKernelGGL(k_verify_finish<true>, gf, dim3(kBlock), 0, s, scenes, gbase, n_scenes, W, block_cnt, n_tiles,
-                       stats);
+    hipLaunchKernelGGL(k_verify_finish<true>, gf, dim3(kFinishThreads), 0, s, scenes, gbase, n_scenes, W, n_tiles, stats);
   } else {
     hipLaunchKernelGGL(k_verify_trace<false>, gt, dim3(kBlock), stack_bytes(stack), s, scenes, gbase, n_scenes, W,
                        min_active, stack, spread);
-    hipLaunchKernelGGL(k_verify_finish<false>, gf, dim3(kBlock), 0, s, scenes, gbase, n_scenes, W, block_cnt, n_tiles,
-                       stats);
-  }
-  if (stats) {
-    const uint32_t sb = std::min(16u, (std::max(n_tiles, gf.x) + 1023) / 1024);
-    hipLaunchKernelGGL(k_verify_stats, dim3(sb), dim3(1024), 0, s, W.part, n_tiles, gf.x, stats);
+    hipLaunchKernelGGL(k_verify_finish<false>, gf, dim3(kFinishThreads), 0, s, scenes, gbase, n_scenes, W, n_tiles, stats);
   }
   return hipGetLastError();
 }
@@ -2215,17 +2365,29 @@ hipError_t launch_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* 
 
 uint32_t scan_tmp_words(uint32_t n) { return 2 * ((n + kScanTile - 1) / kScanTile) + 2; }
 
-hipError_t launch_scatter_queue(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint32_t* offsets,
-                                uint32_t* queue, hipStream_t s) {
-  if (!n_tiles) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter_queue, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, offsets, queue);
+uint32_t queue_chunks(uint32_t n_tiles) { return ((n_tiles + kChunkTiles - 1) / kChunkTiles + 3) / 4 * 4; }
+
+hipError_t launch_build_queue(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const OrderWork& O,
+                              uint32_t* queue, uint32_t* qcount, hipStream_t s) {
+  if (!n_tiles) return launch_scan(nullptr, nullptr, 0, qcount, nullptr, s);  // length 0
+  const uint32_t chunks = (n_tiles + kChunkTiles - 1) / kChunkTiles, stride = queue_chunks(n_tiles);
+  // the grid covers the padding of the rows too, whose counts are zero
+  hipLaunchKernelGGL(k_queue_hist, dim3(stride), dim3(kBlock), 0, s, scenes, tiles, n_tiles, O.hist, stride);
+  const uint32_t* hoff = nullptr;
+  if (chunks > kInlineChunks) {
+    hipLaunchKernelGGL(k_scan_tiles, dim3((kOrderBuckets * stride + kScanTile - 1) / kScanTile), dim3(1024), 0, s, O.hist,
+                       O.hoff, kOrderBuckets * stride, O.scan_tmp);
+    hoff = O.hoff;
+  }
+  hipLaunchKernelGGL(k_queue_scatter, dim3(chunks), dim3(kBlock), 0, s, scenes, tiles, n_tiles, O.hist, hoff, O.scan_tmp,
+                     stride, queue, O.queue, qcount);
   return hipGetLastError();
 }
 
-hipError_t launch_mark_all(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t* block_cnt,
-                           hipStream_t s) {
-  if (!n_tiles) return hipSuccess;
-  hipLaunchKernelGGL(k_mark_all, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, block_cnt);
+hipError_t launch_mark_all(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t* queue,
+                           uint32_t* qcount, hipStream_t s) {
+  if (!n_tiles) return launch_scan(nullptr, nullptr, 0, qcount, nullptr, s);
+  hipLaunchKernelGGL(k_mark_all, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, queue, qcount);
   return hipGetLastError();
 }
 
@@ -2256,57 +2418,38 @@ static void retrace_variant(int v, dim3 g, size_t lds, hipStream_t s, const Scen
   }
 }
 
-hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_scenes, const uint32_t* queue_in,
+hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_scenes, const uint32_t* queue,
                           const uint32_t* qcount, float T, uint64_t seed, uint32_t frame,
                           const uint32_t* frame_ptr, pv_stats* stats, uint32_t n_blocks, uint32_t n_cu, int variant,
-                          uint32_t stack, int min_active, const OrderWork& O, hipStream_t s) {
+                          uint32_t stack, int min_active, uint32_t* deal, hipStream_t s) {
   if (stack < kMinStack || stack > (uint32_t)kMaxStack || min_active < 1 || min_active > 64) return hipErrorInvalidValue;
-  // the queue reordered by first invalid segment (see k_order_hist)
-  hipLaunchKernelGGL(k_order_hist, dim3(O.tiles), dim3(kBlock), 0, s, scenes, gbase, n_scenes, queue_in, qcount, O.hist,
-                     O.tiles);
-  hipError_t e = launch_scan(O.hist, O.hoff, kOrderBuckets * O.tiles, O.htotal, O.scan_tmp, s);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_order_scatter, dim3(O.tiles), dim3(kBlock), 0, s, scenes, gbase, n_scenes, queue_in, qcount,
-                     O.hoff, O.tiles, O.queue, O.deal);
-  const uint32_t* queue = O.queue;
+  const uint32_t spread = std::min(4 * n_blocks, 4 * kSpreadRetrace * n_cu);
   if (n_scenes == 1)
     retrace_variant<true>(variant, dim3(n_blocks), stack_bytes(stack), s, scenes, gbase, n_scenes, queue, qcount, T, seed, frame,
-                          frame_ptr, stats, min_active, stack, std::min(4 * n_blocks, 4 * kSpreadRetrace * n_cu), O.deal);
+                          frame_ptr, stats, min_active, stack, spread, deal);
   else
     retrace_variant<false>(variant, dim3(n_blocks), stack_bytes(stack), s, scenes, gbase, n_scenes, queue, qcount, T, seed, frame,
-                           frame_ptr, stats, min_active, stack, std::min(4 * n_blocks, 4 * kSpreadRetrace * n_cu), O.deal);
+                           frame_ptr, stats, min_active, stack, spread, deal);
   return hipGetLastError();
 }
 
-hipError_t launch_photon_count(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t* counts,
-                               hipStream_t s) {
-  if (!n_tiles) return hipSuccess;
+hipError_t launch_compact(const SceneDev* scenes, int n_scenes, const uint2* tiles, uint32_t n_tiles, uint32_t B,
+                          uint32_t n_counts, uint32_t* counts, uint32_t* offsets, uint32_t* scan_tmp, float* out_pos,
+                          float* out_e, uint32_t capacity, uint32_t* total, uint32_t* base, hipStream_t s) {
+  if (!n_tiles || !n_counts) {
+    // no photon: every count and base is zero
+    hipError_t e = launch_scan(nullptr, nullptr, 0, total, nullptr, s);
+    for (int i = 0; base && e == hipSuccess && i <= n_scenes; ++i) e = launch_scan(nullptr, nullptr, 0, base + i, nullptr, s);
+    return e;
+  }
   hipLaunchKernelGGL(k_photon_count, dim3(n_tiles), dim3(kBlock), 0, s, scenes, tiles, counts);
-  return hipGetLastError();
-}
-
-hipError_t launch_photon_scatter(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t B,
-                                 const uint32_t* offsets, float* out_pos, float* out_e, uint32_t capacity,
-                                 hipStream_t s) {
-  if (!n_tiles) return hipSuccess;
-  hipLaunchKernelGGL(k_photon_scatter, dim3(n_tiles, B), dim3(kBlock), 0, s, scenes, tiles, offsets, out_pos, out_e,
-                     capacity);
-  return hipGetLastError();
-}
-
-// photon ranges of the scenes of a batch: base[s] = offsets[count_base of s],
-// base[n] = total
-__global__ void k_scene_photon_base(const SceneDev* __restrict__ scenes, int n_scenes, const uint32_t* __restrict__ offsets,
-                                    const uint32_t* __restrict__ total, uint32_t* __restrict__ base) {
-  int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n_scenes) base[i] = offsets[scenes[i].count_base];
-  if (i == n_scenes) base[i] = *total;
-}
-
-hipError_t launch_scene_photon_base(const SceneDev* scenes, int n_scenes, const uint32_t* offsets, const uint32_t* total,
-                                    uint32_t* base, hipStream_t s) {
-  hipLaunchKernelGGL(k_scene_photon_base, dim3((n_scenes + 64) / 64), dim3(64), 0, s, scenes, n_scenes, offsets, total,
-                     base);
+  PhotonOffsets O{counts, nullptr, scan_tmp, n_counts, total, base, n_scenes};
+  if (n_counts > kInlineCounts || base) {
+    hipLaunchKernelGGL(k_scan_tiles, dim3((n_counts + kScanTile - 1) / kScanTile), dim3(1024), 0, s, counts, offsets,
+                       n_counts, scan_tmp);
+    O.off = offsets;
+  }
+  hipLaunchKernelGGL(k_photon_scatter, dim3(n_tiles, B), dim3(kBlock), 0, s, scenes, tiles, O, out_pos, out_e, capacity);
   return hipGetLastError();
 }
 

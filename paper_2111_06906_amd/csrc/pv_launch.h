@@ -32,50 +32,48 @@ uint32_t lbvh_sort_tiles(uint32_t n_dyn);
 uint32_t lbvh_pyramid_entries(uint32_t n_dyn);
 hipError_t launch_build_top(SceneDev* scenes, int n_scenes, hipStream_t s);
 // Verification of every path of the tiles: scan, task list, traversal of the
-// box-hit segments, information words of the paths with tasks, per-tile
-// replace counts into block_cnt.  'gbase' / 'n_scenes': scene path ranges
-// (global path ids); 'stack': traversal stack entries per lane (stack_entries
-// of the moved objects' hierarchy depths, at most kMaxStack); 'trace_blocks':
-// grid of the traversal kernel; 'min_active': its walk yield threshold;
-// 'scan_tmp': scan_tmp_words(n_tiles) words.
+// box-hit segments, information words of the paths with tasks, statistics.
+// 'gbase' / 'n_scenes': scene path ranges (global path ids); 'stack':
+// traversal stack entries per lane (stack_entries of the moved objects'
+// hierarchy depths, at most kMaxStack); 'trace_blocks': grid of the traversal
+// kernel; 'min_active': its walk yield threshold; 'scan_tmp':
+// scan_tmp_words(n_tiles) words.
 hipError_t launch_verify(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint32_t* gbase,
-                         int n_scenes, VerifyWork W, uint32_t* block_cnt, pv_stats* stats, uint32_t stack,
-                         uint32_t trace_blocks, uint32_t n_cu, int min_active, uint32_t* scan_tmp, hipStream_t s);
-// blocks of the finishing kernel for a traversal grid (sizes W.part: 4 words
-// per path tile plus 2 per finishing block)
-uint32_t verify_finish_blocks(uint32_t trace_blocks);
+                         int n_scenes, VerifyWork W, pv_stats* stats, uint32_t stack, uint32_t trace_blocks,
+                         uint32_t n_cu, int min_active, uint32_t* scan_tmp, hipStream_t s);
 hipError_t launch_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* total,
                        uint32_t* tile_tmp, hipStream_t s);
 uint32_t scan_tmp_words(uint32_t n);
-hipError_t launch_scatter_queue(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint32_t* offsets,
-                                uint32_t* queue, hipStream_t s);
-hipError_t launch_mark_all(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t* block_cnt,
-                           hipStream_t s);
-// Scratch of the re-trace's work order: the reordered queue (as many entries
-// as the queue can hold), bucket counts per tile and their scan.
+// Scratch of the work queue's order: the ordered queue (as many entries as
+// the queue can hold), bucket counts per chunk of path tiles and their scan.
 struct OrderWork {
   uint32_t* queue;     // [max entries]
-  uint32_t* hist;      // [8 * tiles]
-  uint32_t* hoff;      // [8 * tiles]
-  uint32_t* htotal;    // [1]
-  uint32_t* scan_tmp;  // scan_tmp_words(8 * tiles)
-  uint32_t* deal;      // [kDealGroups * kDealStride] refill counters of the re-trace
-  uint32_t tiles;      // order_tiles(max entries)
+  uint32_t* hist;      // [8 * queue_chunks(tiles)]
+  uint32_t* hoff;      // [8 * queue_chunks(tiles)]
+  uint32_t* scan_tmp;  // scan_tmp_words(8 * queue_chunks(tiles))
+  uint32_t* deal;      // [kDealWords] refill counters of the re-trace, zero between launches
 };
-uint32_t order_tiles(uint32_t max_entries);
-// queue_in / qcount: the work queue (ascending path ids) and its length; the
-// paths are re-traced in the order of their first invalid segment
-hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_scenes, const uint32_t* queue_in,
+uint32_t queue_chunks(uint32_t n_tiles);
+// paths with the replace bit in ascending order ('queue', its length
+// *qcount), and ordered by their first invalid segment (O.queue)
+hipError_t launch_build_queue(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const OrderWork& O,
+                              uint32_t* queue, uint32_t* qcount, hipStream_t s);
+// every path of one scene marked and queued
+hipError_t launch_mark_all(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t* queue,
+                           uint32_t* qcount, hipStream_t s);
+// queue / qcount: the paths to re-trace, dealt in list order
+hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_scenes, const uint32_t* queue,
                           const uint32_t* qcount, float T, uint64_t seed, uint32_t frame,
                           const uint32_t* frame_ptr, pv_stats* stats, uint32_t n_blocks, uint32_t n_cu, int variant,
-                          uint32_t stack, int min_active, const OrderWork& O, hipStream_t s);
-hipError_t launch_photon_count(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t* counts,
-                               hipStream_t s);
-hipError_t launch_photon_scatter(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t B,
-                                 const uint32_t* offsets, float* out_pos, float* out_e, uint32_t capacity,
-                                 hipStream_t s);
-hipError_t launch_scene_photon_base(const SceneDev* scenes, int n_scenes, const uint32_t* offsets, const uint32_t* total,
-                                    uint32_t* base, hipStream_t s);
+                          uint32_t stack, int min_active, uint32_t* deal, hipStream_t s);
+// Photons of the tiles' paths in (scene, row, path) order: counts per (row,
+// path tile) ('counts', n_counts of them, 16-byte aligned), their offsets (in
+// 'offsets' and 'scan_tmp', scan_tmp_words(n_counts) words), the photons (at
+// most 'capacity'), their number, and, for a batch, each scene's first photon
+// and the number of all (base[n_scenes + 1], else null).
+hipError_t launch_compact(const SceneDev* scenes, int n_scenes, const uint2* tiles, uint32_t n_tiles, uint32_t B,
+                          uint32_t n_counts, uint32_t* counts, uint32_t* offsets, uint32_t* scan_tmp, float* out_pos,
+                          float* out_e, uint32_t capacity, uint32_t* total, uint32_t* base, hipStream_t s);
 // Scratch of the distribution-map update (cells: all lights' cells)
 struct DmWork {
   uint32_t* dm_c;      // [cells] paths counted per cell (Compute DM_C)
@@ -90,12 +88,11 @@ struct DmWork {
   uint32_t* scan_tmp2; // scan_tmp_words(tiles)
 };
 // Compute DM_C, prune (Equation 1), fill (Section 3.1) on one scene's store
-// (information words updated, tiles' replace counts into block_cnt[0 ..
-// n_tiles)).  tiles index the descriptor table 'table', and every tile names
+// (information words updated).  tiles index the descriptor table 'table', and every tile names
 // the same scene, 'scene'; the frame number is *frame_ptr when frame_ptr is
 // not NULL (graph replays), else 'frame'.
 hipError_t launch_dm_update(const SceneDev* table, const SceneDev* scene, const uint2* tiles, uint32_t n_tiles,
-                            uint32_t cells, uint32_t n_lights, const DmWork& D, uint32_t* block_cnt, uint64_t seed,
+                            uint32_t cells, uint32_t n_lights, const DmWork& D, uint64_t seed,
                             uint32_t frame, const uint32_t* frame_ptr, hipStream_t s);
 hipError_t launch_energy_fwd(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, uint32_t B,
                              const float* albedo, const float* power, float* E, hipStream_t s);

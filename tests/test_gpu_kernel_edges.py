@@ -142,3 +142,50 @@ def test_ties_between_coincident_triangles(E):
     none = b["hit"] == 0xFFFFFFFF
     hit = np.where(none, b["hit"], np.where(b["hit"] < 2 * S, b["hit"] % S, b["hit"] - S))
     assert np.array_equal(a["hit"], hit)
+
+
+# Queue, its order, statistics and compaction: a lone path, one below and above
+# a chunk of 1,024 paths, and both sides of the sizes from which each list's
+# offsets come from a scan of their own (1,048,576 paths for the queue,
+# 1,572,864 photon rows for the compaction, 4,194,304 paths for the tasks).
+@pytest.mark.parametrize("n,B", [(1, 1), (1023, 3), (1025, 3), (786_433, 2), (1_048_576, 1), (1_048_577, 2),
+                                 (1_572_864, 1), (1_572_865, 1), (4_194_304, 1), (4_194_305, 1)])
+def test_queue_and_compaction_at_edges(E, n, B):
+    import oracle as O
+    import torch
+    sc = scenes.make_tiny(n_paths=n, max_bounces=B, frames=2, seed=11)
+    ctx = E.Context(sc)
+    st = ctx.new_store()
+    ctx.frame_begin(0)
+    ctx.initial_trace(st, 11)
+    ctx.frame_begin(1)
+    stats = ctx.new_stats()
+    ctx.verify(st, stats)
+    info = st.info[:n].cpu().numpy().view(np.uint32)
+    f = O.info_fields(info)
+    queued = f["replace"] != 0
+    np.testing.assert_array_equal(ctx.queue(), np.nonzero(queued)[0])
+    s = ctx.stats_dict(stats)
+    kept = queued & (f["reuse"] != 0)  # replaced from a segment on, the light sample kept
+    assert s["paths_invalid"] == queued.sum() and s["paths_light_lost"] == (queued & ~kept).sum()
+    assert s["segments_examined"] == f["nseg"][~queued].sum() + (f["start"][kept] + 1).sum()
+    # every queued path is re-traced: the rows from its first invalid segment
+    # on are overwritten or end before it
+    row = torch.arange(B, device="cuda")[:, None]
+    q = torch.from_numpy(queued).cuda()
+    st.pos_hit[:, :n, :3] = torch.where(
+        (q & (row >= torch.from_numpy(f["start"].astype(np.int64)).cuda()))[..., None],
+        torch.full((), 1e9, device="cuda"), st.pos_hit[:, :n, :3])
+    ctx.retrace(st, -1.0, 11, 1)
+    d = st.to_numpy()
+    nseg = O.info_fields(d["info"])["nseg"]
+    at = np.minimum(f["start"], B - 1)
+    left = queued & (nseg > f["start"]) & (d["pos"][at, np.arange(n), 0] == 1e9)
+    assert not left.any(), np.nonzero(left)[0][:5]
+    np.testing.assert_array_equal(nseg[~queued], f["nseg"][~queued])
+    pos, en, cnt = ctx.compact_photons(st)
+    there = nseg[None, :] > np.arange(B)[:, None]
+    assert cnt == there.sum()
+    np.testing.assert_array_equal(pos.cpu().numpy(), d["pos"][there])
+    np.testing.assert_array_equal(en.cpu().numpy(), d["energy"][there])
+    ctx.close()
