@@ -84,13 +84,13 @@ __host__ __device__ inline uint32_t leaf_count(int code) { return (((uint32_t)~c
 // Planes are FP16 in the scene's grid, (coordinate - qc) * qs with qs a power
 // of two, rounded outwards, so a quantised box contains its FP32 box; child
 // k's planes are words 3 k .. 3 k + 2, (lower plane | upper plane << 16) per
-// axis; codes as in Node.  An unused slot holds +inf in every plane, which no
-// query's interval reaches.
+// axis; codes as in Node.  An unused slot holds +inf as its lower and
+// -inf as its upper planes, which no query enters.
 struct alignas(64) Wide {
   uint32_t plane[12];
   int32_t child[4];
 };
-constexpr uint32_t kPlanesNone = 0x7C007C00u;  // +inf, +inf
+constexpr uint32_t kPlanesNone = 0xFC007C00u;  // +inf, -inf
 constexpr uint32_t kSlotNone = 0xFFFFFFFFu;
 
 __host__ __device__ inline uint32_t float_bits(float x) {
@@ -536,16 +536,21 @@ __device__ inline void walk_start(Walk& w, int32_t root, float tmax, StackCol co
 
 // Parameters of a query's box tests: 1 / direction and (centre - origin) /
 // direction in the planes' grid, and per axis 16 where the direction is
-// negative (the upper plane is then the nearer one).
+// negative (the upper plane is then the nearer one).  They give a crossing's
+// parameter t as (t - tmin) kTScale, so that the instructions' output clamp to
+// [0, 1] is the interval's lower end at no cost; parameters past 1 / kTScale
+// clamp too, which only enters a box the query has left behind.
+constexpr float kTScale = 1.0f / 1099511627776.0f;  // 2^-40
+
 struct Slab {
   float3 inv, oi;
   uint32_t rx, ry, rz;
 };
 
-__device__ inline Slab make_slab(float3 inv, float3 oi, float scale) {
+__device__ inline Slab make_slab(float3 inv, float3 oi, float scale, float tmin) {
   Slab q;
-  q.inv = mul(inv, scale);
-  q.oi = oi;
+  q.inv = mul(inv, scale * kTScale);
+  q.oi = f3((oi.x - tmin) * kTScale, (oi.y - tmin) * kTScale, (oi.z - tmin) * kTScale);
   q.rx = inv.x < 0.0f ? 16u : 0u;
   q.ry = inv.y < 0.0f ? 16u : 0u;
   q.rz = inv.z < 0.0f ? 16u : 0u;
@@ -553,9 +558,9 @@ __device__ inline Slab make_slab(float3 inv, float3 oi, float scale) {
 }
 
 // a world-space query against the scene's four-wide nodes
-__device__ inline Slab world_slab(const SceneDev& S, float3 o, float3 inv) {
+__device__ inline Slab world_slab(const SceneDev& S, float3 o, float3 inv, float tmin) {
   const float3 c = f3(S.qc[0] - o.x, S.qc[1] - o.y, S.qc[2] - o.z);
-  return make_slab(inv, f3(c.x * inv.x, c.y * inv.y, c.z * inv.z), S.qinv);
+  return make_slab(inv, f3(c.x * inv.x, c.y * inv.y, c.z * inv.z), S.qinv, tmin);
 }
 
 // a condition as the wave's mask, and a mask's bit of this lane: conditions
@@ -589,9 +594,10 @@ __device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, 
 // per visit, as the binary FP32 node took, and about a fifth of the visits (22
 // against 109 for a ray of the 3M-path, 380k-triangle interior), so a shorter
 // chain of dependent loads and fewer of them.  Bound by vector issue: about
-// 85 instructions a visit.  Measured there, one MI355X, four-wide against
+// 83 instructions a visit.  Measured there, one MI355X, four-wide against
 // binary: full trace 4.85 against 5.66 ms, partial re-trace 1.98 against 2.30
-// ms, verification traversal 178 against 224 us.
+// ms, verification traversal 178 against 224 us; with the clamp as the lower
+// end (four instructions a visit) the full trace went from 4.11 to 4.03 ms.
 //
 // Boxes are tested with the slab parameters q and triangles with the ray r
 // itself: a walk through a rigid object's hierarchy in its own object space
@@ -614,8 +620,8 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
   float tb = w.tb;
   uint32_t rec = w.rec;
   bool redo = w.redo;
-  const float tmin = __builtin_canonicalizef(r.tmin);
   while (true) {
+    const float ts = __builtin_canonicalizef((tb - r.tmin) * kTScale);  // tb as a slab parameter
     while (cur >= 0) {
       const int32_t below = top[0], below2 = top[-kBlock];
       // node records are addressed by a 32-bit byte offset (arrays < 4 GiB)
@@ -631,10 +637,10 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
         plane_pair(pl[3 * k], q.rx, q.inv.x, q.oi.x, &nx, &fx);
         plane_pair(pl[3 * k + 1], q.ry, q.inv.y, q.oi.y, &ny, &fy);
         plane_pair(pl[3 * k + 2], q.rz, q.inv.z, q.oi.z, &nz, &fz);
-        e[k] = fmaxf(fmaxf(nx, ny), nz);
+        e[k] = __builtin_amdgcn_fmed3f(fmaxf(fmaxf(nx, ny), nz), 0.0f, 1.0f);
         const float ex = fminf(fminf(fx, fy), fz);
         // the slab interval meets [tmin, tb]
-        h[k] = wave_mask(fmaxf(e[k], tmin) <= fminf(ex, tb));
+        h[k] = wave_mask(e[k] <= fminf(ex, ts));
       }
       // nearest entered child first, the others nearly in order (a child not
       // entered comes last of its pair); exchanges of the masks are scalar work
@@ -785,6 +791,14 @@ __device__ inline void mul64(uint64_t m, uint64_t c, uint64_t* lo, uint64_t* hi)
   *lo = (p2 << 32) | (uint32_t)p0;
 }
 
+// a ^ b ^ c in one instruction per word
+__device__ inline uint64_t xor3(uint64_t a, uint64_t b, uint64_t c) {
+  const uint32_t l = (uint32_t)__builtin_amdgcn_bitop3_b32((uint32_t)a, (uint32_t)b, (uint32_t)c, 0x96);
+  const uint32_t h = (uint32_t)__builtin_amdgcn_bitop3_b32((uint32_t)(a >> 32), (uint32_t)(b >> 32),
+                                                          (uint32_t)(c >> 32), 0x96);
+  return ((uint64_t)h << 32) | l;
+}
+
 __device__ inline void philox4x64(uint64_t c[4], uint64_t k0, uint64_t k1) {
   const uint64_t M0 = 0xD2E7470EE14C6C93ull, M1 = 0xCA5A826395121157ull;
   const uint64_t W0 = 0x9E3779B97F4A7C15ull, W1 = 0xBB67AE8584CAA73Bull;
@@ -793,7 +807,7 @@ __device__ inline void philox4x64(uint64_t c[4], uint64_t k0, uint64_t k1) {
     uint64_t lo0, hi0, lo1, hi1;
     mul64(M0, c[0], &lo0, &hi0);
     mul64(M1, c[2], &lo1, &hi1);
-    const uint64_t n0 = hi1 ^ c[1] ^ k0, n2 = hi0 ^ c[3] ^ k1;
+    const uint64_t n0 = xor3(hi1, c[1], k0), n2 = xor3(hi0, c[3], k1);
     c[0] = n0;
     c[1] = lo1;
     c[2] = n2;
@@ -806,6 +820,11 @@ __device__ inline void philox4x64(uint64_t c[4], uint64_t k0, uint64_t k1) {
 __device__ inline void draw4(uint64_t seed, uint64_t path, uint64_t frame, uint64_t vertex, uint64_t tag,
                              float u[4]) {
   uint64_t c[4] = {path, frame, vertex, tag};
+  // the round keys follow from the uniform seed by scalar additions; kept from
+  // being computed ahead of a caller's loop, where they would spill
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+s"(seed));
+#endif
   philox4x64(c, seed, 0);
 #pragma unroll
   for (int i = 0; i < 4; ++i) u[i] = (float)(uint32_t)(c[i] >> 40) * (1.0f / 16777216.0f);

@@ -989,7 +989,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
             float tmax;
             r = segment_ray(a, b, S->eps_end, &tmax);
             const BoxRay br = segment_box_ray(a, b, S->eps_end);
-            qb = world_slab(*S, a, br.inv);
+            qb = world_slab(*S, a, br.inv, r.tmin);
             int32_t root = G(S->wtop)[1];
             if (kSingle && !vis) {
               // the objects whose boxes the segment reaches, from LDS: one
@@ -1021,7 +1021,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
                                      mi[6] * tb.x + mi[7] * tb.y + mi[8] * tb.z);
                 const float3 od = sub(ob, oa);
                 const float3 binv = rcp3(od);
-                qb = make_slab(binv, f3(-(oa.x * binv.x), -(oa.y * binv.y), -(oa.z * binv.z)), S->qinv);
+                qb = make_slab(binv, f3(-(oa.x * binv.x), -(oa.y * binv.y), -(oa.z * binv.z)), S->qinv, r.tmin);
                 root = moroot[only];
               }
             }
@@ -1735,7 +1735,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
     // ---- walk; the box-test parameters follow from the ray, a few
     // instructions beside the walk's thousands, and hold no registers outside
     if (tracing) {
-      const Slab q = world_slab(S, ray_origin(r), rcp3(r.d));
+      const Slab q = world_slab(S, ray_origin(r), rcp3(r.d), r.tmin);
       walk_run<true>(G(S.wide), G(S.tris), r, q, any, col, limit, wk, min_active);
     }
     // ---- lanes whose walk is finished advance their path.  What several
