@@ -223,8 +223,8 @@ pv_status pv_update_lights(pv_ctx* ctx, uint32_t n, const uint32_t* d_light_ids,
  * light against every triangle of the moved objects (two-sided, hit strictly
  * inside (eps_end, L-eps_end)), a segment also being invalid when its end
  * photon lies on a moved object; the first invalid segment k gives replace=1,
- * start=k, reuse_light=1.  The store's info and origin are rewritten, and the
- * per-block counts of replaced paths are left for pv_build_queue. */
+ * start=k, reuse_light=1.  The store's info and origin are rewritten; the
+ * replaced paths are left for pv_build_queue. */
 pv_status pv_verify_paths(pv_ctx* ctx, const pv_path_store* store, pv_stats* d_stats);
 
 /* Section 4 (pruned-paths array, here the re-trace work list): compact the

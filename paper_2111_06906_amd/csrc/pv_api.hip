@@ -59,18 +59,15 @@ struct pv_ctx {
   SceneDev hs{};               // host image of the descriptor
   SceneDev* d_scene = nullptr; // device descriptor (one entry)
   uint32_t* d_state = nullptr; // first-frame flag
-  uint2* d_obj_tiles = nullptr;  // (scene, object) for the object update kernel
-  uint32_t n_obj_tiles = 0;
-  uint2* d_xf_tiles = nullptr;   // (scene << 8 | object, first triangle) for the transform kernel
-  uint32_t n_xf_tiles = 0;
-  const float** d_in_ptrs = nullptr;  // [2]: object / light transform inputs of the frame
+  uint2* d_place_tiles = nullptr;  // tiles of the frame's beginning (launch_frame_begin)
+  uint2* d_refit_tiles = nullptr;
+  uint32_t n_place_tiles = 0, n_refit_tiles = 0;
   // transforms of the next frame, written sparsely by pv_update_transforms /
   // pv_update_lights (and densely by pv_frame_begin); a pending update begins
   // the frame at the next call that reads the scene
   float *d_obj_staged = nullptr, *d_light_staged = nullptr;
   bool xf_pending = false;
   uint32_t n_materials = 0, n_lights = 0, n_objects = 0;
-  std::vector<uint32_t> h_obj_tris;  // triangles per object
   uint32_t stack_entries = 2;  // traversal stack per lane: whole-scene queries
   uint32_t stack_moved = 2;    // traversal stack per lane: queries against the moved objects
   // deepest leaves: static world, upload-time object topologies, rebuilt
@@ -130,8 +127,9 @@ struct pv_batch {
   uint32_t n = 0;
   Alloc mem;
   SceneDev* d_scenes = nullptr;
-  uint2 *d_path_tiles = nullptr, *d_obj_tiles = nullptr, *d_xf_tiles = nullptr;
-  uint32_t n_path_tiles = 0, n_obj_tiles = 0, n_xf_tiles = 0;
+  uint2 *d_path_tiles = nullptr, *d_place_tiles = nullptr, *d_refit_tiles = nullptr;
+  uint32_t n_path_tiles = 0, n_place_tiles = 0, n_refit_tiles = 0;
+  bool pyramid = false;  // a scene has pyr_full set
   uint32_t *d_queue = nullptr, *d_qcount = nullptr,
            *d_gbase = nullptr, *d_pcounts = nullptr, *d_poffsets = nullptr, *d_ptotal = nullptr, *d_pbase = nullptr,
            *d_frame = nullptr, *d_scan_tmp = nullptr;
@@ -634,12 +632,12 @@ std::vector<uint2> make_tiles(uint32_t scene, uint32_t n) {
 
 uint32_t path_blocks(uint32_t n) { return (n + pv::kBlock - 1) / pv::kBlock; }
 
-// transform tiles of a scene's objects: (scene << 8 | object, first triangle)
-std::vector<uint2> xf_tiles(uint32_t scene, const uint32_t* obj_tris, uint32_t n_objects) {
-  std::vector<uint2> t;
-  for (uint32_t o = 0; o < n_objects; ++o)
-    for (uint32_t f = 0; f < obj_tris[o]; f += pv::kBlock) t.push_back(make_uint2((scene << 8) | o, f));
-  return t;
+// tiles of a scene's frame beginning: dynamic triangles and object nodes
+void frame_tiles(uint32_t scene, uint32_t n_dyn, uint32_t n_obj_nodes, std::vector<uint2>& place,
+                 std::vector<uint2>& refit) {
+  for (uint32_t f = 0; f < n_dyn; f += pv::kBlock) place.push_back(make_uint2(scene, f));
+  refit.push_back(make_uint2(scene, pv::kSlotNone));
+  for (uint32_t f = 0; f < n_obj_nodes; f += pv::kBlock) refit.push_back(make_uint2(scene, f));
 }
 
 // grid of the verification traversal kernel (persistent, grid-stride)
@@ -991,7 +989,6 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     std::vector<ObjDev> objs(d->n_objects);
     std::vector<float> dlocal(9 * n_dyn);
     std::vector<uint32_t> dgid(n_dyn);
-    std::vector<uint32_t> level_nodes, level_off;
     std::vector<uint4> dspan;          // per object node: its children's record ranges
     std::vector<uint32_t> dspan_obj;   // and its object
     std::vector<Wide> owide;           // the objects' four-wide topologies with object-space boxes
@@ -1010,23 +1007,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         return c >= 0 ? c + (int32_t)node_base
                       : pv::leaf_code(pv::leaf_first(c) + S + tri_base, pv::leaf_count(c));
       };
-      // depth of every internal node (parents precede children in the node order)
-      std::vector<uint32_t> depth(hb.nodes.size(), 0);
-      uint32_t maxd = 0;
-      for (size_t i = 0; i < hb.nodes.size(); ++i) {
-        int32_t par = hb.parent[i];
-        depth[i] = par < 0 ? 0 : depth[par >> 1] + 1;
-        maxd = std::max(maxd, depth[i]);
-      }
       ObjDev& ob = objs[o];
-      ob.lvl_base = (uint32_t)level_off.size();
-      ob.n_levels = hb.nodes.empty() ? 0 : maxd + 1;
-      for (int64_t lv = (int64_t)maxd; lv >= 0 && !hb.nodes.empty(); --lv) {
-        level_off.push_back((uint32_t)level_nodes.size());
-        for (size_t i = 0; i < hb.nodes.size(); ++i)
-          if (depth[i] == (uint32_t)lv) level_nodes.push_back(node_base + (uint32_t)i);
-      }
-      level_off.push_back((uint32_t)level_nodes.size());
       for (Node nd : hb.nodes) {
         nd.d.x = rebase(nd.d.x);
         nd.d.y = rebase(nd.d.y);
@@ -1111,7 +1092,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     Wide* d_wide;
     Tri* d_tris;
     float* d_dlocal;
-    uint32_t *d_dgid, *d_lnodes, *d_loff;
+    uint32_t* d_dgid;
     ObjDev* d_objs;
     CK(upload(A, &d_nodes, nodes.data(), nodes.size(), s));
     CK(upload(A, &d_wide, wide.data(), wide.size(), s));
@@ -1139,8 +1120,6 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       CK(upload(A, &d_rmat, rmat.data(), rmat.size(), s));
       hs.rec_mat = d_rmat;
     }
-    CK(upload(A, &d_lnodes, level_nodes.data(), level_nodes.size(), s));
-    CK(upload(A, &d_loff, level_off.data(), level_off.size(), s));
     CK(upload(A, &d_objs, objs.data(), objs.size(), s));
     hs.obj_node_first = obj_node_first;
     hs.n_obj_nodes = (uint32_t)dspan.size();
@@ -1174,14 +1153,15 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       lw.n_dyn = nd;
       lw.first_node = lbvh_first;
       lw.n_nodes = lbvh_nodes;
+      hs.pyr = lw.pyr;
+      hs.n_dyn = nd;
+      hs.pyr_full = *std::max_element(d->h_obj_tris, d->h_obj_tris + d->n_objects) > pv::kLinearTris ? 1u : 0u;
     }
     hs.nodes = d_nodes;
     hs.wide = d_wide;
     hs.tris = d_tris;
     hs.dlocal = d_dlocal;
     hs.dtri_gid = d_dgid;
-    hs.dlevel_nodes = d_lnodes;
-    hs.dlevel_off = d_loff;
     hs.objs = d_objs;
     hs.n_obj = d->n_objects;
     hs.n_dyn_tris = (uint32_t)n_dyn;
@@ -1223,14 +1203,12 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     uint32_t one = 1;
     CK(hipMemcpyAsync(ctx->d_state, &one, 4, hipMemcpyHostToDevice, s));
     CK(hipMemcpyAsync(ctx->d_scene, &hs, sizeof(hs), hipMemcpyHostToDevice, s));
-    std::vector<uint2> ot;
-    for (uint32_t o = 0; o < d->n_objects; ++o) ot.push_back(make_uint2(0, o));
-    CK(upload(A, &ctx->d_obj_tiles, ot.data(), ot.size(), s));
-    ctx->n_obj_tiles = (uint32_t)ot.size();
-    std::vector<uint2> xt = xf_tiles(0, d->h_obj_tris, d->n_objects);
-    CK(upload(A, &ctx->d_xf_tiles, xt.data(), xt.size(), s));
-    ctx->n_xf_tiles = (uint32_t)xt.size();
-    CK(dalloc(A, &ctx->d_in_ptrs, 2));
+    std::vector<uint2> place, refit;
+    frame_tiles(0, (uint32_t)n_dyn, hs.n_obj_nodes, place, refit);
+    CK(upload(A, &ctx->d_place_tiles, place.data(), place.size(), s));
+    CK(upload(A, &ctx->d_refit_tiles, refit.data(), refit.size(), s));
+    ctx->n_place_tiles = (uint32_t)place.size();
+    ctx->n_refit_tiles = (uint32_t)refit.size();
     // staged transforms start as identities (every object and light moves at
     // the first frame anyway); the host copy lives until the synchronisation
     const float id12[12] = {1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0};
@@ -1244,7 +1222,6 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     ctx->n_materials = d->n_materials;
     ctx->n_lights = d->n_lights;
     ctx->n_objects = d->n_objects;
-    ctx->h_obj_tris.assign(d->h_obj_tris, d->h_obj_tris + d->n_objects);
     // the whole-scene top-level tree: the static root beside a median split
     // of the objects (or either alone); the moved-object tree: a median split
     ctx->top_depth = S && d->n_objects ? 1u + ceil_log2(d->n_objects) : ceil_log2(d->n_objects);
@@ -1348,31 +1325,25 @@ namespace {
 // are NULL): moved flags, world triangles of the moved objects, their boxes,
 // the top-level trees.
 pv_status begin_frame(pv_ctx* ctx, const float* d_obj_xf, const float* d_light_xf) {
+  pv::FrameInput in{d_obj_xf, d_light_xf, nullptr, nullptr, nullptr, nullptr};
   if (!d_obj_xf && !d_light_xf) {
-    d_obj_xf = ctx->d_obj_staged;
-    d_light_xf = ctx->d_light_staged;
+    in.obj = ctx->d_obj_staged;
+    in.light = ctx->d_light_staged;
   } else {
     // the staged arrays follow the dense ones, for later sparse updates
-    if (ctx->n_objects)
-      CK(hipMemcpyAsync(ctx->d_obj_staged, d_obj_xf, 48 * (size_t)ctx->n_objects, hipMemcpyDeviceToDevice,
-                        ctx->stream));
-    CK(hipMemcpyAsync(ctx->d_light_staged, d_light_xf, 48 * (size_t)ctx->n_lights, hipMemcpyDeviceToDevice,
-                      ctx->stream));
+    in.obj_staged = ctx->d_obj_staged;
+    in.light_staged = ctx->d_light_staged;
   }
   ctx->xf_pending = false;
-  const float* in[2] = {d_obj_xf, d_light_xf};
-  CK(hipMemcpyAsync(ctx->d_in_ptrs, in, sizeof(in), hipMemcpyHostToDevice, ctx->stream));
-  CK(pv::launch_frame_begin(ctx->d_scene, 1, ctx->d_in_ptrs, ctx->d_in_ptrs + 1, ctx->stream));
-  // world triangles of the moved objects, then their topologies' boxes as
-  // unions over leaf-order ranges
-  CK(pv::launch_transform_objects(ctx->d_scene, ctx->d_xf_tiles, ctx->n_xf_tiles, ctx->stream));
-  CK(pv::launch_refit_objects(ctx->d_scene, ctx->lw, ctx->n_objects, ctx->hs.n_obj_nodes, ctx->stream));
+  CK(pv::launch_frame_begin(ctx->d_scene, 1, ctx->d_place_tiles, ctx->n_place_tiles, ctx->d_refit_tiles,
+                            ctx->n_refit_tiles, in, ctx->hs.pyr_full != 0, !ctx->object_rebuild, ctx->stream));
   // rebuild mode: every object's hierarchy rebuilt from its current
   // triangles; the refit topology (kept current above) stays the hierarchy of
   // an object whose rebuilt tree is too deep for the traversal stacks
-  if (ctx->object_rebuild)
+  if (ctx->object_rebuild) {
     CK(pv::launch_rebuild_objects(ctx->d_scene, ctx->lw, ctx->n_objects, ctx->lbvh_depth, ctx->stream));
-  CK(pv::launch_build_top(ctx->d_scene, 1, ctx->stream));
+    CK(pv::launch_build_top(ctx->d_scene, 1, ctx->stream));
+  }
   ctx->frame_started = true;
   return PV_OK;
 }
@@ -1985,17 +1956,9 @@ static pv_status batch_enqueue(pv_batch* b, pv_stats* d_stats, const float* cons
                                const float* const* light_in, const uint32_t* frame_ptr) {
   pv_ctx* ctx = b->owner;
   hipStream_t st = b->cap_stream;
-  CK(pv::launch_frame_begin(b->d_scenes, (int)b->n, obj_in, light_in, st));
-  if (b->n == 1) {
-    // one scene (its context is the owner): the plain frame's refit, the
-    // topologies' boxes as unions over leaf-order ranges, with many more
-    // threads than the per-object level-by-level refit and the same boxes
-    CK(pv::launch_transform_objects(b->d_scenes, b->d_xf_tiles, b->n_xf_tiles, st));
-    CK(pv::launch_refit_objects(b->d_scenes, ctx->lw, ctx->n_objects, ctx->hs.n_obj_nodes, st));
-  } else {
-    CK(pv::launch_update_objects(b->d_scenes, b->d_obj_tiles, b->n_obj_tiles, b->d_xf_tiles, b->n_xf_tiles, st));
-  }
-  CK(pv::launch_build_top(b->d_scenes, (int)b->n, st));
+  const pv::FrameInput in{nullptr, nullptr, obj_in, light_in, nullptr, nullptr};
+  CK(pv::launch_frame_begin(b->d_scenes, (int)b->n, b->d_place_tiles, b->n_place_tiles, b->d_refit_tiles,
+                            b->n_refit_tiles, in, b->pyramid, true, st));
   CK(pv::launch_verify(b->d_scenes, b->d_path_tiles, b->n_path_tiles, b->d_gbase, (int)b->n, b->vw,
                        d_stats, b->stack_moved, verify_blocks(ctx), (uint32_t)ctx->n_cu, ctx->verify_min_active, b->d_scan_tmp, st));
   // distribution maps: compute DM_C, prune, fill, scene by scene
@@ -2029,7 +1992,7 @@ pv_status pv_batch_create(pv_batch** out, pv_ctx* const* contexts, const pv_path
     b->seed = seed;
     b->retrace_blocks = (uint32_t)ctx->n_cu * 8;
     std::vector<SceneDev> table(n);
-    std::vector<uint2> ptiles, otiles, xtiles;
+    std::vector<uint2> ptiles, place, refit;
     std::vector<uint32_t> gbase(n + 1, 0);
     uint64_t total_paths = 0, counts = 0, cap = 0, task_cap = 0;
     for (uint32_t i = 0; i < n; ++i) {
@@ -2073,8 +2036,8 @@ pv_status pv_batch_create(pv_batch** out, pv_ctx* const* contexts, const pv_path
         b->dms.push_back(pv_batch::Dm{i, hs.tile_base, hs.n_blocks, c->dm_cells, c->n_lights, pv::DmWork{}});
       gbase[i] = (uint32_t)total_paths;
       for (uint2 t : make_tiles(i, st->n_paths)) ptiles.push_back(t);
-      for (uint32_t o = 0; o < c->n_objects; ++o) otiles.push_back(make_uint2(i, o));
-      for (uint2 t : xf_tiles(i, c->h_obj_tris.data(), c->n_objects)) xtiles.push_back(t);
+      frame_tiles(i, hs.n_dyn, hs.n_obj_nodes, place, refit);
+      b->pyramid |= hs.pyr_full != 0;
       total_paths += st->n_paths;
       counts += (uint64_t)hs.n_blocks * st->max_bounces;
       cap += (uint64_t)st->n_paths * st->max_bounces;
@@ -2090,8 +2053,8 @@ pv_status pv_batch_create(pv_batch** out, pv_ctx* const* contexts, const pv_path
     auto chk = [&](hipError_t e) { return e == hipSuccess; };
     const uint32_t chunks = pv::queue_chunks((uint32_t)ptiles.size());
     bool ok = chk(upload(A, &b->d_scenes, table.data(), n, s)) && chk(upload(A, &b->d_path_tiles, ptiles.data(), ptiles.size(), s)) &&
-              chk(upload(A, &b->d_obj_tiles, otiles.data(), otiles.size(), s)) &&
-              chk(upload(A, &b->d_xf_tiles, xtiles.data(), xtiles.size(), s)) &&
+              chk(upload(A, &b->d_place_tiles, place.data(), place.size(), s)) &&
+              chk(upload(A, &b->d_refit_tiles, refit.data(), refit.size(), s)) &&
               chk(upload(A, &b->d_gbase, gbase.data(), gbase.size(), s)) &&
               chk(dalloc(A, &b->d_queue, total_paths)) && chk(dalloc(A, &b->d_qcount, 1)) &&
               chk(dalloc(A, &b->d_pcounts, counts)) &&
@@ -2130,8 +2093,8 @@ pv_status pv_batch_create(pv_batch** out, pv_ctx* const* contexts, const pv_path
       return fail(ctx, PV_ERR_HIP, "batch stream/event creation failed");
     }
     b->n_path_tiles = (uint32_t)ptiles.size();
-    b->n_obj_tiles = (uint32_t)otiles.size();
-    b->n_xf_tiles = (uint32_t)xtiles.size();
+    b->n_place_tiles = (uint32_t)place.size();
+    b->n_refit_tiles = (uint32_t)refit.size();
     b->n_counts = (uint32_t)counts;
     b->capacity = (uint32_t)cap;
     *out = b;

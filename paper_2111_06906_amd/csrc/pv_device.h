@@ -148,16 +148,14 @@ struct ObjDev {
   uint32_t tri_base;   // first record of the object in the object-space vertex arrays
   uint32_t node_base;  // first node of its hierarchy in the scene's node array
   uint32_t n_nodes;    // internal nodes of its hierarchy
-  uint32_t lvl_base;   // first entry of its level offsets (n_levels + 1 entries)
   int32_t root;        // root child code in the scene's node / triangle arrays (current hierarchy)
-  uint32_t n_levels;   // depth levels holding internal nodes
   int32_t sah_root;    // root of the upload-time topology (refit each frame)
   uint32_t lbvh_base;  // first node of its region for the per-frame rebuilt radix tree
   int32_t oroot;       // root of the four-wide upload-time topology with object-space boxes
   int32_t wroot;       // root of the current hierarchy's four-wide form
   int32_t sah_wroot;   // the same of the upload-time topology
   uint32_t lbvh_wbase; // first four-wide node of its region for the rebuilt radix tree
-  uint32_t pad_;
+  uint32_t pad_[3];
 };
 
 struct LightDev {
@@ -201,8 +199,9 @@ struct SceneDev {
   // dynamic objects
   const float* dlocal;    // [n][9] object-space vertices in leaf order
   const uint32_t* dtri_gid;  // [n] global id of each leaf-order triangle
-  const uint32_t* dlevel_nodes;  // internal nodes of each object, deepest level first
-  const uint32_t* dlevel_off;    // per object: offsets of its levels in dlevel_nodes
+  float4* pyr;            // pyramid of box unions over the dynamic triangles (as LbvhWork's)
+  uint32_t n_dyn;         // dynamic triangles
+  uint32_t pyr_full;      // 1: an object's ranges need the pyramid above its low levels
   const ObjDev* objs;
   uint32_t n_obj;
   uint32_t n_dyn_tris;

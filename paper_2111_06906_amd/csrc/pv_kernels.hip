@@ -1,10 +1,7 @@
 // HIP kernels of the path-verification hot path (gfx950).
 //
-//   k_frame_begin   moved flags for objects / lights, transform history
-//   k_update_objects  per moved object: world-space triangles (FP64 fma chain
-//                   -> FP32) and level-by-level box refit of its hierarchy
-//   k_verify        Section 3.1 origin update + Section 3.2 dynamic occlusions,
-//                   first invalid segment, per-block replace counts
+//   k_verify_*      Section 3.1 origin update + Section 3.2 dynamic occlusions,
+//                   first invalid segment
 //   k_scan          exclusive scan of per-block counts (single block)
 //   k_queue_hist / k_queue_scatter   stable re-trace work queue and its order
 //   k_mark_all      full invalidation (baseline / frame 0)
@@ -28,46 +25,6 @@ __device__ inline unsigned long long block_sum_u64(unsigned long long v, unsigne
   for (int w = 0; w < kBlock / 64; ++w) t += sh[w];
   __syncthreads();
   return t;
-}
-
-// ---------------------------------------------------------------------------
-// frame begin: one thread per (scene, object) and per (scene, light)
-
-__global__ void k_frame_begin(SceneDev* scenes, int n_scenes, const float* const* obj_in,
-                              const float* const* light_in) {
-  int s = blockIdx.x;
-  if (s >= n_scenes) return;
-  SceneDev& S = scenes[s];
-  const uint32_t first = S.state[0];
-  for (uint32_t o = threadIdx.x; o < S.n_obj; o += blockDim.x) {
-    const float* nw = obj_in[s] + 12 * o;
-    float* cur = S.obj_xf_cur + 12 * o;
-    float* prev = S.obj_xf_prev + 12 * o;
-    uint32_t moved = first;
-    for (int i = 0; i < 12; ++i) {
-      float c = cur[i], n = nw[i];
-      moved |= (__float_as_uint(c) != __float_as_uint(n)) ? 1u : 0u;
-      prev[i] = c;
-      cur[i] = n;
-    }
-    S.obj_moved[o] = moved;
-  }
-  for (uint32_t l = threadIdx.x; l < S.n_lights; l += blockDim.x) {
-    const float* nw = light_in[s] + 12 * l;
-    float* cur = S.light_xf_cur + 12 * l;
-    float* prev = S.light_xf_prev + 12 * l;
-    uint32_t moved = 0;  // a light's first placement does not invalidate anything
-    if (!first) {
-      for (int i = 0; i < 12; ++i) moved |= (__float_as_uint(cur[i]) != __float_as_uint(nw[i])) ? 1u : 0u;
-    }
-    for (int i = 0; i < 12; ++i) {
-      prev[i] = cur[i];
-      cur[i] = nw[i];
-    }
-    S.light_moved[l] = moved;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) S.state[0] = 0;
 }
 
 // ---------------------------------------------------------------------------
@@ -95,300 +52,6 @@ hipError_t launch_scatter_xf(float* dst, uint32_t n_rows, const uint32_t* ids, c
   if (n > 64) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_scatter_xf, dim3(1), dim3(64), 0, s, dst, n_rows, ids, m, n);
   return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------
-// per moved object, one workgroup: world-space triangles (FP64 fma chain
-// rounded to FP32), then the hierarchy's boxes level by level from the
-// deepest internal nodes up (the topology, fixed for a rigid object, was
-// built at upload), then the object's box.  No atomics: levels are separated
-// by workgroup barriers.
-
-__device__ inline float xform_coord(const float* m, int r, float x, float y, float z) {
-  double v = fma((double)m[4 * r + 0], (double)x,
-                 fma((double)m[4 * r + 1], (double)y, fma((double)m[4 * r + 2], (double)z, (double)m[4 * r + 3])));
-  return (float)v;
-}
-
-__device__ inline float pad_lo(float x) { return x - (1e-6f + fabsf(x) * 1e-6f); }
-__device__ inline float pad_hi(float x) { return x + (1e-6f + fabsf(x) * 1e-6f); }
-
-// box (lo xyz, hi xyz) of a child: a leaf's padded triangle box, or the union
-// of an internal node's two child boxes
-__device__ inline void child_box(const SceneDev& S, int32_t code, float* b) {
-  if (code < 0) {
-    uint32_t f = leaf_first(code), n = leaf_count(code);
-    float lo[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
-    float hi[3] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-    for (uint32_t i = f; i < f + n; ++i) {
-      const Tri t = S.tris[i];
-      for (int k = 0; k < 3; ++k)
-        for (int c = 0; c < 3; ++c) {
-          lo[c] = fminf(lo[c], t.v[k][c]);
-          hi[c] = fmaxf(hi[c], t.v[k][c]);
-        }
-    }
-    for (int k = 0; k < 3; ++k) {
-      b[k] = pad_lo(lo[k]);
-      b[3 + k] = pad_hi(hi[k]);
-    }
-  } else {
-    const Node nd = S.nodes[code];
-    const float* f = reinterpret_cast<const float*>(&nd);
-    for (int k = 0; k < 3; ++k) {
-      b[k] = fminf(f[k], f[6 + k]);
-      b[3 + k] = fmaxf(f[3 + k], f[9 + k]);
-    }
-  }
-}
-
-// world-space triangles of moved objects: one thread per triangle; a tile is
-// (scene << 8 | object, first triangle of the object) for kBlock triangles
-__global__ __launch_bounds__(kBlock) void k_transform(SceneDev* scenes, const uint2* tiles) {
-  const uint2 tile = tiles[blockIdx.x];
-  SceneDev& S = scenes[tile.x >> 8];
-  const uint32_t o = tile.x & 0xffu;
-  if (!S.obj_moved[o]) return;
-  const ObjDev ob = S.objs[o];
-  const uint32_t i = tile.y + threadIdx.x;
-  if (i < ob.n_tris) {
-    const float* m = S.obj_xf_cur + 12 * o;
-    uint32_t rec = ob.tri_base + i;
-    const float* v = S.dlocal + 9 * (size_t)rec;
-    float w[9];
-#pragma unroll
-    for (int k = 0; k < 3; ++k)
-#pragma unroll
-      for (int r = 0; r < 3; ++r) w[3 * k + r] = xform_coord(m, r, v[3 * k], v[3 * k + 1], v[3 * k + 2]);
-    S.tris[S.n_static + rec] = make_tri(w, S.dtri_gid[rec]);
-  }
-}
-
-// per moved object, one workgroup: the hierarchy's boxes level by level from
-// the deepest internal nodes up, then the object's box
-constexpr int kRefitBlock = 1024;  // the deepest levels of an object hold thousands of nodes
-
-__global__ __launch_bounds__(kRefitBlock) void k_update_objects(SceneDev* scenes, const uint2* tiles) {
-  uint2 tile = tiles[blockIdx.x];
-  SceneDev& S = scenes[tile.x];
-  const uint32_t o = tile.y;
-  if (!S.obj_moved[o]) return;
-  const ObjDev ob = S.objs[o];
-  const uint32_t* off = S.dlevel_off + ob.lvl_base;
-  const PlaneWriter wide(S);
-  for (uint32_t lv = 0; lv < ob.n_levels; ++lv) {
-    const uint32_t e = off[lv + 1];
-    for (uint32_t i = off[lv] + threadIdx.x; i < e; i += blockDim.x) {
-      Node* nd = S.nodes + S.dlevel_nodes[i];
-      int4 ch = nd->d;
-      float b[12];
-      child_box(S, ch.x, b);
-      child_box(S, ch.y, b + 6);
-      nd->a = make_float4(b[0], b[1], b[2], b[3]);
-      nd->b = make_float4(b[4], b[5], b[6], b[7]);
-      nd->c = make_float4(b[8], b[9], b[10], b[11]);
-      const uint2 ws = S.wslot[S.dlevel_nodes[i] - S.obj_node_first];
-      if (ws.x != kSlotNone) wide.put(ws.x, b[0], b[1], b[2], b[3], b[4], b[5]);
-      if (ws.y != kSlotNone) wide.put(ws.y, b[6], b[7], b[8], b[9], b[10], b[11]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    float b[6];
-    child_box(S, ob.sah_root, b);
-    for (int k = 0; k < 6; ++k) S.obj_aabb[6 * o + k] = b[k];
-    const_cast<ObjDev*>(S.objs)[o].root = ob.sah_root;  // the refit topology is the current one
-    const_cast<ObjDev*>(S.objs)[o].wroot = ob.sah_wroot;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// top-level trees, rebuilt each frame once the object boxes are current: one
-// over the static root and every object root, one over the moved objects
-// only (the set that verification and the walk's clearance tests query).
-// The objects of a tree are split at their median along the widest axis of
-// their box centres, recursively; the static hierarchy, whose box spans the
-// scene and would widen every node above it, is the root's first child
-// (nearly every query enters the static side first).  One wave per tree, one
-// lane per position of the item order, one level of the recursion per step:
-// every range of the level is stably sorted by rank along its own axis, at
-// once.  A range [lo, hi) splits at mid = (lo + hi) / 2, and each split
-// position belongs to exactly one range, so node mid - 1 of the tree's block
-// holds that range (node n - 1 the root above the static hierarchy).  Sorting
-// only permutes a range's own items, so all nodes are written once the order
-// is final, lane mid - 1 writing its range's from the range's four quarters:
-// the binary node from the halves, and, for the ranges of every second level,
-// the four-wide node from the quarters (of the scene's root from the static
-// hierarchy and the halves).
-
-constexpr int kTopLevels = kTopDepth - 1;  // median levels over <= PV_MAX_OBJECTS objects
-
-__global__ __launch_bounds__(128) void k_build_top(SceneDev* scenes) {
-  static_assert(PV_MAX_OBJECTS <= 64, "one lane per object");
-  static_assert((1 << kTopLevels) >= PV_MAX_OBJECTS, "median levels");
-  __shared__ float sbx[2][2][6][64];  // [tree][buffer][box component][position]
-  __shared__ int2 scode[2][2][64];    // (binary, four-wide) root codes
-  SceneDev& S = scenes[blockIdx.x];
-  const int which = threadIdx.x >> 6;  // tree of this wave
-  const uint32_t lane = threadIdx.x & 63u;
-  const PlaneWriter wide(S);
-  PV_GLOBAL Node* nodes = G(S.nodes);
-  float sbox[6];
-  for (int k = 0; k < 6; ++k) sbox[k] = S.sbox[k];
-  // items of the tree in object order (moved objects compacted by ballot)
-  const bool have = lane < S.n_obj;
-  const bool take = have && (which == 0 || S.obj_moved[lane] != 0);
-  const uint64_t mm = __ballot(take);
-  const uint32_t n = (uint32_t)__popcll(mm);
-  if (take) {
-    const uint32_t i = (uint32_t)__popcll(mm & lanemask_lt());
-    for (int k = 0; k < 6; ++k) sbx[which][0][k][i] = S.obj_aabb[6 * lane + k];
-    scode[which][0][i] = make_int2(S.objs[lane].root, S.objs[lane].wroot);
-  }
-  __syncthreads();
-  uint32_t lo = 0, hi = n;  // range of this lane's position
-  int buf = 0;
-  for (int level = 0; level < kTopLevels; ++level) {
-    const float(*bx)[64] = sbx[which][buf];
-    const bool live = lane < n && hi - lo >= 2;
-    uint32_t dst = lane;
-    if (live) {
-      // widest axis of the range's box centres
-      float clo[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
-      float chi[3] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-      for (uint32_t q = lo; q < hi; ++q)
-        for (int k = 0; k < 3; ++k) {
-          const float c = 0.5f * (bx[k][q] + bx[3 + k][q]);
-          clo[k] = fminf(clo[k], c);
-          chi[k] = fmaxf(chi[k], c);
-        }
-      int ax = 0;
-      for (int k = 1; k < 3; ++k)
-        if (chi[k] - clo[k] > chi[ax] - clo[ax]) ax = k;
-      // stable rank along that axis
-      const float mine = 0.5f * (bx[ax][lane] + bx[3 + ax][lane]);
-      uint32_t rank = 0;
-      for (uint32_t q = lo; q < hi; ++q) {
-        const float c = 0.5f * (bx[ax][q] + bx[3 + ax][q]);
-        rank += (c < mine || (c == mine && q < lane)) ? 1u : 0u;
-      }
-      dst = lo + rank;
-    }
-    float mb[6];
-    for (int k = 0; k < 6; ++k) mb[k] = bx[k][lane];
-    const int2 mc = scode[which][buf][lane];
-    if (lane < n) {
-      for (int k = 0; k < 6; ++k) sbx[which][buf ^ 1][k][dst] = mb[k];
-      scode[which][buf ^ 1][dst] = mc;
-    }
-    __syncthreads();
-    buf ^= 1;
-    if (live) {
-      const uint32_t mid = (lo + hi) / 2;
-      if (lane < mid) hi = mid;
-      else lo = mid;
-    }
-  }
-  const float(*bx)[64] = sbx[which][buf];
-  const int2* code = scode[which][buf];
-  const int32_t sroot = S.sroot, swroot = S.swroot;
-  const bool above = which == 0 && sroot != kRootNone;  // the static hierarchy beside the objects
-  const uint32_t first = S.top_base + (uint32_t)which * kTopNodes;
-  const uint32_t wfirst = S.wtop_base + (uint32_t)which * kTopNodes;
-  // root codes of a range of one or more items (its node's index is its split position - 1)
-  auto bin = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].x : (int32_t)(first + (a + b) / 2 - 1); };
-  auto wid = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].y : (int32_t)(wfirst + (a + b) / 2 - 1); };
-  if (lane + 1 < n) {
-    // the range that splits at lane + 1
-    uint32_t a = 0, b = n, depth = 0;
-    while ((a + b) / 2 != lane + 1) {
-      const uint32_t m = (a + b) / 2;
-      if (lane + 1 < m) b = m;
-      else a = m;
-      ++depth;
-    }
-    const uint32_t mid = lane + 1;
-    // quarters (a half of one item is its own first quarter)
-    const uint32_t q[5] = {a, mid - a == 1 ? mid : (a + mid) / 2, mid, b - mid == 1 ? b : (mid + b) / 2, b};
-    float bb[4][6];
-    for (int j = 0; j < 4; ++j) {
-      for (int k = 0; k < 3; ++k) {
-        bb[j][k] = __builtin_inff();
-        bb[j][3 + k] = -__builtin_inff();
-      }
-      for (uint32_t i = q[j]; i < q[j + 1]; ++i)
-        for (int k = 0; k < 3; ++k) {
-          bb[j][k] = fminf(bb[j][k], bx[k][i]);
-          bb[j][3 + k] = fmaxf(bb[j][3 + k], bx[3 + k][i]);
-        }
-    }
-    float cb[2][6];
-    for (int k = 0; k < 3; ++k)
-      for (int h = 0; h < 2; ++h) {
-        cb[h][k] = fminf(bb[2 * h][k], bb[2 * h + 1][k]);
-        cb[h][3 + k] = fmaxf(bb[2 * h][3 + k], bb[2 * h + 1][3 + k]);
-      }
-    PV_GLOBAL Node& nd = nodes[first + lane];
-    nd.a = make_float4(cb[0][0], cb[0][1], cb[0][2], cb[0][3]);
-    nd.b = make_float4(cb[0][4], cb[0][5], cb[1][0], cb[1][1]);
-    nd.c = make_float4(cb[1][2], cb[1][3], cb[1][4], cb[1][5]);
-    nd.d = make_int4(bin(a, mid), bin(mid, b), -1, 0);
-    if (((depth + (above ? 1u : 0u)) & 1u) == 0) {
-      const uint32_t w = 4 * (wfirst + lane);
-      for (int j = 0; j < 4; ++j) {
-        if (q[j] < q[j + 1]) {
-          wide.put(w + j, bb[j][0], bb[j][1], bb[j][2], bb[j][3], bb[j][4], bb[j][5]);
-          wide.child(w + j, wid(q[j], q[j + 1]));
-        } else {
-          wide.none(w + j);
-        }
-      }
-    }
-    if (above && depth == 0) {
-      // the scene's root: the static hierarchy and the halves of the objects
-      const uint32_t w = 4 * (wfirst + n - 1);
-      wide.put(w, sbox[0], sbox[1], sbox[2], sbox[3], sbox[4], sbox[5]);
-      wide.child(w, swroot);
-      for (int h = 0; h < 2; ++h) wide.put(w + 1 + h, cb[h][0], cb[h][1], cb[h][2], cb[h][3], cb[h][4], cb[h][5]);
-      wide.child(w + 1, wid(a, mid));
-      wide.child(w + 2, wid(mid, b));
-      wide.none(w + 3);
-    }
-  }
-  if (lane != 0) return;
-  // roots: the objects' tree, the single object, or none; the static
-  // hierarchy alone or above them
-  int32_t root = n == 0 ? kRootNone : bin(0, n), wroot = n == 0 ? kRootNone : wid(0, n);
-  if (above && n > 0) {
-    float ob[6] = {__builtin_inff(), __builtin_inff(), __builtin_inff(),
-                   -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-    for (uint32_t i = 0; i < n; ++i)
-      for (int k = 0; k < 3; ++k) {
-        ob[k] = fminf(ob[k], bx[k][i]);
-        ob[3 + k] = fmaxf(ob[3 + k], bx[3 + k][i]);
-      }
-    PV_GLOBAL Node& nd = nodes[first + n - 1];
-    nd.a = make_float4(sbox[0], sbox[1], sbox[2], sbox[3]);
-    nd.b = make_float4(sbox[4], sbox[5], ob[0], ob[1]);
-    nd.c = make_float4(ob[2], ob[3], ob[4], ob[5]);
-    nd.d = make_int4(sroot, root, -1, 0);
-    root = (int32_t)(first + n - 1);
-    if (n == 1) {
-      const uint32_t w = 4 * wfirst;
-      wide.put(w, sbox[0], sbox[1], sbox[2], sbox[3], sbox[4], sbox[5]);
-      wide.child(w, swroot);
-      wide.put(w + 1, ob[0], ob[1], ob[2], ob[3], ob[4], ob[5]);
-      wide.child(w + 1, wroot);
-      wide.none(w + 2);
-      wide.none(w + 3);
-    }
-    wroot = (int32_t)(wfirst + n - 1);
-  } else if (above) {
-    root = sroot;
-    wroot = swroot;
-  }
-  S.top[which] = root;
-  S.wtop[which] = wroot;
 }
 
 // ---------------------------------------------------------------------------
@@ -2285,32 +1948,6 @@ __global__ __launch_bounds__(kBlock) void k_energy_sum(const double* __restrict_
 
 // ---------------------------------------------------------------------------
 // launch wrappers (host side)
-
-hipError_t launch_frame_begin(SceneDev* scenes, int n_scenes, const float* const* obj_in,
-                              const float* const* light_in, hipStream_t s) {
-  hipLaunchKernelGGL(k_frame_begin, dim3(n_scenes), dim3(64), 0, s, scenes, n_scenes, obj_in, light_in);
-  return hipGetLastError();
-}
-
-hipError_t launch_update_objects(SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint2* xf_tiles,
-                                 uint32_t n_xf_tiles, hipStream_t s) {
-  if (!n_tiles) return hipSuccess;
-  hipLaunchKernelGGL(k_transform, dim3(n_xf_tiles), dim3(kBlock), 0, s, scenes, xf_tiles);
-  hipLaunchKernelGGL(k_update_objects, dim3(n_tiles), dim3(kRefitBlock), 0, s, scenes, tiles);
-  return hipGetLastError();
-}
-
-hipError_t launch_transform_objects(SceneDev* scenes, const uint2* xf_tiles, uint32_t n_xf_tiles, hipStream_t s) {
-  if (!n_xf_tiles) return hipSuccess;
-  hipLaunchKernelGGL(k_transform, dim3(n_xf_tiles), dim3(kBlock), 0, s, scenes, xf_tiles);
-  return hipGetLastError();
-}
-
-hipError_t launch_build_top(SceneDev* scenes, int n_scenes, hipStream_t s) {
-  if (n_scenes <= 0) return hipSuccess;
-  k_build_top<<<n_scenes, 128, 0, s>>>(scenes);
-  return hipGetLastError();
-}
 
 // the stack columns of a block, plus one spare entry below each column (a walk
 // whose sentinel was taken points there)

@@ -10,18 +10,26 @@ namespace pv {
 // entry of a repeated id wins, ids >= n_rows are skipped)
 hipError_t launch_scatter_xf(float* dst, uint32_t n_rows, const uint32_t* ids, const float* m, uint32_t n,
                              hipStream_t s);
-hipError_t launch_frame_begin(SceneDev* scenes, int n_scenes, const float* const* obj_in,
-                              const float* const* light_in, hipStream_t s);
-// moved objects: world triangles (xf_tiles: (scene << 8 | object, first
-// triangle) per kBlock triangles), then their hierarchies' boxes (tiles:
-// (scene, object))
-hipError_t launch_update_objects(SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint2* xf_tiles,
-                                 uint32_t n_xf_tiles, hipStream_t s);
-// world triangles of the moved objects only (xf_tiles as above)
-hipError_t launch_transform_objects(SceneDev* scenes, const uint2* xf_tiles, uint32_t n_xf_tiles, hipStream_t s);
-// boxes of the moved objects' upload-time topologies (one scene) as unions
-// over leaf-order ranges (the box pyramid of W), their object boxes and roots
-hipError_t launch_refit_objects(SceneDev* scenes, LbvhWork W, uint32_t n_obj, uint32_t n_obj_nodes, hipStream_t s);
+// A frame's transforms (rows of 12 floats): arrays of one scene, or device
+// tables with one array per scene (then not null); the staged copies to bring
+// up to date (null: none).
+struct FrameInput {
+  const float *obj, *light;
+  const float* const* obj_tab;
+  const float* const* light_tab;
+  float *obj_staged, *light_staged;
+};
+// dynamic triangles of one object up to which its boxes are found without the
+// pyramid's upper levels (SceneDev::pyr_full = 0)
+constexpr uint32_t kLinearTris = 16384;
+// The beginning of a frame: moved flags, transform history, the moved objects'
+// world triangles and boxes, and, with 'top', the top-level trees.
+// place_tiles: (scene, first record) per kBlock dynamic triangles;
+// refit_tiles: per scene (scene, kSlotNone), and (scene, first object node) per
+// kBlock of them; 'pyramid': a scene has pyr_full set.
+hipError_t launch_frame_begin(SceneDev* scenes, int n_scenes, const uint2* place_tiles, uint32_t n_place,
+                              const uint2* refit_tiles, uint32_t n_refit, const FrameInput& in, bool pyramid, bool top,
+                              hipStream_t s);
 // every object's hierarchy rebuilt from its current world triangles (one
 // scene): linear BVH over Morton codes, into the objects' rebuild regions; an
 // object whose tree is deeper than max_depth keeps its current hierarchy

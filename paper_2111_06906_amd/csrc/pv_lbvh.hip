@@ -30,6 +30,9 @@
 // never moved.  The boxes are the same unions of the same padded triangle
 // boxes that a bottom-up refit computes.
 #include "pv_launch.h"
+// The frame's beginning is here too: k_place (moved flags, world triangles,
+// low pyramid levels) and k_refit (the moved objects' boxes, transform
+// history, top-level trees).
 
 namespace pv {
 
@@ -129,10 +132,18 @@ __device__ inline void pyr_put(float4* pyr, uint32_t i, const Box& v) {
 // entries of four levels are loaded before any of them is joined, so their
 // loads are in flight together (min and max: the order of the joins does not
 // change the box).
-__device__ inline Box range_box(const float4* pyr, uint32_t n, uint32_t a, uint32_t b) {
+// Without 'full' the pyramid ends at level kLowLevels, whose entries are then
+// joined one after the other (at most kLinearTris / 256 of them).
+__device__ inline Box range_box(const float4* pyr, uint32_t n, uint32_t a, uint32_t b, bool full = true) {
+  static_assert(kLowLevels % 4 == 0, "levels are taken four at a time");
   Box r = empty_box();
   uint32_t off = 0, m = n;
-  while (a < b) {
+  for (int level = 0; a < b; level += 4) {
+    if (!full && level == kLowLevels) {
+#pragma unroll 8
+      for (uint32_t i = a; i < b; ++i) r = join(r, pyr_get(pyr, off + i));
+      break;
+    }
     Box e[8];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
@@ -299,20 +310,12 @@ __global__ __launch_bounds__(kSortThreads) void k_lbvh_scatter(const uint64_t* _
   }
 }
 
-// level 0 of the pyramid (padded triangle boxes in sorted order, or in record
-// order when val is null) and the levels 1..kLowLevels of each aligned
-// 256-position block
-__global__ __launch_bounds__(kBlock) void k_lbvh_leaves(const SceneDev* __restrict__ scenes, LbvhWork W,
-                                                        const uint32_t* __restrict__ val) {
+// level 0 of the pyramid, box b at position block * 256 + thread, and the
+// levels 1..kLowLevels of that aligned 256-position block
+__device__ inline void pyr_low(float4* pyr, uint32_t n, uint32_t block, Box b) {
   __shared__ float3 slo[kBlock], shi[kBlock];
-  const SceneDev& S = scenes[0];
-  const uint32_t n = W.n_dyn;
-  const uint32_t g = blockIdx.x * kBlock + threadIdx.x;
-  Box b = empty_box();
-  if (g < n) {
-    b = tri_box(S.tris[S.n_static + (val ? val[g] : g)]);
-    pyr_put(W.pyr, g, b);
-  }
+  const uint32_t g = block * kBlock + threadIdx.x;
+  if (g < n) pyr_put(pyr, g, b);
   uint32_t off = 0, m = n;
   for (int l = 1; l <= kLowLevels; ++l) {
     off += m;
@@ -324,23 +327,36 @@ __global__ __launch_bounds__(kBlock) void k_lbvh_leaves(const SceneDev* __restri
     if (threadIdx.x < cnt) {
       const uint32_t i = 2 * threadIdx.x;
       b = join(Box{slo[i], shi[i]}, Box{slo[i + 1], shi[i + 1]});
-      const uint32_t k = (blockIdx.x * kBlock >> l) + threadIdx.x;
-      if (k < m) pyr_put(W.pyr, off + k, b);
+      const uint32_t k = (block * kBlock >> l) + threadIdx.x;
+      if (k < m) pyr_put(pyr, off + k, b);
     }
     __syncthreads();
   }
 }
 
-// the pyramid levels above kLowLevels, one workgroup
-__global__ __launch_bounds__(1024) void k_lbvh_pyramid(LbvhWork W) {
-  const uint32_t n = W.n_dyn;
+// the low pyramid levels over the padded triangle boxes in sorted order
+__global__ __launch_bounds__(kBlock) void k_lbvh_leaves(const SceneDev* __restrict__ scenes, LbvhWork W,
+                                                        const uint32_t* __restrict__ val) {
+  const SceneDev& S = scenes[0];
+  const uint32_t g = blockIdx.x * kBlock + threadIdx.x;
+  Box b = empty_box();
+  if (g < W.n_dyn) b = tri_box(S.tris[S.n_static + val[g]]);
+  pyr_low(W.pyr, W.n_dyn, blockIdx.x, b);
+}
+
+// the pyramid levels above kLowLevels, one workgroup per scene
+__global__ __launch_bounds__(1024) void k_lbvh_pyramid(const SceneDev* __restrict__ scenes, uint32_t all) {
+  const SceneDev& S = scenes[blockIdx.x];
+  if (!all && !S.pyr_full) return;
+  const uint32_t n = S.n_dyn;
+  float4* pyr = S.pyr;
   uint32_t off = pyr_level(n, kLowLevels), m = (n + (1u << kLowLevels) - 1) >> kLowLevels;
   while (m > 1) {
     const uint32_t up = (m + 1) / 2;
     for (uint32_t k = threadIdx.x; k < up; k += blockDim.x) {
-      Box b = pyr_get(W.pyr, off + 2 * k);
-      if (2 * k + 1 < m) b = join(b, pyr_get(W.pyr, off + 2 * k + 1));
-      pyr_put(W.pyr, off + m + k, b);
+      Box b = pyr_get(pyr, off + 2 * k);
+      if (2 * k + 1 < m) b = join(b, pyr_get(pyr, off + 2 * k + 1));
+      pyr_put(pyr, off + m + k, b);
     }
     __syncthreads();
     off += m;
@@ -492,55 +508,354 @@ __global__ void k_lbvh_finish(SceneDev* __restrict__ scenes, LbvhWork W, const u
   objs[o].wroot = wroot;
 }
 
-// Per-frame refit of the upload-time topologies of the moved objects: every
-// node's two child boxes are unions over the children's leaf-order record
-// ranges, read from the pyramid over the records (a subtree holds a
-// contiguous run of the leaf order), so no node waits for its children.
-// The unions equal those of a level-by-level refit bit for bit: the padding
-// is monotone, so the padded box of a union is the union of padded boxes.
-__global__ __launch_bounds__(kBlock) void k_refit_nodes(SceneDev* __restrict__ scenes, LbvhWork W) {
-  SceneDev& S = scenes[0];
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= S.n_obj_nodes || !S.obj_moved[S.dspan_obj[i]]) return;
-  const uint4 r = S.dspan[i];
-  const Box b0 = range_box(W.pyr, W.n_dyn, r.x, r.y), b1 = range_box(W.pyr, W.n_dyn, r.z, r.w);
-  Node& nd = S.nodes[S.obj_node_first + i];
-  nd.a = make_float4(b0.lo.x, b0.lo.y, b0.lo.z, b0.hi.x);
-  nd.b = make_float4(b0.hi.y, b0.hi.z, b1.lo.x, b1.lo.y);
-  nd.c = make_float4(b1.lo.z, b1.hi.x, b1.hi.y, b1.hi.z);
-  const uint2 ws = S.wslot[i];
+// ---------------------------------------------------------------------------
+// top-level trees, rebuilt each frame once the object boxes are current: one
+// over the static root and every object root, one over the moved objects
+// only (the set that verification and the walk's clearance tests query).
+// The objects of a tree are split at their median along the widest axis of
+// their box centres, recursively; the static hierarchy, whose box spans the
+// scene and would widen every node above it, is the root's first child
+// (nearly every query enters the static side first).  One wave per tree, one
+// lane per position of the item order, one level of the recursion per step:
+// every range of the level is stably sorted by rank along its own axis, at
+// once.  A range [lo, hi) splits at mid = (lo + hi) / 2, and each split
+// position belongs to exactly one range, so node mid - 1 of the tree's block
+// holds that range (node n - 1 the root above the static hierarchy).  Sorting
+// only permutes a range's own items, so all nodes are written once the order
+// is final, lane mid - 1 writing its range's from the range's four quarters:
+// the binary node from the halves, and, for the ranges of every second level,
+// the four-wide node from the quarters (of the scene's root from the static
+// hierarchy and the halves).
+
+constexpr int kTopLevels = kTopDepth - 1;  // median levels over <= PV_MAX_OBJECTS objects
+
+// The trees of one scene, by waves 0 and 1 of a workgroup (all its threads
+// come here).
+__device__ inline void build_top(SceneDev& S) {
+  static_assert(PV_MAX_OBJECTS <= 64, "one lane per object");
+  static_assert((1 << kTopLevels) >= PV_MAX_OBJECTS, "median levels");
+  __shared__ float sbx[2][2][6][64];  // [tree][buffer][box component][position]
+  __shared__ int2 scode[2][2][64];    // (binary, four-wide) root codes
+  const bool idle = threadIdx.x >= 128;      // a wave without a tree
+  const int which = (threadIdx.x >> 6) & 1;  // tree of this wave
+  const uint32_t lane = threadIdx.x & 63u;
   const PlaneWriter wide(S);
-  if (ws.x != kSlotNone) wide.put(ws.x, b0.lo.x, b0.lo.y, b0.lo.z, b0.hi.x, b0.hi.y, b0.hi.z);
-  if (ws.y != kSlotNone) wide.put(ws.y, b1.lo.x, b1.lo.y, b1.lo.z, b1.hi.x, b1.hi.y, b1.hi.z);
+  PV_GLOBAL Node* nodes = G(S.nodes);
+  float sbox[6];
+  for (int k = 0; k < 6; ++k) sbox[k] = S.sbox[k];
+  // items of the tree in object order (moved objects compacted by ballot)
+  const bool have = !idle && lane < S.n_obj;
+  const bool take = have && (which == 0 || S.obj_moved[lane] != 0);
+  const uint64_t mm = __ballot(take);
+  const uint32_t n = (uint32_t)__popcll(mm);
+  if (take) {
+    const uint32_t i = (uint32_t)__popcll(mm & lanes_below());
+    for (int k = 0; k < 6; ++k) sbx[which][0][k][i] = S.obj_aabb[6 * lane + k];
+    scode[which][0][i] = make_int2(S.objs[lane].root, S.objs[lane].wroot);
+  }
+  __syncthreads();
+  uint32_t lo = 0, hi = n;  // range of this lane's position
+  int buf = 0;
+  for (int level = 0; level < kTopLevels; ++level) {
+    const float(*bx)[64] = sbx[which][buf];
+    const bool live = lane < n && hi - lo >= 2;
+    uint32_t dst = lane;
+    if (live) {
+      // widest axis of the range's box centres
+      float clo[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
+      float chi[3] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
+      for (uint32_t q = lo; q < hi; ++q)
+        for (int k = 0; k < 3; ++k) {
+          const float c = 0.5f * (bx[k][q] + bx[3 + k][q]);
+          clo[k] = fminf(clo[k], c);
+          chi[k] = fmaxf(chi[k], c);
+        }
+      int ax = 0;
+      for (int k = 1; k < 3; ++k)
+        if (chi[k] - clo[k] > chi[ax] - clo[ax]) ax = k;
+      // stable rank along that axis
+      const float mine = 0.5f * (bx[ax][lane] + bx[3 + ax][lane]);
+      uint32_t rank = 0;
+      for (uint32_t q = lo; q < hi; ++q) {
+        const float c = 0.5f * (bx[ax][q] + bx[3 + ax][q]);
+        rank += (c < mine || (c == mine && q < lane)) ? 1u : 0u;
+      }
+      dst = lo + rank;
+    }
+    float mb[6];
+    for (int k = 0; k < 6; ++k) mb[k] = bx[k][lane];
+    const int2 mc = scode[which][buf][lane];
+    if (lane < n) {
+      for (int k = 0; k < 6; ++k) sbx[which][buf ^ 1][k][dst] = mb[k];
+      scode[which][buf ^ 1][dst] = mc;
+    }
+    __syncthreads();
+    buf ^= 1;
+    if (live) {
+      const uint32_t mid = (lo + hi) / 2;
+      if (lane < mid) hi = mid;
+      else lo = mid;
+    }
+  }
+  const float(*bx)[64] = sbx[which][buf];
+  const int2* code = scode[which][buf];
+  const int32_t sroot = S.sroot, swroot = S.swroot;
+  const bool above = which == 0 && sroot != kRootNone;  // the static hierarchy beside the objects
+  const uint32_t first = S.top_base + (uint32_t)which * kTopNodes;
+  const uint32_t wfirst = S.wtop_base + (uint32_t)which * kTopNodes;
+  // root codes of a range of one or more items (its node's index is its split position - 1)
+  auto bin = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].x : (int32_t)(first + (a + b) / 2 - 1); };
+  auto wid = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].y : (int32_t)(wfirst + (a + b) / 2 - 1); };
+  if (lane + 1 < n) {
+    // the range that splits at lane + 1
+    uint32_t a = 0, b = n, depth = 0;
+    while ((a + b) / 2 != lane + 1) {
+      const uint32_t m = (a + b) / 2;
+      if (lane + 1 < m) b = m;
+      else a = m;
+      ++depth;
+    }
+    const uint32_t mid = lane + 1;
+    // quarters (a half of one item is its own first quarter)
+    const uint32_t q[5] = {a, mid - a == 1 ? mid : (a + mid) / 2, mid, b - mid == 1 ? b : (mid + b) / 2, b};
+    float bb[4][6];
+    for (int j = 0; j < 4; ++j) {
+      for (int k = 0; k < 3; ++k) {
+        bb[j][k] = __builtin_inff();
+        bb[j][3 + k] = -__builtin_inff();
+      }
+      for (uint32_t i = q[j]; i < q[j + 1]; ++i)
+        for (int k = 0; k < 3; ++k) {
+          bb[j][k] = fminf(bb[j][k], bx[k][i]);
+          bb[j][3 + k] = fmaxf(bb[j][3 + k], bx[3 + k][i]);
+        }
+    }
+    float cb[2][6];
+    for (int k = 0; k < 3; ++k)
+      for (int h = 0; h < 2; ++h) {
+        cb[h][k] = fminf(bb[2 * h][k], bb[2 * h + 1][k]);
+        cb[h][3 + k] = fmaxf(bb[2 * h][3 + k], bb[2 * h + 1][3 + k]);
+      }
+    PV_GLOBAL Node& nd = nodes[first + lane];
+    nd.a = make_float4(cb[0][0], cb[0][1], cb[0][2], cb[0][3]);
+    nd.b = make_float4(cb[0][4], cb[0][5], cb[1][0], cb[1][1]);
+    nd.c = make_float4(cb[1][2], cb[1][3], cb[1][4], cb[1][5]);
+    nd.d = make_int4(bin(a, mid), bin(mid, b), -1, 0);
+    if (((depth + (above ? 1u : 0u)) & 1u) == 0) {
+      const uint32_t w = 4 * (wfirst + lane);
+      for (int j = 0; j < 4; ++j) {
+        if (q[j] < q[j + 1]) {
+          wide.put(w + j, bb[j][0], bb[j][1], bb[j][2], bb[j][3], bb[j][4], bb[j][5]);
+          wide.child(w + j, wid(q[j], q[j + 1]));
+        } else {
+          wide.none(w + j);
+        }
+      }
+    }
+    if (above && depth == 0) {
+      // the scene's root: the static hierarchy and the halves of the objects
+      const uint32_t w = 4 * (wfirst + n - 1);
+      wide.put(w, sbox[0], sbox[1], sbox[2], sbox[3], sbox[4], sbox[5]);
+      wide.child(w, swroot);
+      for (int h = 0; h < 2; ++h) wide.put(w + 1 + h, cb[h][0], cb[h][1], cb[h][2], cb[h][3], cb[h][4], cb[h][5]);
+      wide.child(w + 1, wid(a, mid));
+      wide.child(w + 2, wid(mid, b));
+      wide.none(w + 3);
+    }
+  }
+  if (lane != 0 || idle) return;
+  // roots: the objects' tree, the single object, or none; the static
+  // hierarchy alone or above them
+  int32_t root = n == 0 ? kRootNone : bin(0, n), wroot = n == 0 ? kRootNone : wid(0, n);
+  if (above && n > 0) {
+    float ob[6] = {__builtin_inff(), __builtin_inff(), __builtin_inff(),
+                   -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
+    for (uint32_t i = 0; i < n; ++i)
+      for (int k = 0; k < 3; ++k) {
+        ob[k] = fminf(ob[k], bx[k][i]);
+        ob[3 + k] = fmaxf(ob[3 + k], bx[3 + k][i]);
+      }
+    PV_GLOBAL Node& nd = nodes[first + n - 1];
+    nd.a = make_float4(sbox[0], sbox[1], sbox[2], sbox[3]);
+    nd.b = make_float4(sbox[4], sbox[5], ob[0], ob[1]);
+    nd.c = make_float4(ob[2], ob[3], ob[4], ob[5]);
+    nd.d = make_int4(sroot, root, -1, 0);
+    root = (int32_t)(first + n - 1);
+    if (n == 1) {
+      const uint32_t w = 4 * wfirst;
+      wide.put(w, sbox[0], sbox[1], sbox[2], sbox[3], sbox[4], sbox[5]);
+      wide.child(w, swroot);
+      wide.put(w + 1, ob[0], ob[1], ob[2], ob[3], ob[4], ob[5]);
+      wide.child(w + 1, wroot);
+      wide.none(w + 2);
+      wide.none(w + 3);
+    }
+    wroot = (int32_t)(wfirst + n - 1);
+  } else if (above) {
+    root = sroot;
+    wroot = swroot;
+  }
+  S.top[which] = root;
+  S.wtop[which] = wroot;
 }
 
-// each moved object's box (the union of its records) and its refit topology
-// as its current hierarchy
-__global__ void k_refit_objects(SceneDev* __restrict__ scenes, LbvhWork W) {
-  SceneDev& S = scenes[0];
+// the trees alone (after a rebuild of the objects' hierarchies)
+__global__ __launch_bounds__(128) void k_build_top(SceneDev* __restrict__ scenes) { build_top(scenes[blockIdx.x]); }
+
+// ---------------------------------------------------------------------------
+// The beginning of a frame, two launches (a chain of dependent launches costs
+// at least 4.5 us each; the ten of copies, flags, triangles, pyramid levels,
+// boxes and trees took 75 us for 80k dynamic triangles and 30 us for a dozen).
+//
+// k_place: one thread per dynamic triangle record, a workgroup per aligned 256
+// of a scene's (tile = scene, first record), so that it also builds the low
+// pyramid levels.  An object has moved when its new transform differs from the
+// current one, which only k_refit replaces; every workgroup finds the flags by
+// itself (at most 64 objects), a scene's first one writes them.
+
+__device__ inline float xform_coord(const float* m, int r, float x, float y, float z) {
+  double v = fma((double)m[4 * r + 0], (double)x,
+                 fma((double)m[4 * r + 1], (double)y, fma((double)m[4 * r + 2], (double)z, (double)m[4 * r + 3])));
+  return (float)v;
+}
+
+__global__ __launch_bounds__(kBlock) void k_place(const SceneDev* __restrict__ scenes, const uint2* __restrict__ tiles,
+                                                  FrameInput in) {
+  __shared__ uint32_t smoved[PV_MAX_OBJECTS], sbase[PV_MAX_OBJECTS];
+  const uint2 tile = tiles[blockIdx.x];
+  const SceneDev& S = scenes[tile.x];
+  const float* xf = in.obj_tab ? in.obj_tab[tile.x] : in.obj;
+  const uint32_t n = S.n_dyn, n_obj = S.n_obj;
+  for (uint32_t o = threadIdx.x; o < n_obj; o += kBlock) {
+    uint32_t moved = S.state[0];
+    for (int i = 0; i < 12; ++i)
+      moved |= __float_as_uint(S.obj_xf_cur[12 * o + i]) != __float_as_uint(xf[12 * o + i]) ? 1u : 0u;
+    smoved[o] = moved;
+    sbase[o] = S.objs[o].tri_base;
+    if (tile.y == 0) S.obj_moved[o] = moved;
+  }
+  __syncthreads();
+  const uint32_t g = tile.y + threadIdx.x;
+  Box b = empty_box();
+  if (g < n) {
+    uint32_t o = 0, hi = n_obj;  // the last object whose first record is not after g
+    while (hi - o > 1) {
+      const uint32_t mid = (o + hi) >> 1;
+      if (sbase[mid] <= g)
+        o = mid;
+      else
+        hi = mid;
+    }
+    Tri t;
+    if (smoved[o]) {
+      const float* m = xf + 12 * o;
+      const float* v = S.dlocal + 9 * (size_t)g;
+      float w[9];
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int r = 0; r < 3; ++r) w[3 * k + r] = xform_coord(m, r, v[3 * k], v[3 * k + 1], v[3 * k + 2]);
+      t = make_tri(w, S.dtri_gid[g]);
+      S.tris[S.n_static + g] = t;
+    } else {
+      t = S.tris[S.n_static + g];
+    }
+    b = tri_box(t);
+  }
+  pyr_low(S.pyr, n, tile.y / kBlock, b);
+}
+
+// k_refit: child boxes of the moved objects' upload-time topologies, one
+// thread per node (tile = scene, first object node): each box is the union
+// over the leaf-order range of the child's triangles (a subtree is a
+// contiguous run of the leaf order), so no node waits for its children.  The
+// unions equal those of a level-by-level refit bit for bit: the padding is
+// monotone, so the padded box of a union is the union of padded boxes.
+//
+// One workgroup per scene (tile.y = kSlotNone) meanwhile replaces the current
+// transforms, finds the objects' boxes and, with 'top', builds the trees above
+// them: it reads none of the nodes that the others write.
+__global__ __launch_bounds__(kBlock) void k_refit(SceneDev* __restrict__ scenes, const uint2* __restrict__ tiles,
+                                                  FrameInput in, uint32_t top) {
+  const uint2 tile = tiles[blockIdx.x];
+  SceneDev& S = scenes[tile.x];
+  const bool full = S.pyr_full != 0;
+  if (tile.y != kSlotNone) {
+    const uint32_t i = tile.y + threadIdx.x;
+    if (i >= S.n_obj_nodes || !S.obj_moved[S.dspan_obj[i]]) return;
+    const uint4 r = S.dspan[i];
+    const Box b0 = range_box(S.pyr, S.n_dyn, r.x, r.y, full), b1 = range_box(S.pyr, S.n_dyn, r.z, r.w, full);
+    Node& nd = S.nodes[S.obj_node_first + i];
+    nd.a = make_float4(b0.lo.x, b0.lo.y, b0.lo.z, b0.hi.x);
+    nd.b = make_float4(b0.hi.y, b0.hi.z, b1.lo.x, b1.lo.y);
+    nd.c = make_float4(b1.lo.z, b1.hi.x, b1.hi.y, b1.hi.z);
+    const uint2 ws = S.wslot[i];
+    const PlaneWriter wide(S);
+    if (ws.x != kSlotNone) wide.put(ws.x, b0.lo.x, b0.lo.y, b0.lo.z, b0.hi.x, b0.hi.y, b0.hi.z);
+    if (ws.y != kSlotNone) wide.put(ws.y, b1.lo.x, b1.lo.y, b1.lo.z, b1.hi.x, b1.hi.y, b1.hi.z);
+    return;
+  }
+  const float* oxf = in.obj_tab ? in.obj_tab[tile.x] : in.obj;
+  const float* lxf = in.light_tab ? in.light_tab[tile.x] : in.light;
+  const uint32_t first = S.state[0];
+  // an object's row by one thread: transform history, the staged copy that
+  // later sparse updates start from, box and current hierarchy
   ObjDev* objs = const_cast<ObjDev*>(S.objs);
-  const uint32_t o = blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= S.n_obj || !S.obj_moved[o]) return;
-  const ObjDev ob = S.objs[o];
-  const Box b = range_box(W.pyr, W.n_dyn, ob.tri_base, ob.tri_base + ob.n_tris);
-  S.obj_aabb[6 * o + 0] = b.lo.x;
-  S.obj_aabb[6 * o + 1] = b.lo.y;
-  S.obj_aabb[6 * o + 2] = b.lo.z;
-  S.obj_aabb[6 * o + 3] = b.hi.x;
-  S.obj_aabb[6 * o + 4] = b.hi.y;
-  S.obj_aabb[6 * o + 5] = b.hi.z;
-  objs[o].root = ob.sah_root;
-  objs[o].wroot = ob.sah_wroot;
+  for (uint32_t o = threadIdx.x; o < S.n_obj; o += kBlock) {
+    float c[12], v[12];
+    for (int i = 0; i < 12; ++i) {
+      c[i] = S.obj_xf_cur[12 * o + i];
+      v[i] = oxf[12 * o + i];
+    }
+    for (int i = 0; i < 12; ++i) {
+      S.obj_xf_prev[12 * o + i] = c[i];
+      S.obj_xf_cur[12 * o + i] = v[i];
+      if (in.obj_staged) in.obj_staged[12 * o + i] = v[i];
+    }
+    if (!S.obj_moved[o]) continue;
+    const Box b = range_box(S.pyr, S.n_dyn, objs[o].tri_base, objs[o].tri_base + objs[o].n_tris, full);
+    S.obj_aabb[6 * o + 0] = b.lo.x;
+    S.obj_aabb[6 * o + 1] = b.lo.y;
+    S.obj_aabb[6 * o + 2] = b.lo.z;
+    S.obj_aabb[6 * o + 3] = b.hi.x;
+    S.obj_aabb[6 * o + 4] = b.hi.y;
+    S.obj_aabb[6 * o + 5] = b.hi.z;
+    objs[o].root = objs[o].sah_root;  // the refit topology is the current one
+    objs[o].wroot = objs[o].sah_wroot;
+  }
+  for (uint32_t l = threadIdx.x; l < S.n_lights; l += kBlock) {
+    float c[12], v[12];
+    uint32_t moved = 0;
+    for (int i = 0; i < 12; ++i) {
+      c[i] = S.light_xf_cur[12 * l + i];
+      v[i] = lxf[12 * l + i];
+      moved |= __float_as_uint(c[i]) != __float_as_uint(v[i]) ? 1u : 0u;
+    }
+    for (int i = 0; i < 12; ++i) {
+      S.light_xf_prev[12 * l + i] = c[i];
+      S.light_xf_cur[12 * l + i] = v[i];
+      if (in.light_staged) in.light_staged[12 * l + i] = v[i];
+    }
+    S.light_moved[l] = first ? 0u : moved;  // a light's first placement does not invalidate anything
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) S.state[0] = 0;
+  if (top) build_top(S);
 }
 
-hipError_t launch_refit_objects(SceneDev* scenes, LbvhWork W, uint32_t n_obj, uint32_t n_obj_nodes, hipStream_t s) {
-  if (!W.n_dyn || !n_obj) return hipSuccess;
-  const uint32_t nb = (W.n_dyn + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(k_lbvh_leaves, dim3(nb), dim3(kBlock), 0, s, scenes, W, nullptr);
-  if (W.n_dyn > (1u << kLowLevels)) hipLaunchKernelGGL(k_lbvh_pyramid, dim3(1), dim3(1024), 0, s, W);
-  if (n_obj_nodes)
-    hipLaunchKernelGGL(k_refit_nodes, dim3((n_obj_nodes + kBlock - 1) / kBlock), dim3(kBlock), 0, s, scenes, W);
-  hipLaunchKernelGGL(k_refit_objects, dim3((n_obj + 63) / 64), dim3(64), 0, s, scenes, W);
+hipError_t launch_frame_begin(SceneDev* scenes, int n_scenes, const uint2* place_tiles, uint32_t n_place,
+                              const uint2* refit_tiles, uint32_t n_refit, const FrameInput& in, bool pyramid, bool top,
+                              hipStream_t s) {
+  if (n_scenes <= 0) return hipSuccess;
+  if (n_place) hipLaunchKernelGGL(k_place, dim3(n_place), dim3(kBlock), 0, s, scenes, place_tiles, in);
+  if (pyramid) hipLaunchKernelGGL(k_lbvh_pyramid, dim3(n_scenes), dim3(1024), 0, s, scenes, 0u);
+  hipLaunchKernelGGL(k_refit, dim3(n_refit), dim3(kBlock), 0, s, scenes, refit_tiles, in, top ? 1u : 0u);
+  return hipGetLastError();
+}
+
+hipError_t launch_build_top(SceneDev* scenes, int n_scenes, hipStream_t s) {
+  if (n_scenes <= 0) return hipSuccess;
+  k_build_top<<<n_scenes, 128, 0, s>>>(scenes);
   return hipGetLastError();
 }
 
@@ -573,7 +888,7 @@ hipError_t launch_rebuild_objects(SceneDev* scenes, LbvhWork W, uint32_t n_obj, 
     src ^= 1;
   }
   hipLaunchKernelGGL(k_lbvh_leaves, dim3(nb), dim3(kBlock), 0, s, scenes, W, W.val[src]);
-  if (W.n_dyn > (1u << kLowLevels)) hipLaunchKernelGGL(k_lbvh_pyramid, dim3(1), dim3(1024), 0, s, W);
+  if (W.n_dyn > (1u << kLowLevels)) hipLaunchKernelGGL(k_lbvh_pyramid, dim3(1), dim3(1024), 0, s, scenes, 1u);
   hipLaunchKernelGGL(k_lbvh_nodes, dim3(nb), dim3(kBlock), 0, s, scenes, W, W.key[src], W.val[src]);
   hipLaunchKernelGGL(k_lbvh_depth, dim3(nb), dim3(kBlock), 0, s, scenes, W, W.key[src]);
   hipLaunchKernelGGL(k_lbvh_finish, dim3((n_obj + 63) / 64), dim3(64), 0, s, scenes, W, W.val[src], max_depth);

@@ -189,3 +189,31 @@ def test_queue_and_compaction_at_edges(E, n, B):
     np.testing.assert_array_equal(pos.cpu().numpy(), d["pos"][there])
     np.testing.assert_array_equal(en.cpu().numpy(), d["energy"][there])
     ctx.close()
+
+
+# Frame beginning: objects of one triangle, one below and above a 256-record
+# block, and both sides of the object size (16,384 triangles) from which boxes
+# need the upper pyramid levels; some objects stay where they are in a frame.
+@pytest.mark.parametrize("sizes", [[1], [255, 1, 257], [16_384, 2], [16_385, 3, 300]])
+def test_object_boxes_at_edges(E, sizes):
+    from tests.test_gpu_parity import _lockstep
+    sc = scenes.make_tiny(n_paths=1500 + 3, max_bounces=3, frames=4, seed=23)
+    rng = np.random.default_rng(len(sizes))
+    n_obj = len(sizes)
+    sc.obj_local = [(rng.uniform(-0.1, 0.1, (n, 1, 3)) + rng.uniform(-0.02, 0.02, (n, 3, 3))).astype(np.float32)
+                    for n in sizes]
+    sc.obj_mat = [np.ones(n, np.uint32) for n in sizes]
+    base = sc.obj_xforms[:, :1]
+    xf = np.repeat(base, n_obj, axis=1).copy()
+    for o in range(n_obj):
+        xf[:, o, 3] += 0.15 * (o - 1)
+    xf[2, 0] = xf[1, 0]  # the first object rests in frame 2
+    sc.obj_xforms = xf.astype(np.float32)
+    ctx = E.Context(sc)
+    for f in range(4):
+        ctx.frame_begin(f)
+        for o in range(n_obj):
+            h = ctx.object_hierarchy_info(o)
+            assert h["valid"] and not h["rebuilt"], (f, o, h)
+    ctx.close()
+    _lockstep(E, sc, 4, 0.01, "objects of %s triangles" % sizes)
