@@ -558,16 +558,21 @@ void host_boxes(HostBvh& h, const float* v9_leaf_order, float extra = 0.0f) {
   }
 }
 
+struct WideOrigin {
+  uint8_t o[3];
+};
+
 // The four-wide form of a binary hierarchy: from a node's two children, the
 // internal one of largest surface area is replaced by its own two until there
 // are four; empty slots are never entered.  The boxes are taken
-// from 'h' (host_boxes), quantised into the grid (qc, qs).  Appends to 'out',
-// whose indices and the leaves' codes are absolute ('leaf' maps a leaf code
+// from 'h' (host_boxes), quantised into the grid (qc, qs), with 'origins' less
+// an origin near the middle of the node.  Appends to 'out' (plain codes) and
+// the origins to 'org', whose indices and the leaves' codes are absolute ('leaf' maps a leaf code
 // of h); slot[2 i + side] names the slot that took child 'side' of node i.
 // Returns the root code.
 template <typename LeafMap>
-int32_t build_wide(const HostBvh& h, const float qc[3], float qs, LeafMap leaf, std::vector<Wide>& out,
-                   std::vector<uint32_t>* slot) {
+int32_t build_wide(const HostBvh& h, const float qc[3], float qs, bool origins, LeafMap leaf, std::vector<Wide>& out,
+                   std::vector<WideOrigin>& org, std::vector<uint32_t>* slot) {
   if (h.root < 0) return leaf(h.root);
   if (slot) slot->assign(2 * h.nodes.size(), pv::kSlotNone);
   struct Ref {
@@ -604,10 +609,20 @@ int32_t build_wide(const HostBvh& h, const float qc[3], float qs, LeafMap leaf, 
     const uint32_t id = (uint32_t)out.size();
     if (it.parent != pv::kSlotNone) out[it.parent >> 2].child[it.parent & 3u] = (int32_t)id;
     Wide w{};
+    WideOrigin og{};
+    for (int ax = 0; origins && ax < 3; ++ax) {
+      float lo = INFINITY, hi = -INFINITY;
+      for (uint32_t k = 0; k < n; ++k) {
+        lo = std::min(lo, box(c[k])[ax]);
+        hi = std::max(hi, box(c[k])[3 + ax]);
+      }
+      og.o[ax] = (uint8_t)pv::wide_origin(0.5f * lo + 0.5f * hi, qc[ax], qs);
+    }
+    org.push_back(og);
     for (uint32_t k = 0; k < 4; ++k) {
       for (int ax = 0; ax < 3; ++ax)
         w.plane[3 * k + ax] =
-            k < n ? pv::wide_planes(box(c[k])[ax], box(c[k])[3 + ax], qc[ax], qs) : pv::kPlanesNone;
+            k < n ? pv::wide_planes(box(c[k])[ax], box(c[k])[3 + ax], qc[ax], qs, (float)og.o[ax]) : pv::kPlanesNone;
       if (k < n && code(c[k]) < 0) w.child[k] = leaf(code(c[k]));
       if (k < n && slot) (*slot)[2 * (size_t)c[k].node + c[k].side] = 4 * id + k;
     }
@@ -935,11 +950,17 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     // static world: topology + boxes on the host
     std::vector<Node> nodes;  // static, then objects, then the top-level trees
     std::vector<Wide> wide;   // their four-wide forms
+    std::vector<WideOrigin> worg;  // and those nodes' origins
     std::vector<Tri> stris;
     hs.n_static = S;
     hs.sroot = hs.swroot = pv::kRootNone;
+    // nodes have origins where the walk's codes fit 24 bits: a leaf's first
+    // triangle 20, a node's index 23 (a scene has fewer than 4 nodes a triangle)
+    const bool origins = (uint64_t)S + n_dyn <= pv::kOriginTris;
+    hs.wshift = origins ? pv::kOriginShift : 0u;
     hs.qs = 64.0f;  // without static triangles: coordinates of about 1 mid-range
     hs.qinv = 1.0f / 64.0f;
+    for (int k = 0; k < 3; ++k) hs.qc[k] = origins ? -pv::kOriginMid * hs.qinv : 0.0f;
     uint32_t depth = 0, obj_depth = 0;  // deepest leaf: all hierarchies, object hierarchies
     for (int k = 0; k < 3; ++k) {
       hs.sbox[k] = INFINITY;
@@ -966,24 +987,25 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         hs.sbox[k] = pad_lo(hs.sbox[k]);
         hs.sbox[3 + k] = pad_hi(hs.sbox[3 + k]);
       }
-      // the planes' grid: centred on the static world, the largest half
-      // extent scaled to (128, 256] by a power of two: objects up to 255
-      // times as far out keep finite planes, planes under 2^-22 of the half
-      // extent from the centre lose digits
+      // the planes' grid: around the static world, the largest half extent
+      // scaled by a power of two to (64, 128], the reach of the origins, or,
+      // without them, to (128, 256]: objects up to 255 times as far out keep
+      // finite planes, planes under 2^-21 of the half extent from an origin
+      // lose digits
       float half = 0.0f;
-      for (int k = 0; k < 3; ++k) {
-        hs.qc[k] = 0.5f * (hs.sbox[k] + hs.sbox[3 + k]);
-        half = std::max(half, 0.5f * (hs.sbox[3 + k] - hs.sbox[k]));
-      }
+      for (int k = 0; k < 3; ++k) half = std::max(half, 0.5f * (hs.sbox[3 + k] - hs.sbox[k]));
       int ex = 0;
       if (half > 0.0f && std::isfinite(half)) (void)std::frexp(half, &ex);
-      hs.qs = std::ldexp(1.0f, std::min(100, std::max(-100, 8 - ex)));
+      hs.qs = std::ldexp(1.0f, std::min(100, std::max(-100, (origins ? 7 : 8) - ex)));
       hs.qinv = 1.0f / hs.qs;
-      hs.swroot = build_wide(hb, hs.qc, hs.qs, [](int32_t c) { return c; }, wide, nullptr);
+      for (int k = 0; k < 3; ++k)
+        hs.qc[k] = 0.5f * (hs.sbox[k] + hs.sbox[3 + k]) - (origins ? pv::kOriginMid * hs.qinv : 0.0f);
+      hs.swroot = build_wide(hb, hs.qc, hs.qs, origins, [](int32_t c) { return c; }, wide, worg, nullptr);
       nodes = std::move(hb.nodes);
       hs.sroot = hb.root;
     }
 
+    hs.qobj = origins ? -pv::kOriginMid * hs.qinv : 0.0f;
     const uint32_t static_depth = depth;
     // dynamic objects: topology in object space, boxes refit per frame
     std::vector<ObjDev> objs(d->n_objects);
@@ -992,6 +1014,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     std::vector<uint4> dspan;          // per object node: its children's record ranges
     std::vector<uint32_t> dspan_obj;   // and its object
     std::vector<Wide> owide;           // the objects' four-wide topologies with object-space boxes
+    std::vector<WideOrigin> oorg;      // and their origins
     std::vector<uint2> wslot;          // per object node: the four-wide slots of its children
     const uint32_t obj_node_first = (uint32_t)nodes.size();
     uint32_t tri_base = 0, gbase = S;
@@ -1036,6 +1059,14 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         std::memcpy(&dlocal[9 * (size_t)(tri_base + i)], v + 9 * (size_t)hb.order[i], 9 * sizeof(float));
         dgid[tri_base + i] = gbase + hb.order[i];
       }
+      for (int k = 0; k < 3; ++k) {
+        float lo = INFINITY, hi = -INFINITY;
+        for (size_t i = k; i < 9 * (size_t)n; i += 3) {
+          lo = std::min(lo, v[i]);
+          hi = std::max(hi, v[i]);
+        }
+        ob.centre[k] = 0.5f * lo + 0.5f * hi;
+      }
       ob.gbase = gbase;
       ob.n_tris = n;
       ob.tri_base = tri_base;
@@ -1052,10 +1083,10 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         host_boxes(hb, lv9.data(), kObjSpacePad);
         auto leaf = [&](int32_t c) { return rebase(c); };
         std::vector<uint32_t> slot;
-        ob.wroot = ob.sah_wroot = build_wide(hb, hs.qc, hs.qs, leaf, wide, &slot);
+        ob.wroot = ob.sah_wroot = build_wide(hb, hs.qc, hs.qs, origins, leaf, wide, worg, &slot);
         for (size_t i = 0; i < slot.size(); i += 2) wslot.push_back(make_uint2(slot[i], slot[i + 1]));
-        const float zero[3] = {0.0f, 0.0f, 0.0f};
-        ob.oroot = build_wide(hb, zero, hs.qs, leaf, owide, nullptr);
+        const float qo[3] = {hs.qobj, hs.qobj, hs.qobj};
+        ob.oroot = build_wide(hb, qo, hs.qs, origins, leaf, owide, oorg, nullptr);
       }
       tri_base += n;
       gbase += n;
@@ -1087,6 +1118,15 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     }
     for (ObjDev& ob : objs)
       if (ob.oroot >= 0) ob.oroot += ofirst;
+    // plain codes to the walk's, with the origins
+    worg.resize((size_t)ofirst, WideOrigin{});
+    worg.insert(worg.end(), oorg.begin(), oorg.end());
+    for (size_t i = 0; i < wide.size(); ++i)
+      for (int k = 0; k < 4; ++k)
+        wide[i].child[k] = pv::wide_code(wide[i].child[k], hs.wshift) | (k < 3 ? (int32_t)worg[i].o[k] : 0);
+    hs.swroot = pv::wide_code(hs.swroot, hs.wshift);
+    for (ObjDev& ob : objs)
+      for (int32_t* c : {&ob.oroot, &ob.wroot, &ob.sah_wroot}) *c = pv::wide_code(*c, hs.wshift);
     if (wide.size() * sizeof(Wide) > (size_t)UINT32_MAX) return fail(ctx, PV_ERR_CAPACITY, "too many hierarchy nodes");
     Node* d_nodes;
     Wide* d_wide;

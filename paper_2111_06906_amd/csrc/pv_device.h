@@ -82,9 +82,19 @@ __host__ __device__ inline uint32_t leaf_count(int code) { return (((uint32_t)~c
 
 // Four-wide node of one 64-byte line: the walks' own form of the hierarchies.
 // Planes are FP16 in the scene's grid, (coordinate - qc) * qs with qs a power
-// of two, rounded outwards, so a quantised box contains its FP32 box; child
-// k's planes are words 3 k .. 3 k + 2, (lower plane | upper plane << 16) per
-// axis; codes as in Node.  An unused slot holds +inf as its lower and
+// of two, less the node's origin, rounded outwards, so a quantised box contains
+// its FP32 box; child k's planes are words 3 k .. 3 k + 2, (lower plane | upper
+// plane << 16) per axis.  Child words are a walk's codes: those of Node shifted
+// left by 8 (wide_code), and the low bytes of the first three are the origin's
+// x, y, z in whole grid steps, of which the scene spans up to 256.  In scenes
+// too large for 24-bit codes they are the plain codes and the origin is 0, the
+// grid's centre.
+//
+// Why an origin per node: FP16 around the scene's centre leaves a wall's box a
+// thousandth of the scene thick, so nearly every ray that starts on a wall
+// walked down to that wall again (paths in a 300k-triangle interior, counted on
+// the host: 16.5 nodes and 3.9 triangles a ray, 13.4 and 1.9 with FP32 planes,
+// 13.7 and 1.9 with origins).  An unused slot holds +inf as its lower and
 // -inf as its upper planes, which no query enters.
 struct alignas(64) Wide {
   uint32_t plane[12];
@@ -115,12 +125,39 @@ __host__ __device__ inline uint32_t half_down(float x) {
 }
 __host__ __device__ inline uint32_t half_up(float x) { return half_down(-x) ^ 0x8000u; }
 
-// planes of one axis of a box [lo, hi] in the grid (c, s); the subtraction's
-// rounding (2^-24 of its result) goes outwards by twice as much
-__host__ __device__ inline uint32_t wide_planes(float lo, float hi, float c, float s) {
+// Planes go outwards by 2^-13 grid steps beyond their padding: the scene's
+// half extent is 64 to 256 steps, so that is at least 2^-21 of it, what the
+// roundings of a walk's box parameters can move a crossing anywhere inside
+// (about 2^-24 of the extent each, three per plane, and the reciprocal's
+// 2^-23), also where the padding, relative to the coordinate, is smaller.
+constexpr float kPlaneSlack = 1.220703125e-4f;
+
+// planes of one axis of a box [lo, hi] in the grid (c, s), less the origin o;
+// the subtractions' roundings (2^-24 of their results) go outwards by at least
+// as much
+__host__ __device__ inline uint32_t wide_planes(float lo, float hi, float c, float s, float o = 0.0f) {
   const float a = (lo - c) * s, b = (hi - c) * s;
-  const float ra = a < 0.0f ? -a : a, rb = b < 0.0f ? -b : b;
-  return half_down(a - ra * 1.1920929e-7f) | (half_up(b + rb * 1.1920929e-7f) << 16);
+  const float da = a - o, db = b - o;
+  const float ra = __builtin_fabsf(a) + __builtin_fabsf(da), rb = __builtin_fabsf(b) + __builtin_fabsf(db);
+  return half_down(da - (ra * 1.1920929e-7f + kPlaneSlack)) |
+         (half_up(db + (rb * 1.1920929e-7f + kPlaneSlack)) << 16);
+}
+
+// Node origins: whole grid steps 0 .. 255 from the grid's corner (qc, then 128
+// steps below the scene's centre), where codes fit 24 bits.
+constexpr uint32_t kOriginShift = 8;
+constexpr uint32_t kOriginTris = (1u << 20) - 1;  // triangles of a scene whose nodes have origins
+constexpr float kOriginMid = 128.0f;
+
+// one axis of a node's origin: the grid step nearest to x
+__host__ __device__ inline uint32_t wide_origin(float x, float c, float s) {
+  const float m = (x - c) * s + 0.5f;
+  return m >= 0.0f ? (m < 255.0f ? (uint32_t)m : 255u) : 0u;
+}
+
+// a code of Node as a walk's
+__host__ __device__ inline int32_t wide_code(int32_t code, uint32_t shift) {
+  return code == INT32_MIN ? code : (int32_t)((uint32_t)code << shift);
 }
 
 // Triangle record in BVH leaf order, one 64-byte line: each vertex as x, y, z,
@@ -155,7 +192,7 @@ struct ObjDev {
   int32_t wroot;       // root of the current hierarchy's four-wide form
   int32_t sah_wroot;   // the same of the upload-time topology
   uint32_t lbvh_wbase; // first four-wide node of its region for the rebuilt radix tree
-  uint32_t pad_[3];
+  float centre[3];     // middle of its object-space box
 };
 
 struct LightDev {
@@ -194,7 +231,9 @@ struct SceneDev {
   int32_t* wtop;          // [2] per frame: four-wide roots of the whole scene and of the moved objects
   uint32_t wtop_base;     // first four-wide top-level node
   int32_t swroot;         // static root code in 'wide'
-  float qc[3], qs, qinv;  // grid of the planes: centre, scale (a power of two), 1 / scale
+  float qc[3], qs, qinv;  // grid of the planes: origin, scale (a power of two), 1 / scale
+  float qobj;             // the same origin, any axis, of the object-space forms
+  uint32_t wshift;        // kOriginShift: the nodes have origins; 0: they have none
   float sbox[6];          // static world box (lo, hi)
   // dynamic objects
   const float* dlocal;    // [n][9] object-space vertices in leaf order
@@ -255,24 +294,50 @@ struct SceneDev {
 
 // Writer of child boxes into four-wide slots.  Holds the grid and the array in
 // registers: read from the descriptor at every write they would be loaded
-// again after each store.
+// again after each store.  All nodes of an object take the placed middle of
+// its box as their origin, the few top-level nodes the grid's middle: each
+// writer finds it by itself.  'xf': the frame's transform of the object.
 struct PlaneWriter {
   PV_GLOBAL Wide* wide;
   float cx, cy, cz, s;
+  uint32_t shift;
+  uint32_t ox, oy, oz;
   __device__ explicit PlaneWriter(const SceneDev& S)
-      : wide(G(S.wide)), cx(S.qc[0]), cy(S.qc[1]), cz(S.qc[2]), s(S.qs) {}
+      : wide(G(S.wide)), cx(S.qc[0]), cy(S.qc[1]), cz(S.qc[2]), s(S.qs), shift(S.wshift) {
+    ox = oy = oz = shift ? (uint32_t)kOriginMid : 0u;
+  }
+  __device__ PlaneWriter(const SceneDev& S, uint32_t o, const float* xf) : PlaneWriter(S) {
+    if (!shift) return;
+    const PV_GLOBAL float* m = G(xf) + 12 * o;
+    const PV_GLOBAL float* c = G(S.objs)[o].centre;
+    ox = wide_origin(m[0] * c[0] + m[1] * c[1] + m[2] * c[2] + m[3], cx, s);
+    oy = wide_origin(m[4] * c[0] + m[5] * c[1] + m[6] * c[2] + m[7], cy, s);
+    oz = wide_origin(m[8] * c[0] + m[9] * c[1] + m[10] * c[2] + m[11], cz, s);
+  }
+  __device__ uint32_t origin(uint32_t k) const { return k == 0 ? ox : (k == 1 ? oy : (k == 2 ? oz : 0u)); }
   __device__ void put(uint32_t slot, float lx, float ly, float lz, float hx, float hy, float hz) const {
     PV_GLOBAL uint32_t* w = wide[slot >> 2].plane + 3 * (slot & 3u);
-    w[0] = wide_planes(lx, hx, cx, s);
-    w[1] = wide_planes(ly, hy, cy, s);
-    w[2] = wide_planes(lz, hz, cz, s);
+    w[0] = wide_planes(lx, hx, cx, s, (float)ox);
+    w[1] = wide_planes(ly, hy, cy, s, (float)oy);
+    w[2] = wide_planes(lz, hz, cz, s, (float)oz);
   }
   __device__ void none(uint32_t slot) const {
     PV_GLOBAL uint32_t* w = wide[slot >> 2].plane + 3 * (slot & 3u);
     w[0] = w[1] = w[2] = kPlanesNone;
-    wide[slot >> 2].child[slot & 3u] = 0;
+    child(slot, 0);
   }
-  __device__ void child(uint32_t slot, int32_t code) const { wide[slot >> 2].child[slot & 3u] = code; }
+  // code: a walk's (wide_code)
+  __device__ void child(uint32_t slot, int32_t code) const {
+    wide[slot >> 2].child[slot & 3u] = code | (int32_t)origin(slot & 3u);
+  }
+  // a node's origin beside child codes that stay
+  __device__ void put_origin(uint32_t node) const {
+    if (!shift) return;
+    PV_GLOBAL uint8_t* b = (PV_GLOBAL uint8_t*)wide[node].child;
+    b[0] = (uint8_t)ox;
+    b[4] = (uint8_t)oy;
+    b[8] = (uint8_t)oz;
+  }
 };
 
 // Device scratch of the per-frame object hierarchy rebuild (linear BVH over
@@ -593,10 +658,14 @@ __device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, 
 // per visit, as the binary FP32 node took, and about a fifth of the visits (22
 // against 109 for a ray of the 3M-path, 380k-triangle interior), so a shorter
 // chain of dependent loads and fewer of them.  Bound by vector issue: about
-// 83 instructions a visit.  Measured there, one MI355X, four-wide against
+// 90 instructions a visit.  Measured there, one MI355X, four-wide against
 // binary: full trace 4.85 against 5.66 ms, partial re-trace 1.98 against 2.30
 // ms, verification traversal 178 against 224 us; with the clamp as the lower
-// end (four instructions a visit) the full trace went from 4.11 to 4.03 ms.
+// end (four instructions a visit) the full trace went from 4.11 to 4.03 ms, and
+// with the nodes' origins (seven more instructions a visit, but 19.6 visits and
+// 3.1 triangles a ray instead of 21.9 and 4.6) to 3.55 ms.  The origin as eight
+// bytes of an array beside the nodes gave the same visits and 4.39 ms: its load,
+// a fifth per visit, cost more than they saved.
 //
 // Boxes are tested with the slab parameters q and triangles with the ray r
 // itself: a walk through a rigid object's hierarchy in its own object space
@@ -607,7 +676,7 @@ __device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, 
 // would leave more entries than 'limit' (the top's address there) allows, and,
 // with kTies, when two crossings lie within 2.5e-7 of each other, twice the
 // rounding that lets the order of their tests decide.
-template <bool kTies>
+template <bool kTies, bool kOrigin>
 __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const PV_GLOBAL Tri* __restrict__ tris,
                                 const Ray& r, const Slab& q, bool any, StackCol col, StackCol limit, Walk& w,
                                 int min_active) {
@@ -623,19 +692,26 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
     const float ts = __builtin_canonicalizef((tb - r.tmin) * kTScale);  // tb as a slab parameter
     while (cur >= 0) {
       const int32_t below = top[0], below2 = top[-kBlock];
-      // node records are addressed by a 32-bit byte offset (arrays < 4 GiB)
-      const PV_GLOBAL uint4* np = (const PV_GLOBAL uint4*)((const PV_GLOBAL char*)nodes + ((uint32_t)cur << 6));
+      // node records are addressed by a 32-bit byte offset (arrays < 4 GiB); a
+      // code's low byte is not its own
+      const PV_GLOBAL uint4* np = (const PV_GLOBAL uint4*)((const PV_GLOBAL char*)nodes + (kOrigin ? ((uint32_t)cur >> kOriginShift) << 6 : (uint32_t)cur << 6));
       const uint4 na = np[0], nb = np[1], nc = np[2], nd = np[3];
       const uint32_t pl[12] = {na.x, na.y, na.z, na.w, nb.x, nb.y, nb.z, nb.w, nc.x, nc.y, nc.z, nc.w};
       int32_t c[4] = {(int32_t)nd.x, (int32_t)nd.y, (int32_t)nd.z, (int32_t)nd.w};
       float e[4];
       uint64_t h[4];  // entered children, as wave masks
+      float3 oi = q.oi;
+      if (kOrigin) {
+        oi.x = __builtin_fmaf((float)(nd.x & 255u), q.inv.x, oi.x);
+        oi.y = __builtin_fmaf((float)(nd.y & 255u), q.inv.y, oi.y);
+        oi.z = __builtin_fmaf((float)(nd.z & 255u), q.inv.z, oi.z);
+      }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         float nx, ny, nz, fx, fy, fz;
-        plane_pair(pl[3 * k], q.rx, q.inv.x, q.oi.x, &nx, &fx);
-        plane_pair(pl[3 * k + 1], q.ry, q.inv.y, q.oi.y, &ny, &fy);
-        plane_pair(pl[3 * k + 2], q.rz, q.inv.z, q.oi.z, &nz, &fz);
+        plane_pair(pl[3 * k], q.rx, q.inv.x, oi.x, &nx, &fx);
+        plane_pair(pl[3 * k + 1], q.ry, q.inv.y, oi.y, &ny, &fy);
+        plane_pair(pl[3 * k + 2], q.rz, q.inv.z, oi.z, &nz, &fz);
         e[k] = __builtin_amdgcn_fmed3f(fmaxf(fmaxf(nx, ny), nz), 0.0f, 1.0f);
         const float ex = fminf(fminf(fx, fy), fz);
         // the slab interval meets [tmin, tb]
@@ -692,7 +768,8 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
     }
     bool found = false;
     while (leaf != 0) {
-      const uint32_t f = leaf_first(leaf), n = leaf_count(leaf);
+      const int32_t code = leaf >> (kOrigin ? kOriginShift : 0u);
+      const uint32_t f = leaf_first(code), n = leaf_count(code);
       for (uint32_t i = f; i < f + n; ++i) {
         float t;
         bool near_tb = false;
@@ -720,6 +797,16 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
   w.tb = tb;
   w.rec = rec;
   w.redo = redo;
+}
+
+// walk_run in the scene's form of nodes
+template <bool kTies>
+__device__ inline void walk_scene(const SceneDev& S, const Ray& r, const Slab& q, bool any, StackCol col, StackCol limit,
+                                  Walk& w, int min_active) {
+  if (S.wshift)
+    walk_run<kTies, true>(G(S.wide), G(S.tris), r, q, any, col, limit, w, min_active);
+  else
+    walk_run<kTies, false>(G(S.wide), G(S.tris), r, q, any, col, limit, w, min_active);
 }
 
 // The answer to a world-space query by the order that settles near ties: the

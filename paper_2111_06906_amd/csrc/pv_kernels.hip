@@ -684,7 +684,8 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
                                      mi[6] * tb.x + mi[7] * tb.y + mi[8] * tb.z);
                 const float3 od = sub(ob, oa);
                 const float3 binv = rcp3(od);
-                qb = make_slab(binv, f3(-(oa.x * binv.x), -(oa.y * binv.y), -(oa.z * binv.z)), S->qinv, r.tmin);
+                qb = make_slab(binv, f3((S->qobj - oa.x) * binv.x, (S->qobj - oa.y) * binv.y, (S->qobj - oa.z) * binv.z),
+                               S->qinv, r.tmin);
                 root = moroot[only];
               }
             }
@@ -701,7 +702,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
       continue;
     }
     if (busy) {
-      walk_run<false>(G(S->wide), G(S->tris), r, qb, true, col, limit, w, min_active);
+      walk_scene<false>(*S, r, qb, true, col, limit, w, min_active);
       if (walk_done(w)) {
         if (w.redo) walk_exact(G(S->nodes), G(S->tris), r, 1.0f - r.tmin, G(S->top)[vis_task ? 0 : 1], true, col, w);
         if (w.rec != kRecNone) atomicMin(&W.first[gp], j);
@@ -1399,7 +1400,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
     // instructions beside the walk's thousands, and hold no registers outside
     if (tracing) {
       const Slab q = world_slab(S, ray_origin(r), rcp3(r.d), r.tmin);
-      walk_run<true>(G(S.wide), G(S.tris), r, q, any, col, limit, wk, min_active);
+      walk_scene<true>(S, r, q, any, col, limit, wk, min_active);
     }
     // ---- lanes whose walk is finished advance their path.  What several
     // modes share is done once for all of them: the new vertex with its

@@ -420,8 +420,8 @@ __global__ __launch_bounds__(kBlock) void k_lbvh_nodes(SceneDev* __restrict__ sc
 // four-wide form of binary node i of a rebuilt tree: an internal child gives
 // way to its own two (every node gets one; a walk meets those of every second
 // level)
-__device__ inline void collapse_rebuilt(const SceneDev& S, const ObjDev& ob, uint32_t i) {
-  const PlaneWriter wide(S);
+__device__ inline void collapse_rebuilt(const SceneDev& S, const ObjDev& ob, uint32_t o, uint32_t i) {
+  const PlaneWriter wide(S, o, S.obj_xf_cur);
   const PV_GLOBAL Node* nodes = G(S.nodes);
   const Node nd = nodes[ob.lbvh_base + i];
   const uint32_t w = 4 * (ob.lbvh_wbase + i);
@@ -429,7 +429,7 @@ __device__ inline void collapse_rebuilt(const SceneDev& S, const ObjDev& ob, uin
   const float* f = reinterpret_cast<const float*>(&nd);
   auto put = [&](uint32_t slot, const float* b, int32_t code) {
     wide.put(slot, b[0], b[1], b[2], b[3], b[4], b[5]);
-    wide.child(slot, code < 0 ? code : code - (int32_t)ob.lbvh_base + (int32_t)ob.lbvh_wbase);
+    wide.child(slot, wide_code(code < 0 ? code : code - (int32_t)ob.lbvh_base + (int32_t)ob.lbvh_wbase, wide.shift));
   };
   for (uint32_t side = 0; side < 2; ++side) {
     if (ch[side] < 0) {
@@ -462,7 +462,7 @@ __global__ __launch_bounds__(kBlock) void k_lbvh_depth(const SceneDev* __restric
         ++depth;
     const ObjDev ob = S.objs[o];
     const uint32_t i = g - ob.tri_base;
-    if (i + 1 < ob.n_tris) collapse_rebuilt(S, ob, i);
+    if (i + 1 < ob.n_tris) collapse_rebuilt(S, ob, o, i);
   }
   // one atomic per wave when the wave's leaves share an object
   const uint64_t act = __ballot(valid);
@@ -488,14 +488,15 @@ __global__ void k_lbvh_finish(SceneDev* __restrict__ scenes, LbvhWork W, const u
   Box b;
   int32_t root, wroot;
   if (ob.n_tris == 1) {
-    root = wroot = leaf_code(S.n_static + val[ob.tri_base], 1);
+    root = leaf_code(S.n_static + val[ob.tri_base], 1);
+    wroot = wide_code(root, S.wshift);
     b = tri_box(S.tris[leaf_first(root)]);
   } else {
     // the rebuilt tree replaces the refit topology only within the depth the
     // traversal stacks were sized for
     if (W.odepth[o] > max_depth) return;
     root = (int32_t)ob.lbvh_base;
-    wroot = (int32_t)ob.lbvh_wbase;
+    wroot = wide_code((int32_t)ob.lbvh_wbase, S.wshift);
     b = range_box(W.pyr, W.n_dyn, ob.tri_base, ob.tri_base + ob.n_tris);
   }
   S.obj_aabb[6 * o + 0] = b.lo.x;
@@ -605,7 +606,7 @@ __device__ inline void build_top(SceneDev& S) {
   const uint32_t wfirst = S.wtop_base + (uint32_t)which * kTopNodes;
   // root codes of a range of one or more items (its node's index is its split position - 1)
   auto bin = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].x : (int32_t)(first + (a + b) / 2 - 1); };
-  auto wid = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].y : (int32_t)(wfirst + (a + b) / 2 - 1); };
+  auto wid = [&](uint32_t a, uint32_t b) { return b - a == 1 ? code[a].y : wide_code((int32_t)(wfirst + (a + b) / 2 - 1), wide.shift); };
   if (lane + 1 < n) {
     // the range that splits at lane + 1
     uint32_t a = 0, b = n, depth = 0;
@@ -690,7 +691,7 @@ __device__ inline void build_top(SceneDev& S) {
       wide.none(w + 2);
       wide.none(w + 3);
     }
-    wroot = (int32_t)(wfirst + n - 1);
+    wroot = wide_code((int32_t)(wfirst + n - 1), wide.shift);
   } else if (above) {
     root = sroot;
     wroot = swroot;
@@ -790,7 +791,10 @@ __global__ __launch_bounds__(kBlock) void k_refit(SceneDev* __restrict__ scenes,
     nd.b = make_float4(b0.hi.y, b0.hi.z, b1.lo.x, b1.lo.y);
     nd.c = make_float4(b1.lo.z, b1.hi.x, b1.hi.y, b1.hi.z);
     const uint2 ws = S.wslot[i];
-    const PlaneWriter wide(S);
+    const PlaneWriter wide(S, S.dspan_obj[i], in.obj_tab ? in.obj_tab[tile.x] : in.obj);
+    // slot 0 of a node always holds a child: its writer brings the origin
+    if (ws.x != kSlotNone && (ws.x & 3u) == 0) wide.put_origin(ws.x >> 2);
+    if (ws.y != kSlotNone && (ws.y & 3u) == 0) wide.put_origin(ws.y >> 2);
     if (ws.x != kSlotNone) wide.put(ws.x, b0.lo.x, b0.lo.y, b0.lo.z, b0.hi.x, b0.hi.y, b0.hi.z);
     if (ws.y != kSlotNone) wide.put(ws.y, b1.lo.x, b1.lo.y, b1.lo.z, b1.hi.x, b1.hi.y, b1.hi.z);
     return;

@@ -217,3 +217,62 @@ def test_object_boxes_at_edges(E, sizes):
             assert h["valid"] and not h["rebuilt"], (f, o, h)
     ctx.close()
     _lockstep(E, sc, 4, 0.01, "objects of %s triangles" % sizes)
+
+
+# Nodes have origins in scenes of up to 2^20 - 1 triangles: both sides of that
+# size, with refit and rebuilt objects, and both kinds in one batch, give the
+# paths of the scene without the triangles that nothing can reach.
+def _tiny_beside(n_extra):
+    sc = scenes.make_tiny(n_paths=1500 + 3, max_bounces=3, frames=4, seed=29)
+    rng = np.random.default_rng(29)
+    far = (rng.uniform(3.0, 3.2, (n_extra, 1, 3)) + rng.uniform(-1e-3, 1e-3, (n_extra, 3, 3))).astype(np.float32)
+    sc.static_verts = np.concatenate([sc.static_verts, far])
+    sc.static_mat = np.concatenate([sc.static_mat, np.zeros(n_extra, np.uint32)])
+    # the far triangles' side of the box is closed
+    wall = np.array([[[0, 0, 1], [1, 1, 1], [0, 1, 1]], [[0, 0, 1], [1, 0, 1], [1, 1, 1]]], np.float32)
+    sc.static_verts[:2], keep = wall, sc.static_verts[:2].copy()
+    sc.static_verts = np.concatenate([sc.static_verts, keep])
+    sc.static_mat = np.concatenate([sc.static_mat, np.zeros(2, np.uint32)])
+    return sc
+
+
+def _three_frames(E, sc):
+    ctx = E.Context(sc)
+    st = ctx.new_store()
+    ctx.frame_begin(0)
+    ctx.initial_trace(st, 29)
+    out = []
+    for f in range(1, 4):
+        ctx.set_tuning(object_rebuild=1 if f == 3 else 0)
+        ctx.frame_begin(f)
+        ctx.verify(st)
+        ctx.retrace(st, 0.01, 29, f)
+        d = st.to_numpy()
+        out.append({k: d[k] for k in ("pos", "energy", "info", "origin")})
+    ctx.close()
+    return out
+
+
+def test_scene_sizes_with_and_without_node_origins(E):
+    plain = _three_frames(E, _tiny_beside(0))
+    n = (1 << 20) - 1 - (12 + 12)  # box and cube: 24 triangles
+    for extra in (n, n + 1):
+        for f, (a, b) in enumerate(zip(plain, _three_frames(E, _tiny_beside(extra)))):
+            for k in a:
+                np.testing.assert_array_equal(a[k], b[k], err_msg="%s, frame %d, %d extra" % (k, f + 1, extra))
+    scs = [_tiny_beside(0), _tiny_beside(n + 1)]
+    ctxs = [E.Context(sc) for sc in scs]
+    sts = [c.new_store() for c in ctxs]
+    for c, st in zip(ctxs, sts):
+        c.frame_begin(0)
+        c.initial_trace(st, 29)
+    bt = E.Batch(ctxs, sts, 0.01, 29)
+    for f in (1, 2):
+        bt.frame(f)
+        for st in sts:
+            d = st.to_numpy()
+            for k in plain[f - 1]:
+                np.testing.assert_array_equal(plain[f - 1][k], d[k], err_msg="batch %s, frame %d" % (k, f))
+    bt.close()
+    for c in ctxs:
+        c.close()

@@ -53,6 +53,25 @@ int main() {
     const double a = half_value(w & 0xFFFFu) / (double)s + (double)c, b = half_value(w >> 16) / (double)s + (double)c;
     if (!(a <= lo && hi <= b) && ++bad < 20) std::printf("box %.9g %.9g c %.9g s %g: %.9g %.9g\n", lo, hi, c, s, a, b);
   }
+  // with a node's origin: a box inside a grid of 256 steps, origin near its
+  // middle (or clamped, for boxes outside), planes relative to it
+  for (int i = 0; i < 2000000; ++i) {
+    const float half = std::ldexp(1.0f, (int)(g() % 24) - 8);
+    const float s = 128.0f / half, c = (float)(U(g) * half * 4.0) - half;
+    const float size = half * std::ldexp(1.0f, -(int)(g() % 16));
+    const float lo = (float)(c + (i % 8 ? 2.0 : 5.0) * half * std::fabs(U(g))), hi = lo + (float)std::fabs(U(g) * size);
+    const uint32_t o = pv::wide_origin(0.5f * lo + 0.5f * hi, c, s);
+    const uint32_t w = pv::wide_planes(lo, hi, c, s, (float)o);
+    const double a = (half_value(w & 0xFFFFu) + (double)o) / (double)s + (double)c;
+    const double b = (half_value(w >> 16) + (double)o) / (double)s + (double)c;
+    // inside the grid: within an FP16 step of the distance to the origin, and
+    // the slack
+    const double reach = std::max(std::fabs((lo - (double)c) * s - o), std::fabs((hi - (double)c) * s - o));
+    const double slack = (reach * 2e-3 + 4e-4) / s;
+    const bool tight = a >= lo - slack && b <= hi + slack;
+    if (!(o <= 255u && a <= lo && hi <= b && tight) && ++bad < 30)
+      std::printf("box %.9g %.9g c %.9g s %g origin %u: %.9g %.9g\n", lo, hi, c, s, o, a, b);
+  }
   std::printf("planes checked, %ld wrong\n", bad);
   return bad != 0;
 }
