@@ -62,6 +62,7 @@ struct pv_ctx {
   uint2* d_place_tiles = nullptr;  // tiles of the frame's beginning (launch_frame_begin)
   uint2* d_refit_tiles = nullptr;
   uint32_t n_place_tiles = 0, n_refit_tiles = 0;
+  uint32_t max_obj_tris = 0;       // triangles of the largest object
   // transforms of the next frame, written sparsely by pv_update_transforms /
   // pv_update_lights (and densely by pv_frame_begin); a pending update begins
   // the frame at the next call that reads the scene
@@ -1195,7 +1196,8 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       lw.n_nodes = lbvh_nodes;
       hs.pyr = lw.pyr;
       hs.n_dyn = nd;
-      hs.pyr_full = *std::max_element(d->h_obj_tris, d->h_obj_tris + d->n_objects) > pv::kLinearTris ? 1u : 0u;
+      ctx->max_obj_tris = *std::max_element(d->h_obj_tris, d->h_obj_tris + d->n_objects);
+      hs.pyr_full = ctx->max_obj_tris > pv::kLinearTris ? 1u : 0u;
     }
     hs.nodes = d_nodes;
     hs.wide = d_wide;
@@ -1381,7 +1383,8 @@ pv_status begin_frame(pv_ctx* ctx, const float* d_obj_xf, const float* d_light_x
   // triangles; the refit topology (kept current above) stays the hierarchy of
   // an object whose rebuilt tree is too deep for the traversal stacks
   if (ctx->object_rebuild) {
-    CK(pv::launch_rebuild_objects(ctx->d_scene, ctx->lw, ctx->n_objects, ctx->lbvh_depth, ctx->stream));
+    CK(pv::launch_rebuild_objects(ctx->d_scene, ctx->lw, ctx->n_objects, ctx->max_obj_tris, ctx->lbvh_depth,
+                                  ctx->stream));
     CK(pv::launch_build_top(ctx->d_scene, 1, ctx->stream));
   }
   ctx->frame_started = true;

@@ -32,8 +32,10 @@ hipError_t launch_frame_begin(SceneDev* scenes, int n_scenes, const uint2* place
                               hipStream_t s);
 // every object's hierarchy rebuilt from its current world triangles (one
 // scene): linear BVH over Morton codes, into the objects' rebuild regions; an
-// object whose tree is deeper than max_depth keeps its current hierarchy
-hipError_t launch_rebuild_objects(SceneDev* scenes, LbvhWork W, uint32_t n_obj, uint32_t max_depth, hipStream_t s);
+// object whose tree is deeper than max_depth keeps its current hierarchy;
+// max_tris: triangles of the largest object
+hipError_t launch_rebuild_objects(SceneDev* scenes, LbvhWork W, uint32_t n_obj, uint32_t max_tris, uint32_t max_depth,
+                                  hipStream_t s);
 // sort tiles of the rebuild for n_dyn triangles (W.hist holds 256 per tile)
 uint32_t lbvh_sort_tiles(uint32_t n_dyn);
 // entries of W.pyr (two float4 each) for n_dyn triangles

@@ -11,6 +11,8 @@
 //                   keeps the order of equal digits (wave ballots rank the keys
 //                   of one digit inside a wave); the scatter scans the counts
 //                   itself when there are few tiles
+//   k_lbvh_sort     the four above in one launch, one workgroup per object,
+//                   where every object fits a workgroup's memory
 //   k_lbvh_leaves / padded triangle boxes in sorted order and a pyramid of
 //   k_lbvh_pyramid  their unions over aligned power-of-two blocks
 //   k_lbvh_nodes    one thread per internal node of each object's radix tree:
@@ -44,6 +46,7 @@ constexpr uint32_t kSortTile = kSortThreads * kSortItems;  // keys per sort tile
 constexpr int kDigits = 256;
 constexpr int kSortPasses = 5;          // 8-bit digits over the 36 key bits (6 object + 30 Morton)
 constexpr uint32_t kFusedTiles = 256;   // up to this many tiles the scatter scans the counts itself
+constexpr uint32_t kSmallSort = 8192;   // objects of up to this many triangles are sorted by one workgroup each
 constexpr int kLowLevels = 8;           // pyramid levels built inside one 256-entry workgroup
 constexpr uint32_t kDepthGuard = 64;    // > 30 + 28: no radix tree here is that deep
 static_assert(kSortThreads == kDigits, "one thread per digit in the tile histograms");
@@ -175,14 +178,13 @@ __device__ inline int prefix(const uint64_t* __restrict__ key, uint32_t start, i
 
 }  // namespace
 
-__global__ __launch_bounds__(1024) void k_lbvh_bounds(const SceneDev* __restrict__ scenes, LbvhWork W) {
+// centroid bounds (lo xyz, hi xyz) of an object's triangles by a workgroup of
+// 1024 threads, to all
+__device__ inline void object_bounds(const SceneDev& S, const ObjDev& ob, float b[6]) {
   __shared__ float red[6][1024 / 64];
-  const SceneDev& S = scenes[0];
-  const uint32_t o = blockIdx.x;
-  const ObjDev ob = S.objs[o];
   float lo[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
   float hi[3] = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-  for (uint32_t i = threadIdx.x; i < ob.n_tris; i += blockDim.x) {
+  for (uint32_t i = threadIdx.x; i < ob.n_tris; i += 1024) {
     const float3 c = centroid(S.tris[S.n_static + ob.tri_base + i]);
     lo[0] = fminf(lo[0], c.x), lo[1] = fminf(lo[1], c.y), lo[2] = fminf(lo[2], c.z);
     hi[0] = fmaxf(hi[0], c.x), hi[1] = fmaxf(hi[1], c.y), hi[2] = fmaxf(hi[2], c.z);
@@ -199,13 +201,29 @@ __global__ __launch_bounds__(1024) void k_lbvh_bounds(const SceneDev* __restrict
       red[3 + k][w] = hi[k];
     }
   __syncthreads();
-  if (threadIdx.x < 6) {
-    const int k = (int)threadIdx.x;
+  for (int k = 0; k < 6; ++k) {
     float v = red[k][0];
-    for (uint32_t q = 1; q < blockDim.x / 64; ++q) v = k < 3 ? fminf(v, red[k][q]) : fmaxf(v, red[k][q]);
-    W.cbox[6 * o + k] = v;
+    for (uint32_t q = 1; q < 1024 / 64; ++q) v = k < 3 ? fminf(v, red[k][q]) : fmaxf(v, red[k][q]);
+    b[k] = v;
   }
-  if (threadIdx.x == 0) W.odepth[o] = 0;
+}
+
+// Morton code of a triangle's centroid in its object's centroid box
+__device__ inline uint32_t morton(const Tri& t, const float b[6]) {
+  const float3 c = centroid(t);
+  return (spread3(quantise(c.x, b[0], b[3])) << 2) | (spread3(quantise(c.y, b[1], b[4])) << 1) |
+         spread3(quantise(c.z, b[2], b[5]));
+}
+
+__global__ __launch_bounds__(1024) void k_lbvh_bounds(const SceneDev* __restrict__ scenes, LbvhWork W) {
+  const SceneDev& S = scenes[0];
+  const uint32_t o = blockIdx.x;
+  float b[6];
+  object_bounds(S, S.objs[o], b);
+  if (threadIdx.x == 0) {
+    for (int k = 0; k < 6; ++k) W.cbox[6 * o + k] = b[k];
+    W.odepth[o] = 0;
+  }
 }
 
 __global__ __launch_bounds__(kBlock) void k_lbvh_keys(const SceneDev* __restrict__ scenes, LbvhWork W) {
@@ -213,12 +231,102 @@ __global__ __launch_bounds__(kBlock) void k_lbvh_keys(const SceneDev* __restrict
   const uint32_t r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= W.n_dyn) return;
   const uint32_t o = object_of_record(S, r);
-  const float3 c = centroid(S.tris[S.n_static + r]);
-  const float* b = W.cbox + 6 * o;
-  const uint32_t m = (spread3(quantise(c.x, b[0], b[3])) << 2) | (spread3(quantise(c.y, b[1], b[4])) << 1) |
-                     spread3(quantise(c.z, b[2], b[5]));
-  W.key[0][r] = ((uint64_t)o << 30) | m;
+  W.key[0][r] = ((uint64_t)o << 30) | morton(S.tris[S.n_static + r], W.cbox + 6 * o);
   W.val[0][r] = r;
+}
+
+// Keys and their sort for an object of at most kSmallSort triangles by one
+// workgroup: the same stable order by (object, code) as the passes below, whose
+// twelve dependent launches took 85 us for 24 objects of 1,024 triangles.  A
+// thread keeps its keys in registers, wave w those of the w-th sixteenth of the
+// order, 64 at a time; a pass counts its digits per wave (ballots rank equal
+// digits), scans the counts digit by digit, and moves the keys through LDS.
+constexpr uint32_t kSortWaves = 1024 / 64;
+constexpr uint32_t kSortRounds = kSmallSort / 1024;
+
+__global__ __launch_bounds__(1024) void k_lbvh_sort(const SceneDev* __restrict__ scenes, LbvhWork W) {
+  __shared__ uint32_t skey[kSmallSort];
+  __shared__ uint16_t sval[kSmallSort], cnt[kSortWaves][kDigits];
+  __shared__ uint32_t wsum[kDigits / 64];
+  const SceneDev& S = scenes[0];
+  const uint32_t o = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = lane_of();
+  const ObjDev ob = S.objs[o];
+  const uint32_t n = ob.n_tris;
+  float b[6];
+  object_bounds(S, ob, b);
+  const uint32_t rounds = (n + 1023) / 1024, first = wave * rounds * 64 + lane;
+  uint32_t key[kSortRounds], val[kSortRounds], pos[kSortRounds];
+#pragma unroll
+  for (uint32_t i = 0; i < kSortRounds; ++i) {
+    const uint32_t r = first + i * 64;
+    val[i] = r;
+    key[i] = i < rounds && r < n ? morton(S.tris[S.n_static + ob.tri_base + r], b) : 0u;
+  }
+  for (int shift = 0; shift < 30; shift += 8) {
+    for (uint32_t d = lane; d < kDigits; d += 64) cnt[wave][d] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kSortRounds; ++i) {
+      if (i >= rounds) break;
+      const bool have = first + i * 64 < n;
+      const uint32_t d = (key[i] >> shift) & (kDigits - 1u);
+      uint64_t peers = __ballot(have);
+      for (int bit = 0; bit < 8; ++bit) {
+        const bool set = ((d >> bit) & 1u) != 0;
+        const uint64_t m = __ballot(have && set);
+        peers &= set ? m : ~m;
+      }
+      const uint32_t before = have ? cnt[wave][d] : 0u;
+      pos[i] = before + (uint32_t)__popcll(peers & lanes_below());
+      __builtin_amdgcn_wave_barrier();  // every lane has read before the last of its peers writes
+      if (have && (peers >> lane) == 1ull) cnt[wave][d] = (uint16_t)(pos[i] + 1);
+      __builtin_amdgcn_wave_barrier();
+    }
+    __syncthreads();
+    // a thread per digit: exclusive scan over (digit, wave)
+    uint32_t total = 0, x = 0;
+    if (tid < (uint32_t)kDigits) {
+      for (uint32_t w = 0; w < kSortWaves; ++w) total += cnt[w][tid];
+      x = total;
+      for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(x, off, 64);
+        if ((int)lane >= off) x += y;
+      }
+      if (lane == 63) wsum[wave] = x;
+    }
+    __syncthreads();
+    if (tid < (uint32_t)kDigits) {
+      uint32_t at = x - total;
+      for (uint32_t w = 0; w < wave; ++w) at += wsum[w];
+      for (uint32_t w = 0; w < kSortWaves; ++w) {
+        const uint32_t c = cnt[w][tid];
+        cnt[w][tid] = (uint16_t)at;
+        at += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kSortRounds; ++i) {
+      if (i >= rounds || first + i * 64 >= n) break;
+      const uint32_t q = pos[i] + cnt[wave][(key[i] >> shift) & (kDigits - 1u)];
+      skey[q] = key[i];
+      sval[q] = (uint16_t)val[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (uint32_t i = 0; i < kSortRounds; ++i) {
+      if (i >= rounds || first + i * 64 >= n) break;
+      key[i] = skey[first + i * 64];
+      val[i] = sval[first + i * 64];
+    }
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < kSortRounds; ++i) {
+    if (i >= rounds || first + i * 64 >= n) break;
+    W.key[0][ob.tri_base + first + i * 64] = ((uint64_t)o << 30) | key[i];
+    W.val[0][ob.tri_base + first + i * 64] = ob.tri_base + val[i];
+  }
+  if (tid == 0) W.odepth[o] = 0;
 }
 
 // digit counts of one tile, stored digit-major (hist[digit * tiles + tile]),
@@ -871,25 +979,30 @@ uint32_t lbvh_pyramid_entries(uint32_t n_dyn) {
   return std::max(pyr_entries(n_dyn), pyr_level(n_dyn, kLowLevels + 1));
 }
 
-hipError_t launch_rebuild_objects(SceneDev* scenes, LbvhWork W, uint32_t n_obj, uint32_t max_depth, hipStream_t s) {
+hipError_t launch_rebuild_objects(SceneDev* scenes, LbvhWork W, uint32_t n_obj, uint32_t max_tris, uint32_t max_depth,
+                                  hipStream_t s) {
   if (!W.n_dyn || !n_obj) return hipSuccess;
-  hipLaunchKernelGGL(k_lbvh_bounds, dim3(n_obj), dim3(1024), 0, s, scenes, W);
   const uint32_t nb = (W.n_dyn + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL(k_lbvh_keys, dim3(nb), dim3(kBlock), 0, s, scenes, W);
-  const uint32_t tiles = lbvh_sort_tiles(W.n_dyn);
   int src = 0;
-  for (int pass = 0; pass < kSortPasses; ++pass) {
-    const int shift = 8 * pass;
-    hipLaunchKernelGGL(k_lbvh_hist, dim3(tiles), dim3(kSortThreads), 0, s, W.key[src], W.n_dyn, shift, W.hist, tiles);
-    const uint32_t* hoff = nullptr;
-    if (tiles > kFusedTiles) {
-      hipError_t e = launch_scan(W.hist, W.hoff, kDigits * tiles, W.htotal, W.scan_tmp, s);
-      if (e != hipSuccess) return e;
-      hoff = W.hoff;
+  if (max_tris <= kSmallSort) {
+    hipLaunchKernelGGL(k_lbvh_sort, dim3(n_obj), dim3(1024), 0, s, scenes, W);
+  } else {
+    hipLaunchKernelGGL(k_lbvh_bounds, dim3(n_obj), dim3(1024), 0, s, scenes, W);
+    hipLaunchKernelGGL(k_lbvh_keys, dim3(nb), dim3(kBlock), 0, s, scenes, W);
+    const uint32_t tiles = lbvh_sort_tiles(W.n_dyn);
+    for (int pass = 0; pass < kSortPasses; ++pass) {
+      const int shift = 8 * pass;
+      hipLaunchKernelGGL(k_lbvh_hist, dim3(tiles), dim3(kSortThreads), 0, s, W.key[src], W.n_dyn, shift, W.hist, tiles);
+      const uint32_t* hoff = nullptr;
+      if (tiles > kFusedTiles) {
+        hipError_t e = launch_scan(W.hist, W.hoff, kDigits * tiles, W.htotal, W.scan_tmp, s);
+        if (e != hipSuccess) return e;
+        hoff = W.hoff;
+      }
+      hipLaunchKernelGGL(k_lbvh_scatter, dim3(tiles), dim3(kSortThreads), 0, s, W.key[src], W.val[src], W.key[src ^ 1],
+                         W.val[src ^ 1], W.n_dyn, shift, W.hist, hoff, tiles);
+      src ^= 1;
     }
-    hipLaunchKernelGGL(k_lbvh_scatter, dim3(tiles), dim3(kSortThreads), 0, s, W.key[src], W.val[src], W.key[src ^ 1],
-                       W.val[src ^ 1], W.n_dyn, shift, W.hist, hoff, tiles);
-    src ^= 1;
   }
   hipLaunchKernelGGL(k_lbvh_leaves, dim3(nb), dim3(kBlock), 0, s, scenes, W, W.val[src]);
   if (W.n_dyn > (1u << kLowLevels)) hipLaunchKernelGGL(k_lbvh_pyramid, dim3(1), dim3(1024), 0, s, scenes, 1u);

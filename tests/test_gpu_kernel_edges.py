@@ -276,3 +276,36 @@ def test_scene_sizes_with_and_without_node_origins(E):
     bt.close()
     for c in ctxs:
         c.close()
+
+
+# The rebuild's sort: one triangle, both sides of a wave, of a round of 1,024,
+# of the 8,192 triangles that one workgroup sorts, with many equal codes.  The
+# hierarchies are those of the sort in passes, which an object past that size
+# brings for all of them.
+@pytest.mark.parametrize("n", [2, 64, 65, 1024, 1025, 8191, 8192])
+def test_small_and_large_sorts_agree(E, n):
+    def objects(more):
+        rng = np.random.default_rng(n)
+        tris = (rng.integers(-20, 21, (n, 1, 3)) * 0.005 + rng.uniform(-0.02, 0.02, (1, 3, 3))).astype(np.float32)
+        big = (rng.uniform(-0.05, 0.05, (8193, 1, 3)) + rng.uniform(-0.01, 0.01, (8193, 3, 3))).astype(np.float32)
+        sc = scenes.make_tiny(n_paths=1200, max_bounces=3, frames=3, seed=31)
+        sc.obj_local = [tris, big[:8192 + more], tris[:1]]
+        sc.obj_mat = [np.ones(len(t), np.uint32) for t in sc.obj_local]
+        xf = np.repeat(sc.obj_xforms, 3, axis=1).copy()
+        for o in range(3):
+            xf[:, o, 3] += 0.2 * o
+        sc.obj_xforms = xf
+        return sc
+
+    infos = []
+    for more in (0, 1):
+        ctx = E.Context(objects(more))
+        ctx.set_tuning(object_rebuild=1)
+        for f in range(2):
+            ctx.frame_begin(f)
+        infos.append([ctx.object_hierarchy_info(o) for o in range(3)])
+        for o, h in enumerate(infos[-1]):
+            assert h["valid"], (o, h)
+        ctx.close()
+    for o in (0, 2):
+        assert infos[0][o] == infos[1][o], (o, infos[0][o], infos[1][o])
