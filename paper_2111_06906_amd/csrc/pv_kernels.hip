@@ -1138,6 +1138,12 @@ __device__ inline float3 reflect_energy(const SceneDev& S, float3 e, uint32_t ma
   return f3(__fmul_rn(e.x, rho[0]), __fmul_rn(e.y, rho[1]), __fmul_rn(e.z, rho[2]));
 }
 
+// a . b with the order of its roundings spelled out, x's or y's product rounded
+// first: what Equation 2 compares may lie within a rounding of its threshold,
+// where a product contracted another way decides another way
+__device__ inline float dot_x(float3 a, float3 b) { return fmaf(a.z, b.z, fmaf(a.y, b.y, a.x * b.x)); }
+__device__ inline float dot_y(float3 a, float3 b) { return fmaf(a.z, b.z, fmaf(a.x, b.x, a.y * b.y)); }
+
 __device__ inline bool eq2(float3 en, float3 eo, float T) {
   float d0 = __fsub_rn(en.x, eo.x), d1 = __fsub_rn(en.y, eo.y), d2 = __fsub_rn(en.z, eo.z);
   float t0 = __fmul_rn(T, eo.x), t1 = __fmul_rn(T, eo.y), t2 = __fmul_rn(T, eo.z);
@@ -1466,8 +1472,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
           }
           float3 xc = vertex(S, L.p, j + 2);
           float3 d2 = sub(xc, x);
-          float c1 = dot(qd, nh), l2 = length(d2);
-          float c2 = l2 > 0.0f ? dot(d2, nh) / l2 : 0.0f;
+          float c1 = dot_y(qd, nh), l2 = sqrtf(dot_x(d2, d2));
+          float c2 = l2 > 0.0f ? dot_y(d2, nh) / l2 : 0.0f;
           float3 eN = (c1 * c2 < 0.0f) ? reflect_energy(S, en, mat) : f3(0.0f, 0.0f, 0.0f);
           if (S.energy_test == PV_ENERGY_COSINE_RATIO && c1 * c2 < 0.0f) {
             // the kept direction's cosine at the new vertex over the one at the
@@ -1476,7 +1482,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
             const float3 o0 = tri_vertex(to, 0);
             const float3 no = cross(sub(tri_vertex(to, 1), o0), sub(tri_vertex(to, 2), o0));
             const float3 d3 = sub(xc, vertex(S, L.p, j + 1));
-            const float den = fabsf(dot(d3, no)), num = fabsf(c2) * length(d3) * length(no);
+            const float den = fabsf(dot_x(d3, no));
+            const float num = fabsf(c2) * sqrtf(dot_x(d3, d3)) * sqrtf(dot_y(no, no));
             const float ratio = den > 0.0f ? num / den : 0.0f;
             eN = mul(eN, ratio);
           }
@@ -1487,7 +1494,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
             break;
           }
           accepted = true;
-          float dist = length(sub(x, vertex(S, L.p, j + 1)));
+          const float3 step = sub(x, vertex(S, L.p, j + 1));
+          float dist = sqrtf(dot_x(step, step));
           auto moved = [&](uint32_t id) { return tab ? on_moved_obj(*tab, id) : on_moved_obj(S, id); };
           if (dist <= S.eps_close && !moved(h.gid) && !moved(vertex_hit(S, L.p, j + 1)) &&
               !moved(vertex_hit(S, L.p, j + 2))) {
