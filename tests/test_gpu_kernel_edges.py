@@ -279,17 +279,17 @@ def test_scene_sizes_with_and_without_node_origins(E):
 
 
 # The rebuild's sort: one triangle, both sides of a wave, of a round of 1,024,
-# of the 8,192 triangles that one workgroup sorts, with many equal codes.  The
-# hierarchies are those of the sort in passes, which an object past that size
-# brings for all of them.
-@pytest.mark.parametrize("n", [2, 64, 65, 1024, 1025, 8191, 8192])
+# of the two sizes (8,192 and 16,384 triangles) that one workgroup sorts, with
+# many equal codes.  The hierarchies are those of the sort in passes, which an
+# object past that size brings for all of them.
+@pytest.mark.parametrize("n", [2, 64, 65, 1024, 1025, 8192, 8193, 16_383, 16_384])
 def test_small_and_large_sorts_agree(E, n):
     def objects(more):
         rng = np.random.default_rng(n)
         tris = (rng.integers(-20, 21, (n, 1, 3)) * 0.005 + rng.uniform(-0.02, 0.02, (1, 3, 3))).astype(np.float32)
-        big = (rng.uniform(-0.05, 0.05, (8193, 1, 3)) + rng.uniform(-0.01, 0.01, (8193, 3, 3))).astype(np.float32)
+        big = (rng.uniform(-0.05, 0.05, (16385, 1, 3)) + rng.uniform(-0.01, 0.01, (16385, 3, 3))).astype(np.float32)
         sc = scenes.make_tiny(n_paths=1200, max_bounces=3, frames=3, seed=31)
-        sc.obj_local = [tris, big[:8192 + more], tris[:1]]
+        sc.obj_local = [tris, big[:16385] if more else big[:1], tris[:1]]
         sc.obj_mat = [np.ones(len(t), np.uint32) for t in sc.obj_local]
         xf = np.repeat(sc.obj_xforms, 3, axis=1).copy()
         for o in range(3):
