@@ -1230,7 +1230,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     CK(upload(A, &d_dgid, dgid.data(), dgid.size(), s));
     {
       // record of each global triangle id in the leaf-order arrays (the
-      // refit topology's order, which k_transform keeps current)
+      // refit topology's order, which k_place keeps current)
       std::vector<uint32_t> grec((size_t)S + n_dyn, 0u);
       for (uint32_t i = 0; i < S; ++i) {
         grec[stris[i].gid] = i;

@@ -690,6 +690,7 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
   bool redo = w.redo;
   while (true) {
     const float ts = __builtin_canonicalizef((tb - r.tmin) * kTScale);  // tb as a slab parameter
+    const int alive = __popcll(__ballot(1));
     while (cur >= 0) {
       const int32_t below = top[0], below2 = top[-kBlock];
       // node records are addressed by a 32-bit byte offset (arrays < 4 GiB); a
@@ -755,11 +756,11 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
       leaf = post ? cur : leaf;
       cur = post ? next : cur;
       top = post ? top - kBlock : top;
-      // once at most a third of the lanes still here hold no leaf, the wave
-      // tests leaves: waiting for the last lane left 33 of 64 lanes active on
-      // average and took 5% longer on partial re-traces, waiting for half of
-      // them 1% longer on full traces
-      if (3 * __popcll(__ballot(leaf == 0)) <= __popcll(__ballot(1))) break;
+      // once at most a quarter of the lanes that began this descent are still
+      // here without a leaf, the wave tests leaves: full trace 3.49 ms (3.55
+      // with a third of those still here, 3.56 with half of all), 3M-path
+      // partial re-trace frame 2.04 ms (2.07, 2.09)
+      if (4 * __popcll(__ballot(leaf == 0)) <= alive) break;
     }
     if (leaf == 0 && is_leaf(cur)) {
       leaf = cur;

@@ -285,6 +285,18 @@ __device__ inline uint32_t wave_quota(uint32_t count, uint32_t waves) {
   return min(64u, max(1u, (count + waves - 1) / waves));
 }
 
+// Lanes below which a walk yields.  While there is work to deal, min_active.
+// Once the wave has asked in vain nothing takes a finished lane's place and
+// that number, sooner or later above the lanes left, would stop the walk after
+// every descent for the state machine: then a share of the lanes still walking
+// (half of what min_active is of a full wave).  With it a 60k-path
+// frame took 506 us instead of 547, a 300k-path camera frame 431 instead of
+// 463, a 750k-path spot frame 1015 instead of 1120, full trace 3.44 ms instead
+// of 3.49; a yield at the last lane only, 3.49.
+__device__ inline int yield_below(int min_active, bool drained, int walking) {
+  return drained ? max(1, walking * min_active / 128) : min_active;
+}
+
 // The counters are zero between launches: the last workgroup to end a launch
 // that dealt from them clears them again (arrivals are counted per group, then
 // over the groups, so that no word takes more than a few dozen additions).
@@ -701,8 +713,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
       if (__ballot(!drained) == 0) break;
       continue;
     }
+    const int yield = yield_below(min_active, __ballot(drained) != 0, (int)__popcll(__ballot(busy)));
     if (busy) {
-      walk_scene<false>(*S, r, qb, true, col, limit, w, min_active);
+      walk_scene<false>(*S, r, qb, true, col, limit, w, yield);
       if (walk_done(w)) {
         if (w.redo) walk_exact(G(S->nodes), G(S->tris), r, 1.0f - r.tmin, G(S->top)[vis_task ? 0 : 1], true, col, w);
         if (w.rec != kRecNone) atomicMin(&W.first[gp], j);
@@ -1210,14 +1223,15 @@ __device__ inline void clear_rows(const SceneDev& S, uint32_t p, uint32_t from) 
 __device__ inline float3 normalize3(float3 v) { return mul(v, 1.0f / length(v)); }
 
 
-// Bound by vector issue (91% of a full trace's cycles at five waves per SIMD).
-// 96 registers hold five waves without spills because little outlives a walk
+// Bound by vector issue (90% of a full trace's cycles at five waves per SIMD)
+// and, as much, by the texture addresser (88% busy, a cycle per lane and load).
+// 96 registers hold five waves with hardly a spill because little outlives a walk
 // (struct Lane); sampling, hit normals, photon writes and path ends are shared
 // by the modes that need them, since a wave holds lanes of several modes at
 // once and would run each mode's copy in turn.  Measured over the 3M-path,
-// 380k-triangle interior, one MI355X: full trace 4.08 ms (4.85 with a copy
-// per mode, all of a path's state kept and four waves), partial re-trace
-// 1.63 ms (1.98).
+// 380k-triangle interior, one MI355X: full trace 4.08 ms against 4.85 with a
+// copy per mode, all of a path's state kept and four waves, partial re-trace
+// 1.63 against 1.98 ms; now 3.40 and 1.46 ms with what the walk gained since.
 //
 // Re-trace state machine: every iteration each busy lane issues exactly one
 // query (closest hit over the scene, or any hit against the moved objects),
@@ -1400,13 +1414,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
   wk.cur = kRootNone;
   wk.leaf = 0;
   bool tracing = false, any = false;
+  bool drained = false;  // the wave has asked for work in vain
   while (true) {
     const SceneDev& S = scenes[kSingle ? 0u : L.s];
     // ---- walk; the box-test parameters follow from the ray, a few
     // instructions beside the walk's thousands, and hold no registers outside
+    const int yield = yield_below(min_active, drained, (int)__popcll(__ballot(tracing)));
     if (tracing) {
       const Slab q = world_slab(S, ray_origin(r), rcp3(r.d), r.tmin);
-      walk_scene<true>(S, r, q, any, col, limit, wk, min_active);
+      walk_scene<true>(S, r, q, any, col, limit, wk, yield);
     }
     // ---- lanes whose walk is finished advance their path.  What several
     // modes share is done once for all of them: the new vertex with its
@@ -1576,6 +1592,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
       }
     }
     const uint32_t mode = lane_mode(L.st);
+    drained = __ballot(mode == ST_END) != 0;
     if (__ballot(mode != ST_END && mode != ST_IDLE) == 0) {
       if (__ballot(mode == ST_IDLE) == 0) break;
       continue;
