@@ -539,8 +539,8 @@ def main():
                    "paths": N, "max_bounces": B, "frames_timed": K},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": PEAK_HBM_GBS, "unit": "GB/s",
                      "frac": achieved / PEAK_HBM_GBS, "traffic": traffic,
-                     "kernel": "verification call (k_verify_scan, task scan + k_verify_gather, k_verify_trace, "
-                               "k_verify_finish, k_verify_stats)",
+                     "kernel": "verification call (k_verify_scan, k_verify_gather, k_verify_trace, "
+                               "k_verify_finish)",
                      "algorithmic_bytes_per_launch": bytes_verify / K, "avg_launch_ms": avg_verify_s * 1e3},
         "phases_ms_per_frame": {k: v / K for k, v in phase.items()},
         "hbm_reference": {"copy_1gib_gbs": copy_gbs,
