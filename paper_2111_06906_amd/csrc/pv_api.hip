@@ -644,8 +644,8 @@ struct WideOrigin {
 // of h); slot[2 i + side] names the slot that took child 'side' of node i.
 // Returns the root code.
 template <typename LeafMap>
-int32_t build_wide(const HostBvh& h, const float qc[3], float qs, bool origins, LeafMap leaf, std::vector<Wide>& out,
-                   std::vector<WideOrigin>& org, std::vector<uint32_t>* slot) {
+int32_t build_wide(const HostBvh& h, const float qc[3], float qs, float slack, bool origins, LeafMap leaf,
+                   std::vector<Wide>& out, std::vector<WideOrigin>& org, std::vector<uint32_t>* slot) {
   if (h.root < 0) return leaf(h.root);
   if (slot) slot->assign(2 * h.nodes.size(), pv::kSlotNone);
   struct Ref {
@@ -695,7 +695,8 @@ int32_t build_wide(const HostBvh& h, const float qc[3], float qs, bool origins, 
     for (uint32_t k = 0; k < 4; ++k) {
       for (int ax = 0; ax < 3; ++ax)
         w.plane[3 * k + ax] =
-            k < n ? pv::wide_planes(box(c[k])[ax], box(c[k])[3 + ax], qc[ax], qs, (float)og.o[ax]) : pv::kPlanesNone;
+            k < n ? pv::wide_planes(box(c[k])[ax], box(c[k])[3 + ax], qc[ax], qs, (float)og.o[ax], slack)
+                  : pv::kPlanesNone;
       if (k < n && code(c[k]) < 0) w.child[k] = leaf(code(c[k]));
       if (k < n && slot) (*slot)[2 * (size_t)c[k].node + c[k].side] = 4 * id + k;
     }
@@ -1033,6 +1034,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     hs.wshift = origins ? pv::kOriginShift : 0u;
     hs.qs = 64.0f;  // without static triangles: coordinates of about 1 mid-range
     hs.qinv = 1.0f / 64.0f;
+    hs.qslack = pv::kPlaneSlack;
     for (int k = 0; k < 3; ++k) hs.qc[k] = origins ? -pv::kOriginMid * hs.qinv : 0.0f;
     uint32_t depth = 0, obj_depth = 0;  // deepest leaf: all hierarchies, object hierarchies
     for (int k = 0; k < 3; ++k) {
@@ -1082,9 +1084,10 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       if (half > 0.0f && std::isfinite(half)) (void)std::frexp(half, &ex);
       hs.qs = std::ldexp(1.0f, std::min(100, std::max(-100, (origins ? 7 : 8) - ex)));
       hs.qinv = 1.0f / hs.qs;
+      hs.qslack = std::max(pv::kPlaneSlack, pv::kPlaneSlackMin * hs.qs);
       for (int k = 0; k < 3; ++k)
         hs.qc[k] = 0.5f * (hs.sbox[k] + hs.sbox[3 + k]) - (origins ? pv::kOriginMid * hs.qinv : 0.0f);
-      hs.swroot = build_wide(hb, hs.qc, hs.qs, origins, [](int32_t c) { return c; }, wide, worg, nullptr);
+      hs.swroot = build_wide(hb, hs.qc, hs.qs, hs.qslack, origins, [](int32_t c) { return c; }, wide, worg, nullptr);
       nodes = std::move(hb.nodes);
       hs.sroot = hb.root;
     }
@@ -1168,10 +1171,10 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         host_boxes(hb, lv9.data(), kObjSpacePad);
         auto leaf = [&](int32_t c) { return rebase(c); };
         std::vector<uint32_t> slot;
-        ob.wroot = ob.sah_wroot = build_wide(hb, hs.qc, hs.qs, origins, leaf, wide, worg, &slot);
+        ob.wroot = ob.sah_wroot = build_wide(hb, hs.qc, hs.qs, hs.qslack, origins, leaf, wide, worg, &slot);
         for (size_t i = 0; i < slot.size(); i += 2) wslot.push_back(make_uint2(slot[i], slot[i + 1]));
         const float qo[3] = {hs.qobj, hs.qobj, hs.qobj};
-        ob.oroot = build_wide(hb, qo, hs.qs, origins, leaf, owide, oorg, nullptr);
+        ob.oroot = build_wide(hb, qo, hs.qs, hs.qslack, origins, leaf, owide, oorg, nullptr);
       }
       tri_base += n;
       gbase += n;

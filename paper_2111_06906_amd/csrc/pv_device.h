@@ -125,22 +125,32 @@ __host__ __device__ inline uint32_t half_down(float x) {
 }
 __host__ __device__ inline uint32_t half_up(float x) { return half_down(-x) ^ 0x8000u; }
 
-// Planes go outwards by 2^-13 grid steps beyond their padding: the scene's
-// half extent is 64 to 256 steps, so that is at least 2^-21 of it, what the
-// roundings of a walk's box parameters can move a crossing anywhere inside
-// (about 2^-24 of the extent each, three per plane, and the reciprocal's
-// 2^-23), also where the padding, relative to the coordinate, is smaller.
-constexpr float kPlaneSlack = 1.220703125e-4f;
+// Planes go outwards beyond their boxes' padding, for the roundings of a walk's
+// slab parameters.  With every rounding 2^-24 of its result, and in distances
+// along the axis, a plane P seen from a ray's origin o is off by at most
+// 8 |qc - o| + |origin - qc| + 4 |P - qc| times 2^-24: qc - o, its product with
+// 1 / d and that less tmin; the origin's multiply-add; the plane's multiply-add,
+// the hardware reciprocal (2) and the interval's end.  The part of the box is
+// kPlaneRel of its distance to qc (those 5, 2 for wide_planes' own subtractions,
+// and two more).  The part of the ray is a constant, kPlaneSlack grid steps: for
+// origins up to kRayReach steps from qc along every axis, four or more times the
+// largest half extent; in scenes of less than half a unit at least
+// kPlaneSlackMin units, which covers origins up to the 5 units that the FP32
+// boxes' padding covered.
+constexpr float kPlaneSlack = 4.8828125e-4f;  // 2^-11
+constexpr float kRayReach = 1024.0f;          // 8 x 1024 = 2^-11 x 2^24
+constexpr float kPlaneSlackMin = 2.4e-6f;     // 8 x 5 x 2^-24
+constexpr float kPlaneRel = 5.3644180e-7f;    // 9 x 2^-24
 
-// planes of one axis of a box [lo, hi] in the grid (c, s), less the origin o;
-// the subtractions' roundings (2^-24 of their results) go outwards by at least
-// as much
-__host__ __device__ inline uint32_t wide_planes(float lo, float hi, float c, float s, float o = 0.0f) {
+// planes of one axis of a box [lo, hi] in the grid (c, s), less the origin o and
+// going outwards by 'slack' (both in units of 1 / s); the subtractions'
+// roundings (2^-24 of their results) go outwards too
+__host__ __device__ inline uint32_t wide_planes(float lo, float hi, float c, float s, float o = 0.0f,
+                                                float slack = 0.0f) {
   const float a = (lo - c) * s, b = (hi - c) * s;
   const float da = a - o, db = b - o;
   const float ra = __builtin_fabsf(a) + __builtin_fabsf(da), rb = __builtin_fabsf(b) + __builtin_fabsf(db);
-  return half_down(da - (ra * 1.1920929e-7f + kPlaneSlack)) |
-         (half_up(db + (rb * 1.1920929e-7f + kPlaneSlack)) << 16);
+  return half_down(da - (ra * kPlaneRel + slack)) | (half_up(db + (rb * kPlaneRel + slack)) << 16);
 }
 
 // Node origins: whole grid steps 0 .. 255 from the grid's corner (qc, then 128
@@ -232,6 +242,7 @@ struct SceneDev {
   uint32_t wtop_base;     // first four-wide top-level node
   int32_t swroot;         // static root code in 'wide'
   float qc[3], qs, qinv;  // grid of the planes: origin, scale (a power of two), 1 / scale
+  float qslack;           // how far they go outwards, in steps
   float qobj;             // the same origin, any axis, of the object-space forms
   uint32_t wshift;        // kOriginShift: the nodes have origins; 0: they have none
   float sbox[6];          // static world box (lo, hi)
@@ -299,11 +310,11 @@ struct SceneDev {
 // writer finds it by itself.  'xf': the frame's transform of the object.
 struct PlaneWriter {
   PV_GLOBAL Wide* wide;
-  float cx, cy, cz, s;
+  float cx, cy, cz, s, slack;
   uint32_t shift;
   uint32_t ox, oy, oz;
   __device__ explicit PlaneWriter(const SceneDev& S)
-      : wide(G(S.wide)), cx(S.qc[0]), cy(S.qc[1]), cz(S.qc[2]), s(S.qs), shift(S.wshift) {
+      : wide(G(S.wide)), cx(S.qc[0]), cy(S.qc[1]), cz(S.qc[2]), s(S.qs), slack(S.qslack), shift(S.wshift) {
     ox = oy = oz = shift ? (uint32_t)kOriginMid : 0u;
   }
   __device__ PlaneWriter(const SceneDev& S, uint32_t o, const float* xf) : PlaneWriter(S) {
@@ -317,9 +328,9 @@ struct PlaneWriter {
   __device__ uint32_t origin(uint32_t k) const { return k == 0 ? ox : (k == 1 ? oy : (k == 2 ? oz : 0u)); }
   __device__ void put(uint32_t slot, float lx, float ly, float lz, float hx, float hy, float hz) const {
     PV_GLOBAL uint32_t* w = wide[slot >> 2].plane + 3 * (slot & 3u);
-    w[0] = wide_planes(lx, hx, cx, s, (float)ox);
-    w[1] = wide_planes(ly, hy, cy, s, (float)oy);
-    w[2] = wide_planes(lz, hz, cz, s, (float)oz);
+    w[0] = wide_planes(lx, hx, cx, s, (float)ox, slack);
+    w[1] = wide_planes(ly, hy, cy, s, (float)oy, slack);
+    w[2] = wide_planes(lz, hz, cz, s, (float)oz, slack);
   }
   __device__ void none(uint32_t slot) const {
     PV_GLOBAL uint32_t* w = wide[slot >> 2].plane + 3 * (slot & 3u);
