@@ -61,7 +61,7 @@ struct pv_ctx {
   Alloc scene_mem;
   SceneDev hs{};               // host image of the descriptor
   SceneDev* d_scene = nullptr; // device descriptor (one entry)
-  uint32_t* d_state = nullptr; // first-frame flag
+  uint32_t* d_state = nullptr; // SceneDev::state
   uint2* d_place_tiles = nullptr;  // tiles of the frame's beginning (launch_frame_begin)
   uint2* d_refit_tiles = nullptr;
   uint32_t n_place_tiles = 0, n_refit_tiles = 0;
@@ -1032,14 +1032,27 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     // triangle 20, a node's index 23 (a scene has fewer than 4 nodes a triangle)
     const bool origins = (uint64_t)S + n_dyn <= pv::kOriginTris;
     hs.wshift = origins ? pv::kOriginShift : 0u;
-    hs.qs = 64.0f;  // without static triangles: coordinates of about 1 mid-range
-    hs.qinv = 1.0f / 64.0f;
-    hs.qslack = pv::kPlaneSlack;
-    for (int k = 0; k < 3; ++k) hs.qc[k] = origins ? -pv::kOriginMid * hs.qinv : 0.0f;
     uint32_t depth = 0, obj_depth = 0;  // deepest leaf: all hierarchies, object hierarchies
     for (int k = 0; k < 3; ++k) {
       hs.sbox[k] = INFINITY;
       hs.sbox[3 + k] = -INFINITY;
+    }
+    // the planes' grid: around the static world, or, without one, around the
+    // origin as far as twice the objects' coordinates in their own spaces (where
+    // transforms place them beyond, nodes bring units of their own)
+    auto set_grid = [&hs](const pv::PlaneGrid& g) {
+      std::memcpy(hs.qc, g.qc, sizeof(hs.qc));
+      std::memcpy(hs.qm, g.qm, sizeof(hs.qm));
+      hs.qs = g.qs;
+      hs.qinv = g.qinv;
+      hs.qslack = g.slack;
+    };
+    if (!S) {
+      float far = 0.0f;
+      for (uint64_t i = 0; i < 9 * n_dyn; ++i) far = std::max(far, std::fabs(d->h_obj_verts[i]));
+      far *= 2.0f;
+      const float lo[3] = {-far, -far, -far}, hi[3] = {far, far, far};
+      set_grid(pv::plane_grid(lo, hi, origins));
     }
     // the objects' topologies in object space (boxes refit each frame), beside
     // the static hierarchy's
@@ -1073,26 +1086,12 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         hs.sbox[k] = pad_lo(hs.sbox[k]);
         hs.sbox[3 + k] = pad_hi(hs.sbox[3 + k]);
       }
-      // the planes' grid: around the static world, the largest half extent
-      // scaled by a power of two to (64, 128], the reach of the origins, or,
-      // without them, to (128, 256]: objects up to 255 times as far out keep
-      // finite planes, planes under 2^-21 of the half extent from an origin
-      // lose digits
-      float half = 0.0f;
-      for (int k = 0; k < 3; ++k) half = std::max(half, 0.5f * (hs.sbox[3 + k] - hs.sbox[k]));
-      int ex = 0;
-      if (half > 0.0f && std::isfinite(half)) (void)std::frexp(half, &ex);
-      hs.qs = std::ldexp(1.0f, std::min(100, std::max(-100, (origins ? 7 : 8) - ex)));
-      hs.qinv = 1.0f / hs.qs;
-      hs.qslack = std::max(pv::kPlaneSlack, pv::kPlaneSlackMin * hs.qs);
-      for (int k = 0; k < 3; ++k)
-        hs.qc[k] = 0.5f * (hs.sbox[k] + hs.sbox[3 + k]) - (origins ? pv::kOriginMid * hs.qinv : 0.0f);
+      set_grid(pv::plane_grid(hs.sbox, hs.sbox + 3, origins));
       hs.swroot = build_wide(hb, hs.qc, hs.qs, hs.qslack, origins, [](int32_t c) { return c; }, wide, worg, nullptr);
       nodes = std::move(hb.nodes);
       hs.sroot = hb.root;
     }
 
-    hs.qobj = origins ? -pv::kOriginMid * hs.qinv : 0.0f;
     const uint32_t static_depth = depth;
     // dynamic objects: topology in object space, boxes refit per frame
     std::vector<ObjDev> objs(d->n_objects);
@@ -1147,6 +1146,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         std::memcpy(&dlocal[9 * (size_t)(tri_base + i)], v + 9 * (size_t)hb.order[i], 9 * sizeof(float));
         dgid[tri_base + i] = gbase + hb.order[i];
       }
+      float obox[6];
       for (int k = 0; k < 3; ++k) {
         float lo = INFINITY, hi = -INFINITY;
         for (size_t i = k; i < 9 * (size_t)n; i += 3) {
@@ -1154,6 +1154,9 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
           hi = std::max(hi, v[i]);
         }
         ob.centre[k] = 0.5f * lo + 0.5f * hi;
+        ob.half[k] = 0.5f * hi - 0.5f * lo;
+        obox[k] = lo;
+        obox[3 + k] = hi;
       }
       ob.gbase = gbase;
       ob.n_tris = n;
@@ -1173,8 +1176,10 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
         std::vector<uint32_t> slot;
         ob.wroot = ob.sah_wroot = build_wide(hb, hs.qc, hs.qs, hs.qslack, origins, leaf, wide, worg, &slot);
         for (size_t i = 0; i < slot.size(); i += 2) wslot.push_back(make_uint2(slot[i], slot[i + 1]));
-        const float qo[3] = {hs.qobj, hs.qobj, hs.qobj};
-        ob.oroot = build_wide(hb, qo, hs.qs, hs.qslack, origins, leaf, owide, oorg, nullptr);
+        const pv::PlaneGrid og = pv::plane_grid(obox, obox + 3, origins);
+        std::memcpy(ob.og, og.qc, sizeof(ob.og));
+        ob.oinv = og.qinv;
+        ob.oroot = build_wide(hb, og.qc, og.qs, pv::kObjSlack, origins, leaf, owide, oorg, nullptr);
       }
       tri_base += n;
       gbase += n;
@@ -1226,9 +1231,9 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     CK(upload(A, &d_wide, wide.data(), wide.size(), s));
     CK(dalloc(A, &d_tris, (size_t)S + n_dyn));
     if (S) CK(hipMemcpyAsync(d_tris, stris.data(), sizeof(Tri) * S, hipMemcpyHostToDevice, s));
-    const int32_t no_roots[2] = {pv::kRootNone, pv::kRootNone};  // set per frame by the top-level build
+    const int32_t no_roots[3] = {pv::kRootNone, pv::kRootNone, 0};  // set per frame by the top-level build
     CK(upload(A, &hs.top, no_roots, 2, s));
-    CK(upload(A, &hs.wtop, no_roots, 2, s));
+    CK(upload(A, &hs.wtop, no_roots, 3, s));
     CK(upload(A, &d_dlocal, dlocal.data(), dlocal.size(), s));
     CK(upload(A, &d_dgid, dgid.data(), dgid.size(), s));
     {
@@ -1327,10 +1332,10 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     hs.gpath_base = 0;
 
     CK(dalloc(A, &ctx->d_scene, 1));
-    CK(dalloc(A, &ctx->d_state, 1));
+    CK(dalloc(A, &ctx->d_state, 2));
     hs.state = ctx->d_state;
-    uint32_t one = 1;
-    CK(hipMemcpyAsync(ctx->d_state, &one, 4, hipMemcpyHostToDevice, s));
+    const uint32_t state0[2] = {1, 0};
+    CK(hipMemcpyAsync(ctx->d_state, state0, sizeof(state0), hipMemcpyHostToDevice, s));
     CK(hipMemcpyAsync(ctx->d_scene, &hs, sizeof(hs), hipMemcpyHostToDevice, s));
     std::vector<uint2> place, refit;
     frame_tiles(0, (uint32_t)n_dyn, hs.n_obj_nodes, place, refit);

@@ -86,9 +86,10 @@ __host__ __device__ inline uint32_t leaf_count(int code) { return (((uint32_t)~c
 // its FP32 box; child k's planes are words 3 k .. 3 k + 2, (lower plane | upper
 // plane << 16) per axis.  Child words are a walk's codes: those of Node shifted
 // left by 8 (wide_code), and the low bytes of the first three are the origin's
-// x, y, z in whole grid steps, of which the scene spans up to 256.  In scenes
-// too large for 24-bit codes they are the plain codes and the origin is 0, the
-// grid's centre.
+// x, y, z in whole grid steps, of which the static world spans up to 256, and
+// that of the fourth the exponent of the node's own unit (node_grid; 0 unless
+// a dynamic object lies outside that span).  In scenes too large for 24-bit
+// codes they are the plain codes and the origin is 0, the grid's centre.
 //
 // Why an origin per node: FP16 around the scene's centre leaves a wall's box a
 // thousandth of the scene thick, so nearly every ray that starts on a wall
@@ -131,15 +132,18 @@ __host__ __device__ inline uint32_t half_up(float x) { return half_down(-x) ^ 0x
 // 8 |qc - o| + |origin - qc| + 4 |P - qc| times 2^-24: qc - o, its product with
 // 1 / d and that less tmin; the origin's multiply-add; the plane's multiply-add,
 // the hardware reciprocal (2) and the interval's end.  The part of the box is
-// kPlaneRel of its distance to qc (those 5, 2 for wide_planes' own subtractions,
-// and two more).  The part of the ray is a constant, kPlaneSlack grid steps: for
-// origins up to kRayReach steps from qc along every axis, four or more times the
-// largest half extent; in scenes of less than half a unit at least
-// kPlaneSlackMin units, which covers origins up to the 5 units that the FP32
-// boxes' padding covered.
+// kPlaneRel of its distance to qc (those 5, one for the wider slabs of
+// WALK_SCALED, 2 for wide_planes' own subtractions, and one more).  The part of
+// the ray is a constant, kPlaneSlack grid steps: for origins up to kRayReach
+// steps from qc along every axis, four or more times the largest half extent;
+// in scenes of less than half a unit at least kPlaneSlackMin units, which covers
+// origins up to the 5 units that the FP32 boxes' padding covered.  Rays from
+// further out are WALK_SCALED's, or not answered by these planes
+// (SceneDev::wtop[2]).
 constexpr float kPlaneSlack = 4.8828125e-4f;  // 2^-11
 constexpr float kRayReach = 1024.0f;          // 8 x 1024 = 2^-11 x 2^24
 constexpr float kPlaneSlackMin = 2.4e-6f;     // 8 x 5 x 2^-24
+constexpr float kUnitSlack = 6.1035156e-5f;   // 2^-14, of a node's own unit: the ray's part is the wider slabs'
 constexpr float kPlaneRel = 5.3644180e-7f;    // 9 x 2^-24
 
 // planes of one axis of a box [lo, hi] in the grid (c, s), less the origin o and
@@ -153,6 +157,14 @@ __host__ __device__ inline uint32_t wide_planes(float lo, float hi, float c, flo
   return half_down(da - (ra * kPlaneRel + slack)) | (half_up(db + (rb * kPlaneRel + slack)) << 16);
 }
 
+// The same for object-space forms, in their own grids: a world segment mapped
+// by the inverse transform is off by up to 12 x 2^-24 of the larger of its
+// ends' object-space coordinates besides (the translation's subtraction, and
+// three products of rounded factors and their sums), for ends and corner within
+// kObjReach steps, at least 97 half extents of the object.
+constexpr float kObjSlack = 0.015625f;   // 2^-6
+constexpr float kObjReach = 12483.0f;    // 21 x 12483 <= 2^-6 x 2^24
+
 // Node origins: whole grid steps 0 .. 255 from the grid's corner (qc, then 128
 // steps below the scene's centre), where codes fit 24 bits.
 constexpr uint32_t kOriginShift = 8;
@@ -163,6 +175,78 @@ constexpr float kOriginMid = 128.0f;
 __host__ __device__ inline uint32_t wide_origin(float x, float c, float s) {
   const float m = (x - c) * s + 0.5f;
   return m >= 0.0f ? (m < 255.0f ? (uint32_t)m : 255u) : 0u;
+}
+
+// The planes' grid of a box: its middle qm in whole steps, so that the corner
+// qc, 128 steps below it, is exact too; the step a power of two by which the
+// largest half extent is 64 to 128 steps, the reach of the origins, or, in
+// scenes without origins, 128 to 256 from qc = qm.
+struct PlaneGrid {
+  float qc[3], qm[3], qs, qinv, slack;
+};
+
+__host__ inline PlaneGrid plane_grid(const float* lo, const float* hi, bool origins) {
+  PlaneGrid g;
+  float half = 0.0f;
+  for (int k = 0; k < 3; ++k) half = fmaxf(half, 0.5f * (hi[k] - lo[k]));
+  int ex = 0;
+  if (half > 0.0f && half < __builtin_inff()) (void)__builtin_frexpf(half, &ex);
+  ex = (origins ? 7 : 8) - ex;
+  g.qs = __builtin_ldexpf(1.0f, ex < -100 ? -100 : (ex > 100 ? 100 : ex));
+  g.qinv = 1.0f / g.qs;
+  g.slack = fmaxf(kPlaneSlack, kPlaneSlackMin * g.qs);
+  for (int k = 0; k < 3; ++k) {
+    const float m = __builtin_rintf((0.5f * lo[k] + 0.5f * hi[k]) * g.qs) * g.qinv;
+    g.qm[k] = m - m == 0.0f ? m : 0.0f;
+    g.qc[k] = g.qm[k] - (origins ? kOriginMid * g.qinv : 0.0f);
+  }
+  return g;
+}
+
+// Grid of one node's planes: lower corner c and scale s of the planes, and the
+// origin, as the bytes that the node holds and as the float that is subtracted.
+// The unit is the grid's step, 2^0, or 2^e steps, counted from the grid's
+// middle, where the step does not serve: for what lies more than 16 steps
+// beyond the origins' range, whose planes would lose digits with their distance
+// from the last origin and be infinite past 65,504 steps (a walk through
+// objects a thousand half extents out took 100 times as long), and for what
+// reaches so far out that rays from it would begin beyond kRayReach.  With
+// 'fine' (no static world sets the step) also for what the step is too coarse
+// for.  All planes are then within 2^-18 of the distance from the middle.
+struct NodeGrid {
+  float c[3], s, f[3];
+  uint32_t o[3];
+  int e;
+};
+
+// ceil(log2(x)) of a positive finite x, within +-40 (slab parameters of a ray
+// along an axis are near 2^60 and take the unit's factor)
+__host__ __device__ inline int ceil_exp(float x) {
+  const uint32_t u = float_bits(x);
+  const int e = (int)(u >> 23) - 127 + ((u & 0x7FFFFFu) ? 1 : 0);
+  return e < -40 ? -40 : (e > 40 ? 40 : e);
+}
+
+// at, half: middle and largest half extent of what the node's planes bound
+__host__ __device__ inline NodeGrid node_grid(const float* qc, const float* qm, float qs, const float* at, float half,
+                                              bool fine) {
+  float need = 0.0f;
+  for (int k = 0; k < 3; ++k) need = __builtin_fmaxf(need, __builtin_fabsf((at[k] - qm[k]) * qs));
+  const float hs = half * qs;
+  NodeGrid g;
+  g.e = 0;
+  const bool inside = need <= 144.0f && need + hs <= kRayReach - kOriginMid;
+  if (!inside || (fine && (hs < 0.0625f || need + hs < 1.0f))) {
+    const int e = ceil_exp(__builtin_fmaxf(need, hs) * (1.0f / 128.0f));
+    g.e = fine && inside ? e : (e > 1 ? e : 1);
+  }
+  g.s = g.e ? __builtin_ldexpf(qs, -g.e) : qs;
+  for (int k = 0; k < 3; ++k) {
+    g.c[k] = g.e ? qm[k] : qc[k];
+    g.o[k] = g.e ? wide_origin(at[k] - qm[k], -kOriginMid / g.s, g.s) : wide_origin(at[k], qc[k], qs);
+    g.f[k] = (float)g.o[k] - (g.e ? kOriginMid : 0.0f);
+  }
+  return g;
 }
 
 // a code of Node as a walk's
@@ -202,7 +286,8 @@ struct ObjDev {
   int32_t wroot;       // root of the current hierarchy's four-wide form
   int32_t sah_wroot;   // the same of the upload-time topology
   uint32_t lbvh_wbase; // first four-wide node of its region for the rebuilt radix tree
-  float centre[3];     // middle of its object-space box
+  float centre[3], half[3];  // its object-space box: middle and half extents
+  float og[3], oinv;         // grid of its object-space form: corner (qc), 1 / scale
 };
 
 struct LightDev {
@@ -238,12 +323,15 @@ struct SceneDev {
   int32_t sroot;          // static root code (kRootNone without static triangles)
   // the four-wide form: [static][objects][rebuilt objects][2 x kTopNodes][objects in object space]
   Wide* wide;
-  int32_t* wtop;          // [2] per frame: four-wide roots of the whole scene and of the moved objects
+  // [3] per frame: four-wide roots of the whole scene and of the moved objects,
+  // and the reach of the nodes' planes (bits of a float; kRayReach steps,
+  // infinite or kReachNone)
+  int32_t* wtop;
   uint32_t wtop_base;     // first four-wide top-level node
   int32_t swroot;         // static root code in 'wide'
-  float qc[3], qs, qinv;  // grid of the planes: origin, scale (a power of two), 1 / scale
-  float qslack;           // how far they go outwards, in steps
-  float qobj;             // the same origin, any axis, of the object-space forms
+  // grid of the planes: corner, middle, scale (a power of two), 1 / scale
+  float qc[3], qm[3], qs, qinv;
+  float qslack;           // their slack, in steps
   uint32_t wshift;        // kOriginShift: the nodes have origins; 0: they have none
   float sbox[6];          // static world box (lo, hi)
   // dynamic objects
@@ -296,41 +384,72 @@ struct SceneDev {
   uint32_t count_base;    // first entry of this scene's (row, block) photon counts
   uint32_t tile_base;     // first path tile (block of kBlock paths) of this scene
   uint32_t task_base;     // first entry of this scene's tile regions of verification tasks
-  uint32_t* state;        // [1] first-frame flag of the scene
+  uint32_t* state;        // [2] first frame to come; a frame so far was read as WALK_SCALED
   // distribution maps (Section 3.1): grid {gu, gv, rings, sectors}, dm[0] = 0
   // when none; first cell of each light in the maps of all lights
   int32_t dm[4];
   uint32_t dm_off[PV_MAX_LIGHTS + 1];
 };
 
+// How walks read four-wide nodes.
+enum WalkForm : int {
+  WALK_PLAIN,   // no origins
+  WALK_ORIGIN,  // an origin, the unit is the grid's step
+  WALK_SCALED   // an origin and a unit of its own in every node; any ray origin
+};
+
+// SceneDev::wtop[2]: how far from plane_base a query may begin in this frame,
+// along every axis.  With origins it is kRayReach steps, which no query needs to
+// look at (nothing that the frame's rays begin on lies further out), or
+// infinite: the nodes are read as WALK_SCALED.
+constexpr float kReachNone = -1.0f;  // no query: without origins, and objects beyond FP16
+
+// Grid of all nodes of an object placed by the rows m: its origin is the
+// placed middle of the object's box.
+template <typename M>
+__device__ inline NodeGrid object_grid(const SceneDev& S, uint32_t o, M m) {
+  const PV_GLOBAL ObjDev* ob = G(S.objs) + o;
+  float at[3], half = 0.0f;
+  for (int k = 0; k < 3; ++k) {
+    const float a = m[4 * k], b = m[4 * k + 1], c = m[4 * k + 2];
+    at[k] = a * ob->centre[0] + b * ob->centre[1] + c * ob->centre[2] + m[4 * k + 3];
+    half = fmaxf(half, fabsf(a) * ob->half[0] + fabsf(b) * ob->half[1] + fabsf(c) * ob->half[2]);
+  }
+  return node_grid(S.qc, S.qm, S.qs, at, half, S.sroot == kRootNone);
+}
+
 // Writer of child boxes into four-wide slots.  Holds the grid and the array in
 // registers: read from the descriptor at every write they would be loaded
-// again after each store.  All nodes of an object take the placed middle of
-// its box as their origin, the few top-level nodes the grid's middle: each
-// writer finds it by itself.  'xf': the frame's transform of the object.
+// again after each store.  Each writer of an object's nodes finds their grid by
+// itself (object_grid); the few top-level nodes have the grid's middle as their
+// origin, and a unit of 2^e steps.
 struct PlaneWriter {
   PV_GLOBAL Wide* wide;
-  float cx, cy, cz, s, slack;
   uint32_t shift;
-  uint32_t ox, oy, oz;
-  __device__ explicit PlaneWriter(const SceneDev& S)
-      : wide(G(S.wide)), cx(S.qc[0]), cy(S.qc[1]), cz(S.qc[2]), s(S.qs), slack(S.qslack), shift(S.wshift) {
-    ox = oy = oz = shift ? (uint32_t)kOriginMid : 0u;
+  float slack0, slack;
+  NodeGrid g;
+  __device__ PlaneWriter(const SceneDev& S, int e) : wide(G(S.wide)), shift(S.wshift), slack0(S.qslack) {
+    g.e = shift ? e : 0;
+    g.s = g.e ? __builtin_ldexpf(S.qs, -g.e) : S.qs;
+    for (int k = 0; k < 3; ++k) {
+      g.c[k] = g.e ? S.qm[k] : S.qc[k];
+      g.o[k] = shift ? (uint32_t)kOriginMid : 0u;
+      g.f[k] = shift && !g.e ? kOriginMid : 0.0f;
+    }
+    slack = g.e ? kUnitSlack : slack0;
   }
-  __device__ PlaneWriter(const SceneDev& S, uint32_t o, const float* xf) : PlaneWriter(S) {
-    if (!shift) return;
-    const PV_GLOBAL float* m = G(xf) + 12 * o;
-    const PV_GLOBAL float* c = G(S.objs)[o].centre;
-    ox = wide_origin(m[0] * c[0] + m[1] * c[1] + m[2] * c[2] + m[3], cx, s);
-    oy = wide_origin(m[4] * c[0] + m[5] * c[1] + m[6] * c[2] + m[7], cy, s);
-    oz = wide_origin(m[8] * c[0] + m[9] * c[1] + m[10] * c[2] + m[11], cz, s);
+  __device__ PlaneWriter(const SceneDev& S, uint32_t o, const float* xf) : PlaneWriter(S, 0) {
+    if (shift) g = object_grid(S, o, G(xf) + 12 * o);
+    slack = g.e ? kUnitSlack : slack0;
   }
-  __device__ uint32_t origin(uint32_t k) const { return k == 0 ? ox : (k == 1 ? oy : (k == 2 ? oz : 0u)); }
+  __device__ uint32_t low_byte(uint32_t k) const {
+    return k == 0 ? g.o[0] : (k == 1 ? g.o[1] : (k == 2 ? g.o[2] : (uint32_t)g.e & 255u));
+  }
   __device__ void put(uint32_t slot, float lx, float ly, float lz, float hx, float hy, float hz) const {
     PV_GLOBAL uint32_t* w = wide[slot >> 2].plane + 3 * (slot & 3u);
-    w[0] = wide_planes(lx, hx, cx, s, (float)ox, slack);
-    w[1] = wide_planes(ly, hy, cy, s, (float)oy, slack);
-    w[2] = wide_planes(lz, hz, cz, s, (float)oz, slack);
+    w[0] = wide_planes(lx, hx, g.c[0], g.s, g.f[0], slack);
+    w[1] = wide_planes(ly, hy, g.c[1], g.s, g.f[1], slack);
+    w[2] = wide_planes(lz, hz, g.c[2], g.s, g.f[2], slack);
   }
   __device__ void none(uint32_t slot) const {
     PV_GLOBAL uint32_t* w = wide[slot >> 2].plane + 3 * (slot & 3u);
@@ -339,15 +458,13 @@ struct PlaneWriter {
   }
   // code: a walk's (wide_code)
   __device__ void child(uint32_t slot, int32_t code) const {
-    wide[slot >> 2].child[slot & 3u] = code | (int32_t)origin(slot & 3u);
+    wide[slot >> 2].child[slot & 3u] = code | (shift ? (int32_t)low_byte(slot & 3u) : 0);
   }
-  // a node's origin beside child codes that stay
+  // a node's origin and unit beside child codes that stay
   __device__ void put_origin(uint32_t node) const {
     if (!shift) return;
     PV_GLOBAL uint8_t* b = (PV_GLOBAL uint8_t*)wide[node].child;
-    b[0] = (uint8_t)ox;
-    b[4] = (uint8_t)oy;
-    b[8] = (uint8_t)oz;
+    for (uint32_t k = 0; k < 4; ++k) b[4 * k] = (uint8_t)low_byte(k);
   }
 };
 
@@ -609,6 +726,13 @@ __device__ inline void walk_start(Walk& w, int32_t root, float tmax, StackCol co
   w.redo = false;
 }
 
+// leaves a query to walk_exact
+__device__ inline void walk_leave(Walk& w) {
+  w.cur = kRootNone;
+  w.leaf = 0;
+  w.redo = true;
+}
+
 // Parameters of a query's box tests: 1 / direction and (centre - origin) /
 // direction in the planes' grid, and per axis 16 where the direction is
 // negative (the upper plane is then the nearer one).  They give a crossing's
@@ -616,6 +740,8 @@ __device__ inline void walk_start(Walk& w, int32_t root, float tmax, StackCol co
 // [0, 1] is the interval's lower end at no cost; parameters past 1 / kTScale
 // clamp too, which only enters a box the query has left behind.
 constexpr float kTScale = 1.0f / 1099511627776.0f;  // 2^-40
+
+constexpr float kWiden = 9.5367432e-7f;  // 2^-20, of |qm - o| / d with WALK_SCALED
 
 struct Slab {
   float3 inv, oi;
@@ -632,11 +758,24 @@ __device__ inline Slab make_slab(float3 inv, float3 oi, float scale, float tmin)
   return q;
 }
 
-// a world-space query against the scene's four-wide nodes
-__device__ inline Slab world_slab(const SceneDev& S, float3 o, float3 inv, float tmin) {
-  const float3 c = f3(S.qc[0] - o.x, S.qc[1] - o.y, S.qc[2] - o.z);
+// what a scene's planes count from: the grid's corner, or with WALK_SCALED its
+// middle (the same without origins)
+template <bool kScaled>
+__device__ inline float3 plane_base(const SceneDev& S) {
+  const float* q = kScaled ? S.qm : S.qc;
+  return f3(q[0], q[1], q[2]);
+}
+
+// a world-space query from o against the scene's four-wide nodes; c: plane_base - o
+__device__ inline Slab world_slab(const SceneDev& S, float3 c, float3 inv, float tmin) {
   return make_slab(inv, f3(c.x * inv.x, c.y * inv.y, c.z * inv.z), S.qinv, tmin);
 }
+
+__device__ inline float reach3(float3 v) { return fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fabsf(v.z)); }
+__device__ inline float frame_reach(const SceneDev& S) { return __int_as_float(G(S.wtop)[2]); }
+
+// whether a query without origins is left to walk_exact; c: plane_base - o
+__device__ inline bool walk_far(const SceneDev& S, float3 c) { return !S.wshift && !(reach3(c) <= frame_reach(S)); }
 
 // a condition as the wave's mask, and a mask's bit of this lane: conditions
 // combined as masks are scalar work beside the vector pipeline
@@ -654,10 +793,10 @@ typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 // both parameters of an axis' planes, nearer one first: a rotation by the
 // axis' sign instead of a minimum and a maximum, and mixed-precision fused
 // multiply-adds that read the FP16 planes in place
-__device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, float oi, float* n, float* f) {
+__device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, float on, float of, float* n, float* f) {
   const half2v h = __builtin_bit_cast(half2v, __builtin_amdgcn_alignbit(w, w, rot));
-  *n = __builtin_fmaf((float)h.x, inv, oi);
-  *f = __builtin_fmaf((float)h.y, inv, oi);
+  *n = __builtin_fmaf((float)h.x, inv, on);
+  *f = __builtin_fmaf((float)h.y, inv, of);
 }
 
 // Speculative traversal (Aila and Laine 2009): a lane that reaches a leaf
@@ -687,7 +826,11 @@ __device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, 
 // would leave more entries than 'limit' (the top's address there) allows, and,
 // with kTies, when two crossings lie within 2.5e-7 of each other, twice the
 // rounding that lets the order of their tests decide.
-template <bool kTies, bool kOrigin>
+//
+// With WALK_SCALED a node has its own unit, and the slabs are widened by 2^-20
+// of |qm - o| / d, twice what the ray's part of their roundings is: for ray
+// origins anywhere.
+template <bool kTies, int kForm>
 __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const PV_GLOBAL Tri* __restrict__ tris,
                                 const Ray& r, const Slab& q, bool any, StackCol col, StackCol limit, Walk& w,
                                 int min_active) {
@@ -699,6 +842,7 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
   float tb = w.tb;
   uint32_t rec = w.rec;
   bool redo = w.redo;
+  constexpr bool kOrigin = kForm != WALK_PLAIN, kScaled = kForm == WALK_SCALED;
   while (true) {
     const float ts = __builtin_canonicalizef((tb - r.tmin) * kTScale);  // tb as a slab parameter
     const int alive = __popcll(__ballot(1));
@@ -712,22 +856,38 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
       int32_t c[4] = {(int32_t)nd.x, (int32_t)nd.y, (int32_t)nd.z, (int32_t)nd.w};
       float e[4];
       uint64_t h[4];  // entered children, as wave masks
-      float3 oi = q.oi;
-      if (kOrigin) {
-        oi.x = __builtin_fmaf((float)(nd.x & 255u), q.inv.x, oi.x);
-        oi.y = __builtin_fmaf((float)(nd.y & 255u), q.inv.y, oi.y);
-        oi.z = __builtin_fmaf((float)(nd.z & 255u), q.inv.z, oi.z);
+      float3 on = q.oi, of;
+      float te = ts;
+      if (kScaled) {
+        // in the node's unit: every parameter times 2^-x
+        const int x = -(int)(int8_t)(nd.w & 255u);
+        const float3 og = f3((float)(nd.x & 255u) - kOriginMid, (float)(nd.y & 255u) - kOriginMid,
+                             (float)(nd.z & 255u) - kOriginMid);
+        auto wide = [&](float oi, float w, float g, float inv) {
+          const float u = __builtin_ldexpf(oi, x);
+          return __builtin_fmaf(g, inv, __builtin_fmaf(w, fabsf(u), u));
+        };
+        of = f3(wide(on.x, kWiden, og.x, q.inv.x), wide(on.y, kWiden, og.y, q.inv.y), wide(on.z, kWiden, og.z, q.inv.z));
+        on = f3(wide(on.x, -kWiden, og.x, q.inv.x), wide(on.y, -kWiden, og.y, q.inv.y), wide(on.z, -kWiden, og.z, q.inv.z));
+        te = __builtin_canonicalizef(__builtin_ldexpf(ts, x));
+      } else {
+        if (kOrigin) {
+          on.x = __builtin_fmaf((float)(nd.x & 255u), q.inv.x, on.x);
+          on.y = __builtin_fmaf((float)(nd.y & 255u), q.inv.y, on.y);
+          on.z = __builtin_fmaf((float)(nd.z & 255u), q.inv.z, on.z);
+        }
+        of = on;
       }
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         float nx, ny, nz, fx, fy, fz;
-        plane_pair(pl[3 * k], q.rx, q.inv.x, oi.x, &nx, &fx);
-        plane_pair(pl[3 * k + 1], q.ry, q.inv.y, oi.y, &ny, &fy);
-        plane_pair(pl[3 * k + 2], q.rz, q.inv.z, oi.z, &nz, &fz);
+        plane_pair(pl[3 * k], q.rx, q.inv.x, on.x, of.x, &nx, &fx);
+        plane_pair(pl[3 * k + 1], q.ry, q.inv.y, on.y, of.y, &ny, &fy);
+        plane_pair(pl[3 * k + 2], q.rz, q.inv.z, on.z, of.z, &nz, &fz);
         e[k] = __builtin_amdgcn_fmed3f(fmaxf(fmaxf(nx, ny), nz), 0.0f, 1.0f);
         const float ex = fminf(fminf(fx, fy), fz);
         // the slab interval meets [tmin, tb]
-        h[k] = wave_mask(e[k] <= fminf(ex, ts));
+        h[k] = wave_mask(e[k] <= fminf(ex, te));
       }
       // nearest entered child first, the others nearly in order (a child not
       // entered comes last of its pair); exchanges of the masks are scalar work
@@ -812,13 +972,13 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
 }
 
 // walk_run in the scene's form of nodes
-template <bool kTies>
+template <bool kTies, bool kScaled>
 __device__ inline void walk_scene(const SceneDev& S, const Ray& r, const Slab& q, bool any, StackCol col, StackCol limit,
                                   Walk& w, int min_active) {
   if (S.wshift)
-    walk_run<kTies, true>(G(S.wide), G(S.tris), r, q, any, col, limit, w, min_active);
+    walk_run<kTies, kScaled ? WALK_SCALED : WALK_ORIGIN>(G(S.wide), G(S.tris), r, q, any, col, limit, w, min_active);
   else
-    walk_run<kTies, false>(G(S.wide), G(S.tris), r, q, any, col, limit, w, min_active);
+    walk_run<kTies, WALK_PLAIN>(G(S.wide), G(S.tris), r, q, any, col, limit, w, min_active);
 }
 
 // The answer to a world-space query by the order that settles near ties: the

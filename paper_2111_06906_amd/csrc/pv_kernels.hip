@@ -158,6 +158,29 @@ __device__ inline BoxRay segment_box_ray(float3 a, float3 b, float eps) {
   return r;
 }
 
+__device__ inline float uniform(float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); }
+
+// plane_base of a single-scene launch's scene, in scalar registers
+template <bool kScaled>
+__device__ inline float3 scene_base(const SceneDev& S) {
+  const float3 b = plane_base<kScaled>(S);
+  return f3(uniform(b.x), uniform(b.y), uniform(b.z));
+}
+
+// Whether a launch's nodes are read as WALK_SCALED: where the frame of any of
+// its scenes asks for it (called by whole workgroups; the other scenes' nodes
+// read the same way).  A kernel holds its persistent loop twice, once for each
+// form, so that the usual one's registers and code are its own: as a branch
+// inside the walk the rare form made the re-trace spill 13 registers instead of
+// 2 (full trace 3.54 ms instead of 3.46, paper-scale frame 2.06 instead of 2.01).
+template <bool kSingle>
+__device__ inline bool any_scaled(const SceneDev* scenes, int n_scenes) {
+  if (kSingle) return uniform(frame_reach(scenes[0])) == __builtin_inff();
+  bool scaled = false;
+  for (int i = (int)threadIdx.x; i < n_scenes; i += (int)blockDim.x) scaled |= frame_reach(scenes[i]) == __builtin_inff();
+  return __syncthreads_or(scaled) != 0;
+}
+
 __device__ inline int light_of(const SceneDev& S, uint32_t p) {
   const PV_GLOBAL LightDev* lights = G(S.lights);
   for (uint32_t l = 0; l < S.n_lights; ++l)
@@ -563,61 +586,31 @@ __global__ __launch_bounds__(kBlock) void k_verify_gather(const SceneDev* __rest
   }
 }
 
+// The moved objects of a single scene: boxes, roots of their current
+// hierarchies, of their upload-time topologies with object-space boxes
+// with the least tmin of a segment that is walked there (longer ones, and those
+// of a transform without an inverse, are walked in world space), the inverses of
+// their transforms (rows of the inverse 3x3, then the translation), and the
+// grids of the object-space forms (what their planes count from, and the step).
+struct MovedTab {
+  MovedSet M;
+  int32_t root[PV_MAX_OBJECTS], oroot[PV_MAX_OBJECTS];
+  float tmin[PV_MAX_OBJECTS];
+  float inv[PV_MAX_OBJECTS][12];
+  float4 grid[PV_MAX_OBJECTS];
+};
+
 // Persistent: a lane whose walk has finished takes the wave's next task
 // (dealt by deal()) while the other lanes continue.
 
-template <bool kSingle>
-__global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restrict__ scenes,
-                                                         const uint32_t* __restrict__ gbase, int n_scenes,
-                                                         VerifyWork W, int min_active, uint32_t entries,
-                                                         uint32_t spread_waves) {
+template <bool kSingle, bool kScaled>
+__device__ __forceinline__ void verify_loop(const SceneDev* __restrict__ scenes, const uint32_t* __restrict__ gbase,
+                                            int n_scenes, const VerifyWork& W, const MovedTab& T, int min_active,
+                                            uint32_t entries, uint32_t spread_waves) {
   extern __shared__ int32_t sstack[];  // traversal stacks, launch-time size
-  __shared__ MovedSet M;                // single scene: the moved objects' boxes
-  __shared__ int32_t mroot[PV_MAX_OBJECTS];  // and their hierarchies' roots
-  // their upload-time topologies with object-space boxes (kRootNone: walk in
-  // world space) and the inverse of their current transforms (rows of the
-  // inverse 3x3, then the translation)
-  __shared__ int32_t moroot[PV_MAX_OBJECTS];
-  __shared__ float minv[PV_MAX_OBJECTS][12];
   const StackCol col = (StackCol)(sstack + kBlock + threadIdx.x);  // entry 0 of the column; entry -1 spare
   const StackCol limit = col + (int)(entries - 5) * kBlock;  // top from which a full node would pass the last entry
-  if (kSingle) {
-    if (threadIdx.x < 64) {
-      const SceneDev& S0 = scenes[0];
-      const uint32_t o = threadIdx.x;
-      const bool mv = o < S0.n_obj && G(S0.obj_moved)[o] != 0;
-      const uint64_t mm = __ballot(mv);
-      if (mv) {
-        const uint32_t i = (uint32_t)__popcll(mm & lanemask_lt());
-        const ObjDev ob = G(S0.objs)[o];
-        mroot[i] = ob.wroot;
-        // inverse of the 3x3 part by cofactors in FP64
-        const PV_GLOBAL float* x = G(S0.obj_xf_cur) + 12 * o;
-        const double m0 = x[0], m1 = x[1], m2 = x[2], m4 = x[4], m5 = x[5], m6 = x[6];
-        const double m8 = x[8], m9 = x[9], m10 = x[10];
-        const double c00 = m5 * m10 - m6 * m9, c01 = m2 * m9 - m1 * m10, c02 = m1 * m6 - m2 * m5;
-        const double det = m0 * c00 + m4 * c01 + m8 * c02;
-        const bool ok = fabs(det) > 1e-12 && isfinite(det);
-        const double id = ok ? 1.0 / det : 0.0;
-        minv[i][0] = (float)(c00 * id);
-        minv[i][1] = (float)(c01 * id);
-        minv[i][2] = (float)(c02 * id);
-        minv[i][3] = (float)((m6 * m8 - m4 * m10) * id);
-        minv[i][4] = (float)((m0 * m10 - m2 * m8) * id);
-        minv[i][5] = (float)((m2 * m4 - m0 * m6) * id);
-        minv[i][6] = (float)((m4 * m9 - m5 * m8) * id);
-        minv[i][7] = (float)((m1 * m8 - m0 * m9) * id);
-        minv[i][8] = (float)((m0 * m5 - m1 * m4) * id);
-        minv[i][9] = x[3];
-        minv[i][10] = x[7];
-        minv[i][11] = x[11];
-        moroot[i] = ok ? ob.oroot : kRootNone;
-      }
-    }
-    load_moved(scenes[0], M);  // ends with a barrier
-  }
-  __shared__ uint32_t sgb[kSingle ? 1 : kLdsScenes + 1];
-  if (!kSingle) gbase = stage_gbase(gbase, n_scenes, sgb);
+  const float3 base0 = scene_base<kScaled>(scenes[0]);
   const uint32_t total = *W.total;
   const uint32_t wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
   const uint32_t quota = wave_quota(total, spread_waves);
@@ -664,7 +657,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
             float tmax;
             r = segment_ray(a, b, S->eps_end, &tmax);
             const BoxRay br = segment_box_ray(a, b, S->eps_end);
-            qb = world_slab(*S, a, br.inv, r.tmin);
+            const float3 c = sub(kSingle ? base0 : plane_base<kScaled>(*S), a);
+            qb = world_slab(*S, c, br.inv, r.tmin);
+            bool far = walk_far(*S, c);
             int32_t root = G(S->wtop)[1];
             if (kSingle && !vis) {
               // the objects whose boxes the segment reaches, from LDS: one
@@ -673,20 +668,20 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
               // the moved-object tree; none, not at all
               uint32_t nh = 0;
               int only = 0;
-              for (int i = 0; i < M.n; ++i) {
-                const float4 lo = M.lo[i], hi = M.hi[i];
+              for (int i = 0; i < T.M.n; ++i) {
+                const float4 lo = T.M.lo[i], hi = T.M.hi[i];
                 const bool h = box_entry(lo.x, lo.y, lo.z, hi.x, hi.y, hi.z, br, br.tmax) != __builtin_inff();
                 nh += h ? 1u : 0u;
                 only = h ? i : only;
               }
-              root = nh == 0 ? kRootNone : (nh == 1 ? mroot[only] : root);
-              if (nh == 1 && moroot[only] != kRootNone) {
+              root = nh == 0 ? kRootNone : (nh == 1 ? T.root[only] : root);
+              if (nh == 1 && r.tmin >= T.tmin[only]) {
                 // a rigid object is walked in its own space: the segment
                 // mapped by the inverse transform (same parameter interval)
                 // meets the fixed object-space boxes, which are tighter than
                 // the world boxes of the rotated nodes; triangles are still
                 // tested in world space
-                const float* mi = minv[only];
+                const float* mi = T.inv[only];
                 const float3 ta = sub(a, f3(mi[9], mi[10], mi[11])), tb = sub(b, f3(mi[9], mi[10], mi[11]));
                 const float3 oa = f3(mi[0] * ta.x + mi[1] * ta.y + mi[2] * ta.z,
                                      mi[3] * ta.x + mi[4] * ta.y + mi[5] * ta.z,
@@ -694,17 +689,18 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
                 const float3 ob = f3(mi[0] * tb.x + mi[1] * tb.y + mi[2] * tb.z,
                                      mi[3] * tb.x + mi[4] * tb.y + mi[5] * tb.z,
                                      mi[6] * tb.x + mi[7] * tb.y + mi[8] * tb.z);
-                const float3 od = sub(ob, oa);
-                const float3 binv = rcp3(od);
-                qb = make_slab(binv, f3((S->qobj - oa.x) * binv.x, (S->qobj - oa.y) * binv.y, (S->qobj - oa.z) * binv.z),
-                               S->qinv, r.tmin);
-                root = moroot[only];
+                const float4 og = T.grid[only];
+                const float3 oc = sub(xyz(og), oa), binv = rcp3(sub(ob, oa));
+                qb = make_slab(binv, f3(oc.x * binv.x, oc.y * binv.y, oc.z * binv.z), og.w, r.tmin);
+                root = T.oroot[only];
+                far = false;
               }
             }
             if (vis) root = G(S->wtop)[0];
             vis_task = vis;
             walk_start(w, root, tmax, col);
             busy = root != kRootNone;
+            if (far) walk_leave(w);
           }
         }
       }
@@ -715,7 +711,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
     }
     const int yield = yield_below(min_active, __ballot(drained) != 0, (int)__popcll(__ballot(busy)));
     if (busy) {
-      walk_scene<false>(*S, r, qb, true, col, limit, w, yield);
+      walk_scene<false, kScaled>(*S, r, qb, true, col, limit, w, yield);
       if (walk_done(w)) {
         if (w.redo) walk_exact(G(S->nodes), G(S->tris), r, 1.0f - r.tmin, G(S->top)[vis_task ? 0 : 1], true, col, w);
         if (w.rec != kRecNone) atomicMin(&W.first[gp], j);
@@ -724,6 +720,69 @@ __global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restr
     }
   }
   if (quota >= 64) deal_done(W.deal);  // uniform over the grid
+}
+
+template <bool kSingle>
+__global__ __launch_bounds__(kBlock) void k_verify_trace(const SceneDev* __restrict__ scenes,
+                                                         const uint32_t* __restrict__ gbase, int n_scenes,
+                                                         VerifyWork W, int min_active, uint32_t entries,
+                                                         uint32_t spread_waves) {
+  __shared__ MovedTab T;
+  const bool scaled = any_scaled<kSingle>(scenes, n_scenes);
+  if (kSingle) {
+    if (threadIdx.x < 64) {
+      const SceneDev& S0 = scenes[0];
+      const uint32_t o = threadIdx.x;
+      const bool mv = o < S0.n_obj && G(S0.obj_moved)[o] != 0;
+      const uint64_t mm = __ballot(mv);
+      if (mv) {
+        const uint32_t i = (uint32_t)__popcll(mm & lanemask_lt());
+        const ObjDev ob = G(S0.objs)[o];
+        T.root[i] = ob.wroot;
+        // inverse of the 3x3 part by cofactors in FP64
+        const PV_GLOBAL float* x = G(S0.obj_xf_cur) + 12 * o;
+        const double m0 = x[0], m1 = x[1], m2 = x[2], m4 = x[4], m5 = x[5], m6 = x[6];
+        const double m8 = x[8], m9 = x[9], m10 = x[10];
+        const double c00 = m5 * m10 - m6 * m9, c01 = m2 * m9 - m1 * m10, c02 = m1 * m6 - m2 * m5;
+        const double det = m0 * c00 + m4 * c01 + m8 * c02;
+        const bool ok = fabs(det) > 1e-12 && isfinite(det);
+        const double id = ok ? 1.0 / det : 0.0;
+        T.inv[i][0] = (float)(c00 * id);
+        T.inv[i][1] = (float)(c01 * id);
+        T.inv[i][2] = (float)(c02 * id);
+        T.inv[i][3] = (float)((m6 * m8 - m4 * m10) * id);
+        T.inv[i][4] = (float)((m0 * m10 - m2 * m8) * id);
+        T.inv[i][5] = (float)((m2 * m4 - m0 * m6) * id);
+        T.inv[i][6] = (float)((m4 * m9 - m5 * m8) * id);
+        T.inv[i][7] = (float)((m1 * m8 - m0 * m9) * id);
+        T.inv[i][8] = (float)((m0 * m5 - m1 * m4) * id);
+        T.inv[i][9] = x[3];
+        T.inv[i][10] = x[7];
+        T.inv[i][11] = x[11];
+        T.oroot[i] = ob.oroot;
+        // a segment of length L that reaches the object's world box stays within
+        // 'norm' (L + the box's extent) of the object's middle in object space
+        float norm = 0.0f, side = 0.0f, base = 0.0f;
+        for (int k = 0; k < 3; ++k) {
+          const PV_GLOBAL float* bb = G(S0.obj_aabb) + 6 * o;
+          norm = fmaxf(norm, fabsf(T.inv[i][3 * k]) + fabsf(T.inv[i][3 * k + 1]) + fabsf(T.inv[i][3 * k + 2]));
+          side = fmaxf(side, bb[3 + k] - bb[k]);
+          base = fmaxf(base, fmaxf(fabsf(ob.centre[k]), fabsf(ob.centre[k] - ob.og[k])));
+        }
+        const float most = (kObjReach * ob.oinv - base) / norm - side;
+        T.tmin[i] = ok && most > 0.0f ? S0.eps_end / most : __builtin_inff();
+        const float mid = scaled && S0.wshift ? kOriginMid * ob.oinv : 0.0f;
+        T.grid[i] = make_float4(ob.og[0] + mid, ob.og[1] + mid, ob.og[2] + mid, ob.oinv);  // exact
+      }
+    }
+    load_moved(scenes[0], T.M);  // ends with a barrier
+  }
+  __shared__ uint32_t sgb[kSingle ? 1 : kLdsScenes + 1];
+  if (!kSingle) gbase = stage_gbase(gbase, n_scenes, sgb);
+  if (scaled)
+    verify_loop<kSingle, true>(scenes, gbase, n_scenes, W, T, min_active, entries, spread_waves);
+  else
+    verify_loop<kSingle, false>(scenes, gbase, n_scenes, W, T, min_active, entries, spread_waves);
 }
 
 // The tasks of a path are adjacent in the list: the thread holding a path's
@@ -1374,29 +1433,18 @@ __device__ inline float3 sample_ray(const SceneDev& S, const Lane& L, uint64_t s
   return done ? w : q;
 }
 
-template <bool kSingle, int kWaves>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))) void k_retrace(const SceneDev* __restrict__ scenes, const uint32_t* __restrict__ gbase,
-                                                    int n_scenes, const uint32_t* __restrict__ queue,
-                                                    const uint32_t* __restrict__ qcount, float T,
-                                                    uint64_t seed, uint32_t frame_arg, const uint32_t* frame_ptr,
-                                                    pv_stats* stats, int min_active, uint32_t entries,
-                                                    uint32_t spread_waves, uint32_t* __restrict__ deal_ctr) {
+template <bool kSingle, bool kScaled>
+__device__ __forceinline__ void retrace_loop(const SceneDev* __restrict__ scenes, const uint32_t* __restrict__ gbase,
+                                             int n_scenes, const uint32_t* __restrict__ queue,
+                                             const uint32_t* __restrict__ qcount, float T, uint64_t seed,
+                                             uint32_t frame, const PV_LDS SceneTab* tab, uint32_t* scount,
+                                             pv_stats* stats, int min_active, uint32_t entries, uint32_t spread_waves,
+                                             uint32_t* __restrict__ deal_ctr) {
   extern __shared__ int32_t sstack[];  // traversal stacks, launch-time size
-  __shared__ uint32_t scount[4];
-  __shared__ SceneTab stab;
   const StackCol col = (StackCol)(sstack + kBlock + threadIdx.x);  // entry 0 of the column; entry -1 spare
   const StackCol limit = col + (int)(entries - 5) * kBlock;  // top from which a full node would pass the last entry
-  const uint32_t frame = frame_ptr ? *frame_ptr : frame_arg;
   uint32_t n_rays = 0, n_photons = 0, n_acc = 0, n_trunc = 0;  // of the wave
-  const PV_LDS SceneTab* tab = nullptr;
-  if (threadIdx.x < 4) scount[threadIdx.x] = 0;
-  if (kSingle) {
-    load_tab(scenes[0], stab);
-    tab = (const PV_LDS SceneTab*)&stab;
-  }
-  __shared__ uint32_t sgb[kSingle ? 1 : kLdsScenes + 1];
-  if (!kSingle) gbase = stage_gbase(gbase, n_scenes, sgb);
-  __syncthreads();
+  const float3 base0 = scene_base<kScaled>(scenes[0]);
   // the work queue, dealt by deal() from the counters 'deal_ctr'
   const uint32_t count = *qcount;
   const uint32_t wave = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
@@ -1421,8 +1469,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
     // instructions beside the walk's thousands, and hold no registers outside
     const int yield = yield_below(min_active, drained, (int)__popcll(__ballot(tracing)));
     if (tracing) {
-      const Slab q = world_slab(S, ray_origin(r), rcp3(r.d), r.tmin);
-      walk_scene<true>(S, r, q, any, col, limit, wk, yield);
+      const float3 c = sub(kSingle ? base0 : plane_base<kScaled>(S), ray_origin(r));
+      const Slab q = world_slab(S, c, rcp3(r.d), r.tmin);
+      if (walk_far(S, c)) walk_leave(wk);
+      walk_scene<true, kScaled>(S, r, q, any, col, limit, wk, yield);
     }
     // ---- lanes whose walk is finished advance their path.  What several
     // modes share is done once for all of them: the new vertex with its
@@ -1651,6 +1701,34 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))
       atomicAdd(to[threadIdx.x], (unsigned long long)scount[threadIdx.x]);
     }
   }
+}
+
+template <bool kSingle, int kWaves>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWaves))) void k_retrace(const SceneDev* __restrict__ scenes, const uint32_t* __restrict__ gbase,
+                                                    int n_scenes, const uint32_t* __restrict__ queue,
+                                                    const uint32_t* __restrict__ qcount, float T,
+                                                    uint64_t seed, uint32_t frame_arg, const uint32_t* frame_ptr,
+                                                    pv_stats* stats, int min_active, uint32_t entries,
+                                                    uint32_t spread_waves, uint32_t* __restrict__ deal_ctr) {
+  __shared__ uint32_t scount[4];
+  __shared__ SceneTab stab;
+  __shared__ uint32_t sgb[kSingle ? 1 : kLdsScenes + 1];
+  const uint32_t frame = frame_ptr ? *frame_ptr : frame_arg;
+  if (threadIdx.x < 4) scount[threadIdx.x] = 0;
+  const PV_LDS SceneTab* tab = nullptr;
+  if (kSingle) {
+    load_tab(scenes[0], stab);
+    tab = (const PV_LDS SceneTab*)&stab;
+  } else {
+    gbase = stage_gbase(gbase, n_scenes, sgb);
+  }
+  __syncthreads();
+  if (any_scaled<kSingle>(scenes, n_scenes))
+    retrace_loop<kSingle, true>(scenes, gbase, n_scenes, queue, qcount, T, seed, frame, tab, scount, stats, min_active,
+                                entries, spread_waves, deal_ctr);
+  else
+    retrace_loop<kSingle, false>(scenes, gbase, n_scenes, queue, qcount, T, seed, frame, tab, scount, stats, min_active,
+                                 entries, spread_waves, deal_ctr);
 }
 
 // ---------------------------------------------------------------------------

@@ -641,9 +641,26 @@ __global__ void k_lbvh_finish(SceneDev* __restrict__ scenes, LbvhWork W, const u
 
 constexpr int kTopLevels = kTopDepth - 1;  // median levels over <= PV_MAX_OBJECTS objects
 
+// Whether a frame's walks need nodes with units of their own: an object has
+// one, or a light's rays begin beyond what the grid's planes cover.
+template <typename M>
+__device__ inline bool object_scaled(const SceneDev& S, uint32_t o, M m) {
+  return S.wshift && object_grid(S, o, m).e != 0;
+}
+
+template <typename M>
+__device__ inline bool light_scaled(const SceneDev& S, uint32_t l, M m) {
+  const PV_GLOBAL LightDev* lt = G(S.lights) + l;
+  float d = 0.0f;
+  for (int k = 0; k < 3; ++k)
+    d = fmaxf(d, fabsf(m[4 * k + 3] - S.qc[k]) + fabsf(m[4 * k]) * lt->half[0] + fabsf(m[4 * k + 1]) * lt->half[1]);
+  return S.wshift && !(d <= kRayReach * S.qinv);
+}
+
 // The trees of one scene, by waves 0 and 1 of a workgroup (all its threads
-// come here).
-__device__ inline void build_top(SceneDev& S) {
+// come here).  scaled (the first wave's): an object, a light or an earlier frame
+// asks for units.
+__device__ inline void build_top(SceneDev& S, bool scaled) {
   static_assert(PV_MAX_OBJECTS <= 64, "one lane per object");
   static_assert((1 << kTopLevels) >= PV_MAX_OBJECTS, "median levels");
   __shared__ float sbx[2][2][6][64];  // [tree][buffer][box component][position]
@@ -651,7 +668,6 @@ __device__ inline void build_top(SceneDev& S) {
   const bool idle = threadIdx.x >= 128;      // a wave without a tree
   const int which = (threadIdx.x >> 6) & 1;  // tree of this wave
   const uint32_t lane = threadIdx.x & 63u;
-  const PlaneWriter wide(S);
   PV_GLOBAL Node* nodes = G(S.nodes);
   float sbox[6];
   for (int k = 0; k < 6; ++k) sbox[k] = S.sbox[k];
@@ -660,10 +676,35 @@ __device__ inline void build_top(SceneDev& S) {
   const bool take = have && (which == 0 || S.obj_moved[lane] != 0);
   const uint64_t mm = __ballot(take);
   const uint32_t n = (uint32_t)__popcll(mm);
-  if (take) {
-    const uint32_t i = (uint32_t)__popcll(mm & lanes_below());
-    for (int k = 0; k < 6; ++k) sbx[which][0][k][i] = S.obj_aabb[6 * lane + k];
-    scode[which][0][i] = make_int2(S.objs[lane].root, S.objs[lane].wroot);
+  float ext = 0.0f;  // the objects' largest distance from the grid's middle, in steps
+  if (have) {
+    float b6[6];
+    for (int k = 0; k < 6; ++k) {
+      b6[k] = S.obj_aabb[6 * lane + k];
+      ext = fmaxf(ext, fabsf((b6[k] - S.qm[k % 3]) * S.qs));
+    }
+    if (take) {
+      const uint32_t i = (uint32_t)__popcll(mm & lanes_below());
+      for (int k = 0; k < 6; ++k) sbx[which][0][k][i] = b6[k];
+      scode[which][0][i] = make_int2(S.objs[lane].root, S.objs[lane].wroot);
+    }
+  }
+  // unit of the top-level nodes: FP16 planes serve boxes at any distance from
+  // their origin alike, up to 65,504 units
+  const bool reach = __ballot(!(ext <= 30000.0f)) == 0 && (S.sroot != kRootNone || __ballot(ext >= 1.0f) != 0);
+  int unit = 0;
+  if (!reach) {
+    for (int o = 32; o > 0; o >>= 1) ext = fmaxf(ext, __shfl_xor(ext, o, 64));
+    unit = ceil_exp(ext * (1.0f / 128.0f));
+  }
+  const PlaneWriter wide(S, unit);
+  const bool asked = __ballot(scaled) != 0;
+  if (which == 0 && lane == 0 && !idle) {
+    // once scaled, always: paths may keep vertices from where things were then
+    const bool units = S.wshift && (asked || wide.g.e);
+    if (units) S.state[1] = 1;
+    const float near_ = kRayReach * S.qinv;
+    S.wtop[2] = __float_as_int(S.wshift ? (units ? __builtin_inff() : near_) : (reach ? near_ : kReachNone));
   }
   __syncthreads();
   uint32_t lo = 0, hi = n;  // range of this lane's position
@@ -812,7 +853,14 @@ __device__ inline void build_top(SceneDev& S) {
 }
 
 // the trees alone (after a rebuild of the objects' hierarchies)
-__global__ __launch_bounds__(128) void k_build_top(SceneDev* __restrict__ scenes) { build_top(scenes[blockIdx.x]); }
+__global__ __launch_bounds__(128) void k_build_top(SceneDev* __restrict__ scenes) {
+  SceneDev& S = scenes[blockIdx.x];
+  const uint32_t i = threadIdx.x;
+  bool scaled = S.state[1] != 0;
+  if (i < S.n_obj) scaled |= object_scaled(S, i, S.obj_xf_cur + 12 * i);
+  if (i < S.n_lights) scaled |= light_scaled(S, i, S.light_xf_cur + 12 * i);
+  build_top(S, scaled);
+}
 
 // ---------------------------------------------------------------------------
 // The beginning of a frame, two launches (a chain of dependent launches costs
@@ -913,8 +961,10 @@ __global__ __launch_bounds__(kBlock) void k_refit(SceneDev* __restrict__ scenes,
   const float* oxf = in.obj_tab ? in.obj_tab[tile.x] : in.obj;
   const float* lxf = in.light_tab ? in.light_tab[tile.x] : in.light;
   const uint32_t first = S.state[0];
+  static_assert(PV_MAX_OBJECTS <= 64 && PV_MAX_LIGHTS <= 64, "the first wave takes all rows");
   // an object's row by one thread: transform history, the staged copy that
   // later sparse updates start from, box and current hierarchy
+  bool scaled = S.state[1] != 0;
   ObjDev* objs = const_cast<ObjDev*>(S.objs);
   for (uint32_t o = threadIdx.x; o < S.n_obj; o += kBlock) {
     float c[12], v[12];
@@ -922,6 +972,7 @@ __global__ __launch_bounds__(kBlock) void k_refit(SceneDev* __restrict__ scenes,
       c[i] = S.obj_xf_cur[12 * o + i];
       v[i] = oxf[12 * o + i];
     }
+    if (top) scaled |= object_scaled(S, o, v);
     for (int i = 0; i < 12; ++i) {
       S.obj_xf_prev[12 * o + i] = c[i];
       S.obj_xf_cur[12 * o + i] = v[i];
@@ -946,6 +997,7 @@ __global__ __launch_bounds__(kBlock) void k_refit(SceneDev* __restrict__ scenes,
       v[i] = lxf[12 * l + i];
       moved |= __float_as_uint(c[i]) != __float_as_uint(v[i]) ? 1u : 0u;
     }
+    if (top) scaled |= light_scaled(S, l, v);
     for (int i = 0; i < 12; ++i) {
       S.light_xf_prev[12 * l + i] = c[i];
       S.light_xf_cur[12 * l + i] = v[i];
@@ -955,7 +1007,7 @@ __global__ __launch_bounds__(kBlock) void k_refit(SceneDev* __restrict__ scenes,
   }
   __syncthreads();
   if (threadIdx.x == 0) S.state[0] = 0;
-  if (top) build_top(S);
+  if (top) build_top(S, scaled);
 }
 
 hipError_t launch_frame_begin(SceneDev* scenes, int n_scenes, const uint2* place_tiles, uint32_t n_place,

@@ -1,0 +1,146 @@
+"""Scenes whose dynamic objects set the scale: no static world or a tiny one,
+objects far from it, in other units, and lights outside.  Boxes only prune, so
+paths are those of the same scene at unit scale, bit for bit where the scale is a
+power of two, and the time is that of the same scene near the origin."""
+import numpy as np
+import pytest
+
+from paper_2111_06906_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def E():
+    from paper_2111_06906_amd import engine
+    return engine
+
+
+def _objects_only(world=1.0, local=1.0, offset=0.0, n_paths=20_000, static=0.0, frames=3):
+    """The 3x3-room interior as one object beside its eight tori, scaled by
+    'world', its objects modelled at 'local' times their size, moved by
+    'offset'; static: size of the one static triangle (0: none)."""
+    sc = scenes.make_rooms("rooms", 3, 3, 20_000, 8, (50, 25), n_paths, 5, frames, 0.01, 3, n_lights=1,
+                           torus_size=(0.2, 0.07))
+    rooms = sc.static_verts.reshape(-1, 3, 3)
+    still = np.tile(np.array([1, 0, 0, 0, 0, 1, 0, 0, 0, 0, 1, 0], np.float32), (frames, 1, 1))
+    xf = np.concatenate([still, sc.obj_xforms[:frames]], axis=1).astype(np.float64).reshape(frames, -1, 3, 4)
+    xf[..., 3] = xf[..., 3] * world + offset
+    xf[..., :3] *= world / local
+    sc.obj_xforms = xf.reshape(frames, -1, 12).astype(np.float32)
+    sc.obj_local = [(o.reshape(-1, 3, 3).astype(np.float64) * local).astype(np.float32) for o in [rooms, *sc.obj_local]]
+    sc.obj_mat = [sc.static_mat] + list(sc.obj_mat)
+    lx = sc.light_xforms[:frames].astype(np.float64).reshape(frames, -1, 3, 4)
+    lx[..., 3] = lx[..., 3] * world + offset
+    sc.light_xforms = lx.reshape(frames, -1, 12).astype(np.float32)
+    sc.light_half = (sc.light_half * world).astype(np.float32)
+    sc.eps_end *= world
+    sc.eps_close *= world
+    tri = np.array([[[0, 0, 0], [1, 0, 0], [0, 1, 0]]], np.float32) * static + np.float32(0.3 * world + offset)
+    sc.static_verts = tri.astype(np.float32) if static else np.zeros((0, 3, 3), np.float32)
+    sc.static_mat = np.zeros(1 if static else 0, np.uint32)
+    return sc
+
+
+def _run(E, sc, rebuild=0, batch=False):
+    ctx = E.Context(sc)
+    ctx.set_tuning(object_rebuild=rebuild)
+    st = ctx.new_store()
+    ctx.frame_begin(0)
+    ctx.initial_trace(st, 5)
+    stats = ctx.new_stats()
+    if batch:
+        b = E.Batch([ctx], [st], 0.01, 5)
+        for f in (1, 2):
+            b.frame(f, stats)
+        b.close()
+    else:
+        for f in (1, 2):
+            ctx.frame_begin(f)
+            ctx.verify(st, stats)
+            ctx.retrace(st, 0.01, 5, f, stats)
+    d = st.to_numpy()
+    d["stats"] = stats.cpu().numpy()
+    ctx.close()
+    return d
+
+
+@pytest.fixture(scope="module")
+def unit(E):
+    return _run(E, _objects_only())
+
+
+# Coordinates 2^-10 to 4 (a ray reaches 16 units), objects in their own units
+# 2^-12 to 2^12 of the world's.  Scaling by powers of two is exact; the boxes'
+# absolute padding may settle a tie at an edge (one ray in 10^4) another way.
+@pytest.mark.parametrize("world,local,rebuild,batch", [
+    (2.0 ** -10, 2.0 ** -10, 0, False), (2.0 ** -7, 1.0, 0, False), (2.0 ** -7, 1.0, 1, False), (4.0, 4.0, 0, False),
+    (4.0, 2.0 ** -8, 0, True), (1.0, 2.0 ** 12, 0, False), (1.0, 2.0 ** -12, 0, False)])
+def test_scaled_scenes_have_the_same_paths(E, unit, world, local, rebuild, batch):
+    d = _run(E, _objects_only(world, local), rebuild, batch)
+    n = d["info"].shape[0]
+    same = (d["info"] == unit["info"]) & np.all(d["hit"] == unit["hit"], axis=0)
+    there = unit["hit"] != 0xFFFFFFFF
+    same &= np.all((d["pos"] == unit["pos"] * np.float32(world)).all(-1) | ~there, axis=0)
+    assert same.sum() >= n - n // 1000, (n - same.sum(), n)
+
+
+def _times(E, sc):
+    """Full trace, verification and re-trace of the second frame, in us."""
+    import torch
+    ctx = E.Context(sc)
+    st = ctx.new_store()
+    ctx.frame_begin(0)
+
+    def timed(f):
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        torch.cuda.synchronize()
+        ev[0].record()
+        f()
+        ev[1].record()
+        torch.cuda.synchronize()
+        return ev[0].elapsed_time(ev[1]) * 1e3
+
+    full = min(timed(lambda: ctx.initial_trace(st, 5)) for _ in range(4))
+    keep = [t.clone() for t in (st.pos_hit, st.energy, st.origin, st.info)]
+    ctx.frame_begin(1)
+    verify, trace = [], []
+    for _ in range(4):
+        for t, k in zip((st.pos_hit, st.energy, st.origin, st.info), keep):
+            t.copy_(k)
+        verify.append(timed(lambda: ctx.verify(st)))
+        trace.append(timed(lambda: ctx.retrace(st, 0.01, 5, 1)))
+    ctx.close()
+    return np.array([full, min(verify), min(trace)])
+
+
+# Culling ended where planes counted from a grid that the objects had no part in:
+# 65 ms a trace instead of 0.6 at coordinates near 1000, 63 instead of 0.5 beside
+# a static triangle of 0.0005 units.  FP32 coordinates near 1000 themselves take
+# about 1.5 times as long.
+def test_time_does_not_follow_the_placement(E):
+    near = _times(E, _objects_only())
+    for label, sc in (("offset 100", _objects_only(offset=100.0)), ("offset 1000", _objects_only(offset=1000.0)),
+                      ("static 0.002", _objects_only(static=0.002)), ("static 0.0005", _objects_only(static=0.0005)),
+                      ("local 4096", _objects_only(local=4096.0))):
+        t = _times(E, sc)
+        print(label, t, near)
+        assert (t <= 4.0 * near).all(), (label, t, near)
+
+
+# A light several half extents outside the static world (its rays begin beyond
+# what the grid's planes cover), and an object that leaves and returns: the same
+# paths as the oracle's, within the harness' rules.
+def test_light_and_object_outside_lockstep(E):
+    from tests.test_gpu_parity import _lockstep
+    sc = scenes.make_rooms("outside", 2, 2, 3000, 3, (16, 8), 4000 + 5, 5, 4, 0.01, 17, n_lights=2, lights_move=True)
+    sc.obj_xforms = sc.obj_xforms.copy()
+    sc.obj_xforms[1:3, 0, 3] += np.array([40.0, 3.0], np.float32)
+    _lockstep(E, sc, 4, 0.01, "object leaves and returns")
+    # the light high above an opened roof: every third static triangle is gone
+    sc = scenes.make_rooms("above", 2, 2, 3000, 3, (16, 8), 40_000 + 5, 5, 3, 0.01, 19, n_lights=2, lights_move=True)
+    keep = np.arange(sc.n_static) % 3 != 0
+    sc.static_verts, sc.static_mat = sc.static_verts[keep], sc.static_mat[keep]
+    sc.light_xforms = sc.light_xforms.copy()
+    sc.light_xforms[:, 0, 7] += 14.5
+    _lockstep(E, sc, 3, 0.01, "light above", require_replaced=False)

@@ -23,3 +23,7 @@ def _run(tmp_path, driver):
 
 def test_slabs_are_conservative(tmp_path):
     _run(tmp_path, "wide_walk_driver.cpp")
+
+
+def test_units_contain_and_are_conservative(tmp_path):
+    _run(tmp_path, "wide_units_driver.cpp")
