@@ -823,9 +823,10 @@ __device__ __forceinline__ void plane_pair(uint32_t w, uint32_t rot, float inv, 
 // interval, while triangles stay in world space.
 //
 // w.redo asks the caller to take walk_exact's answer instead: set when a walk
-// would leave more entries than 'limit' (the top's address there) allows, and,
-// with kTies, when two crossings lie within 2.5e-7 of each other, twice the
-// rounding that lets the order of their tests decide.
+// would leave more entries than 'limit' (the top's address there) allows, which
+// leaves no crossing, and, with kTies, when the closest crossing and one of
+// another leaf lie within 2.5e-7 of each other, twice the rounding that lets the
+// order of their tests decide.
 //
 // With WALK_SCALED a node has its own unit, and the slabs are widened by 2^-20
 // of |qm - o| / d, twice what the ray's part of their roundings is: for ray
@@ -917,6 +918,7 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
       cur = lane_bit(h[0]) ? c[0] : below;
       if (top > limit) {  // rare: no room for another full node
         redo = true;
+        rec = kRecNone;
         cur = kRootNone;
         leaf = 0;
         break;
@@ -946,7 +948,9 @@ __device__ inline void walk_run(const PV_GLOBAL Wide* __restrict__ nodes, const 
         float t;
         bool near_tb = false;
         const bool hit = tri_hit(r, tris + i, tb, &t, kTies ? &near_tb : nullptr);
-        if (kTies) redo = near_tb || (redo && !hit);  // a clearly closer crossing ends a tie
+        // both walks test one leaf's triangles in the same order; a clearly
+        // closer crossing ends a tie
+        if (kTies) redo = (near_tb && rec - f >= n) || (redo && !(hit && !near_tb));
         tb = hit ? t : tb;
         rec = hit ? i : rec;
         found |= hit;
@@ -986,8 +990,14 @@ __device__ inline void walk_scene(const SceneDev& S, const Ray& r, const Slab& q
 // when both at once) before the other, a later crossing taken only when
 // strictly closer.  Two crossings within rounding of each other (an edge of a
 // wall on a floor) are otherwise decided by the order of their tests, which
-// the four-wide walk's looser boxes change.  Rare (one ray in 10^4), so
-// nothing here is tuned.  any: stop at the first crossing.
+// the four-wide walk's looser boxes change.  any: stop at the first crossing.
+//
+// A tie is settled among the crossings near the one that w holds: boxes that end
+// before or begin after it are left out, which changes neither the order of the
+// others nor what is taken among them, and a descent to a point is left of the
+// walk.  Two-sided assets hold every triangle twice: a full trace of 500k paths
+// through a room of 50k such pairs took 2.29 ms with every tie walked again in
+// full and takes 0.83 (0.72 without the copies; 1.10 with the binary walk alone).
 __device__ inline void walk_exact(const PV_GLOBAL Node* __restrict__ nodes, const PV_GLOBAL Tri* __restrict__ tris,
                                   const Ray& r, float tmax, int32_t root, bool any, StackCol col, Walk& w) {
   const float3 o = ray_origin(r), d = r.d;
@@ -997,12 +1007,14 @@ __device__ inline void walk_exact(const PV_GLOBAL Node* __restrict__ nodes, cons
              1.0f / (fabsf(d.y) > tiny ? d.y : copysignf(tiny, d.y)),
              1.0f / (fabsf(d.z) > tiny ? d.z : copysignf(tiny, d.z)));
   q.oi = f3(-(o.x * q.inv.x), -(o.y * q.inv.y), -(o.z * q.inv.z));
-  q.tmin = r.tmin;
-  q.tmax = tmax;
+  const bool tie = w.rec != kRecNone;
+  constexpr float kNear = 2e-6f;
+  q.tmin = tie ? fmaxf(r.tmin, w.tb * (1.0f - kNear)) : r.tmin;
+  q.tmax = tie ? fminf(tmax, w.tb * (1.0f + kNear)) : tmax;
   StackCol top = col;
   top[0] = kRootNone;
   int32_t cur = root;
-  float tb = tmax;
+  float tb = q.tmax;
   uint32_t rec = kRecNone;
   while (cur != kRootNone) {
     if (cur >= 0) {
@@ -1032,6 +1044,7 @@ __device__ inline void walk_exact(const PV_GLOBAL Node* __restrict__ nodes, cons
     cur = top[0];
     top -= kBlock;
   }
+  if (tie && rec == kRecNone) return;
   w.tb = tb;
   w.rec = rec;
 }
