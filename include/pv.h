@@ -497,7 +497,9 @@ pv_status pv_hierarchy_info(const float* h_verts, uint32_t n, int32_t kind, uint
  * nodes and the object's triangles to the host): out[0] internal nodes,
  * out[1] leaves, out[2] depth of the deepest leaf, out[3] = 1 when the leaves
  * partition the object's triangles, every box on the way to a leaf contains
- * its triangles and the depth fits the traversal stack, out[4] = 1 when the
+ * its triangles, the same holds for the four-wide form that the walks read, a
+ * rebuilt hierarchy's leaves are in the order of their codes, and the depth
+ * fits the traversal stack, out[4] = 1 when the
  * hierarchy is the per-frame rebuilt one (PV_TUNE_OBJECT_REBUILD), 0 for the
  * refit upload-time topology.  PV_ERR_ARG for an object index out of range,
  * PV_ERR_STATE before a scene upload. */

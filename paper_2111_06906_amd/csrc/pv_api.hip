@@ -15,6 +15,7 @@
 #include <system_error>
 #include <vector>
 
+#include "pv_check.h"
 #include "pv_device.h"
 #include "pv_launch.h"
 
@@ -1738,6 +1739,7 @@ pv_status pv_object_hierarchy_info(pv_ctx* ctx, uint32_t obj, uint32_t* out) {
     // lie in the object's topology or rebuild region, its leaves partition the
     // object's triangle records, every box on the way to a leaf contains that
     // leaf's triangles, and no leaf is deeper than the stack allows
+    std::vector<uint32_t> order;  // leaves' records, depth first
     const bool in_rebuild = ob.root >= 0 && (uint32_t)ob.root >= ob.lbvh_base;
     const uint32_t lo = in_rebuild ? ob.lbvh_base : ob.node_base;
     const uint32_t hi = in_rebuild ? ob.lbvh_base + (ob.n_tris - 1) : ob.node_base + ob.n_nodes;
@@ -1769,6 +1771,7 @@ pv_status pv_object_hierarchy_info(pv_ctx* ctx, uint32_t obj, uint32_t* out) {
             break;
           }
           seen[i - first] = 1;
+          order.push_back(i - first);
           const Tri& t = tris[i - first];
           for (int q = 0; q < 3; ++q) {
             const float* v = t.v[q];
@@ -1785,7 +1788,7 @@ pv_status pv_object_hierarchy_info(pv_ctx* ctx, uint32_t obj, uint32_t* out) {
       ++n_int;
       const Node& nd = nodes[it.code];
       const float* f = reinterpret_cast<const float*>(&nd);
-      for (int side = 0; side < 2; ++side) {
+      for (int side = 2; side-- > 0;) {  // the first child is popped first
         It ch;
         ch.code = side ? nd.d.y : nd.d.x;
         ch.depth = it.depth + 1;
@@ -1796,6 +1799,14 @@ pv_status pv_object_hierarchy_info(pv_ctx* ctx, uint32_t obj, uint32_t* out) {
     }
     for (uint32_t i = 0; i < ob.n_tris && ok; ++i)
       if (!seen[i]) ok = false;
+    // the form that the walks read, and the rebuild's order of the leaves
+    std::vector<Wide> wide(hs.wtop_base);
+    CK(hipMemcpy(wide.data(), hs.wide, sizeof(Wide) * wide.size(), hipMemcpyDeviceToHost));
+    float reach = 0.0f;
+    CK(hipMemcpy(&reach, hs.wtop + 2, 4, hipMemcpyDeviceToHost));
+    const pv::PlanesOf planes{hs.qc, hs.qm, hs.qs, hs.wshift, reach == INFINITY};
+    ok = ok && pv::check_wide(wide.data(), hs.wtop_base, ob.wroot, planes, tris.data(), first, ob.n_tris);
+    if (in_rebuild) ok = ok && pv::check_code_order(order, tris.data(), ob.n_tris);
     const uint32_t allowed = ctx->lbvh_used ? std::max(ctx->obj_depth, ctx->lbvh_depth) : ctx->obj_depth;
     out[0] = n_int;
     out[1] = n_leaf;

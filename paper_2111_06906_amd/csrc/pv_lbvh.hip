@@ -75,10 +75,17 @@ __device__ inline uint32_t object_of_record(const SceneDev& S, uint32_t r) {
 
 __device__ inline float3 vertex_of(const Tri& t, int i) { return make_float3(t.v[i][0], t.v[i][1], t.v[i][2]); }
 
-__device__ inline float3 centroid(const Tri& t) {
-  const float s = 1.0f / 3.0f;
+constexpr float kThird = 1.0f / 3.0f;
+
+// three times the centroid
+__device__ inline float3 vertex_sum(const Tri& t) {
   const float3 a = vertex_of(t, 0), b = vertex_of(t, 1), c = vertex_of(t, 2);
-  return make_float3((a.x + b.x + c.x) * s, (a.y + b.y + c.y) * s, (a.z + b.z + c.z) * s);
+  return make_float3(a.x + b.x + c.x, a.y + b.y + c.y, a.z + b.z + c.z);
+}
+
+__device__ inline float3 centroid(const Tri& t) {
+  const float3 v = vertex_sum(t);
+  return make_float3(v.x * kThird, v.y * kThird, v.z * kThird);
 }
 
 // 10 bits spread to every third bit
@@ -91,9 +98,11 @@ __device__ inline uint32_t spread3(uint32_t v) {
   return v;
 }
 
-__device__ inline uint32_t quantise(float c, float lo, float hi) {
+// one axis of a centroid's code (sum: three times the centroid), its roundings
+// spelled out: the order of codes is that of pv_check.h's
+__device__ inline uint32_t quantise(float sum, float lo, float hi) {
   const float ext = hi - lo;
-  const float u = ext > 0.0f ? (c - lo) / ext : 0.0f;
+  const float u = ext > 0.0f ? fmaf(sum, kThird, -lo) / ext : 0.0f;
   return min((uint32_t)fmaxf(u * 1024.0f, 0.0f), 1023u);
 }
 
@@ -210,7 +219,7 @@ __device__ inline void object_bounds(const SceneDev& S, const ObjDev& ob, float 
 
 // Morton code of a triangle's centroid in its object's centroid box
 __device__ inline uint32_t morton(const Tri& t, const float b[6]) {
-  const float3 c = centroid(t);
+  const float3 c = vertex_sum(t);
   return (spread3(quantise(c.x, b[0], b[3])) << 2) | (spread3(quantise(c.y, b[1], b[4])) << 1) |
          spread3(quantise(c.z, b[2], b[5]));
 }

@@ -27,3 +27,7 @@ def test_slabs_are_conservative(tmp_path):
 
 def test_units_contain_and_are_conservative(tmp_path):
     _run(tmp_path, "wide_units_driver.cpp")
+
+
+def test_hierarchy_checks_refuse_planted_mistakes(tmp_path):
+    _run(tmp_path, "hierarchy_check_driver.cpp")
