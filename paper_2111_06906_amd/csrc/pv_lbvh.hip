@@ -252,6 +252,14 @@ __global__ __launch_bounds__(kBlock) void k_lbvh_keys(const SceneDev* __restrict
 // digits), scans the counts digit by digit, and moves the keys through LDS.
 constexpr uint32_t kSortWaves = 1024 / 64;
 
+// The lanes of a wave exchange words in LDS: its operations take effect in
+// program order, and the fence keeps the compiler from moving one lane's access
+// across another's (a scheduling barrier alone does not say so).
+__device__ __forceinline__ void sync_wave() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // kMax: triangles of the largest object, 8,192 or kSmallSort (24 objects of
 // 1,024: 14.8 us; eight of 10,000, a frame begin with rebuild 213 to 176 us)
 template <uint32_t kMax>
@@ -290,9 +298,9 @@ __global__ __launch_bounds__(1024) void k_lbvh_sort(const SceneDev* __restrict__
       }
       const uint32_t before = have ? cnt[wave][d] : 0u;
       pos[i] = before + (uint32_t)__popcll(peers & lanes_below());
-      __builtin_amdgcn_wave_barrier();  // every lane has read before the last of its peers writes
+      sync_wave();  // every lane has read before the last of its peers writes
       if (have && (peers >> lane) == 1ull) cnt[wave][d] = (uint16_t)(pos[i] + 1);
-      __builtin_amdgcn_wave_barrier();
+      sync_wave();
     }
     __syncthreads();
     // a thread per digit: exclusive scan over (digit, wave)
