@@ -298,12 +298,19 @@ __device__ inline uint32_t deal(uint32_t* __restrict__ ctrs, uint32_t wave, uint
 // q = ceil(count / waves), and nothing is dealt.  (64: the list is dealt.)
 // A wave's time is the sum over its rounds of the longest walk among its
 // lanes, so that few lanes per wave finish sooner as long as waves share no
-// SIMD with many others: 45k paths of a 60k-path frame, 24 objects, re-traced
-// in 340 us over three workgroups per compute unit (all of which fit beside
-// each other at the largest stack), 360 over two, 382 over one and 445 dealt;
-// their verification tasks in 69 us over two, 77 over one, 84 over four and
-// 81 dealt.
-constexpr uint32_t kSpreadRetrace = 3, kSpreadVerify = 2;  // workgroups per compute unit
+// SIMD with many others, and all of them are there from the start.
+//
+// Re-traced paths of a 50k-triangle interior spread over four workgroups per
+// compute unit, against dealt, in us: 77k 266 and 334, 103k 300 and 314, 129k
+// 320 and 326, 155k 323 and 335, 181k 335 and 355, 215k 348 and 355, camera
+// paths 96k 303 and 330, 193k 356 and 371, 225k 371 and 386; lists of up to 51k
+// within 3%.  So spreading is the better of the two up to the 64 lanes at which
+// it ends.  Over three workgroups the same lists take up to 7% longer; where
+// only three fit beside each other (the largest stacks: 24 rebuilt objects, 45k
+// paths) a fourth makes it 398 us instead of 300.  Verification tasks over two
+// workgroups: 59k 61 and 67 us, 88k 72 and 78, 118k 80 and 83 (over four 61, 72
+// and 78, but 29k 65 instead of 58).
+constexpr uint32_t kSpreadRetrace = 4, kSpreadVerify = 2;  // workgroups per compute unit, as far as they fit
 __device__ inline uint32_t wave_quota(uint32_t count, uint32_t waves) {
   return min(64u, max(1u, (count + waves - 1) / waves));
 }
@@ -2055,6 +2062,7 @@ __global__ __launch_bounds__(kBlock) void k_energy_sum(const double* __restrict_
 
 // the stack columns of a block, plus one spare entry below each column (a walk
 // whose sentinel was taken points there)
+constexpr size_t kLdsPerCu = 160 * 1024, kStaticLds = 3 * 1024;  // the latter: what the re-trace declares besides
 static size_t stack_bytes(uint32_t entries) { return (size_t)(entries + 1) * kBlock * sizeof(int32_t); }
 
 hipError_t launch_verify(const SceneDev* scenes, const uint2* tiles, uint32_t n_tiles, const uint32_t* gbase,
@@ -2164,7 +2172,8 @@ hipError_t launch_retrace(const SceneDev* scenes, const uint32_t* gbase, int n_s
                           const uint32_t* frame_ptr, pv_stats* stats, uint32_t n_blocks, uint32_t n_cu, int variant,
                           uint32_t stack, int min_active, uint32_t* deal, hipStream_t s) {
   if (stack < kMinStack || stack > (uint32_t)kMaxStack || min_active < 1 || min_active > 64) return hipErrorInvalidValue;
-  const uint32_t spread = std::min(4 * n_blocks, 4 * kSpreadRetrace * n_cu);
+  const uint32_t fit = (uint32_t)(kLdsPerCu / (stack_bytes(stack) + kStaticLds));  // workgroups beside each other
+  const uint32_t spread = std::min(4 * n_blocks, 4 * std::min(kSpreadRetrace, fit) * n_cu);
   if (n_scenes == 1)
     retrace_variant<true>(variant, dim3(n_blocks), stack_bytes(stack), s, scenes, gbase, n_scenes, queue, qcount, T, seed, frame,
                           frame_ptr, stats, min_active, stack, spread, deal);
