@@ -1889,9 +1889,9 @@ __global__ __launch_bounds__(kBlock) void k_energy_fwd(const SceneDev* __restric
 // with fewer the lanes that share a column take turns.  LDS float atomics on
 // one shared set cost about 120 cycles a wave instruction whatever the
 // conflicts (one or 64 copies timed the same) and were more than half of the
-// kernel.  Every kGradFold rounds the columns are folded into FP64 registers,
-// so an FP32 accumulator takes fewer additions than the 256 paths of a tile
-// would give it; each workgroup's FP64 sums go to their own slots, which
+// kernel.  After 'fold_rounds' rounds the columns are folded into FP64 registers, so
+// that an accumulator takes kGradAdds additions at most between two folds
+// (grad_fold); each workgroup's FP64 sums go to their own slots, which
 // k_energy_sum adds in a fixed order (FP64 atomics of every workgroup on one
 // set took about 100 us).  Bound by memory: 16 B of every photon row but the
 // last and 12 B of upstream gradient per photon.  Measured at 1M paths x 7
@@ -1902,7 +1902,8 @@ __global__ __launch_bounds__(kBlock) void k_energy_fwd(const SceneDev* __restric
 template <int kRows>
 __global__ __launch_bounds__(64) void k_energy_bwd(const SceneDev* __restrict__ scenes, const float* __restrict__ albedo,
                                                    const float* __restrict__ power, const float* __restrict__ gE,
-                                                   uint32_t n_mat, uint32_t cols, double* __restrict__ part) {
+                                                   uint32_t n_mat, uint32_t cols, uint32_t fold_rounds,
+                                                   double* __restrict__ part) {
   extern __shared__ float sh[];
   const SceneDev& S = scenes[0];
   const uint32_t rows = n_mat + S.n_lights, width = 3 * rows, lane = threadIdx.x;
@@ -1973,7 +1974,7 @@ __global__ __launch_bounds__(64) void k_energy_bwd(const SceneDev* __restrict__ 
   uint32_t held = 0;  // rounds since the last fold
   if (blockIdx.x * 64 < S.n_paths) load(blockIdx.x * 64);
   for (uint32_t base = blockIdx.x * 64; base < S.n_paths; base += gridDim.x * 64) {
-    if (held == kGradFold) {
+    if (held == fold_rounds) {
       fold();
       held = 0;
     }
@@ -2226,6 +2227,18 @@ static uint32_t grad_cols(uint32_t rows) {
   while (cols > 8 && rows * cols * 12 > 27 * 1024) cols >>= 1;
   return cols;
 }
+// Rounds of 64 paths between two folds: an accumulator serves 64 / cols lanes,
+// and up to B - 1 vertices of a path may lie on one material.  With 32 rounds
+// whatever the columns, 256 materials of which one takes nearly all hits had
+// 3,584 additions in a row at 15 bounces, and the gradient of 1.6M paths an
+// error of 4.4e-7 (FP32 accumulators per 256 paths had 6.1e-8; now 3.0e-8).  A
+// fold costs about a round: 586 us there instead of 548, 157 and 154 at 60
+// materials and 7 bounces, nothing measurable at 32.
+constexpr uint32_t kGradAdds = 224;
+static uint32_t grad_fold(uint32_t cols, uint32_t B) {
+  const uint32_t adds = (64 / cols) * (std::max(B, 2u) - 1);
+  return std::min(32u, std::max(1u, kGradAdds / adds));
+}
 // LDS bytes of a workgroup: the accumulators and the albedos (rows: materials and lights)
 static uint32_t grad_lds(uint32_t rows) { return rows * (grad_cols(rows) + 1) * 12; }
 // single-wave workgroups per compute unit: what the LDS holds, at most 16
@@ -2246,10 +2259,12 @@ hipError_t launch_energy_bwd(const SceneDev* scene, uint32_t n_paths, uint32_t B
   // an empty store: one workgroup writes zero sums
   const dim3 g(std::max(1u, std::min((n_paths + 63) / 64, n_cu * grad_waves_per_cu(rows))));
   const size_t lds = grad_lds(rows);
+  const uint32_t fold = grad_fold(cols, B);
   if (B <= (uint32_t)kFewRows)
-    hipLaunchKernelGGL(k_energy_bwd<kFewRows>, g, dim3(64), lds, s, scene, albedo, power, gE, n_mat, cols, part);
+    hipLaunchKernelGGL(k_energy_bwd<kFewRows>, g, dim3(64), lds, s, scene, albedo, power, gE, n_mat, cols, fold, part);
   else
-    hipLaunchKernelGGL(k_energy_bwd<PV_MAX_BOUNCES>, g, dim3(64), lds, s, scene, albedo, power, gE, n_mat, cols, part);
+    hipLaunchKernelGGL(k_energy_bwd<PV_MAX_BOUNCES>, g, dim3(64), lds, s, scene, albedo, power, gE, n_mat, cols, fold,
+                       part);
   hipLaunchKernelGGL(k_energy_sum, dim3((width + 15) / 16), dim3(kBlock), 0, s, part, g.x, width, g_albedo, 3 * n_mat,
                      g_power);
   return hipGetLastError();

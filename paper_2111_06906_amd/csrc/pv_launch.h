@@ -109,7 +109,6 @@ hipError_t launch_energy_fwd(const SceneDev* scenes, const uint2* tiles, uint32_
 // Gradients over one scene's store.  part: grad_part_words(n_cu) doubles, the
 // sums of each workgroup
 constexpr uint32_t kMaxGradMaterials = 256;
-constexpr uint32_t kGradFold = 32;  // rounds of 64 paths between two folds into FP64
 uint32_t grad_part_words(uint32_t n_cu);
 hipError_t launch_energy_bwd(const SceneDev* scene, uint32_t n_paths, uint32_t B, const float* albedo,
                              const float* power, const float* gE, uint32_t n_mat, uint32_t n_lights, uint32_t n_cu,
