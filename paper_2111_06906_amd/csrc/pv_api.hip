@@ -39,12 +39,57 @@ namespace {
 
 thread_local std::string g_create_error;
 
+// Device memory of one owner.  Small arrays share a block (an allocation and its
+// release take about 8 us each, and a scene has about forty arrays), and those
+// that are uploaded while a stage is open share one copy too.
 struct Alloc {
+  static constexpr size_t kBlockBytes = 1u << 20, kSmall = 64u << 10, kAlign = 256;
   std::vector<void*> ptrs;
+  uint8_t* block = nullptr;  // the open block
+  size_t used = 0;
+  uint8_t* stage = nullptr;  // the block of the open stage, and its bytes on the host
+  std::vector<uint8_t> staged;
   ~Alloc() { release(); }
   void release() {
     for (void* p : ptrs) (void)hipFree(p);
     ptrs.clear();
+    block = stage = nullptr;
+    staged.clear();
+  }
+  hipError_t take(void** out, size_t bytes) {
+    bytes = (bytes + kAlign - 1) / kAlign * kAlign;
+    const bool small = bytes <= kSmall;
+    if (small && block && used + bytes <= kBlockBytes) {
+      *out = block + used;
+      used += bytes;
+      return hipSuccess;
+    }
+    void* p = nullptr;
+    const hipError_t e = hipMalloc(&p, small ? kBlockBytes : bytes);
+    if (e != hipSuccess) return e;
+    ptrs.push_back(p);
+    *out = p;
+    if (small) {
+      block = static_cast<uint8_t*>(p);
+      used = bytes;
+    }
+    return hipSuccess;
+  }
+  hipError_t open_stage() {
+    void* p = nullptr;
+    const hipError_t e = hipMalloc(&p, kBlockBytes);
+    if (e != hipSuccess) return e;
+    ptrs.push_back(p);
+    stage = static_cast<uint8_t*>(p);
+    staged.clear();
+    return hipSuccess;
+  }
+  // copies what was staged; the caller waits for the stream before 'staged' changes
+  hipError_t close_stage(hipStream_t s) {
+    const hipError_t e = staged.empty() ? hipSuccess
+                                        : hipMemcpyAsync(stage, staged.data(), staged.size(), hipMemcpyHostToDevice, s);
+    stage = nullptr;
+    return e;
   }
 };
 
@@ -227,15 +272,20 @@ pv_status fail(pv_ctx* c, pv_status code, const std::string& msg) {
 template <typename T>
 hipError_t dalloc(Alloc& a, T** out, size_t count) {
   void* p = nullptr;
-  hipError_t e = hipMalloc(&p, std::max<size_t>(count, 1) * sizeof(T));
-  if (e != hipSuccess) return e;
-  a.ptrs.push_back(p);
-  *out = static_cast<T*>(p);
-  return hipSuccess;
+  const hipError_t e = a.take(&p, std::max<size_t>(count, 1) * sizeof(T));
+  if (e == hipSuccess) *out = static_cast<T*>(p);
+  return e;
 }
 
 template <typename T>
 hipError_t upload(Alloc& a, T** out, const T* src, size_t count, hipStream_t s) {
+  const size_t bytes = count * sizeof(T), at = (a.staged.size() + Alloc::kAlign - 1) / Alloc::kAlign * Alloc::kAlign;
+  if (a.stage && count && bytes <= Alloc::kSmall && at + bytes <= Alloc::kBlockBytes) {
+    a.staged.resize(at + bytes);
+    std::memcpy(a.staged.data() + at, src, bytes);
+    *out = reinterpret_cast<T*>(a.stage + at);
+    return hipSuccess;
+  }
   hipError_t e = dalloc(a, out, count);
   if (e != hipSuccess || count == 0) return e;
   return hipMemcpyAsync(*out, src, count * sizeof(T), hipMemcpyHostToDevice, s);
@@ -450,23 +500,29 @@ HostBvh build_sah(const float* v9, uint32_t n) {
             bb[b].grow(tb[t]);
             ++bc[b];
           }
-          float ra[K];
+          // an empty bin changes neither side of a split: its areas are the last
+          // one's, and the split behind it costs what the one before it does
+          float ra[K], area = 0.0f;
           uint32_t rc[K];
           Box acc;
           acc.reset();
           uint32_t c = 0;
           for (int b = K - 1; b > 0; --b) {
-            acc.grow(bb[b]);
-            c += bc[b];
-            ra[b] = acc.area();
+            if (bc[b]) {
+              acc.grow(bb[b]);
+              c += bc[b];
+              area = acc.area();
+            }
+            ra[b] = area;
             rc[b] = c;
           }
           acc.reset();
           c = 0;
           for (int b = 0; b < K - 1; ++b) {
+            if (!bc[b]) continue;
             acc.grow(bb[b]);
             c += bc[b];
-            if (c == 0 || rc[b + 1] == 0) continue;
+            if (rc[b + 1] == 0) continue;
             float cost = acc.area() * c + ra[b + 1] * rc[b + 1];
             if (cost < best) {
               best = cost;
@@ -1011,6 +1067,7 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     const uint32_t T = S + (uint32_t)n_dyn;
 
     // materials by global triangle id
+    CK(A.open_stage());
     std::vector<uint32_t> tri_mat(T);
     for (uint32_t i = 0; i < S; ++i) tri_mat[i] = d->h_static_mat[i];
     for (uint64_t i = 0; i < n_dyn; ++i) tri_mat[S + i] = d->h_obj_mat[i];
@@ -1230,8 +1287,13 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     ObjDev* d_objs;
     CK(upload(A, &d_nodes, nodes.data(), nodes.size(), s));
     CK(upload(A, &d_wide, wide.data(), wide.size(), s));
-    CK(dalloc(A, &d_tris, (size_t)S + n_dyn));
-    if (S) CK(hipMemcpyAsync(d_tris, stris.data(), sizeof(Tri) * S, hipMemcpyHostToDevice, s));
+    if (((size_t)S + n_dyn) * sizeof(Tri) <= Alloc::kSmall) {
+      stris.resize((size_t)S + n_dyn);  // the objects' are written each frame
+      CK(upload(A, &d_tris, stris.data(), stris.size(), s));
+    } else {
+      CK(dalloc(A, &d_tris, (size_t)S + n_dyn));
+      if (S) CK(hipMemcpyAsync(d_tris, stris.data(), sizeof(Tri) * S, hipMemcpyHostToDevice, s));
+    }
     const int32_t no_roots[3] = {pv::kRootNone, pv::kRootNone, 0};  // set per frame by the top-level build
     CK(upload(A, &hs.top, no_roots, 2, s));
     CK(upload(A, &hs.wtop, no_roots, 3, s));
@@ -1332,12 +1394,10 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     hs.radius = d->photon_radius;
     hs.gpath_base = 0;
 
-    CK(dalloc(A, &ctx->d_scene, 1));
-    CK(dalloc(A, &ctx->d_state, 2));
-    hs.state = ctx->d_state;
     const uint32_t state0[2] = {1, 0};
-    CK(hipMemcpyAsync(ctx->d_state, state0, sizeof(state0), hipMemcpyHostToDevice, s));
-    CK(hipMemcpyAsync(ctx->d_scene, &hs, sizeof(hs), hipMemcpyHostToDevice, s));
+    CK(upload(A, &ctx->d_state, state0, 2, s));
+    hs.state = ctx->d_state;
+    CK(upload(A, &ctx->d_scene, &hs, 1, s));
     std::vector<uint2> place, refit;
     frame_tiles(0, (uint32_t)n_dyn, hs.n_obj_nodes, place, refit);
     CK(upload(A, &ctx->d_place_tiles, place.data(), place.size(), s));
@@ -1352,7 +1412,9 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     CK(upload(A, &ctx->d_obj_staged, ident.data(), 12 * (size_t)std::max(d->n_objects, 1u), s));
     CK(upload(A, &ctx->d_light_staged, ident.data(), 12 * (size_t)d->n_lights, s));
     ctx->xf_pending = false;
+    CK(A.close_stage(s));
     CK(hipStreamSynchronize(s));
+    A.staged = {};
     ctx->hs = hs;
     ctx->n_materials = d->n_materials;
     ctx->n_lights = d->n_lights;
