@@ -152,7 +152,7 @@ struct pv_ctx {
   Alloc dm_mem;
   pv::DmWork dw{};
   // tuning (pv_set_tuning / pv_autotune)
-  int retrace_variant = 1;  // five waves per SIMD: 96 registers, no spills
+  int retrace_variant = 1;  // five waves per SIMD in 96 registers
   // defaults: the settings the autotuner picks on the 3M-path, 380k-triangle
   // interior (twice the workgroups that fit at once: the later ones take
   // what is left of the dealt work lists)
@@ -163,7 +163,7 @@ struct pv_ctx {
   float tune_report[7] = {0, 0, 0, 0, 0, 0, 0};  // pv_autotune_report
   // bound store
   bool bound = false;
-  bool counts_ready = false;   // per-block replace counts written by verify
+  bool counts_ready = false;   // information words verified since the store was bound or tuned on
   bool queue_stale = false;    // verify ran after the last queue build
   bool queue_ordered = false;  // ow.queue holds the queue in the re-trace's order
   pv_path_store bstore{};
@@ -192,7 +192,6 @@ struct pv_batch {
   const float** d_light_in = nullptr;
   float T = -1.0f;
   uint64_t seed = 0;
-  uint32_t retrace_blocks = 0;
   uint32_t stack_entries = 2, stack_moved = 2;  // largest of the scenes'
   uint32_t max_bounces = 1;                      // largest B of the scenes' stores (photon rows)
   bool captured = false;
@@ -1348,7 +1347,6 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
       CK(dalloc(A, &lw.cbox, 6 * (size_t)d->n_objects));
       lw.n_dyn = nd;
       lw.first_node = lbvh_first;
-      lw.n_nodes = lbvh_nodes;
       hs.pyr = lw.pyr;
       hs.n_dyn = nd;
       ctx->max_obj_tris = *std::max_element(d->h_obj_tris, d->h_obj_tris + d->n_objects);
@@ -1361,10 +1359,8 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     hs.dtri_gid = d_dgid;
     hs.objs = d_objs;
     hs.n_obj = d->n_objects;
-    hs.n_dyn_tris = (uint32_t)n_dyn;
     CK(dalloc(A, &hs.obj_aabb, 6 * (size_t)d->n_objects));
     CK(dalloc(A, &hs.obj_xf_cur, 12 * (size_t)d->n_objects));
-    CK(dalloc(A, &hs.obj_xf_prev, 12 * (size_t)d->n_objects));
     CK(dalloc(A, &hs.obj_moved, d->n_objects));
 
     // lights (path ranges filled at store binding time)
@@ -1385,7 +1381,6 @@ pv_status pv_upload_scene(pv_ctx* ctx, const pv_scene_desc* d) {
     hs.lights = d_lights;
     hs.n_lights = d->n_lights;
     CK(dalloc(A, &hs.light_xf_cur, 12 * (size_t)d->n_lights));
-    CK(dalloc(A, &hs.light_xf_prev, 12 * (size_t)d->n_lights));
     CK(dalloc(A, &hs.light_moved, d->n_lights));
     hs.verify_boxes = ctx->verify_boxes ? 1u : 0u;
     hs.energy_test = (uint32_t)ctx->energy_test;
@@ -2198,7 +2193,6 @@ pv_status pv_batch_create(pv_batch** out, pv_ctx* const* contexts, const pv_path
     b->n = n;
     b->T = threshold;
     b->seed = seed;
-    b->retrace_blocks = (uint32_t)ctx->n_cu * 8;
     std::vector<SceneDev> table(n);
     std::vector<uint2> ptiles, place, refit;
     std::vector<uint32_t> gbase(n + 1, 0);

@@ -342,10 +342,8 @@ struct SceneDev {
   uint32_t pyr_full;      // 1: an object's ranges need the pyramid above its low levels
   const ObjDev* objs;
   uint32_t n_obj;
-  uint32_t n_dyn_tris;
   float* obj_aabb;        // [n_obj][6] world boxes (lo, hi)
   float* obj_xf_cur;      // [n_obj][12]
-  float* obj_xf_prev;
   uint32_t* obj_moved;    // [n_obj]
   // per internal node of the objects' upload-time topologies (nodes
   // [obj_node_first, obj_node_first + n_obj_nodes) of the scene): the
@@ -361,7 +359,6 @@ struct SceneDev {
   // lights
   const LightDev* lights;
   float* light_xf_cur;    // [L][12]
-  float* light_xf_prev;
   uint32_t* light_moved;  // [L]
   uint32_t n_lights;
   // materials
@@ -489,7 +486,6 @@ struct LbvhWork {
   float* cbox;           // [n_obj][6] centroid bounds
   uint32_t n_dyn;        // dynamic triangles of the scene
   uint32_t first_node;   // scene node index of the first rebuilt node
-  uint32_t n_nodes;      // rebuilt nodes of all objects
 };
 
 // first entry of pyramid level l over n positions (level sizes n, ceil(n/2), ...)

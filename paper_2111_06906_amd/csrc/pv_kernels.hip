@@ -2101,10 +2101,6 @@ hipError_t launch_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* 
     hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, s, in, out, n, total);
     return hipGetLastError();
   }
-  if (!tile_tmp) {
-    hipLaunchKernelGGL(k_scan, dim3(1), dim3(1024), 0, s, in, out, n, total);
-    return hipGetLastError();
-  }
   // tile_tmp holds 2 * ceil(n / kScanTile) words: tile sums, then their offsets
   const uint32_t tiles = (n + kScanTile - 1) / kScanTile;
   hipLaunchKernelGGL(k_scan_tiles, dim3(tiles), dim3(1024), 0, s, in, out, n, tile_tmp);

@@ -22,7 +22,7 @@ struct FrameInput {
 // dynamic triangles of one object up to which its boxes are found without the
 // pyramid's upper levels (SceneDev::pyr_full = 0)
 constexpr uint32_t kLinearTris = 16384;
-// The beginning of a frame: moved flags, transform history, the moved objects'
+// The beginning of a frame: moved flags, current transforms, the moved objects'
 // world triangles and boxes, and, with 'top', the top-level trees.
 // place_tiles: (scene, first record) per kBlock dynamic triangles;
 // refit_tiles: per scene (scene, kSlotNone), and (scene, first object node) per

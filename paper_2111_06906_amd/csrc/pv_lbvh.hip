@@ -33,8 +33,8 @@
 // boxes that a bottom-up refit computes.
 #include "pv_launch.h"
 // The frame's beginning is here too: k_place (moved flags, world triangles,
-// low pyramid levels) and k_refit (the moved objects' boxes, transform
-// history, top-level trees).
+// low pyramid levels) and k_refit (the moved objects' boxes, current
+// transforms, top-level trees).
 
 namespace pv {
 
@@ -979,19 +979,15 @@ __global__ __launch_bounds__(kBlock) void k_refit(SceneDev* __restrict__ scenes,
   const float* lxf = in.light_tab ? in.light_tab[tile.x] : in.light;
   const uint32_t first = S.state[0];
   static_assert(PV_MAX_OBJECTS <= 64 && PV_MAX_LIGHTS <= 64, "the first wave takes all rows");
-  // an object's row by one thread: transform history, the staged copy that
-  // later sparse updates start from, box and current hierarchy
+  // an object's row by one thread: current transform, the staged copy that later
+  // sparse updates start from, box and current hierarchy
   bool scaled = S.state[1] != 0;
   ObjDev* objs = const_cast<ObjDev*>(S.objs);
   for (uint32_t o = threadIdx.x; o < S.n_obj; o += kBlock) {
-    float c[12], v[12];
-    for (int i = 0; i < 12; ++i) {
-      c[i] = S.obj_xf_cur[12 * o + i];
-      v[i] = oxf[12 * o + i];
-    }
+    float v[12];
+    for (int i = 0; i < 12; ++i) v[i] = oxf[12 * o + i];
     if (top) scaled |= object_scaled(S, o, v);
     for (int i = 0; i < 12; ++i) {
-      S.obj_xf_prev[12 * o + i] = c[i];
       S.obj_xf_cur[12 * o + i] = v[i];
       if (in.obj_staged) in.obj_staged[12 * o + i] = v[i];
     }
@@ -1016,7 +1012,6 @@ __global__ __launch_bounds__(kBlock) void k_refit(SceneDev* __restrict__ scenes,
     }
     if (top) scaled |= light_scaled(S, l, v);
     for (int i = 0; i < 12; ++i) {
-      S.light_xf_prev[12 * l + i] = c[i];
       S.light_xf_cur[12 * l + i] = v[i];
       if (in.light_staged) in.light_staged[12 * l + i] = v[i];
     }
