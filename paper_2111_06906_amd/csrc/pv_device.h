@@ -632,9 +632,11 @@ __device__ inline float slab_entry(float lx, float ly, float lz, float hx, float
 
 // Watertight ray/triangle test (Woop, Benthin, Wald, JCGT 2013), two-sided.
 // Returns true with *t when the triangle is crossed at a parameter strictly
-// inside (tmin, tmax).  The edge functions are evaluated without contraction
-// so that triangles sharing an edge see the same value with opposite sign.
-// Written without early exits (the caller's loop stays one predicated block);
+// inside (tmin, tmax).  An edge function compiles to a product and a fused
+// multiply-add (the _rn intrinsics do not keep the compiler from contracting), so
+// triangles sharing an edge see opposite values up to the product's rounding, and
+// exactly so only where the edge is read in the same order; results hang on these
+// roundings.  Written without early exits (the caller's loop stays one predicated block);
 // only an exactly zero edge function takes the double-precision branch.
 // near_tb (may be null): set when the triangle is crossed past tmin within
 // 2.5e-7 (relative) of tmax.

@@ -307,7 +307,7 @@ __device__ inline uint32_t deal(uint32_t* __restrict__ ctrs, uint32_t wave, uint
 // within 3%.  So spreading is the better of the two up to the 64 lanes at which
 // it ends.  Over three workgroups the same lists take up to 7% longer; where
 // only three fit beside each other (the largest stacks: 24 rebuilt objects, 45k
-// paths) a fourth makes it 398 us instead of 300.  Verification tasks over two
+// paths) a fourth makes it about 400 us instead of 302.  Verification tasks over two
 // workgroups: 59k 61 and 67 us, 88k 72 and 78, 118k 80 and 83 (over four 61, 72
 // and 78, but 29k 65 instead of 58).
 constexpr uint32_t kSpreadRetrace = 4, kSpreadVerify = 2;  // workgroups per compute unit, as far as they fit
@@ -1290,14 +1290,17 @@ __device__ inline float3 normalize3(float3 v) { return mul(v, 1.0f / length(v));
 
 
 // Bound by vector issue (90% of a full trace's cycles at five waves per SIMD)
-// and, as much, by the texture addresser (88% busy, a cycle per lane and load).
-// 96 registers hold five waves with hardly a spill because little outlives a walk
-// (struct Lane); sampling, hit normals, photon writes and path ends are shared
+// and, as much, by the vector memory path (texture addresser 85% busy, a cycle
+// per lane and load, its data return 96%); a 3M-path partial re-trace by the
+// latter (77%, 75%, 94%, 39% of the lanes active), a list of 45k paths by neither
+// (49%, 39%, 63%): with 11% of its lanes active it waits for its longest paths.
+// 96 registers hold five waves without a spill (the batch form spills 6) because
+// little outlives a walk (struct Lane); sampling, hit normals, photon writes and path ends are shared
 // by the modes that need them, since a wave holds lanes of several modes at
 // once and would run each mode's copy in turn.  Measured over the 3M-path,
 // 380k-triangle interior, one MI355X: full trace 4.08 ms against 4.85 with a
 // copy per mode, all of a path's state kept and four waves, partial re-trace
-// 1.63 against 1.98 ms; now 3.40 and 1.46 ms with what the walk gained since.
+// 1.63 against 1.98 ms; now 3.39 and 1.45 ms with what the walk gained since.
 //
 // Re-trace state machine: every iteration each busy lane issues exactly one
 // query (closest hit over the scene, or any hit against the moved objects),
